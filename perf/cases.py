@@ -282,3 +282,82 @@ def tolerance(case):
     if MODELS[case["model"]]["dtype"] == 0:
         return {"rel": 4e-6}
     return {"rel": 2.4e-1} if case["mx"] else {"rel": 2e-2}
+
+
+def _exact_norm(x, w, kind, eps):
+    if kind == 0:
+        g, b = next(w), next(w)
+        return torch.nn.functional.layer_norm(x, (x.shape[-1],), g, b, eps)
+    return x * torch.rsqrt(x.pow(2).mean(-1, keepdim=True) + eps) * next(w)
+
+
+def _exact_gelu(x, tanh=False):
+    return torch.nn.functional.gelu(x, approximate="tanh" if tanh else "none")
+
+
+def _exact_attention(q, k, v, heads):
+    """q [Q, E], k and v [N, E] of one slice."""
+    hd = q.shape[-1] // heads
+    q, k, v = (t.reshape(t.shape[0], heads, hd).transpose(0, 1).contiguous() for t in (q, k, v))
+    p = torch.softmax(torch.matmul(q, k.transpose(1, 2).contiguous()) / math.sqrt(hd), dim=-1)
+    return torch.matmul(p, v).transpose(0, 1).reshape(-1, heads * hd)
+
+
+def exact(case, seed):
+    """The tokens of `run` by the textbook definitions in float64.  The MXFP8 option has none: its result is that of
+    rounded codes, and two computations of it decorrelate over the layers."""
+    if case["path"] == "handover" or case["mx"]:
+        return None
+    d, F = _desc(case), torch.nn.functional
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    raw = _weights(d, gen)
+    n = sum(_counts(case))
+    tiles = torch.rand((n, 3, d.tile_size, d.tile_size), generator=gen, device="cuda").mul_(2.0).sub_(1.0)
+    if case["path"] == "range":
+        tiles = tiles[case["begin"]:case["end"]]
+        n = len(tiles)
+    patches, n_out, pin = _dims(d)
+    D, g, P = d.hidden, d.tile_size // d.patch, d.patch
+    w = (t.double() for t in raw)   # in the order of _weight_specs, one at a time
+    a = tiles.double().reshape(n, 3, g, P, g, P).permute(0, 2, 4, 1, 3, 5).reshape(n * patches, 3 * P * P)
+    x = F.linear(a, next(w), next(w)).reshape(n, patches, D)
+    pos = next(w)
+    if d.class_token:
+        x = torch.cat([next(w).expand(n, 1, D), x], dim=1)
+    x = x + pos
+    del a, tiles
+    for _ in range(d.layers):
+        u = _exact_norm(x, w, d.norm, d.eps)
+        q, k, v = F.linear(u, next(w), next(w)).split(D, dim=-1)
+        if d.qk_norm:   # 1: over all heads together, 2: by head
+            hd = D if d.qk_norm == 1 else D // d.heads
+            q, k = (_exact_norm(t.reshape(-1, hd), w, 1, d.eps).reshape(t.shape) for t in (q, k))
+        o = torch.stack([_exact_attention(q[t], k[t], v[t], d.heads) for t in range(n)])
+        o = F.linear(o, next(w), next(w))
+        x = x + (o * next(w) if d.layer_scale else o)
+        del u, q, k, v, o
+        u = F.linear(_exact_norm(x, w, d.norm, d.eps), next(w), next(w))
+        u = F.linear(_exact_gelu(u, d.act == 1), next(w), next(w))
+        x = x + (u * next(w) if d.layer_scale else u)
+        del u
+    if d.final_norm:
+        x = _exact_norm(x, w, d.norm, d.eps)
+    x = x[:, d.class_token:]
+    if d.pixel_shuffle:
+        x = x.reshape(n, g // 2, 2, g // 2, 2, D).permute(0, 1, 3, 2, 4, 5).reshape(n, n_out, pin)
+    if d.proj_prenorm:
+        x = _exact_norm(x, w, 0, d.eps)
+    if d.proj_kind == 2:
+        E = d.proj_out
+        kv, query, r_pos = F.linear(x, next(w)), next(w), next(w)
+        query, kv = (_exact_norm(t, w, 0, d.eps) for t in (query, kv))
+        in_w, in_b = next(w).split(E), next(w).split(E)
+        query = F.linear(query, in_w[0], in_b[0])
+        k, v = F.linear(kv + r_pos, in_w[1], in_b[1]), F.linear(kv, in_w[2], in_b[2])
+        x = torch.stack([_exact_attention(query, k[t], v[t], d.proj_heads) for t in range(n)])
+        x = F.linear(_exact_norm(F.linear(x, next(w), next(w)), w, 0, d.eps), next(w))
+    elif d.proj_kind == 0:
+        x = F.linear(x, next(w), next(w))
+    else:
+        x = F.linear(_exact_gelu(F.linear(x, next(w), next(w))), next(w), next(w))
+    return x.reshape(-1, BLOCK, d.proj_out) if case["path"] == "paged" else x.reshape(-1, d.proj_out)
