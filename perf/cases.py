@@ -235,7 +235,9 @@ def run(st):
         return st.out[st.begin * per:st.end * per]
     if st.path == "paged":
         B.encode_paged(st.enc, st.tiles, st.offsets, st.cache, st.tables)
-        return st.cache.pool_tensor()
+        pool = st.cache.pool_tensor()
+        pool.cache = st.cache   # a view of the cache's memory: whoever holds the output holds the cache
+        return pool
     if st.path == "split":
         B.encode_trunk_paged(st.enc, st.tiles, 0, st.half, st.workers[0], st.worker_ids[0])
         B.encode_trunk_paged(st.enc, st.tiles, st.half, st.n, st.workers[1], st.worker_ids[1])
