@@ -33,9 +33,9 @@ epd_status epd_op_gemm_bf16(const void* A, const void* W, const float* bias, voi
 /* One launch of the bf16 MFMA GEMM in a chosen form, for tests that hold the forms against each
  * other: epi 0 bias, 1 bias + GELU(erf), 2 bias + GELU(tanh) -> C [M,N] bf16; epi 3 -> R [M,N]
  * fp32 += A W^T + bias (C unused).  form 0 = what the library would pick, 1 = 256x128 tile,
- * 2 = 128x128 tile, 3 = 128x128 tile with the loads four slabs ahead (K % 256 == 0), 6 = 256x256 tile with the plain loop, 7 = pipelined loop, 8 = pipelined loop with both operand slabs
+ * 2, 3 (K % 256 == 0) and 14 = 128x128 tile, both operand slabs in an LDS ring, 13 = 128x64 tile of the same kernel, 6 = 256x256 tile with the plain loop, 7 = pipelined loop, 8 = pipelined loop with both operand slabs
  * loaded straight into LDS, 9 = persistent kernel (not epi 3), 10 = persistent kernel of the residual product (epi 3 only),
- * 11 = 64x64 tiles with both operand slabs in an LDS ring (what the library picks for launches of a slice or two).
+ * 11 = 64x64 tile of the ring kernel (11, 13, 14: what the library picks from for launches of a few slices).
  * 12 = the persistent residual product on 256x192 tiles (epi 3 only, N % 192 == 0: what the library picks for a
  * width like 1152, which is six such tile columns and four and a half 256-wide ones).
  * M >= 1 (any), N % 128 == 0 (N % 256 == 0 for forms 6 to 10), K % 128 == 0; bias [N] fp32.

@@ -28,6 +28,7 @@
 // 16-byte fp32 accesses in the epilogue.  For the attention values (EPI_VT)
 // the roles are swapped, so a lane owns four consecutive tokens of one
 // feature, which is what the transposed value layout wants.
+#include <cmath>
 #include <cstdlib>
 #include <type_traits>
 
@@ -52,8 +53,8 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 //             both operands two slabs ahead in two register sets, fragment reads left to the
 //             compiler: the reference the pipelined loop is checked against bit for bit);
 //   BN = 128  256x128 tile, 64x64 per wave, PIPE = 0: outputs narrower than 256 columns;
-//   BN = 128, BM = 128  128x128 tile, 32x64 per wave, PIPE = 0, two workgroups per CU: launches of
-//             a few slices, whose time is a sum of single-tile latencies.
+//   BN = 128, BM = 128  128x128 tile, 32x64 per wave, PIPE = 0 or 2, two workgroups per CU: launches of a few
+//             slices with a folded pre-norm (the others take the tiles of gemm_bf16_ring.hip).
 // (Tried and dropped, none faster on the six workloads: 4 waves of 128x128 with AGPR
 // accumulators, 256x128 tiles with two 4-wave workgroups per CU, 32-deep slabs.)
 template <int BN, int NT, int BM_ = BM>
@@ -1314,176 +1315,6 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist_res(const GemmPara
   }
 }
 
-// ---------------------------------------------------------------------------
-// Small-tile form for launches of one or two slices (a worker's share of a request under intra-request
-// parallelism, Section 3.2.2).  Such a launch has a handful of 128 x 128 tiles, most CUs idle and the busy ones
-// waiting for operand slabs: its time is the latency chain of one tile, not matrix work.  Here a tile is
-// 64 x 64 (four times as many workgroups, each asking for a quarter of the bytes), four waves of 32 x 32, and
-// both operand slabs go from global memory straight into an LDS ring of RING stages, RING - 1 slabs ahead of
-// the MFMAs, one barrier per slab.  An element's k-steps are added in the order of every other form (same
-// instruction, k ascending), so the bits are those of the large tiles.  The epilogue writes from registers:
-// a lane owns one token and 4 consecutive features per register group (EPI_VT: one feature, 4 tokens).
-// ---------------------------------------------------------------------------
-constexpr int SM_T = 64, SM_RING = 4;
-constexpr int SM_STAGE = 2 * SM_T * BK;   // bf16 elements of a ring stage: activation slab, then weight slab
-constexpr size_t SM_LDS = (size_t)SM_RING * SM_STAGE * sizeof(bf16_t);
-
-// DUAL (EPI_BIAS): tile columns from Npad on are a second product over the same activations, the value projection,
-// whose tiles run with the operand roles of EPI_VT and leave through its store (GemmParams::n2).
-template <int EPI, bool DUAL = false>
-__global__ __launch_bounds__(256, 2) void k_gemm_bf16_small(const GemmParams p, const int gm, const int bw_) {
-  static_assert(!DUAL || EPI == EPI_BIAS, "the second product rides on the plain bias epilogue");
-  constexpr bool tok_major = (EPI == EPI_VT);
-  constexpr int LPS = 4;   // direct loads per thread and slab: two 32-row halves of each operand
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* ring = reinterpret_cast<bf16_t*>(smem);
-
-  // XCD x (workgroups are dealt round-robin) takes a contiguous run of the tile sequence; the sequence walks
-  // bands of bw_ tile columns top to bottom, so the ~32 tiles an XCD holds at once share few operand panels
-  const int gn = (p.Npad + (DUAL ? p.n2_pad : 0)) / SM_T;
-  int id = blockIdx.x;
-  {
-    const int nb = gridDim.x, x = id & 7, slot = id >> 3, q = nb >> 3, r = nb & 7;
-    id = x * q + (x < r ? x : r) + slot;
-  }
-  const int band_tiles = gm * bw_, full_bands = gn / bw_;
-  int band = id / band_tiles, in_band = id % band_tiles, bw = bw_;
-  if (band >= full_bands) { band = full_bands; in_band = id - full_bands * band_tiles; bw = gn - full_bands * bw_; }
-  const int m0 = (in_band / bw) * SM_T;
-  const int n0 = (band * bw_ + in_band % bw) * SM_T;
-  const bool vt_tile = tok_major || (DUAL && n0 >= p.Npad);   // uniform over the workgroup
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int l32 = lane & 31, lh = lane >> 5;
-  const int ld_row = tid >> 3, ld_c = tid & 7;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  // the lane that lands on physical chunk ld_c of its LDS row fetches logical chunk ld_c ^ SWZ(row)
-  const unsigned a_voff = ((unsigned)ld_row * (unsigned)p.lda + ((ld_c ^ SWZ(ld_row)) * 8)) * 2;
-  const unsigned b_voff = ((unsigned)ld_row * (unsigned)p.K + ((ld_c ^ SWZ(ld_row)) * 8)) * 2;
-  const int KT_ = p.K / BK;
-
-  // slab kt -> ring stage kt % RING (rows of a ragged last tile past M are read like any other: A holds whole
-  // 256-row tiles; their results are never stored)
-  auto issue = [&](int kt) {
-    bf16_t* st = ring + (kt % SM_RING) * SM_STAGE;
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const bf16_t* g = p.A + (long)(m0 + 32 * i) * p.lda + kt * BK;   // uniform
-      const unsigned lds_addr = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(st + (wave_u * 64 + 256 * i) * 8);
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                   :: "v"(a_voff), "s"(g), "s"(lds_addr) : "memory", "m0");
-    }
-#pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const bf16_t* g = p.W + (long)(n0 + 32 * i) * p.K + kt * BK;
-      const unsigned lds_addr = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(st + SM_T * BK + (wave_u * 64 + 256 * i) * 8);
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                   :: "v"(b_voff), "s"(g), "s"(lds_addr) : "memory", "m0");
-    }
-  };
-  auto wait_vm = [&](auto n) {
-    constexpr int N = decltype(n)::value;
-    __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | (0x7 << 4) | (0xf << 8));
-  };
-
-#pragma unroll
-  for (int s = 0; s < SM_RING - 1; ++s)
-    if (s < KT_) issue(s);
-
-  // what the epilogue reads, fetched under the main loop: bias, and the residual rows it adds to.
-  // Register group g of a lane: tile row (token) wm * 32 + l32, tile columns wn * 32 + 8 g + 4 lh .. + 3
-  // (EPI_VT: feature wn * 32 + l32, tokens wm * 32 + 8 g + 4 lh .. + 3)
-  const int row = m0 + wm * 32 + l32;                 // token of this lane (not EPI_VT)
-  const int col0 = n0 + wn * 32 + 4 * lh;             // first feature of register group 0 (not EPI_VT)
-  f32x4 b4[4], x4[4];
-  float b1 = 0.f;
-  if (vt_tile) {
-    b1 = p.bias[n0 + wn * 32 + l32];
-  } else {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) b4[g] = *reinterpret_cast<const f32x4*>(p.bias + col0 + 8 * g);
-  }
-  if constexpr (EPI == EPI_BIAS_RESIDUAL) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      if (row < p.M && col0 + 8 * g < p.N) x4[g] = *reinterpret_cast<const f32x4*>(p.R + (long)row * p.ldr + col0 + 8 * g);
-  } else if constexpr (EPI == EPI_BIAS_POS) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      if (row < p.M && col0 + 8 * g < p.N) x4[g] = *reinterpret_cast<const f32x4*>(p.pos + (long)(row % p.n_pos) * p.N + col0 + 8 * g);
-  }
-
-  f32x16 acc;
-#pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  const int frag_sw = SWZ(l32);
-  auto main_loop = [&](auto tm) {
-  constexpr bool TOKM = decltype(tm)::value;
-  for (int kt = 0; kt < KT_; ++kt) {
-    // Loads complete in order: slab kt has landed once at most LPS x (slabs issued behind it) of this
-    // thread's loads are outstanding.  (The epilogue's own loads above are older than every slab but the
-    // first RING - 1, and counted among the outstanding ones only before those have landed.)
-    const int behind = KT_ - 1 - kt;
-    if (behind >= SM_RING - 2) wait_vm(std::integral_constant<int, (SM_RING - 2) * LPS>{});
-    else if (behind == 1) wait_vm(std::integral_constant<int, LPS>{});
-    else wait_vm(std::integral_constant<int, 0>{});
-    __syncthreads();   // everyone's part of slab kt is in LDS, and everyone is done reading slab kt - 1
-    if (kt + SM_RING - 1 < KT_) issue(kt + SM_RING - 1);   // into the stage slab kt - 1 has left
-    const bf16_t* a_s = ring + (kt % SM_RING) * SM_STAGE + (wm * 32 + l32) * BK;
-    const bf16_t* b_s = ring + (kt % SM_RING) * SM_STAGE + SM_T * BK + (wn * 32 + l32) * BK;
-    bf16x8 xf[BK / 16], wf[BK / 16];
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) {
-      const int coff = ((2 * kk + lh) ^ frag_sw) * 8;
-      xf[kk] = *reinterpret_cast<const bf16x8*>(a_s + coff);
-      wf[kk] = *reinterpret_cast<const bf16x8*>(b_s + coff);
-    }
-    __builtin_amdgcn_sched_barrier(0);   // all fragment reads of the slab first: their latency is paid once
-#pragma unroll
-    for (int kk = 0; kk < BK / 16; ++kk) acc = TOKM ? mfma32(xf[kk], wf[kk], acc) : mfma32(wf[kk], xf[kk], acc);
-  }
-  };
-  if (DUAL && vt_tile) main_loop(std::true_type{});
-  else main_loop(std::integral_constant<bool, tok_major>{});
-
-  if (vt_tile) {
-    const int f = n0 - (DUAL ? p.Npad : 0) + wn * 32 + l32;   // feature of the value projection
-    if (f < (DUAL ? p.n2 : p.N)) {
-      const int h = f / p.hd_pad, d = f % p.hd_pad;
-#pragma unroll
-      for (int g = 0; g < 4; ++g) {
-        const int tok = m0 + wm * 32 + 8 * g + 4 * lh;   // n_tok % 8 == 0: the four tokens share a slice
-        if (tok < p.M) {
-          bf16x4 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) o[e] = (bf16_t)(acc[4 * g + e] + b1);
-          const int t = tok / p.n_tok, n = tok % p.n_tok;
-          *reinterpret_cast<bf16x4*>(p.VT + (((long)t * p.heads + h) * p.hd_pad + d) * p.n_tok + n) = o;
-        }
-      }
-    }
-  } else if (row < p.M) {
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      const int col = col0 + 8 * g;
-      if (col >= p.N) continue;
-      const f32x4 v = {acc[4 * g + 0] + b4[g][0], acc[4 * g + 1] + b4[g][1], acc[4 * g + 2] + b4[g][2], acc[4 * g + 3] + b4[g][3]};
-      if constexpr (EPI == EPI_BIAS_RESIDUAL) {
-        *reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + col) = x4[g] + v;
-      } else if constexpr (EPI == EPI_BIAS_POS) {
-        *reinterpret_cast<f32x4*>(p.R + p.xrows.row(row) * p.ldr + col) = v + x4[g];
-      } else {
-        bf16x4 o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) o[e] = (bf16_t)apply_act_fast<EPI>(v[e]);
-        const long orow = p.row_map ? (long)p.row_map[row / p.block_tokens] * p.block_tokens + row % p.block_tokens : row;
-        *reinterpret_cast<bf16x4*>(p.C + orow * p.ldc + col) = o;
-      }
-    }
-  }
-}
-
 // behind the operand slabs: the tile's bias values, and for a folded pre-norm the column sums of its
 // weights and the mean / rstd of its rows
 template <int BN, int NT, int BM_ = BM>
@@ -1527,37 +1358,76 @@ int cu_count() {
   return n;
 }
 
-template <int EPI, bool DUAL = false>
-hipError_t launch_small_e(const GemmParams& p, hipStream_t st) {
-  const int gm = (p.M + SM_T - 1) / SM_T, gn = (p.Npad + (DUAL ? p.n2_pad : 0)) / SM_T;
-  if (gm * gn == 0) return hipSuccess;
-  k_gemm_bf16_small<EPI, DUAL><<<dim3(gm * gn), dim3(256), SM_LDS, st>>>(p, gm, gn < 4 ? gn : 4);
+// the ring kernel has neither the folded pre-norm nor the bf16 copy of the residual rows
+bool ring_has(const GemmParams& p) { return !p.stats && !p.xb; }
+hipError_t launch_ring(const GemmParams& p, int tile, hipStream_t st) {
   ++g_kernel_launches;
-  return hipGetLastError();
+  return bf16_gemm_ring(p, tile, st);
 }
-// the small-tile form has neither the folded pre-norm nor the bf16 copy of the residual rows
-bool small_form_has(const GemmParams& p) { return !p.stats && !p.xb; }
-hipError_t launch_small(const GemmParams& p, hipStream_t st) {
-  if (p.n2_pad > 0) return p.epi == EPI_BIAS ? launch_small_e<EPI_BIAS, true>(p, st) : hipErrorInvalidValue;
-  switch (p.epi) {
-    case EPI_BIAS: return launch_small_e<EPI_BIAS>(p, st);
-    case EPI_BIAS_GELU_ERF: return launch_small_e<EPI_BIAS_GELU_ERF>(p, st);
-    case EPI_BIAS_GELU_TANH: return launch_small_e<EPI_BIAS_GELU_TANH>(p, st);
-    case EPI_BIAS_RESIDUAL: return launch_small_e<EPI_BIAS_RESIDUAL>(p, st);
-    case EPI_BIAS_POS: return launch_small_e<EPI_BIAS_POS>(p, st);
-    case EPI_VT: return launch_small_e<EPI_VT>(p, st);
-  }
-  return hipErrorInvalidValue;
+
+// Times of a product by form, in microseconds, as the dispatch compares them.  Fitted to the products of the running
+// encoder (three shapes, 1-20 slices, weights cold; each within 15 %, most within 5 %): a workgroup's chain of KT
+// 64-deep slabs plus its fixed cost (first slab, epilogue), times the rounds the launch's tiles make on the CUs.
+// FC2 of a 1024 / 4096 wide encoder, 64 x 64 | 128 x 64 | 128 x 128 tiles: one slice 23 | 33 | 41, three 45 | 42 | 48,
+// seven 96 | 85 | 81 us; the forms before them 24, 56 and 89.
+struct RingPick { int tile; double us; };
+RingPick best_ring(int M, int n_cols, int K, bool f32_out) {
+  const double cus = cu_count(), kt = K / BK;
+  auto per_cu = [&](int tm, int tn) { return (double)((M + tm - 1) / tm) * ((n_cols + tn - 1) / tn) / cus; };
+  RingPick best = {RING_64x64, 4.0 + 0.1 * kt + fmax(1.0, per_cu(64, 64)) * (1.0 + 0.185 * kt)};
+  const double r1 = ceil(per_cu(128, 64));   // two workgroups share a CU: a tile alone on its CU takes 3/4 of two
+  const double t1 = 3.0 + (r1 == 1.0 ? 0.48 * kt + (f32_out ? 2.0 : 0.5) : r1 * ((f32_out ? 2.1 : 0.5) + 0.325 * kt));
+  if (t1 < best.us) best = {RING_128x64, t1};
+  const double t2 = 1.0 + ceil(per_cu(128, 128)) * (f32_out ? 8.0 + 0.5 * kt : 5.0 + 0.45 * kt);
+  if (t2 < best.us) best = {RING_128x128, t2};
+  return best;
 }
-template <int EPI, bool DUAL = false>
-hipError_t set_attr_small() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_small<EPI, DUAL>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)SM_LDS);
+// one round of 256 x 256 tiles, `tiles` of them (the CUs share the power budget: a full round takes longer)
+double round_256(double tiles, int K, int epi) {
+  const double kt = K / BK, fill = tiles / cu_count();
+  if (epi == EPI_BIAS_RESIDUAL || epi == EPI_BIAS_POS) return 15.0 + 1.65 * kt + fill * (8.0 + 0.15 * kt);
+  return 2.0 + 1.78 * kt + fill * 4.0 + (epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH ? 3.0 : 0.0);
 }
-// EPD_SMALL_TILES=0: launches of a slice or two stay on the 128 x 128 tiles (what the small form was measured against)
-bool small_tiles() {
-  static const bool on = !(getenv("EPD_SMALL_TILES") && getenv("EPD_SMALL_TILES")[0] == '0');
-  return on;
+// one round of 256 x 192 tiles (residual products only)
+double round_192(double tiles, int K) {
+  const double kt = K / BK;
+  return 13.0 + 1.45 * kt + tiles / cu_count() * (6.0 + 0.1 * kt);
+}
+// `tiles` tiles in rounds of one per CU
+template <typename F>
+double rounds_of(long tiles, F round) {
+  const long cus = cu_count(), full = tiles / cus, rem = tiles % cus;
+  return full * round((double)cus) + (rem > 0 ? round((double)rem) : 0.0);
+}
+// The tile rows of a launch of 256 x 256 tiles that go ahead as whole rounds when the rows of its last, partly filled
+// round are cut off as a launch of ring tiles (every form sums an element's k-steps in the same order: same bits).
+// 0: no cut, because the ring launch and the second launch's 2 us would take longer than the partly filled round.  The
+// cut keeps a slice (transposed store) or a cache block (row map) on one side.  FC1 of a 13-slice call of the
+// 1024-wide encoder (832 tiles): 105 + 23 us with 256 x 128 tiles behind the cut, 105 + 15 us with ring tiles.
+long cut_rows(const GemmParams& p) {
+  const long cus = cu_count(), gn = p.Npad / 256, gm = (p.M + BM - 1) / BM, tiles = gm * gn, full = tiles / cus, rem = tiles % cus;
+  if (full < 1 || rem == 0 || p.epi == EPI_BIAS_POS) return 0;
+  // Past a few rounds the chip sits against its power limit and an idle tail is paid back in clock: there only the long
+  // residual products are cut, and only when at most half of the CUs are left with a tile (40 slices of the 6B shape
+  // with all products cut: +1.4 % on the call).
+  if (full > 4 && !(p.epi == EPI_BIAS_RESIDUAL && p.K >= 2048)) return 0;
+  long rows_a = full * cus / gn, unit = 1;
+  if (p.epi == EPI_VT) { if (p.n_tok % BM != 0) return 0; unit = p.n_tok / BM; }
+  rows_a -= rows_a % unit;
+  if (rows_a < 1 || rows_a >= gm) return 0;
+  if (p.row_map && (p.block_tokens < 1 || (rows_a * BM) % p.block_tokens != 0)) return 0;
+  const bool f32_out = p.epi == EPI_BIAS_RESIDUAL;
+  if (full > 4 && (gm - rows_a) * gn * 2 > cus) return 0;
+  const double whole = rounds_of(tiles, [&](double n) { return round_256(n, p.K, p.epi); });
+  const double cut = rounds_of(rows_a * gn, [&](double n) { return round_256(n, p.K, p.epi); }) + 2.0 +
+                     best_ring(p.M - (int)(rows_a * BM), p.Npad, p.K, f32_out).us;
+  return cut < whole ? rows_a : 0;
+}
+double launch_256(const GemmParams& p) {
+  const long gn = p.Npad / 256, gm = (p.M + BM - 1) / BM, rows_a = cut_rows(p);
+  auto round = [&](double n) { return round_256(n, p.K, p.epi); };
+  if (rows_a == 0) return rounds_of(gm * gn, round);
+  return rounds_of(rows_a * gn, round) + 2.0 + best_ring(p.M - (int)(rows_a * BM), p.Npad, p.K, p.epi == EPI_BIAS_RESIDUAL).us;
 }
 
 // Activation slabs straight into LDS (no register hop): the persistent kernels (-5 % on the q/k, value and FC1
@@ -1675,6 +1545,23 @@ hipError_t dispatch(const GemmParams& p, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
+// 128 x 128 tiles: compiled for the folded pre-norm and the emitting residual epilogues only (ring tiles otherwise)
+template <int PIPE>
+hipError_t dispatch_128_fold(const GemmParams& p, hipStream_t st) {
+  if (p.stats) {
+    switch (p.epi) {
+      case EPI_BIAS: return launch<128, 512, 64, EPI_BIAS, PIPE, 128, 2>(p, st);
+      case EPI_BIAS_GELU_ERF: return launch<128, 512, 64, EPI_BIAS_GELU_ERF, PIPE, 128, 2>(p, st);
+      case EPI_BIAS_GELU_TANH: return launch<128, 512, 64, EPI_BIAS_GELU_TANH, PIPE, 128, 2>(p, st);
+      case EPI_VT: return launch<128, 512, 64, EPI_VT, PIPE, 128, 2>(p, st);
+    }
+    return hipErrorInvalidValue;
+  }
+  if (p.epi != EPI_BIAS_RESIDUAL || !p.xb) return hipErrorInvalidValue;
+  return p.stats_out ? launch<128, 512, 64, EPI_BIAS_RESIDUAL, PIPE, 128, 2>(p, st)
+                     : launch<128, 512, 64, EPI_BIAS_RESIDUAL, PIPE, 128, 1>(p, st);
+}
+
 template <int BN, int NT, int WN, int EPI, int PIPE, int BM_, int FOLD = 0>
 hipError_t set_attr() {
   return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16<BN, NT, WN, EPI, PIPE, BM_, FOLD>),
@@ -1698,15 +1585,33 @@ hipError_t set_attr_all() {
   return set_attr<BN, NT, WN, EPI_VT, PIPE, BM_, 2>();
 }
 
+template <int PIPE>
+hipError_t set_attr_128_fold() {
+  hipError_t e;
+  if ((e = set_attr<128, 512, 64, EPI_BIAS, PIPE, 128, 2>()) != hipSuccess) return e;
+  if ((e = set_attr<128, 512, 64, EPI_BIAS_GELU_ERF, PIPE, 128, 2>()) != hipSuccess) return e;
+  if ((e = set_attr<128, 512, 64, EPI_BIAS_GELU_TANH, PIPE, 128, 2>()) != hipSuccess) return e;
+  if ((e = set_attr<128, 512, 64, EPI_BIAS_RESIDUAL, PIPE, 128, 1>()) != hipSuccess) return e;
+  if ((e = set_attr<128, 512, 64, EPI_BIAS_RESIDUAL, PIPE, 128, 2>()) != hipSuccess) return e;
+  return set_attr<128, 512, 64, EPI_VT, PIPE, 128, 2>();
+}
+
 }  // namespace
 
 long bf16_gemm_kernel_launches() { return g_kernel_launches; }
 
-// The q/k and the value projection of a single slice as one launch of small tiles: three tiles per CU on the
-// 300M shape, where two launches of two and one were measured 5 us slower per layer.
+// The q/k and the value projection as one launch of ring tiles, where that is estimated to take less than the two
+// launches each in its own best form (1024-wide encoder, us per layer: one slice 21.0 -> 15.2, five 58.9 -> 45.6, ten
+// 93.7 -> 82.2; 13 slices 98.3 as two launches, 105 as one).
 bool bf16_gemm_pair_fits(const GemmParams& p) {
-  return p.cfg == 0 && p.epi == EPI_BIAS && p.n2_pad > 0 && p.n2_pad % SM_T == 0 && small_tiles() && small_form_has(p) &&
-         (long)((p.M + SM_T - 1) / SM_T) * ((p.Npad + p.n2_pad) / SM_T) * 2 <= 7L * cu_count();
+  if (p.cfg != 0 || p.epi != EPI_BIAS || p.n2_pad <= 0 || p.n2_pad % 128 != 0 || p.Npad % 128 != 0 || !ring_has(p)) return false;
+  GemmParams q = p, v = p;
+  q.n2_pad = v.n2_pad = 0; v.epi = EPI_VT; v.Npad = p.n2_pad;
+  auto alone = [](const GemmParams& g) {
+    const double ring = best_ring(g.M, g.Npad, g.K, false).us;
+    return g.Npad % 256 == 0 ? fmin(ring, launch_256(g)) : ring;
+  };
+  return best_ring(p.M, p.Npad + p.n2_pad, p.K, false).us < alone(q) + alone(v);
 }
 
 hipError_t bf16_gemm_init() {
@@ -1727,16 +1632,68 @@ hipError_t bf16_gemm_init() {
   if ((e = set_attr_persist<EPI_BIAS_GELU_TANH, true>()) != hipSuccess) return e;
   if ((e = set_attr_persist<EPI_VT, true>()) != hipSuccess) return e;
   if ((e = set_attr_all<128, 512, 64>()) != hipSuccess) return e;
-  if ((e = set_attr_all<128, 512, 64, 0, 128>()) != hipSuccess) return e;
-  if ((e = set_attr_all<128, 512, 64, 2, 128>()) != hipSuccess) return e;
-  if ((e = set_attr_small<EPI_BIAS>()) != hipSuccess) return e;
-  if ((e = set_attr_small<EPI_BIAS_GELU_ERF>()) != hipSuccess) return e;
-  if ((e = set_attr_small<EPI_BIAS_GELU_TANH>()) != hipSuccess) return e;
-  if ((e = set_attr_small<EPI_BIAS_RESIDUAL>()) != hipSuccess) return e;
-  if ((e = set_attr_small<EPI_BIAS_POS>()) != hipSuccess) return e;
-  if ((e = set_attr_small<EPI_VT>()) != hipSuccess) return e;
-  if ((e = set_attr_small<EPI_BIAS, true>()) != hipSuccess) return e;
+  if ((e = set_attr_128_fold<0>()) != hipSuccess) return e;
+  if ((e = set_attr_128_fold<2>()) != hipSuccess) return e;
   return hipSuccess;
+}
+
+// Products without a folded pre-norm or emitted rows: the form with the smallest estimated time (best_ring, round_256,
+// round_192).  All forms leave the same bits: a tile shape changes which lane holds an element, never the order in
+// which its k-steps are summed.
+static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
+  const bool residual = p.epi == EPI_BIAS_RESIDUAL;
+  const RingPick ring = best_ring(p.M, p.Npad, p.K, residual || p.epi == EPI_BIAS_POS);
+  const long gm = (p.M + BM - 1) / BM;
+  if (p.Npad % 256 != 0) {
+    // 128 columns over many rows stream the activations at the memory's rate: 256 x 128 tiles fetch each row once (the
+    // cut columns of the 6B shape's FC2, 40960 rows: 277 us, on 128 x 64 ring tiles 315)
+    if (p.Npad == 128 && gm * 2 > cu_count()) return dispatch<128, 512, 64>(p, st);
+    return launch_ring(p, ring.tile, st);
+  }
+  const long tiles_all = gm * (p.Npad / 256), cus = cu_count();
+  // A width like 3200 leaves the last 256-wide tile column half used.  When that column is also what
+  // spills the launch into a nearly empty last round (at most a quarter of the CUs busy), the residual
+  // product is cut by columns: the whole 256-wide tile columns, and the last 128 columns as a launch of
+  // their own (weight rows, bias and residual columns are pointer offsets): -4 % on the 6B shape's FC2,
+  // +1 % on a SigLIP-shaped batch of 480 slices whose 2560 tiles are ten full rounds anyway.
+  if (residual && p.N > 256 && p.N % 256 != 0 && p.N % 256 <= 128 &&
+      tiles_all >= cus && tiles_all % cus != 0 && (tiles_all % cus) * 4 <= cus) {
+    const int n_a = p.N / 256 * 256;
+    GemmParams a = p, b = p;
+    a.N = n_a; a.Npad = n_a;
+    b.N = p.N - n_a; b.Npad = 128;
+    b.W = p.W + (long)n_a * p.K; b.bias = p.bias + n_a; b.R = p.R + n_a;
+    const hipError_t e = dispatch_plain(a, st);
+    return e != hipSuccess ? e : dispatch_plain(b, st);
+  }
+  double best = launch_256(p);
+  // A width of 1152 is four and a half 256-wide tile columns and six 192-wide ones: 240 tiles in one round instead of
+  // 200 for the residual products of the 10-slice SigLIP-shaped request (-8 % on both), but 12 rounds for 10 in a
+  // micro-batch of 128 slices.
+  bool w192 = false;
+  if (residual && persist_res() && tiles_192() && p.N % 192 == 0 && p.N % 256 != 0) {
+    const double t = rounds_of(gm * (p.N / 192), [&](double n) { return round_192(n, p.K); });
+    if (t < best) { best = t; w192 = true; }
+  }
+  if (ring.us < 0.98 * best) return launch_ring(p, ring.tile, st);
+  if (w192) return launch_persist_res<192>(p, st);
+  auto wide = [&](const GemmParams& g) {
+    if (!residual && p.epi != EPI_BIAS_POS) return dispatch_persist(g, st);
+    if (residual && persist_res()) return launch_persist_res(g, st);
+    return (a_direct() && g.K >= 2048) ? dispatch<256, 512, 64, 3>(g, st) : dispatch<256, 512, 64, 1>(g, st);
+  };
+  const long rows_a = cut_rows(p);
+  if (rows_a == 0) return wide(p);
+  GemmParams a = p, b = p;
+  a.M = (int)(rows_a * BM);
+  b.M = p.M - a.M;
+  b.A = p.A + (long)a.M * p.lda;
+  if (residual) b.R = p.R + (long)a.M * p.ldr;
+  else if (p.epi == EPI_VT) b.VT = p.VT + (long)a.M * p.heads * p.hd_pad;   // whole slices: a.M / n_tok of [heads * hd_pad][n_tok]
+  else if (p.row_map) b.row_map = p.row_map + a.M / p.block_tokens;
+  else b.C = p.C + (long)a.M * p.ldc;
+  const hipError_t e = wide(a);
+  return e != hipSuccess ? e : launch_ring(b, best_ring(b.M, b.Npad, b.K, residual).tile, st);
 }
 
 hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
@@ -1748,35 +1705,24 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
     return hipErrorInvalidValue;
   const bool f32_out = p.epi == EPI_BIAS_RESIDUAL || p.epi == EPI_BIAS_POS;
   if (!f32_out && p.epi != EPI_VT && (p.N % 8 != 0 || p.ldc % 8 != 0)) return hipErrorInvalidValue;
-  if (p.n2_pad > 0) return bf16_gemm_pair_fits(p) ? launch_small(p, st) : hipErrorInvalidValue;
+  if (p.n2_pad > 0)
+    return bf16_gemm_pair_fits(p) ? launch_ring(p, best_ring(p.M, p.Npad + p.n2_pad, p.K, false).tile, st) : hipErrorInvalidValue;
   switch (p.cfg) {
     case 1: return dispatch<128, 512, 64>(p, st);
-    case 2: return dispatch<128, 512, 64, 0, 128>(p, st);
-    case 3: if (p.K % 256 == 0) return dispatch<128, 512, 64, 2, 128>(p, st); break;
+    case 2: return ring_has(p) ? launch_ring(p, RING_128x128, st) : dispatch_128_fold<0>(p, st);
+    case 3: if (!ring_has(p)) { if (p.K % 256 == 0) return dispatch_128_fold<2>(p, st); break; } return launch_ring(p, RING_128x128, st);
     case 6: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 0>(p, st); break;
     case 7: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 1>(p, st); break;
     case 8: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 3>(p, st); break;
     case 9: if (p.Npad % 256 == 0 && p.epi != EPI_BIAS_RESIDUAL && p.epi != EPI_BIAS_POS) return dispatch_persist(p, st); break;
     case 10: if (p.Npad % 256 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_persist_res(p, st); break;
-    case 11: if (small_form_has(p)) return launch_small(p, st); break;
+    case 11: if (ring_has(p)) return launch_ring(p, RING_64x64, st); break;
+    case 13: if (ring_has(p)) return launch_ring(p, RING_128x64, st); break;
+    case 14: if (ring_has(p)) return launch_ring(p, RING_128x128, st); break;
     case 12: if (p.N % 192 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_persist_res<192>(p, st); break;
   }
-  // One or two slices: 64 x 64 tiles while there are at most two of them per CU (measured against the
-  // 128 x 128 tiles on 1024 and 2048 rows: ahead up to 512 tiles, behind from 1024 on).  Same bits.
-  if (p.cfg == 0 && small_tiles() && small_form_has(p) &&
-      (long)((p.M + SM_T - 1) / SM_T) * (p.Npad / SM_T) <= 2L * cu_count())
-    return launch_small(p, st);
-  // A width of 1152 is four and a half 256-wide tile columns and six 192-wide ones.  The residual product takes
-  // 256 x 192 tiles when their rounds, at T192 of a 256 x 256 tile's time each, come to less: the 10-slice
-  // SigLIP-shaped request (240 tiles in one round instead of 200: -8 % on both of its residual products), not a
-  // micro-batch of 128 slices (12 rounds for 10).  Same bits.
-  if (p.cfg == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb && persist_res() && tiles_192() && p.N % 192 == 0 && p.N % 256 != 0) {
-    const long cus = cu_count(), gm = (p.M + BM - 1) / BM;
-    const long t256 = gm * ((p.N + 255) / 256), t192 = gm * (p.N / 192);
-    constexpr double T192 = 0.92;   // measured: a 256 x 192 tile takes 0.92 of a 256 x 256 tile's time (more operand bytes per flop)
-    if (t256 * 2 > cus && (double)((t192 + cus - 1) / cus) * T192 < (double)((t256 + cus - 1) / cus))
-      return launch_persist_res<192>(p, st);
-  }
+  if (ring_has(p)) return dispatch_plain(p, st);
+  // from here on: products with a folded pre-norm or an emitting residual epilogue (EPD_NORM_MODE)
   if (p.Npad % 256 != 0) return dispatch<128, 512, 64>(p, st);
   // A width like 3200 leaves the last 256-wide tile column half used.  When that column is also what
   // spills the launch into a nearly empty last round (at most a quarter of the CUs busy), the residual
@@ -1797,47 +1743,18 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
     return e != hipSuccess ? e : bf16_gemm(b, st);
   }
   // Small batches: when 256-wide tiles would leave half of the CUs without one, 128 x 128 tiles
-  // quadruple the number of workgroups (two of them fit a CU) and shorten the one round there is.  Same
-  // bits: a tile shape changes which lane holds an element, never the order in which its k-steps are
-  // summed.  With at most one such tile per CU the launch is bound by the bytes it keeps in flight:
-  // the loop with four register sets (loads four slabs ahead; K in whole groups of four slabs) takes
-  // it.  (Measured and not kept: 256 x 128 tiles for this regime, 17 % slower on one slice; the
-  // pipelined loop on them, 8 % slower still.)
+  // quadruple the number of workgroups (two of them fit a CU) and shorten the one round there is; with at
+  // most one such tile per CU with the loop that loads four slabs ahead (K in whole groups of four slabs).
   const long tiles256 = (long)((p.M + BM - 1) / BM) * (p.Npad / 256);
-  if (tiles256 * 4 <= cu_count() && p.K % 256 == 0) return dispatch<128, 512, 64, 2, 128>(p, st);
-  if (tiles256 * 2 <= cu_count()) return dispatch<128, 512, 64, 0, 128>(p, st);   // beyond that the small tiles lose (13 slices: +9 %)
-  if (p.epi != EPI_BIAS_RESIDUAL && p.epi != EPI_BIAS_POS) {
-    // A batch of a few rounds whose last round fills at most half of the CUs (the SigLIP-shaped request of
-    // 10 slices: 360 tiles of its q/k projection = 1.4 rounds) is cut by rows like the long-K residual
-    // products below: whole rounds on the persistent kernel, the remaining rows as one round of 256 x 128
-    // tiles.  Same bits.  The plain loop of those tiles is slower per flop, so the cut pays only while the
-    // last round is a large part of the launch.
-    if (p.cfg == 0 && p.epi != EPI_VT && (!p.row_map || p.block_tokens > 0)) {
-      const long cu = cu_count(), gn = p.Npad / 256, gm = (p.M + BM - 1) / BM;
-      const long rounds = tiles256 / cu, rem = tiles256 % cu;
-      const long rows_a = rounds * cu / gn;
-      const long tiles_b = (gm - rows_a) * gn;
-      if (rounds >= 1 && rounds <= 4 && rem > 0 && rows_a >= 1 && rows_a < gm && tiles_b * 2 <= cu &&
-          (!p.row_map || (rows_a * BM) % p.block_tokens == 0)) {
-        GemmParams a = p, b = p;
-        a.M = (int)(rows_a * BM);
-        b.M = p.M - a.M;
-        b.A = p.A + (long)a.M * p.lda;
-        if (p.stats) b.stats = p.stats + (long)a.M * p.n_part * 2;
-        if (p.row_map) b.row_map = p.row_map + a.M / p.block_tokens;
-        else b.C = p.C + (long)a.M * p.ldc;
-        const hipError_t e = dispatch_persist(a, st);
-        return e != hipSuccess ? e : dispatch<128, 512, 64>(b, st);
-      }
-    }
-    return dispatch_persist(p, st);
-  }
+  if (tiles256 * 4 <= cu_count() && p.K % 256 == 0) return dispatch_128_fold<2>(p, st);
+  if (tiles256 * 2 <= cu_count()) return dispatch_128_fold<0>(p, st);
+  if (p.epi != EPI_BIAS_RESIDUAL) return dispatch_persist(p, st);
   // A last round that fills at most half of the CUs costs a whole tile time.  The residual product
   // (rows are independent, all addressing is by pointer) is cut by rows instead: whole rounds of
   // 256-wide tiles, then the remaining rows as one round of 128-wide tiles, half as long.  Same bits.
   // Measured: -4 % on the K = 12800 product of the 6B shape, -1 % at K = 4096, +2 % at K = 1024 (the
   // second launch costs more than the short tiles save; +0.6 % with the persistent kernel), hence the K limit.
-  if (p.epi == EPI_BIAS_RESIDUAL && p.K >= 2048) {
+  if (p.K >= 2048) {
     const long cu = cu_count(), gn = p.Npad / 256, gm = (p.M + BM - 1) / BM;
     const long rounds = tiles256 / cu, rem = tiles256 % cu;
     const long rows_a = rounds * cu / gn;                    // tile rows of the whole rounds
@@ -1848,13 +1765,11 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
       b.M = p.M - a.M;
       b.A = p.A + (long)a.M * p.lda;
       b.R = p.R + (long)a.M * p.ldr;
-      if (p.xb) { b.xb = p.xb + (long)a.M * p.ldxb; b.stats_out = p.stats_out + (long)a.M * p.n_part_out * 2; }
-      const hipError_t e = (persist_res() && !a.xb) ? launch_persist_res(a, st)
-                           : a_direct() ? dispatch<256, 512, 64, 3>(a, st) : dispatch<256, 512, 64, 1>(a, st);   // K >= 2048 here
+      b.xb = p.xb + (long)a.M * p.ldxb; b.stats_out = p.stats_out + (long)a.M * p.n_part_out * 2;
+      const hipError_t e = a_direct() ? dispatch<256, 512, 64, 3>(a, st) : dispatch<256, 512, 64, 1>(a, st);   // K >= 2048 here
       return e != hipSuccess ? e : dispatch<128, 512, 64>(b, st);
     }
   }
-  if (p.epi == EPI_BIAS_RESIDUAL && persist_res() && !p.xb) return launch_persist_res(p, st);
   return (a_direct() && p.K >= 2048) ? dispatch<256, 512, 64, 3>(p, st) : dispatch<256, 512, 64, 1>(p, st);
 }
 

@@ -37,9 +37,9 @@ void f32_take_rows(const float* in, SliceRows src, float* out, long rows, int D,
 // beyond N); K % 128 == 0; N % 4 == 0 (N % 8 == 0 for bf16 outputs); Npad % 128 == 0.
 struct GemmParams {
   int epi;
-  int cfg;                    // 0: chosen by shape and epilogue; tests / timing: 1 = 256x128 tile, 2 / 3 = 128x128 tile (loads two / four slabs ahead), 6 = 256x256 plain loop,
+  int cfg;                    // 0: chosen by shape and epilogue; tests / timing: 1 = 256x128 tile, 2 / 3 = 128x128 ring tiles (folded pre-norm: loads two / four slabs ahead), 6 = 256x256 plain loop,
                               // 7 = 256x256 pipelined loop, 8 = the same with both operands straight into LDS,
-                              // 9 = 256x256 persistent (bf16-output epilogues), 10 = persistent residual product, 11 = 64x64 tiles (small launches),
+                              // 9 = 256x256 persistent (bf16-output epilogues), 10 = persistent residual product, 11 / 13 / 14 = ring tiles 64x64 / 128x64 / 128x128,
                               // 12 = persistent residual product on 256x192 tiles (N % 192 == 0)
   int band;                   // 0: automatic; else tile columns per L2 band (must divide Npad / BN)
   const bf16_t* A; long lda;
@@ -77,6 +77,9 @@ struct GemmParams {
 hipError_t bf16_gemm(const GemmParams& p, hipStream_t st);
 // true: bf16_gemm runs p with its second product (n2_pad > 0) as one launch; false: the caller issues two products
 bool bf16_gemm_pair_fits(const GemmParams& p);
+// the product on the ring kernel's tiles (gemm_bf16_ring.hip: launches of a few slices), any epilogue, n2_pad included
+enum RingTile { RING_64x64 = 0, RING_128x64 = 1, RING_128x128 = 2 };
+hipError_t bf16_gemm_ring(const GemmParams& p, int tile, hipStream_t st);
 long bf16_gemm_kernel_launches();   // kernels launched by bf16_gemm on the calling host thread so far (a figure for the profiling hooks)
 hipError_t bf16_gemm_init();  // raises the dynamic-LDS limit of the kernels (idempotent: safe from any thread, any number of times)
 

@@ -235,6 +235,27 @@ def test_gemm_forms_agree_bit_for_bit(M, N, K, epi):
         assert rel_err(got, want) < 6e-3
 
 
+@pytest.mark.parametrize("M,N,K", [(1, 128, 128), (77, 384, 128), (130, 128, 256), (1000, 1152, 384), (3096, 256, 640), (4100, 1152, 128)])
+@pytest.mark.parametrize("epi", [0, 2, 3])
+def test_ring_tiles_agree_bit_for_bit(M, N, K, epi):
+    """The ring kernel's three tiles (64x64, 128x64, 128x128) leave the bits of the 256x128 form: contractions shorter
+    than the ring (two slabs), of one and of several turns of it, ragged rows, widths of odd multiples of 128."""
+    rng = np.random.default_rng(M + N + K + epi)
+    A = B.to_device(_bf16_grid(rng, (M, K), 0.5), True)
+    W = B.to_device(_bf16_grid(rng, (N, K), 0.05), True)
+    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32) * 0.1).cuda()
+    r0 = torch.from_numpy(rng.standard_normal((M, N)).astype(np.float32)).cuda()
+
+    def run(form):
+        out = B.op_gemm_bf16_form(A, W, bias, epi, form, r0.clone() if epi == 3 else None)
+        torch.cuda.synchronize()
+        return out.view(torch.int16 if epi != 3 else torch.int32).cpu().numpy()
+
+    ref = run(1)
+    for form in (11, 13, 14, 0):
+        assert np.array_equal(run(form), ref), form
+
+
 @pytest.mark.parametrize("M,N,K", [(256, 384, 128), (1000, 1152, 256), (2900, 1152, 1152), (77, 384, 384), (10240, 1152, 128)])
 def test_gemm_192_wide_tiles_agree_bit_for_bit(M, N, K):
     """The residual product on 256 x 192 tiles (widths that are whole multiples of 192 and not of 256) leaves the
