@@ -718,10 +718,20 @@ epd_status run_f32(epd_ctx* c, const float* tiles, int T, float* out, hipStream_
     f32_gemm(EPI_BIAS_POS, Ape, x.Kp, (const float*)c->pe.W, c->pe.b, X, x.D, c->pos + (long)x.cls * x.D, x.N, Mpatch, x.D, x.Kp, st,
              nullptr, 1, xr);
     if (x.Ns != x.N) fill_slice_rows(X, x.D, T, x.Ns, x.Nt, c->cls, c->pos, st); }
+  // pre-norm + product: one launch for short rows, two otherwise
+  auto norm_gemm = [&](int family, int epi, const float* g, const float* b, const Linear& lin, float* out_rows, int n) {
+    const float* W = (const float*)lin.W;
+    if (f32_norm_gemm_fits(x.D, x.D, X, W, g, b)) {
+      ProfScope ps(c, family, st);
+      f32_norm_gemm(epi, d.norm, g, b, d.eps, X, x.D, W, lin.b, out_rows, n, M, n, x.D, st);
+    } else {
+      { ProfScope ps(c, 1, st); f32_norm(d.norm, X, x.D, Xn, x.D, g, b, M, x.D, 1, d.eps, st); }
+      { ProfScope ps(c, family, st); f32_gemm(epi, Xn, x.D, W, lin.b, out_rows, n, nullptr, 1, M, n, x.D, st); }
+    }
+  };
   for (int l = 0; l < (stage == STAGE_PROJECT ? 0 : x.L); ++l) {
     const LayerW& w = c->layers[l];
-    { ProfScope ps(c, 1, st); f32_norm(d.norm, X, x.D, Xn, x.D, w.n1_g, w.n1_b, M, x.D, 1, d.eps, st); }
-    { ProfScope ps(c, 2, st); f32_gemm(EPI_BIAS, Xn, x.D, (const float*)w.qkv.W, w.qkv.b, QKV, 3 * x.D, nullptr, 1, M, 3 * x.D, x.D, st); }
+    norm_gemm(2, EPI_BIAS, w.n1_g, w.n1_b, w.qkv, QKV, 3 * x.D);
     if (d.qk_norm == EPD_QKNORM_FULL) {
       ProfScope ps(c, 4, st);
       f32_norm(1, QKV, 3 * x.D, QKV, 3 * x.D, w.qn_g, nullptr, M, x.D, 1, d.eps, st);
@@ -733,8 +743,7 @@ epd_status run_f32(epd_ctx* c, const float* tiles, int T, float* out, hipStream_
     }
     { ProfScope ps(c, 3, st); f32_attention(QKV, 3 * x.D, x.Ns, 0, QKV + x.D, QKV + 2 * x.D, 3 * x.D, O, x.D, T, x.Ns, x.H, x.hd, scale, st); }
     { ProfScope ps(c, 6, st); f32_gemm(EPI_BIAS_RESIDUAL, O, x.D, (const float*)w.o.W, w.o.b, X, x.D, nullptr, 1, M, x.D, x.D, st); }
-    { ProfScope ps(c, 1, st); f32_norm(d.norm, X, x.D, Xn, x.D, w.n2_g, w.n2_b, M, x.D, 1, d.eps, st); }
-    { ProfScope ps(c, 7, st); f32_gemm(act_epi, Xn, x.D, (const float*)w.fc1.W, w.fc1.b, Hd, x.F, nullptr, 1, M, x.F, x.D, st); }
+    norm_gemm(7, act_epi, w.n2_g, w.n2_b, w.fc1, Hd, x.F);
     { ProfScope ps(c, 8, st); f32_gemm(EPI_BIAS_RESIDUAL, Hd, x.F, (const float*)w.fc2.W, w.fc2.b, X, x.D, nullptr, 1, M, x.D, x.F, st); }
   }
   if (d.final_norm && stage != STAGE_PROJECT) { ProfScope ps(c, 1, st); f32_norm(d.norm, X, x.D, X, x.D, c->fn_g, c->fn_b, M, x.D, 1, d.eps, st); }

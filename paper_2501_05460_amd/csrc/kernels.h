@@ -20,6 +20,11 @@ void f32_gemm(int epi, const float* A, int lda, const float* W, const float* bia
               const int* row_map = nullptr, int block_tokens = 1, SliceRows xrows = SliceRows{0, 0, 0});
 void f32_norm(int kind, const float* in, long ld_in, float* out, long ld_out, const float* gamma,
               const float* beta, long rows, int dim, int groups, float eps, hipStream_t st);
+// C = act(norm(A) W^T + bias) in one launch (kind 0 LayerNorm, 1 RMSNorm; epilogues BIAS, GELU_*), for the row lengths and
+// alignments that f32_norm_gemm_fits names (a rule on the shape alone, never on the number of rows)
+bool f32_norm_gemm_fits(int lda, int K, const float* A, const float* W, const float* gamma, const float* beta);
+void f32_norm_gemm(int epi, int kind, const float* gamma, const float* beta, float eps, const float* A, int lda, const float* W,
+                   const float* bias, float* C, int ldc, int M, int N, int K, hipStream_t st);
 // Slice t: keys / values rows t*N .. t*N+N-1 (row stride ld).  Encoder layers: n_q = N queries from the
 // slice's own rows.  q_shared: the n_q query rows (stride ld_q) are the same for every slice (resampler).
 // Output row t*n_q + i.

@@ -1,7 +1,10 @@
-// fp32 mode of the encode stage: plain, bounds-checked kernels with fp32
-// storage and fp32 accumulation.  This mode exists for the small fp32
-// configuration (launch-latency bound) and as the on-device numerical
-// reference of the bf16 MFMA path; it is not tuned.
+// fp32 mode of the encode stage: bounds-checked kernels with fp32 storage and
+// fp32 accumulation (the products on the fp32 matrix instruction).  This mode
+// exists for the small fp32 configuration, whose time is the latency chain of
+// some 36 short launches, and as the on-device numerical reference of the bf16
+// MFMA path.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace epd {
@@ -32,83 +35,164 @@ void f32_im2col(const float* tiles, float* A, int T, int S, int p, hipStream_t s
 }
 
 // ------------------------------------------------------------------ GEMM ----
-// C[M,N] = A[M,K] * W[N,K]^T, TS x TS block tile (64: 4x4 outputs per thread, 32: 2x2), 64-deep k slab, 256 threads.
-// The launches of this mode are small: with 64 x 64 tiles the tiny configuration has a dozen workgroups on 256
-// CUs and its time is one thread's chain of 16 K multiply-adds, so launches that would leave most CUs idle take
-// 32 x 32 tiles (a quarter of the chain, four times the workgroups).  A thread adds the k-steps of an element in
-// ascending order whatever the tile or slab shape: same bits.
-constexpr int F32_BK = 64;
-template <int EPI, int TS>
-__global__ __launch_bounds__(256) void k_f32_gemm(const float* __restrict__ A, int lda,
+// C[M,N] = A[M,K] * W[N,K]^T on v_mfma_f32_16x16x4_f32.  One workgroup per 16 R x 16 R tile; its four waves split K
+// (whole 16-element chunks, a share of ceil(chunks / 4) each) and their partial tiles are added in LDS.
+// The launches of this mode are small: what bounds them is one wave's chain of loads and multiply-adds, so the
+// contraction is cut in four and the tile is 16 x 16 while 32 x 32 tiles would leave CUs idle (M = 256, N = 192,
+// K = 768, one slice of the tiny configuration: 192 workgroups with chains of 48 instructions; 36 us with one thread's
+// chain of 768 multiply-adds through LDS tiles, 6 us now).  Operands come straight from global memory: lane l holds
+// row l % 16, elements 4 (l / 16) .. + 3 of a chunk (one 16-byte load), and instruction e of a chunk multiplies
+// element e of all four groups, the same four elements of both operands.  An element's sum is ordered by K alone, so its
+// bits do not depend on the tile or the batch.
+constexpr int F32_GROUP = 6;   // chunks loaded ahead as one batch
+// NORM: the rows of A are normalised on the way in (LayerNorm / RMSNorm over their K elements).  A share of the
+// contraction then has to fit one batch of loads (K <= 64 F32_GROUP): a wave holds its part of the rows, the statistics
+// meet in LDS, twice (mean, then squared deviations), and the normalised row never goes to memory: the launch of its own
+// (5 us of which the work is less than one) is gone.  Bits depend on K alone here too (multiply-adds are written out: both
+// tile sizes have to contract alike).
+struct F32Norm { const float* gamma; const float* beta; int rms; float eps; };
+template <int EPI, int R, bool VEC, bool NORM = false>
+__global__ __launch_bounds__(256) void k_f32_gemm(const F32Norm norm, const float* __restrict__ A, int lda,
                                                   const float* __restrict__ W,
                                                   const float* __restrict__ bias, float* C, int ldc,
                                                   const float* __restrict__ pos, int n_pos, int M,
                                                   int N, int K, const int* __restrict__ row_map,
                                                   int block_tokens, SliceRows xrows) {
-  constexpr int R = TS / 16;   // outputs per thread in each direction
-  __shared__ float sA[F32_BK][TS + 1];
-  __shared__ float sW[F32_BK][TS + 1];
-  const int tid = threadIdx.x;
-  const int tx = tid % 16, ty = tid / 16;
-  const int m0 = blockIdx.y * TS, n0 = blockIdx.x * TS;
-  float acc[R][R] = {};
-  // the slab after the current one waits in registers, so its memory latency passes under the current slab's
-  // arithmetic instead of in front of every slab
-  constexpr int PER_T = TS * F32_BK / 256;
-  float ra[PER_T], rw[PER_T];
-  auto fetch = [&](int k0) {
-#pragma unroll
-    for (int u = 0; u < PER_T; ++u) {
-      const int i = tid + 256 * u;
-      const int r = i / F32_BK, kk = i % F32_BK;
-      const int gm = m0 + r, gn = n0 + r, gk = k0 + kk;
-      ra[u] = (gm < M && gk < K) ? A[(long)gm * lda + gk] : 0.f;
-      rw[u] = (gn < N && gk < K) ? W[(long)gn * K + gk] : 0.f;
-    }
-  };
-  fetch(0);
-  for (int k0 = 0; k0 < K; k0 += F32_BK) {
-#pragma unroll
-    for (int u = 0; u < PER_T; ++u) {
-      const int i = tid + 256 * u;
-      sA[i % F32_BK][i / F32_BK] = ra[u];
-      sW[i % F32_BK][i / F32_BK] = rw[u];
-    }
-    __syncthreads();
-    if (k0 + F32_BK < K) fetch(k0 + F32_BK);
-#pragma unroll 16
-    for (int kk = 0; kk < F32_BK; ++kk) {
-      float a[R], w[R];
-#pragma unroll
-      for (int i = 0; i < R; ++i) a[i] = sA[kk][ty * R + i];
-#pragma unroll
-      for (int j = 0; j < R; ++j) w[j] = sW[kk][tx * R + j];
-#pragma unroll
-      for (int i = 0; i < R; ++i)
-#pragma unroll
-        for (int j = 0; j < R; ++j) acc[i][j] = fmaf(a[i], w[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int i = 0; i < R; ++i) {
-    int r = m0 + ty * R + i;
-    if (r >= M) continue;
-#pragma unroll
-    for (int j = 0; j < R; ++j) {
-      int c = n0 + tx * R + j;
-      if (c >= N) continue;
-      float v = acc[i][j] + (bias ? bias[c] : 0.f);
-      // paged output: row r of the product lives in block row_map[r / block_tokens]
-      const long orow = row_map ? (long)row_map[r / block_tokens] * block_tokens + r % block_tokens : r;
-      long o = orow * ldc + c;
-      if (EPI == EPI_BIAS_RESIDUAL) {
-        C[o] += v;
-      } else if (EPI == EPI_BIAS_POS) {
-        C[xrows.row(r) * ldc + c] = v + pos[(long)(r % n_pos) * N + c];   // patch embedding: through the slice layout
+  constexpr int T = 16 * R;
+  __shared__ float part[4][T * T];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r16 = lane & 15, q = lane >> 4;
+  const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
+  const int chunks = (K + 15) / 16, share = (chunks + 3) / 4;
+  const int c_begin = wave * share, c_end = min(chunks, c_begin + share);
+  auto load = [&](const float* base, long ld, int row, int rows, int c) -> f32x4 {
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    const int k = c * 16 + 4 * q;
+    if (c < c_end && row < rows) {
+      const float* p = base + (long)row * ld + k;
+      if (VEC) {
+        if (k < K) v = *reinterpret_cast<const f32x4*>(p);   // K % 4 == 0
       } else {
-        C[o] = apply_act<EPI>(v);
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          if (k + e < K) v[e] = p[e];
       }
+    }
+    return v;
+  };
+  f32x4 acc[R][R];
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  f32x4 a[2][F32_GROUP][R], w[2][F32_GROUP][R];
+  auto fetch = [&](auto set, int c0) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int g = 0; g < F32_GROUP; ++g)
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        a[S][g][i] = load(A, lda, m0 + 16 * i + r16, M, c0 + g);
+        w[S][g][i] = load(W, K, n0 + 16 * i + r16, N, c0 + g);
+      }
+  };
+  auto multiply = [&](auto set) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int g = 0; g < F32_GROUP; ++g)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+          for (int j = 0; j < R; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[S][g][i][e], w[S][g][j][e], acc[i][j], 0, 0, 0);
+  };
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+  fetch(S0{}, c_begin);
+  if constexpr (NORM) {
+    __shared__ float red[2][4][T];
+    float mean[R], rstd[R];
+    // sum over a row: this lane's elements, the lanes of the row in this wave, the four waves
+    auto row_sum = [&](int pass, float (&x)[R]) {
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        x[i] += __shfl_xor(x[i], 16, 64);
+        x[i] += __shfl_xor(x[i], 32, 64);
+        if (q == 0) red[pass][wave][16 * i + r16] = x[i];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < R; ++i) {
+        const int r = 16 * i + r16;
+        x[i] = (red[pass][0][r] + red[pass][1][r]) + (red[pass][2][r] + red[pass][3][r]);
+      }
+    };
+    auto in_row = [&](int g) { return c_begin + g < c_end && (c_begin + g) * 16 + 4 * q < K; };   // K % 4 == 0
+    float s1[R], s2[R];
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      s1[i] = s2[i] = 0.f;
+#pragma unroll
+      for (int g = 0; g < F32_GROUP; ++g) s1[i] += (a[0][g][i][0] + a[0][g][i][1]) + (a[0][g][i][2] + a[0][g][i][3]);
+    }
+    if (!norm.rms) row_sum(0, s1);   // uniform
+#pragma unroll
+    for (int i = 0; i < R; ++i) {
+      mean[i] = norm.rms ? 0.f : s1[i] / K;
+#pragma unroll
+      for (int g = 0; g < F32_GROUP; ++g)
+        if (in_row(g)) {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) { const float d = a[0][g][i][e] - mean[i]; s2[i] = fmaf(d, d, s2[i]); }
+        }
+    }
+    row_sum(1, s2);
+#pragma unroll
+    for (int i = 0; i < R; ++i) rstd[i] = 1.0f / sqrtf(s2[i] / K + norm.eps);
+#pragma unroll
+    for (int g = 0; g < F32_GROUP; ++g)
+      if (in_row(g)) {
+        const int k = (c_begin + g) * 16 + 4 * q;
+        const f32x4 gm = *reinterpret_cast<const f32x4*>(norm.gamma + k);
+        const f32x4 bt = norm.rms ? f32x4{0.f, 0.f, 0.f, 0.f} : *reinterpret_cast<const f32x4*>(norm.beta + k);
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) a[0][g][i][e] = fmaf((a[0][g][i][e] - mean[i]) * rstd[i], gm[e], bt[e]);
+      }
+  }
+  for (int c = c_begin; c < c_end; c += 2 * F32_GROUP) {   // chunks past the share are zeros
+    fetch(S1{}, c + F32_GROUP);
+    multiply(S0{});
+    if (c + F32_GROUP >= c_end) break;
+    fetch(S0{}, c + 2 * F32_GROUP);
+    multiply(S1{});
+  }
+  // result register e of lane l: row 4 (l / 16) + e, column l % 16
+#pragma unroll
+  for (int i = 0; i < R; ++i)
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) part[wave][(16 * i + 4 * q + e) * T + 16 * j + r16] = acc[i][j][e];
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < R * R; ++u) {
+    const int idx = tid + 256 * u;
+    const int r = m0 + idx / T, c = n0 + idx % T;
+    if (r >= M || c >= N) continue;
+    const float v = ((part[0][idx] + part[1][idx]) + (part[2][idx] + part[3][idx])) + (bias ? bias[c] : 0.f);
+    // paged output: row r of the product lives in block row_map[r / block_tokens]
+    const long orow = row_map ? (long)row_map[r / block_tokens] * block_tokens + r % block_tokens : r;
+    const long o = orow * ldc + c;
+    if (EPI == EPI_BIAS_RESIDUAL) {
+      C[o] += v;
+    } else if (EPI == EPI_BIAS_POS) {
+      C[xrows.row(r) * ldc + c] = v + pos[(long)(r % n_pos) * N + c];   // patch embedding: through the slice layout
+    } else {
+      C[o] = apply_act<EPI>(v);
     }
   }
 }
@@ -123,17 +207,17 @@ static int f32_cu_count() {
   return n;
 }
 
-template <int TS>
-static void f32_gemm_ts(int epi, const float* A, int lda, const float* W, const float* bias, float* C, int ldc,
-                        const float* pos, int n_pos, int M, int N, int K, hipStream_t st, const int* row_map,
-                        int block_tokens, SliceRows xrows) {
-  dim3 grid((N + TS - 1) / TS, (M + TS - 1) / TS), block(256);
+template <int R, bool VEC>
+static void f32_gemm_r(int epi, const float* A, int lda, const float* W, const float* bias, float* C, int ldc,
+                       const float* pos, int n_pos, int M, int N, int K, hipStream_t st, const int* row_map,
+                       int block_tokens, SliceRows xrows) {
+  dim3 grid((N + 16 * R - 1) / (16 * R), (M + 16 * R - 1) / (16 * R)), block(256);
   switch (epi) {
-    case EPI_BIAS: k_f32_gemm<EPI_BIAS, TS><<<grid, block, 0, st>>>(A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
-    case EPI_BIAS_GELU_ERF: k_f32_gemm<EPI_BIAS_GELU_ERF, TS><<<grid, block, 0, st>>>(A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
-    case EPI_BIAS_GELU_TANH: k_f32_gemm<EPI_BIAS_GELU_TANH, TS><<<grid, block, 0, st>>>(A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
-    case EPI_BIAS_RESIDUAL: k_f32_gemm<EPI_BIAS_RESIDUAL, TS><<<grid, block, 0, st>>>(A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
-    default: k_f32_gemm<EPI_BIAS_POS, TS><<<grid, block, 0, st>>>(A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
+    case EPI_BIAS: k_f32_gemm<EPI_BIAS, R, VEC><<<grid, block, 0, st>>>(F32Norm{}, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
+    case EPI_BIAS_GELU_ERF: k_f32_gemm<EPI_BIAS_GELU_ERF, R, VEC><<<grid, block, 0, st>>>(F32Norm{}, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
+    case EPI_BIAS_GELU_TANH: k_f32_gemm<EPI_BIAS_GELU_TANH, R, VEC><<<grid, block, 0, st>>>(F32Norm{}, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
+    case EPI_BIAS_RESIDUAL: k_f32_gemm<EPI_BIAS_RESIDUAL, R, VEC><<<grid, block, 0, st>>>(F32Norm{}, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
+    default: k_f32_gemm<EPI_BIAS_POS, R, VEC><<<grid, block, 0, st>>>(F32Norm{}, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, row_map, block_tokens, xrows); break;
   }
 }
 
@@ -141,9 +225,40 @@ void f32_gemm(int epi, const float* A, int lda, const float* W, const float* bia
               const float* pos, int n_pos, int M, int N, int K, hipStream_t st, const int* row_map,
               int block_tokens, SliceRows xrows) {
   if (M == 0 || N == 0) return;
-  const long tiles64 = (long)((N + 63) / 64) * ((M + 63) / 64);
-  if (tiles64 * 2 <= f32_cu_count()) f32_gemm_ts<32>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
-  else f32_gemm_ts<64>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
+  const long tiles32 = (long)((N + 31) / 32) * ((M + 31) / 32);
+  const bool vec = K % 4 == 0 && lda % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
+  const bool small = tiles32 < 2 * f32_cu_count();   // 16 x 16 tiles until 32 x 32 ones put two workgroups on every CU
+  if (vec) {
+    if (small) f32_gemm_r<1, true>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
+    else f32_gemm_r<2, true>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
+  } else {
+    if (small) f32_gemm_r<1, false>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
+    else f32_gemm_r<2, false>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
+  }
+}
+
+bool f32_norm_gemm_fits(int lda, int K, const float* A, const float* W, const float* gamma, const float* beta) {
+  return K <= 4 * F32_GROUP * 16 && K % 4 == 0 && lda % 4 == 0 &&
+         (((uintptr_t)A | (uintptr_t)W | (uintptr_t)gamma | (uintptr_t)beta) & 15) == 0;
+}
+
+void f32_norm_gemm(int epi, int kind, const float* gamma, const float* beta, float eps, const float* A, int lda, const float* W,
+                   const float* bias, float* C, int ldc, int M, int N, int K, hipStream_t st) {
+  if (M == 0 || N == 0) return;
+  const F32Norm nm{gamma, beta, kind == 1 ? 1 : 0, eps};
+  const bool small = (long)((N + 31) / 32) * ((M + 31) / 32) < 2 * f32_cu_count();
+  const int t = small ? 16 : 32;
+  const dim3 grid((N + t - 1) / t, (M + t - 1) / t), block(256);
+  const SliceRows xr{0, 0, 0};
+#define F32_NORM_GEMM(EPI)                                                                                              \
+  if (small) k_f32_gemm<EPI, 1, true, true><<<grid, block, 0, st>>>(nm, A, lda, W, bias, C, ldc, nullptr, 1, M, N, K, nullptr, 1, xr); \
+  else k_f32_gemm<EPI, 2, true, true><<<grid, block, 0, st>>>(nm, A, lda, W, bias, C, ldc, nullptr, 1, M, N, K, nullptr, 1, xr);
+  switch (epi) {
+    case EPI_BIAS_GELU_ERF: F32_NORM_GEMM(EPI_BIAS_GELU_ERF) break;
+    case EPI_BIAS_GELU_TANH: F32_NORM_GEMM(EPI_BIAS_GELU_TANH) break;
+    default: F32_NORM_GEMM(EPI_BIAS) break;
+  }
+#undef F32_NORM_GEMM
 }
 
 // ------------------------------------------------------------------ norm ----
@@ -234,10 +349,166 @@ __global__ __launch_bounds__(128) void k_f32_attention(const float* __restrict__
   }
 }
 
+// The same on v_mfma_f32_16x16x4_f32: one workgroup per 16 queries of one (slice, head).  The query-per-block kernel
+// above reads every key and value once per query and its time is one thread's chain over head dim and keys; here 16
+// queries share them and the four waves split the keys of the first product and the head dim of the second (one slice of
+// the tiny configuration, 256 tokens, 3 heads of 64: 30 us -> 12 us).  The logits [16][keys] stay in LDS; keys past N count
+// as weight zero and their rows are not read.  hd % 16 == 0, rows 16-byte aligned.
+// A lane's operand registers as in the GEMM: row l % 16, elements 4 (l / 16) .. + 3 of a 16-element chunk.
+constexpr int F32_ATTN_MAX_KEYS = 2048;   // 16 rows of logits in LDS
+// HC: head dim / 16 when it is compiled in (the loads of a wave's keys and values are then issued as batches: 15.3 -> 11.8 us),
+// 0: any.
+template <int HC>
+__global__ __launch_bounds__(256) void k_f32_attention_mfma(const float* __restrict__ q, long ld_q, int q_shared,
+                                                            const float* __restrict__ k, const float* __restrict__ v,
+                                                            long ld, float* __restrict__ o, long ldo, int n_q, int N, int hd,
+                                                            float scale) {
+  extern __shared__ float sm[];
+  const int NP = (N + 15) / 16 * 16, LD = NP + 4;   // + 4: rows start 4 banks apart
+  float* inv = sm + 16 * LD;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, r16 = lane & 15, g = lane >> 4;
+  const int q0 = blockIdx.x * 16, h = blockIdx.y, t = blockIdx.z;
+  const long row0 = (long)t * N;
+  const int qi = min(q0 + r16, n_q - 1);   // rows past n_q repeat the last query, never stored
+  const float* qp = q + ((q_shared ? 0 : row0) + qi) * ld_q + (long)h * hd + 4 * g;
+  // logits: wave w takes key blocks w, w + 4, ..; result register e = query 4 g + e, key l % 16
+  constexpr int HCR = HC > 0 ? HC : 1, KB = HC > 0 ? 4 : 1;   // key blocks of a wave loaded together
+  f32x4 qr[HCR];
+  if constexpr (HC > 0) {
+#pragma unroll
+    for (int d = 0; d < HC; ++d) qr[d] = *reinterpret_cast<const f32x4*>(qp + 16 * d);
+  }
+  for (int kb0 = wave * 16; kb0 < NP; kb0 += 64 * KB) {
+    f32x4 acc[KB], kr[KB][HCR];
+    if constexpr (HC > 0) {
+#pragma unroll
+      for (int b = 0; b < KB; ++b) {
+        const int key = kb0 + 64 * b + r16;
+        const float* kp = k + (row0 + (key < N ? key : 0)) * ld + (long)h * hd + 4 * g;
+#pragma unroll
+        for (int d = 0; d < HC; ++d) kr[b][d] = *reinterpret_cast<const f32x4*>(kp + 16 * d);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < KB; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if constexpr (HC > 0) {
+#pragma unroll
+      for (int d = 0; d < HC; ++d)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int b = 0; b < KB; ++b) acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(qr[d][e], kr[b][d][e], acc[b], 0, 0, 0);
+    } else {
+      const float* kp = k + (row0 + (kb0 + r16 < N ? kb0 + r16 : 0)) * ld + (long)h * hd + 4 * g;
+#pragma unroll 4
+      for (int d = 0; d < hd; d += 16) {
+        const f32x4 a = *reinterpret_cast<const f32x4*>(qp + d), b = *reinterpret_cast<const f32x4*>(kp + d);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e], acc[0], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < KB; ++b) {
+      const int key = kb0 + 64 * b + r16;
+      if (key < NP) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sm[(4 * g + e) * LD + key] = key < N ? acc[b][e] * scale : -INFINITY;
+      }
+    }
+  }
+  // the values of the first 256 keys, for the wave's first head-dim block, are on their way during the softmax
+  constexpr int VG = HC > 0 ? 4 : 0;
+  float vpre[VG > 0 ? VG : 1][4][4];
+  auto vload = [&](const float* vp, int j0, float (&b)[4][4]) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) { const int j = j0 + 16 * c + 4 * g + e; b[c][e] = j < N ? vp[(long)j * ld] : 0.f; }
+  };
+  if constexpr (HC > 0) {
+    if (wave * 16 < hd) {
+#pragma unroll
+      for (int u = 0; u < VG; ++u) vload(v + row0 * ld + (long)h * hd + wave * 16 + r16, 64 * u, vpre[u]);
+    }
+  }
+  __syncthreads();
+  // softmax: 16 threads per query
+  {
+    float* row = sm + (tid >> 4) * LD;
+    const int j0 = tid & 15;
+    float mx = -INFINITY;
+    for (int j = j0; j < NP; j += 16) mx = fmaxf(mx, row[j]);
+#pragma unroll
+    for (int s = 8; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
+    float sum = 0.f;
+    for (int j = j0; j < NP; j += 16) {
+      const float e = expf(row[j] - mx);
+      row[j] = e;
+      sum += e;
+    }
+#pragma unroll
+    for (int s = 8; s > 0; s >>= 1) sum += __shfl_xor(sum, s, 64);
+    if (j0 == 0) inv[tid >> 4] = 1.0f / sum;
+  }
+  __syncthreads();
+  // output: wave w takes head-dim blocks w, w + 4, ..; lane l supplies keys 4 (l / 16) + e of column l % 16
+  for (int d0 = wave * 16; d0 < hd; d0 += 64) {
+    const float* vp = v + row0 * ld + (long)h * hd + d0 + r16;
+    f32x4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    auto group = [&](int j0, const float (&b)[4][4]) {   // four chains, one per 16-key block of a group of 64 keys
+      f32x4 a[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        const int j = j0 + 16 * c + 4 * g;
+        a[c] = j < NP ? *reinterpret_cast<const f32x4*>(sm + r16 * LD + j) : f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][e], b[c][e], acc[c], 0, 0, 0);
+    };
+    int j0 = 0;
+    if (HC > 0 && d0 == wave * 16) {
+#pragma unroll
+      for (int u = 0; u < VG; ++u) {
+        if (64 * u < NP) group(64 * u, vpre[u]);   // uniform
+      }
+      j0 = 64 * VG;
+    }
+    for (; j0 < NP; j0 += 64) {
+      float b[4][4];
+      vload(vp, j0, b);
+      group(j0, b);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = q0 + 4 * g + e;
+      if (row < n_q) o[((long)t * n_q + row) * ldo + (long)h * hd + d0 + r16] = ((acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e])) * inv[4 * g + e];
+    }
+  }
+}
+
 void f32_attention(const float* q, long ld_q, int n_q, int q_shared, const float* k, const float* v, long ld,
                    float* o, long ldo, int T, int N, int H, int hd, float scale, hipStream_t st) {
   if (T == 0) return;
-  size_t smem = (size_t)(N + hd) * sizeof(float);
+  const bool aligned = ld_q % 4 == 0 && ld % 4 == 0 && (((uintptr_t)q | (uintptr_t)k) & 15) == 0;
+  if (hd % 16 == 0 && N <= F32_ATTN_MAX_KEYS && aligned) {
+    const size_t smem = (size_t)(16 * ((N + 15) / 16 * 16 + 4) + 16) * sizeof(float);
+    constexpr int most = (int)((16 * (F32_ATTN_MAX_KEYS + 4) + 16) * sizeof(float));
+    static const hipError_t attr4 = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_f32_attention_mfma<4>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    static const hipError_t attr0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_f32_attention_mfma<0>),
+                                                        hipFuncAttributeMaxDynamicSharedMemorySize, most);
+    if (attr4 == hipSuccess && attr0 == hipSuccess) {
+      const dim3 grid((n_q + 15) / 16, H, T);
+      if (hd == 64) k_f32_attention_mfma<4><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
+      else k_f32_attention_mfma<0><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
+      return;
+    }
+  }
+  const size_t smem = (size_t)(N + hd) * sizeof(float);
   k_f32_attention<<<dim3(n_q, H, T), dim3(128), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, N, hd, scale);
 }
 

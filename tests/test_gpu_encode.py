@@ -211,6 +211,21 @@ def test_seeded_random_descriptions_vs_oracle(case, dtype):
     assert e < tol(desc)
 
 
+@pytest.mark.parametrize("heads,hd,patch,tile,cls,norm", [
+    (1, 64, 7, 56, 1, 0),      # 147-element patch vectors (no 16-byte rows), 65 tokens: one past the 64-key group
+    (6, 64, 14, 70, 0, 1),     # hidden 384: the longest row normalised inside its product; 25 tokens, 9 past a 16-query block
+    (4, 100, 14, 56, 1, 0),    # hidden 400: norm as a launch of its own; head dim no multiple of 16
+    (2, 80, 14, 238, 1, 1),    # 290 tokens: past the 256 keys whose values are fetched ahead; head dim not compiled in
+])
+def test_fp32_products_and_attention_at_their_edges_vs_oracle(heads, hd, patch, tile, cls, norm):
+    """fp32 mode where the tiles, the contraction's four shares and the key groups end unevenly.  Bound: the mode's
+    1e-4 (two layers of sums of at most 400 fp32 terms, 400 x 2^-24 = 2.4e-5 each at worst)."""
+    desc = small_desc(wl.DT_FP32, tile_size=tile, patch=patch, hidden=heads * hd, heads=heads, layers=2, norm=norm,
+                      class_token=cls, pixel_shuffle=0, proj_prenorm=0)
+    got, want = run_case(desc, 61 + hd, 3, [0, 1, 3], std=0.06)
+    assert rel_err(got, want) < tol(desc)
+
+
 @pytest.mark.parametrize("variant", ["plain", "class_token_rms"])
 @pytest.mark.parametrize("dtype", [wl.DT_FP32, wl.DT_BF16])
 def test_residual_stream_layer_by_layer_vs_oracle_trace(dtype, variant):
