@@ -2,6 +2,8 @@
 // fp32 -> bf16 pre-norms (with the optional pixel-shuffle gather in front of
 // the projector), the in-place q/k RMSNorm, weight packing, and the MFMA
 // layout probe.
+#include <cstring>
+
 #include "kernels.h"
 
 namespace epd {
@@ -545,15 +547,9 @@ void scale_vector(float* v, int n, float c, hipStream_t st) {
 // of 16 KiB: a thread issues four 16-byte loads before the four stores, so a
 // wave keeps 4 KiB in flight.  Streaming (nontemporal) on both sides: nothing
 // is read twice.  HBM-bound: every byte is read once and written once.
-__global__ __launch_bounds__(256) void k_mm_copy_blocks(const unsigned char* __restrict__ src_pool,
-                                                        const int* __restrict__ src_ids,
-                                                        unsigned char* __restrict__ dst_pool,
-                                                        const int* __restrict__ dst_ids, long block_bytes,
-                                                        int per_block) {
-  const int b = blockIdx.x / per_block, part = blockIdx.x % per_block;
-  const long sb = src_ids ? src_ids[b] : b, db = dst_ids ? dst_ids[b] : b;
-  const u32x4* s = reinterpret_cast<const u32x4*>(src_pool + sb * block_bytes);
-  u32x4* d = reinterpret_cast<u32x4*>(dst_pool + db * block_bytes);
+__device__ __forceinline__ void copy_block(const unsigned char* src, unsigned char* dst, long block_bytes, int part, int per_block) {
+  const u32x4* s = reinterpret_cast<const u32x4*>(src);
+  u32x4* d = reinterpret_cast<u32x4*>(dst);
   const long n16 = block_bytes >> 4;
   for (long base = (long)part * 1024; base < n16; base += (long)per_block * 1024) {
     const long i = base + threadIdx.x;
@@ -566,16 +562,57 @@ __global__ __launch_bounds__(256) void k_mm_copy_blocks(const unsigned char* __r
       if (i + j * 256 < n16) __builtin_nontemporal_store(v[j], d + i + j * 256);
   }
 }
+__global__ __launch_bounds__(256) void k_mm_copy_blocks(const unsigned char* __restrict__ src_pool,
+                                                        const int* __restrict__ src_ids,
+                                                        unsigned char* __restrict__ dst_pool,
+                                                        const int* __restrict__ dst_ids, long block_bytes,
+                                                        int per_block) {
+  const int b = blockIdx.x / per_block, part = blockIdx.x % per_block;
+  const long sb = src_ids ? src_ids[b] : b, db = dst_ids ? dst_ids[b] : b;
+  copy_block(src_pool + sb * block_bytes, dst_pool + db * block_bytes, block_bytes, part, per_block);
+}
+// The ids ride in the kernel's arguments: n source ids and, when the destination is paged too (PAIRS), n destination ids.
+template <bool PAIRS>
+__global__ __launch_bounds__(256) void k_mm_copy_blocks_args(const MmIdArgs ids, int n, const unsigned char* __restrict__ src_pool,
+                                                             unsigned char* __restrict__ dst_pool, long block_bytes,
+                                                             int per_block) {
+  const int b = blockIdx.x / per_block, part = blockIdx.x % per_block;
+  const long sb = ids.v[b], db = PAIRS ? ids.v[n + b] : b;
+  copy_block(src_pool + sb * block_bytes, dst_pool + db * block_bytes, block_bytes, part, per_block);
+}
+
+static int copy_parts(long block_bytes) {   // one 16 KiB chunk per workgroup while the grid stays modest
+  const long n = ((block_bytes >> 4) + 1023) / 1024;
+  return n < 1 ? 1 : n > 8 ? 8 : (int)n;
+}
 
 void mm_copy_blocks(const void* src_pool, const int* src_ids, void* dst_pool, const int* dst_ids,
                     int n_blocks, long block_bytes, hipStream_t st) {
   if (n_blocks <= 0 || block_bytes <= 0) return;
-  const long n16 = block_bytes >> 4;
-  int per_block = (int)((n16 + 1023) / 1024);  // one 16 KiB chunk per workgroup while the grid stays modest
-  if (per_block < 1) per_block = 1;
-  if (per_block > 8) per_block = 8;
+  const int per_block = copy_parts(block_bytes);
   k_mm_copy_blocks<<<dim3((unsigned)n_blocks * per_block), dim3(256), 0, st>>>(
       (const unsigned char*)src_pool, src_ids, (unsigned char*)dst_pool, dst_ids, block_bytes, per_block);
+}
+
+void mm_copy_blocks_args(const void* src_pool, const int* src_ids, void* dst_pool, const int* dst_ids,
+                         int n_blocks, long block_bytes, hipStream_t st) {
+  if (block_bytes <= 0) return;
+  const int per_block = copy_parts(block_bytes), most = dst_ids ? MM_ARG_IDS / 2 : MM_ARG_IDS;
+  for (int at = 0; at < n_blocks; at += most) {
+    const int n = n_blocks - at < most ? n_blocks - at : most;
+    MmIdArgs ids;
+    memcpy(ids.v, src_ids + at, (size_t)n * sizeof(int));
+    if (dst_ids) memcpy(ids.v + n, dst_ids + at, (size_t)n * sizeof(int));
+    const int used = dst_ids ? 2 * n : n;
+    memset(ids.v + used, 0, (size_t)(MM_ARG_IDS - used) * sizeof(int));
+    const dim3 grid((unsigned)n * per_block);
+    if (dst_ids)
+      k_mm_copy_blocks_args<true><<<grid, dim3(256), 0, st>>>(ids, n, (const unsigned char*)src_pool, (unsigned char*)dst_pool,
+                                                              block_bytes, per_block);
+    else
+      k_mm_copy_blocks_args<false><<<grid, dim3(256), 0, st>>>(ids, n, (const unsigned char*)src_pool,
+                                                               (unsigned char*)dst_pool + (long)at * block_bytes, block_bytes, per_block);
+  }
 }
 
 // ------------------------------------- residual stream <-> paged cache rows ----

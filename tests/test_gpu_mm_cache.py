@@ -158,3 +158,27 @@ def test_paged_encode_leaves_other_blocks_untouched_and_rejects_bad_tables():
     for c in (cache, other, odd):
         c.close()
     enc.close()
+
+
+@pytest.mark.parametrize("n", [1, 448, 449, 896, 897, 1792, 1793])
+def test_copies_of_lists_around_the_argument_limits(n):
+    """Short id lists ride in the arguments of one or several launches (448 pairs or 896 ids each), longer ones are
+    uploaded: the same bytes moved on both sides of each limit, held against plain indexing."""
+    dim, total = 8, 2000
+    src, dst = B.MMCache(total, BT, dim, True), B.MMCache(total, BT, dim, True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    src.pool_tensor().view(torch.int16).copy_(torch.randint(-32768, 32767, (total, BT, dim), dtype=torch.int16, device="cuda", generator=g))
+    dst.pool_tensor().view(torch.int16).fill_(77)
+    rng = np.random.default_rng(n)
+    a, b = np.array(src.alloc(total * BT)), np.array(dst.alloc(total * BT))
+    sa, db = rng.permutation(a)[:n], rng.permutation(b)[:n]
+    src.transfer_to(sa.tolist(), dst, db.tolist())
+    got = src.gather(sa.tolist())
+    torch.cuda.synchronize()
+    want = torch.full((total, BT, dim), 77, dtype=torch.int16, device="cuda")
+    rows = src.pool_tensor().view(torch.int16)[torch.from_numpy(sa).cuda()]
+    want[torch.from_numpy(db).cuda()] = rows
+    assert torch.equal(dst.pool_tensor().view(torch.int16), want)
+    assert torch.equal(got.view(torch.int16).view(n, BT, dim), rows)
+    src.close()
+    dst.close()
