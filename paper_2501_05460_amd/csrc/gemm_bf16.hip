@@ -1391,7 +1391,7 @@ double round_256(double tiles, int K, int epi) {
 // one round of 256 x 192 tiles (residual products only)
 double round_192(double tiles, int K) {
   const double kt = K / BK;
-  return 13.0 + 1.45 * kt + tiles / cu_count() * (6.0 + 0.1 * kt);
+  return 8.0 + 1.42 * kt + tiles / cu_count() * (6.0 + 0.1 * kt);
 }
 // `tiles` tiles in rounds of one per CU
 template <typename F>
@@ -1399,9 +1399,13 @@ double rounds_of(long tiles, F round) {
   const long cus = cu_count(), full = tiles / cus, rem = tiles % cus;
   return full * round((double)cus) + (rem > 0 ? round((double)rem) : 0.0);
 }
+// the rows behind a cut: a second launch, on a chip warm from the first (measured a tenth above the ring's own estimate)
+double behind_cut(const GemmParams& p, long rows_a) {
+  return 4.0 + 1.1 * best_ring(p.M - (int)(rows_a * BM), p.Npad, p.K, p.epi == EPI_BIAS_RESIDUAL).us;
+}
 // The tile rows of a launch of 256 x 256 tiles that go ahead as whole rounds when the rows of its last, partly filled
 // round are cut off as a launch of ring tiles (every form sums an element's k-steps in the same order: same bits).
-// 0: no cut, because the ring launch and the second launch's 2 us would take longer than the partly filled round.  The
+// 0: no cut, because the ring launch would take longer than the partly filled round.  The
 // cut keeps a slice (transposed store) or a cache block (row map) on one side.  FC1 of a 13-slice call of the
 // 1024-wide encoder (832 tiles): 105 + 23 us with 256 x 128 tiles behind the cut, 105 + 15 us with ring tiles.
 long cut_rows(const GemmParams& p) {
@@ -1420,15 +1424,14 @@ long cut_rows(const GemmParams& p) {
   const bool f32_out = p.epi == EPI_BIAS_RESIDUAL;
   if ((gm - rows_a) * gn * 2 > cus) return 0;
   const double whole = rounds_of(tiles, [&](double n) { return round_256(n, p.K, p.epi); });
-  const double cut = rounds_of(rows_a * gn, [&](double n) { return round_256(n, p.K, p.epi); }) + 2.0 +
-                     best_ring(p.M - (int)(rows_a * BM), p.Npad, p.K, f32_out).us;
+  const double cut = rounds_of(rows_a * gn, [&](double n) { return round_256(n, p.K, p.epi); }) + behind_cut(p, rows_a);
   return cut < whole ? rows_a : 0;
 }
 double launch_256(const GemmParams& p) {
   const long gn = p.Npad / 256, gm = (p.M + BM - 1) / BM, rows_a = cut_rows(p);
   auto round = [&](double n) { return round_256(n, p.K, p.epi); };
   if (rows_a == 0) return rounds_of(gm * gn, round);
-  return rounds_of(rows_a * gn, round) + 2.0 + best_ring(p.M - (int)(rows_a * BM), p.Npad, p.K, p.epi == EPI_BIAS_RESIDUAL).us;
+  return rounds_of(rows_a * gn, round) + behind_cut(p, rows_a);
 }
 
 // Activation slabs straight into LDS (no register hop): the persistent kernels (-5 % on the q/k, value and FC1
@@ -1674,7 +1677,7 @@ static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
   bool w192 = false;
   if (residual && persist_res() && tiles_192() && p.N % 192 == 0 && p.N % 256 != 0) {
     const double t = rounds_of(gm * (p.N / 192), [&](double n) { return round_192(n, p.K); });
-    if (t < best) { best = t; w192 = true; }
+    if (t < 1.04 * best) { best = t; w192 = true; }   // the estimates are no closer than that: 23 slices of 729 tokens, FC2 227 us cut, 225 on 192-wide tiles
   }
   if (ring.us < 0.98 * best) return launch_ring(p, ring.tile, st);
   if (w192) return launch_persist_res<192>(p, st);
