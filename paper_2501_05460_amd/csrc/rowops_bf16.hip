@@ -92,6 +92,22 @@ __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
       s += a.x + a.y + a.z + a.w;
     }
   }
+  // Gain and shift are fetched behind the row and in front of its sums: asked for after them, their latency would stand
+  // between the statistics and the store (1024 rows of 1152: 7.7 -> 5.3 us; 106496 rows of 1024: 111 -> 100 us).
+  constexpr bool PRE = NV > 0 && NV <= 8;
+  float4 gpre[PRE ? NV : 1], bpre[PRE ? NV : 1];
+  if constexpr (PRE) {
+    if (p.kind != 2) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i) {
+        const int c = lane + 64 * i;
+        if (c < nchunk) {
+          gpre[i] = *(reinterpret_cast<const float4*>(p.gamma) + c);
+          if (p.kind == 0) bpre[i] = *(reinterpret_cast<const float4*>(p.beta) + c);
+        }
+      }
+    }
+  }
   float mean = 0.f, rstd = 1.f;
   if (p.kind != 2) {
     if (p.kind == 0) mean = wave_sum(s) / p.dim;
@@ -115,16 +131,16 @@ __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
     rstd = 1.0f / sqrtf(wave_sum(qs) / p.dim + p.eps);
   }
   bf16_t* out = p.out + R * p.ld_out;
-  auto emit = [&](int c, float4 a) {
+  auto emit = [&](int c, float4 a, const float4* gk, const float4* bk) {
     float r[4] = {a.x, a.y, a.z, a.w};
     if (p.kind != 2) {
-      const float4 gm = *(reinterpret_cast<const float4*>(p.gamma) + c);
+      const float4 gm = *gk;
       r[0] = (r[0] - mean) * rstd * gm.x;
       r[1] = (r[1] - mean) * rstd * gm.y;
       r[2] = (r[2] - mean) * rstd * gm.z;
       r[3] = (r[3] - mean) * rstd * gm.w;
       if (p.kind == 0) {
-        const float4 bt = *(reinterpret_cast<const float4*>(p.beta) + c);
+        const float4 bt = *bk;
         r[0] += bt.x; r[1] += bt.y; r[2] += bt.z; r[3] += bt.w;
       }
     }
@@ -137,10 +153,14 @@ __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
       const int c = lane + 64 * i;
-      if (c < nchunk) emit(c, v[i]);
+      if (c < nchunk) {
+        if constexpr (PRE) emit(c, v[i], &gpre[i], &bpre[i]);
+        else emit(c, v[i], reinterpret_cast<const float4*>(p.gamma) + c, reinterpret_cast<const float4*>(p.beta) + c);
+      }
     }
   } else {
-    for (int c = lane; c < nchunk; c += 64) emit(c, *src(c));
+    for (int c = lane; c < nchunk; c += 64)
+      emit(c, *src(c), reinterpret_cast<const float4*>(p.gamma) + c, reinterpret_cast<const float4*>(p.beta) + c);
   }
 }
 
