@@ -75,6 +75,20 @@ __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) v[i] = lane + 64 * i < nchunk ? load(lane + 64 * i) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
+  // gain and shift in front of the sums: behind them their latency would stand between the statistics and the store (26624
+  // rows of 1024: 33.7 -> 30.1 us)
+  constexpr bool PRE = NV > 0 && NV <= 8;
+  float4 gpre[PRE ? NV : 1], bpre[PRE ? NV : 1];
+  if constexpr (PRE) {
+    if (p.kind != 2) {
+#pragma unroll
+      for (int i = 0; i < NV; ++i)
+        if (lane + 64 * i < nchunk) {
+          gpre[i] = *(reinterpret_cast<const float4*>(p.gamma) + lane + 64 * i);
+          if (p.kind == 0) bpre[i] = *(reinterpret_cast<const float4*>(p.beta) + lane + 64 * i);
+        }
+    }
+  }
   float mean = 0.f, rstd = 1.f;
   if (p.kind != 2) {
     float s = 0.f;
@@ -103,16 +117,16 @@ __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
   }
   unsigned* codes = reinterpret_cast<unsigned*>(p.codes + R * p.ld_codes);
   // every lane of the wave takes part (the exchanges below are wave-wide); lanes past the row carry zeros
-  auto emit = [&](int c, float4 a, bool in_row) {
+  auto emit = [&](int c, float4 a, bool in_row, const float4* gk, const float4* bk) {
     float r[4] = {a.x, a.y, a.z, a.w};
     if (p.kind != 2 && in_row) {
-      const float4 gm = *(reinterpret_cast<const float4*>(p.gamma) + c);
+      const float4 gm = *gk;
       r[0] = (r[0] - mean) * rstd * gm.x;
       r[1] = (r[1] - mean) * rstd * gm.y;
       r[2] = (r[2] - mean) * rstd * gm.z;
       r[3] = (r[3] - mean) * rstd * gm.w;
       if (p.kind == 0) {
-        const float4 bt = *(reinterpret_cast<const float4*>(p.beta) + c);
+        const float4 bt = *bk;
         r[0] += bt.x; r[1] += bt.y; r[2] += bt.z; r[3] += bt.w;
       }
     }
@@ -133,11 +147,16 @@ __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
   if (NV > 0) {
 #pragma unroll
     for (int i = 0; i < NV; ++i)
-      if (64 * i < nchunk) emit(lane + 64 * i, v[i], lane + 64 * i < nchunk);
+      if (64 * i < nchunk) {
+        if constexpr (PRE) emit(lane + 64 * i, v[i], lane + 64 * i < nchunk, &gpre[i], &bpre[i]);
+        else emit(lane + 64 * i, v[i], lane + 64 * i < nchunk, reinterpret_cast<const float4*>(p.gamma) + lane + 64 * i,
+                  reinterpret_cast<const float4*>(p.beta) + lane + 64 * i);
+      }
   } else {
     for (int c0 = 0; c0 < nchunk; c0 += 64) {
       const bool in_row = c0 + lane < nchunk;
-      emit(c0 + lane, in_row ? load(c0 + lane) : make_float4(0.f, 0.f, 0.f, 0.f), in_row);
+      emit(c0 + lane, in_row ? load(c0 + lane) : make_float4(0.f, 0.f, 0.f, 0.f), in_row,
+           reinterpret_cast<const float4*>(p.gamma) + c0 + lane, reinterpret_cast<const float4*>(p.beta) + c0 + lane);
     }
   }
 }
