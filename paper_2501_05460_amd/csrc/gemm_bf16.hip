@@ -1638,6 +1638,7 @@ hipError_t bf16_gemm_init() {
   if ((e = set_attr_all<128, 512, 64>()) != hipSuccess) return e;
   if ((e = set_attr_128_fold<0>()) != hipSuccess) return e;
   if ((e = set_attr_128_fold<2>()) != hipSuccess) return e;
+  if ((e = bf16_gemm_ring_init()) != hipSuccess) return e;
   return hipSuccess;
 }
 

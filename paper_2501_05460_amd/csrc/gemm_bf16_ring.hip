@@ -339,16 +339,23 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
 template <int EPI, bool DUAL, int WTM, int WTN, int RING, int OCC>
 hipError_t launch_ring(const GemmParams& p, hipStream_t st) {
   constexpr int TM = 64 * WTM, TN = 64 * WTN;
-  // once per instantiation; the initialisation of a function-local static is safe against concurrent callers
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_ring<EPI, DUAL, WTM, WTN, RING, OCC>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_lds<WTM, WTN, RING>());
-  if (attr != hipSuccess) return attr;
   if (p.Npad % TN != 0 || p.n2_pad % TN != 0) return hipErrorInvalidValue;
   const int gm = (p.M + TM - 1) / TM, gn = (p.Npad + (DUAL ? p.n2_pad : 0)) / TN;
   if (gm * gn == 0) return hipSuccess;
   // bands of eight tile columns: within 2 % of four at any size, 4 % ahead on average with 128 x 64 tiles
   k_gemm_bf16_ring<EPI, DUAL, WTM, WTN, RING, OCC><<<dim3(gm * gn), dim3(256), ring_lds<WTM, WTN, RING>(), st>>>(p, gm, gn < 8 ? gn : 8);
   return hipGetLastError();
+}
+template <int EPI, bool DUAL, int WTM, int WTN, int RING, int OCC>
+hipError_t set_attr_ring() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_ring<EPI, DUAL, WTM, WTN, RING, OCC>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)ring_lds<WTM, WTN, RING>());
+}
+template <int EPI, bool DUAL = false>
+hipError_t set_attr_tiles() {
+  hipError_t e = set_attr_ring<EPI, DUAL, 1, 1, 4, 2>();
+  if (e == hipSuccess) e = set_attr_ring<EPI, DUAL, 2, 1, 3, 2>();
+  return e != hipSuccess ? e : set_attr_ring<EPI, DUAL, 2, 2, 4, 1>();
 }
 template <int EPI, bool DUAL = false>
 hipError_t launch_tile(const GemmParams& p, int tile, hipStream_t st) {
@@ -360,6 +367,16 @@ hipError_t launch_tile(const GemmParams& p, int tile, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 }  // namespace
+
+hipError_t bf16_gemm_ring_init() {
+  hipError_t e = set_attr_tiles<EPI_BIAS>();
+  if (e == hipSuccess) e = set_attr_tiles<EPI_BIAS, true>();
+  if (e == hipSuccess) e = set_attr_tiles<EPI_BIAS_GELU_ERF>();
+  if (e == hipSuccess) e = set_attr_tiles<EPI_BIAS_GELU_TANH>();
+  if (e == hipSuccess) e = set_attr_tiles<EPI_BIAS_RESIDUAL>();
+  if (e == hipSuccess) e = set_attr_tiles<EPI_BIAS_POS>();
+  return e != hipSuccess ? e : set_attr_tiles<EPI_VT>();
+}
 
 hipError_t bf16_gemm_ring(const GemmParams& p, int tile, hipStream_t st) {
   if (p.stats || p.xb) return hipErrorInvalidValue;   // neither the folded pre-norm nor the bf16 copy of the residual rows
