@@ -55,7 +55,10 @@ __device__ __forceinline__ float max4abs(float a, float b, float c, float d) {
 // One wave per row; lane l owns the 4-element chunks l + 64 i, so a block of 32 elements is 8 neighbouring
 // lanes and a slab of 128 elements the 32 lanes of a half-wave.  The row stays in registers (NV chunks per
 // lane; NV = 0: read again for every pass).
-template <bool IN_BF16, int NV>
+// PRE (a norm, kind 0 or 1): gain and shift are fetched in front of the sums.  It pays while they fit beside the row, with
+// NV the row's own count of chunks (65536 rows of 768 | 1024 | 1152 in us: 45.3 -> 44.4 | 55.9 -> 53.6 | 65.2 -> 64.2,
+// 1152 with NV = 8 77.7); at six chunks and more it loses (1536 | 2048: 94.3 -> 96.2 | 128.7 -> 137.5).
+template <bool IN_BF16, int NV, bool PRE>
 __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
   const long R = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (R >= p.rows) return;
@@ -75,19 +78,15 @@ __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
 #pragma unroll
     for (int i = 0; i < NV; ++i) v[i] = lane + 64 * i < nchunk ? load(lane + 64 * i) : make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  // gain and shift in front of the sums: behind them their latency would stand between the statistics and the store (26624
-  // rows of 1024: 33.7 -> 30.1 us)
-  constexpr bool PRE = NV > 0 && NV <= 8;
+  // gain and shift in front of the sums: behind them their latency would stand between the statistics and the store
   float4 gpre[PRE ? NV : 1], bpre[PRE ? NV : 1];
   if constexpr (PRE) {
-    if (p.kind != 2) {
 #pragma unroll
-      for (int i = 0; i < NV; ++i)
-        if (lane + 64 * i < nchunk) {
-          gpre[i] = *(reinterpret_cast<const float4*>(p.gamma) + lane + 64 * i);
-          if (p.kind == 0) bpre[i] = *(reinterpret_cast<const float4*>(p.beta) + lane + 64 * i);
-        }
-    }
+    for (int i = 0; i < NV; ++i)
+      if (lane + 64 * i < nchunk) {
+        gpre[i] = *(reinterpret_cast<const float4*>(p.gamma) + lane + 64 * i);
+        if (p.kind == 0) bpre[i] = *(reinterpret_cast<const float4*>(p.beta) + lane + 64 * i);
+      }
   }
   float mean = 0.f, rstd = 1.f;
   if (p.kind != 2) {
@@ -118,6 +117,7 @@ __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
   unsigned* codes = reinterpret_cast<unsigned*>(p.codes + R * p.ld_codes);
   // every lane of the wave takes part (the exchanges below are wave-wide); lanes past the row carry zeros
   auto emit = [&](int c, float4 a, bool in_row, const float4* gk, const float4* bk) {
+#pragma clang fp contract(off)   // the same bits for every NV
     float r[4] = {a.x, a.y, a.z, a.w};
     if (p.kind != 2 && in_row) {
       const float4 gm = *gk;
@@ -532,11 +532,21 @@ hipError_t mx_rows(const MxRowParams& p, hipStream_t st) {
     return hipErrorInvalidValue;
   const dim3 grid((unsigned)((p.rows + 3) / 4)), block(256);
   const int per_lane = (p.dim / 4 + 63) / 64;
-#define MX_ROWS(BF, NV) k_mx_rows<BF, NV><<<grid, block, 0, st>>>(p)
+#define MX_ROWS(BF, NV, PRE) k_mx_rows<BF, NV, PRE><<<grid, block, 0, st>>>(p)
   if (p.in_bf16) {
-    if (per_lane <= 4) MX_ROWS(true, 4); else if (per_lane <= 8) MX_ROWS(true, 8); else if (per_lane <= 16) MX_ROWS(true, 16); else MX_ROWS(true, 0);
+    if (per_lane <= 4) MX_ROWS(true, 4, false); else if (per_lane <= 8) MX_ROWS(true, 8, false);
+    else if (per_lane <= 16) MX_ROWS(true, 16, false); else MX_ROWS(true, 0, false);
+  } else if (p.kind != 2 && per_lane <= 5) {
+    switch (per_lane) {
+      case 1: MX_ROWS(false, 1, true); break;
+      case 2: MX_ROWS(false, 2, true); break;
+      case 3: MX_ROWS(false, 3, true); break;
+      case 4: MX_ROWS(false, 4, true); break;
+      case 5: MX_ROWS(false, 5, true); break;
+    }
   } else {
-    if (per_lane <= 4) MX_ROWS(false, 4); else if (per_lane <= 8) MX_ROWS(false, 8); else if (per_lane <= 16) MX_ROWS(false, 16); else MX_ROWS(false, 0);
+    if (per_lane <= 4) MX_ROWS(false, 4, false); else if (per_lane <= 8) MX_ROWS(false, 8, false);
+    else if (per_lane <= 16) MX_ROWS(false, 16, false); else MX_ROWS(false, 0, false);
   }
 #undef MX_ROWS
   return hipGetLastError();

@@ -44,7 +44,13 @@ void bf16_im2col(const float* tiles, bf16_t* A, int lda, int T, int S, int p, hi
 // ------------------------------------------------------------- row norms ----
 // One wave per output row, rows of `dim` floats (dim % 4 == 0) held in
 // registers when they fit (NV float4 per lane), otherwise re-read.
-template <int NV>
+// NORM: 0 conversion only (kind 2), 1 a norm, its gain and shift read after the statistics, 2 a norm whose gain and shift
+// are fetched behind the row and in front of its sums, so that their latency does not stand between the statistics and
+// the store.  NORM 2 pays when NV is the row's own count of chunks: every register that holds no part of the row costs
+// as much as one that does (65536 rows of 1152, in us: NORM 1 69.1, NORM 2 65.0 with NV = 5 and 79.0 with NV = 8; 32768
+// rows of 1024, NV = 4: 35.0 -> 30.4; 1024 rows of 1152: 7.5 -> 7.1).  At 13 chunks and more it loses (32768 rows of 3200:
+// 117 -> 138).
+template <int NV, int NORM>
 __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
   const long R = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (R >= p.rows) return;
@@ -92,24 +98,21 @@ __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
       s += a.x + a.y + a.z + a.w;
     }
   }
-  // Gain and shift are fetched behind the row and in front of its sums: asked for after them, their latency would stand
-  // between the statistics and the store (1024 rows of 1152: 7.7 -> 5.3 us; 106496 rows of 1024: 111 -> 100 us).
-  constexpr bool PRE = NV > 0 && NV <= 8;   // at 16 chunks per lane the registers cost more (40960 rows of 3200: 133 -> 139 us)
+  constexpr bool PRE = NORM == 2;
+  static_assert(!PRE || NV > 0, "the row sits in registers");
   float4 gpre[PRE ? NV : 1], bpre[PRE ? NV : 1];
   if constexpr (PRE) {
-    if (p.kind != 2) {
 #pragma unroll
-      for (int i = 0; i < NV; ++i) {
-        const int c = lane + 64 * i;
-        if (c < nchunk) {
-          gpre[i] = *(reinterpret_cast<const float4*>(p.gamma) + c);
-          if (p.kind == 0) bpre[i] = *(reinterpret_cast<const float4*>(p.beta) + c);
-        }
+    for (int i = 0; i < NV; ++i) {
+      const int c = lane + 64 * i;
+      if (c < nchunk) {
+        gpre[i] = *(reinterpret_cast<const float4*>(p.gamma) + c);
+        if (p.kind == 0) bpre[i] = *(reinterpret_cast<const float4*>(p.beta) + c);
       }
     }
   }
   float mean = 0.f, rstd = 1.f;
-  if (p.kind != 2) {
+  if (NORM) {
     if (p.kind == 0) mean = wave_sum(s) / p.dim;
     float qs = 0.f;
     if (NV > 0) {
@@ -132,8 +135,9 @@ __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
   }
   bf16_t* out = p.out + R * p.ld_out;
   auto emit = [&](int c, float4 a, const float4* gk, const float4* bk) {
+#pragma clang fp contract(off)   // no gain-and-shift fma in some chunks and not in others: the same bits for every NV
     float r[4] = {a.x, a.y, a.z, a.w};
-    if (p.kind != 2) {
+    if (NORM) {
       const float4 gm = *gk;
       r[0] = (r[0] - mean) * rstd * gm.x;
       r[1] = (r[1] - mean) * rstd * gm.y;
@@ -168,10 +172,23 @@ void bf16_rowop(const RowOpParams& p, hipStream_t st) {
   if (p.rows == 0) return;
   dim3 grid((unsigned)((p.rows + 3) / 4)), block(256);
   const int per_lane = (p.dim / 4 + 63) / 64;
-  if (per_lane <= 4) k_bf16_rowop<4><<<grid, block, 0, st>>>(p);
-  else if (per_lane <= 8) k_bf16_rowop<8><<<grid, block, 0, st>>>(p);
-  else if (per_lane <= 16) k_bf16_rowop<16><<<grid, block, 0, st>>>(p);
-  else k_bf16_rowop<0><<<grid, block, 0, st>>>(p);
+#define ROWOP(NV, NORM) k_bf16_rowop<NV, NORM><<<grid, block, 0, st>>>(p)
+  if (p.kind == 2) {
+    if (per_lane <= 4) ROWOP(4, 0); else if (per_lane <= 8) ROWOP(8, 0); else if (per_lane <= 16) ROWOP(16, 0); else ROWOP(0, 0);
+    return;
+  }
+  switch (per_lane) {
+    case 1: ROWOP(1, 2); break;
+    case 2: ROWOP(2, 2); break;
+    case 3: ROWOP(3, 2); break;
+    case 4: ROWOP(4, 2); break;
+    case 5: ROWOP(5, 2); break;
+    case 6: ROWOP(6, 2); break;
+    case 7: ROWOP(7, 2); break;
+    case 8: ROWOP(8, 2); break;
+    default: if (per_lane <= 16) ROWOP(16, 1); else ROWOP(0, 1);
+  }
+#undef ROWOP
 }
 
 // ---------------------------------------- pre-norm of bf16 rows, in place ----

@@ -211,6 +211,16 @@ def test_seeded_random_descriptions_vs_oracle(case, dtype):
     assert e < tol(desc)
 
 
+@pytest.mark.parametrize("heads,hd", [(1, 64), (4, 128), (9, 72), (8, 128), (9, 128), (21, 72), (13, 128), (16, 128), (18, 128)])
+def test_pre_norms_at_every_register_count_vs_oracle(heads, hd):
+    """bf16 pre-norms over rows of 1 to 9 chunks of 256 elements (up to eight sit in registers with their gain and shift),
+    whole and ending inside a chunk, LayerNorm and RMSNorm.  Bound: the mode's 2e-2."""
+    for norm in (wl.NORM_LAYERNORM, wl.NORM_RMSNORM):
+        desc = small_desc(wl.DT_BF16, tile_size=56, hidden=heads * hd, heads=heads, mlp=64, layers=1, norm=norm)
+        got, want = run_case(desc, 17 + heads, 2, [0, 2], std=0.05)
+        assert rel_err(got, want) < tol(desc)
+
+
 @pytest.mark.parametrize("heads,hd,patch,tile,cls,norm", [
     (1, 64, 7, 56, 1, 0),      # 147-element patch vectors (no 16-byte rows), 65 tokens: one past the 64-key group
     (6, 64, 14, 70, 0, 1),     # hidden 384: the longest row normalised inside its product; 25 tokens, 9 past a 16-query block

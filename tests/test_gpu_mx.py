@@ -146,6 +146,14 @@ def test_norm_then_conversion_vs_oracle(kind, dim):
     assert rel_err(val, ref) < 0.126
 
 
+@pytest.mark.parametrize("dim", [256, 512, 640, 768, 1280, 1408])
+def test_norm_then_conversion_at_every_register_count(dim):
+    """One to five chunks of a row per lane with gain and shift held beside it, six without; 640 and 1408 end inside a
+    chunk's 64 lanes.  The bounds are those of the test above."""
+    for kind in (0, 1):
+        test_norm_then_conversion_vs_oracle(kind, dim)
+
+
 def _mx_operands(rng, M, N, K, std_w=0.05):
     x = rng.normal(size=(M, K)) * np.exp(rng.uniform(-2, 2, size=(M, K // 32)).repeat(32, axis=1))
     w = rng.normal(size=(N, K)) * std_w
