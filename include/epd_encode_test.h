@@ -45,6 +45,12 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
                                  int32_t M, int32_t N, int32_t K, int32_t epi, int32_t form,
                                  void* hip_stream);
 
+/* Which form the library takes for a product of M rows, N columns (padded as the library pads its weights) and K, by
+ * epilogue as above and 4 = patch embedding, 5 = value projection (slices of n_tok rows each): *form as above (9 / 10 / 7
+ * for 256x256 tiles, 0: whole 256-wide tile columns and the rest apart); *rows: the rows in front of a row cut, M
+ * without one.  Host only: launches nothing, and counts 256 CUs where there is no device. */
+epd_status epd_op_gemm_bf16_choice(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t n_tok, int32_t* form, int32_t* rows);
+
 /* The pre-norms of a layer have no kernel of their own in bf16 mode: the residual epilogue that updates a row
  * x also stores bf16(x) and the row's statistics, and the product that follows the norm runs on bf16(x) against
  * weights that carry the norm's gain, applying mean and 1 / sqrt(variance + eps) in its epilogue.  Statistics of

@@ -32,7 +32,8 @@ PROF_FAMILIES = ("embed", "norm", "gemm_qkv", "attention", "qk_norm", "proj_inpu
 EXPORTS = (
     "epd_weight_count", "epd_check_desc", "epd_check_offsets", "epd_create", "epd_encode",
     "epd_encode_range", "epd_tokens_per_tile", "epd_out_dim", "epd_last_error", "epd_destroy",
-    "epd_debug_read_stream", "epd_op_gemm_bf16", "epd_op_gemm_bf16_form", "epd_op_attention_bf16", "epd_op_mfma_probe",
+    "epd_debug_read_stream", "epd_op_gemm_bf16", "epd_op_gemm_bf16_form", "epd_op_gemm_bf16_choice",
+    "epd_op_attention_bf16", "epd_op_mfma_probe",
     "epd_profile_enable", "epd_profile_read", "epd_op_mfma_peak", "epd_op_copy_peak", "epd_op_coissue",
     "epd_op_row_stats", "epd_op_gemm_residual_stats", "epd_op_norm_gemm_bf16",
     "epd_op_mx_rows", "epd_op_mx_gemm", "epd_op_mx_mfma_probe", "epd_op_attention_mx",
@@ -99,6 +100,8 @@ def lib() -> ctypes.CDLL:
         L.epd_op_gemm_bf16.restype = i32
         L.epd_op_gemm_bf16_form.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]
         L.epd_op_gemm_bf16_form.restype = i32
+        L.epd_op_gemm_bf16_choice.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+        L.epd_op_gemm_bf16_choice.restype = i32
         L.epd_op_attention_bf16.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
         L.epd_op_attention_bf16.restype = i32
         L.epd_op_mfma_probe.argtypes = [vp, vp, vp, vp]
@@ -402,6 +405,15 @@ def op_gemm_bf16(A: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tensor],
     if s != EPD_OK:
         raise EpdError(s, lib().epd_last_error(None).decode())
     return C, ms.value
+
+
+def op_gemm_bf16_choice(M: int, N: int, K: int, epi: int, n_tok: int = 1):
+    """(form, rows in front of a row cut) the library takes for a product of this shape; host only."""
+    form, rows = ctypes.c_int32(), ctypes.c_int32()
+    s = lib().epd_op_gemm_bf16_choice(M, N, K, epi, n_tok, ctypes.byref(form), ctypes.byref(rows))
+    if s != EPD_OK:
+        raise EpdError(s, lib().epd_last_error(None).decode())
+    return form.value, rows.value
 
 
 def op_gemm_bf16_form(A: torch.Tensor, W: torch.Tensor, bias: torch.Tensor, epi: int, form: int,

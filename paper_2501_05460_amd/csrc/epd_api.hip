@@ -1400,6 +1400,20 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
   return EPD_OK;
 }
 
+epd_status epd_op_gemm_bf16_choice(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t n_tok, int32_t* form, int32_t* rows) {
+  if (!form || !rows || M <= 0 || N <= 0 || N % 4 || K <= 0 || K % 128 || epi < EPI_BIAS || epi > EPI_VT || (epi == EPI_VT && n_tok <= 0)) {
+    set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_choice: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  GemmParams p;
+  memset(&p, 0, sizeof(p));
+  p.epi = epi; p.M = M; p.N = N; p.K = K; p.Npad = pad_n(N); p.n_tok = n_tok;
+  long front = 0;
+  *form = bf16_gemm_choice(p, &front);
+  *rows = (int32_t)front;
+  return EPD_OK;
+}
+
 epd_status epd_op_row_stats(const float* x, int64_t rows, int32_t dim, void* xb, float* stats, void* hip_stream) {
   if (!x || !xb || !stats || rows < 0 || dim <= 0 || dim % 4) return EPD_ERR_INVALID_ARG;
   bf16_row_stats(x, dim, rows, dim, (bf16_t*)xb, dim, stats, (dim + STAT_GROUP - 1) / STAT_GROUP, (hipStream_t)hip_stream);

@@ -1360,38 +1360,64 @@ int cu_count() {
 
 // the ring kernel has neither the folded pre-norm nor the bf16 copy of the residual rows
 bool ring_has(const GemmParams& p) { return !p.stats && !p.xb; }
+
+// Tile columns that hold nothing but padding are not launched by the 64- and 128-wide forms: a width of 1152 is padded to
+// 1280 and has nine columns of 128 (residual products of 5888 rows of the SigLIP shape, ten columns: 33 + 94 us, nine: 32
+// + 90).  A second product begins behind the padded first one.
+int whole_128(int n) { return (n + 127) / 128 * 128; }
+GemmParams without_padded_columns(GemmParams p) {
+  if (p.n2_pad > 0) p.n2_pad = whole_128(p.n2);
+  else p.Npad = whole_128(p.N);
+  return p;
+}
 hipError_t launch_ring(const GemmParams& p, int tile, hipStream_t st) {
   ++g_kernel_launches;
-  return bf16_gemm_ring(p, tile, st);
+  return bf16_gemm_ring(without_padded_columns(p), tile, st);
 }
 
 // Times of a product by form, in microseconds, as the dispatch compares them.  Fitted to the products of the running
-// encoder (three shapes, 1-20 slices, weights cold; each within 15 %, most within 5 %): a workgroup's chain of KT
-// 64-deep slabs plus its fixed cost (first slab, epilogue), times the rounds the launch's tiles make on the CUs.
-// FC2 of a 1024 / 4096 wide encoder, 64 x 64 | 128 x 64 | 128 x 128 tiles: one slice 23 | 33 | 41, three 45 | 42 | 48,
-// seven 96 | 85 | 81 us; the forms before them 24, 56 and 89.
+// encoder, each form forced for one product at a time (three shapes, 256 to 65536 rows, K 1024 to 12800, weights cold; half
+// of them within 2-4 %, rms 4-7 %): a workgroup's chain of KT 64-deep slabs plus its fixed cost (first slab, epilogue),
+// times the rounds the launch's tiles make on the CUs, and a part that grows with the tiles alone (the CUs share memory
+// and power).  Of 385 products measured in all forms, the one taken is within 3 % of the fastest for 87 %, within 5 % for 95 %.
 struct RingPick { int tile; double us; };
-RingPick best_ring(int M, int n_cols, int K, bool f32_out) {
+bool f32_rows(int epi) { return epi == EPI_BIAS_RESIDUAL || epi == EPI_BIAS_POS; }   // reads and writes rows of the stream
+bool has_gelu(int epi) { return epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH; }
+RingPick best_ring(int M, int n_cols, int K, int epi) {
   const double cus = cu_count(), kt = K / BK;
+  const bool f32 = f32_rows(epi);
   auto per_cu = [&](int tm, int tn) { return (double)((M + tm - 1) / tm) * ((n_cols + tn - 1) / tn) / cus; };
-  RingPick best = {RING_64x64, 4.0 + 0.1 * kt + fmax(1.0, per_cu(64, 64)) * (1.0 + 0.185 * kt)};
+  const double t0 = f32 ? 6.0 + 0.09 * kt + fmax(1.0, per_cu(64, 64)) * (0.4 + 0.217 * kt)
+                        : 5.0 + 0.12 * kt + fmax(1.0, per_cu(64, 64)) * 0.198 * kt;
+  RingPick best = {RING_64x64, t0};
   const double r1 = ceil(per_cu(128, 64));   // two workgroups share a CU: a tile alone on its CU takes 3/4 of two
-  const double t1 = 3.0 + (r1 == 1.0 ? 0.48 * kt + (f32_out ? 2.0 : 0.5) : r1 * ((f32_out ? 2.1 : 0.5) + 0.325 * kt));
+  const double t1 = f32 ? 6.2 + (r1 == 1.0 ? 0.15 + 0.445 * kt : r1 * (1.2 + 0.33 * kt))
+                        : 5.4 + (r1 == 1.0 ? 0.35 + 0.42 * kt : r1 * (0.27 + 0.315 * kt)) + (has_gelu(epi) ? 0.8 : 0.0);
   if (t1 < best.us) best = {RING_128x64, t1};
-  const double t2 = 1.0 + ceil(per_cu(128, 128)) * (f32_out ? 8.0 + 0.5 * kt : 5.0 + 0.45 * kt);
+  const double r2 = per_cu(128, 128);
+  const double t2 = f32 ? 5.5 + ceil(r2) * (4.5 + 0.4 * kt) + r2 * 0.187 * kt
+                        : 5.8 + ceil(r2) * (2.3 + 0.34 * kt) + r2 * 0.18 * kt + (has_gelu(epi) ? 1.7 : 0.0);
   if (t2 < best.us) best = {RING_128x128, t2};
   return best;
 }
-// one round of 256 x 256 tiles, `tiles` of them (the CUs share the power budget: a full round takes longer)
+// one round of 256 x 256 tiles, `tiles` of them
 double round_256(double tiles, int K, int epi) {
   const double kt = K / BK, fill = tiles / cu_count();
-  if (epi == EPI_BIAS_RESIDUAL || epi == EPI_BIAS_POS) return 15.0 + 1.65 * kt + fill * (8.0 + 0.15 * kt);
-  return 2.0 + 1.78 * kt + fill * 4.0 + (epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH ? 3.0 : 0.0);
+  if (f32_rows(epi)) return 18.0 + 1.36 * kt + fill * (1.0 + 0.29 * kt);
+  return 9.0 + 1.45 * kt + fill * (0.02 * kt - 1.0) + (has_gelu(epi) ? 1.4 : 0.0);
 }
 // one round of 256 x 192 tiles (residual products only)
 double round_192(double tiles, int K) {
   const double kt = K / BK;
-  return 8.0 + 1.42 * kt + tiles / cu_count() * (6.0 + 0.1 * kt);
+  return 13.7 + 1.27 * kt + tiles / cu_count() * (0.234 * kt - 0.5);
+}
+// 256 x 128 tiles, one workgroup per CU: a launch that is one round of them (6400 columns over 1024 rows of K = 3200: 55 us,
+// 68 on 128 x 128 ring tiles; 1152 columns over 5888 rows of K = 4352: 88 against 93); not launched for more
+double one_round_128(const GemmParams& p) {
+  const double kt = p.K / BK, tiles = (double)((p.M + BM - 1) / BM) * (whole_128(p.N) / 128), fill = tiles / cu_count();
+  if (fill > 1.0) return INFINITY;
+  if (f32_rows(p.epi)) return 16.6 + 0.765 * kt + fill * (5.5 + 0.253 * kt);
+  return 7.5 + 0.79 * kt + fill * (0.3 + 0.247 * kt) + (has_gelu(p.epi) ? 1.8 : 0.0);
 }
 // `tiles` tiles in rounds of one per CU
 template <typename F>
@@ -1399,15 +1425,16 @@ double rounds_of(long tiles, F round) {
   const long cus = cu_count(), full = tiles / cus, rem = tiles % cus;
   return full * round((double)cus) + (rem > 0 ? round((double)rem) : 0.0);
 }
-// the rows behind a cut: a second launch, on a chip warm from the first (measured a tenth above the ring's own estimate)
+// The rows behind a cut, as a second launch.  Ring tiles always: 256 x 128 tiles there were measured beside them on 230
+// products, up to 54 us slower and never more than 5 us (0.5 %) faster (3072 rows of 2304 columns, K = 1152, one whole round
+// of them: equal; FC1 of a 13-slice call of the 1024-wide encoder: 128 against 120 us with its 3 whole rounds).
 double behind_cut(const GemmParams& p, long rows_a) {
-  return 4.0 + 1.1 * best_ring(p.M - (int)(rows_a * BM), p.Npad, p.K, p.epi == EPI_BIAS_RESIDUAL).us;
+  return 4.0 + best_ring(p.M - (int)(rows_a * BM), p.N, p.K, p.epi).us;
 }
 // The tile rows of a launch of 256 x 256 tiles that go ahead as whole rounds when the rows of its last, partly filled
 // round are cut off as a launch of ring tiles (every form sums an element's k-steps in the same order: same bits).
 // 0: no cut, because the ring launch would take longer than the partly filled round.  The
-// cut keeps a slice (transposed store) or a cache block (row map) on one side.  FC1 of a 13-slice call of the
-// 1024-wide encoder (832 tiles): 105 + 23 us with 256 x 128 tiles behind the cut, 105 + 15 us with ring tiles.
+// cut keeps a slice (transposed store) or a cache block (row map) on one side.
 long cut_rows(const GemmParams& p) {
   const long cus = cu_count(), gn = p.Npad / 256, gm = (p.M + BM - 1) / BM, tiles = gm * gn, full = tiles / cus, rem = tiles % cus;
   if (full < 1 || rem == 0 || p.epi == EPI_BIAS_POS) return 0;
@@ -1421,17 +1448,9 @@ long cut_rows(const GemmParams& p) {
   rows_a -= rows_a % unit;
   if (rows_a < 1 || rows_a >= gm) return 0;
   if (p.row_map && (p.block_tokens < 1 || (rows_a * BM) % p.block_tokens != 0)) return 0;
-  const bool f32_out = p.epi == EPI_BIAS_RESIDUAL;
   if ((gm - rows_a) * gn * 2 > cus) return 0;
-  const double whole = rounds_of(tiles, [&](double n) { return round_256(n, p.K, p.epi); });
-  const double cut = rounds_of(rows_a * gn, [&](double n) { return round_256(n, p.K, p.epi); }) + behind_cut(p, rows_a);
-  return cut < whole ? rows_a : 0;
-}
-double launch_256(const GemmParams& p) {
-  const long gn = p.Npad / 256, gm = (p.M + BM - 1) / BM, rows_a = cut_rows(p);
   auto round = [&](double n) { return round_256(n, p.K, p.epi); };
-  if (rows_a == 0) return rounds_of(gm * gn, round);
-  return rounds_of(rows_a * gn, round) + behind_cut(p, rows_a);
+  return rounds_of(rows_a * gn, round) + behind_cut(p, rows_a) < rounds_of(tiles, round) ? rows_a : 0;
 }
 
 // Activation slabs straight into LDS (no register hop): the persistent kernels (-5 % on the q/k, value and FC1
@@ -1604,20 +1623,6 @@ hipError_t set_attr_128_fold() {
 
 long bf16_gemm_kernel_launches() { return g_kernel_launches; }
 
-// The q/k and the value projection as one launch of ring tiles, where that is estimated to take less than the two
-// launches each in its own best form (1024-wide encoder, us per layer: one slice 21.0 -> 15.2, five 58.9 -> 45.6, ten
-// 93.7 -> 82.2; 13 slices 98.3 as two launches, 105 as one).
-bool bf16_gemm_pair_fits(const GemmParams& p) {
-  if (p.cfg != 0 || p.epi != EPI_BIAS || p.n2_pad <= 0 || p.n2_pad % 128 != 0 || p.Npad % 128 != 0 || !ring_has(p)) return false;
-  GemmParams q = p, v = p;
-  q.n2_pad = v.n2_pad = 0; v.epi = EPI_VT; v.Npad = p.n2_pad;
-  auto alone = [](const GemmParams& g) {
-    const double ring = best_ring(g.M, g.Npad, g.K, false).us;
-    return g.Npad % 256 == 0 ? fmin(ring, launch_256(g)) : ring;
-  };
-  return best_ring(p.M, p.Npad + p.n2_pad, p.K, false).us < alone(q) + alone(v);
-}
-
 hipError_t bf16_gemm_init() {
   hipError_t e = set_attr_all<256, 512, 64>();
   if (e != hipSuccess) return e;
@@ -1642,63 +1647,102 @@ hipError_t bf16_gemm_init() {
   return hipSuccess;
 }
 
-// Products without a folded pre-norm or emitted rows: the form with the smallest estimated time (best_ring, round_256,
-// round_192).  All forms leave the same bits: a tile shape changes which lane holds an element, never the order in
-// which its k-steps are summed.
-static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
+// Products without a folded pre-norm or emitted rows: the form with the smallest estimated time.  All forms leave the same
+// bits: a tile shape changes which lane holds an element, never the order in which its k-steps are summed.
+enum PlainForm { PLAIN_RING, PLAIN_256x128, PLAIN_256, PLAIN_192, PLAIN_COLUMNS };
+struct Plain { PlainForm form; int tile; long rows_a; double us; };   // tile: of the ring launch (whole or behind the cut); rows_a: see cut_rows
+static Plain choose_plain(const GemmParams& p) {
   const bool residual = p.epi == EPI_BIAS_RESIDUAL;
-  const RingPick ring = best_ring(p.M, p.Npad, p.K, residual || p.epi == EPI_BIAS_POS);
-  const long gm = (p.M + BM - 1) / BM;
-  if (p.Npad % 256 != 0) {
-    // 128 columns over many rows stream the activations at the memory's rate: 256 x 128 tiles fetch each row once (the
-    // cut columns of the 6B shape's FC2, 40960 rows: 277 us, on 128 x 64 ring tiles 315)
-    if (p.Npad == 128 && gm * 2 > cu_count()) return dispatch<128, 512, 64>(p, st);
-    return launch_ring(p, ring.tile, st);
-  }
-  const long tiles_all = gm * (p.Npad / 256), cus = cu_count();
+  const long gm = (p.M + BM - 1) / BM, cus = cu_count();
+  const RingPick ring = best_ring(p.M, p.N, p.K, p.epi);
+  Plain best = {PLAIN_RING, ring.tile, 0, ring.us};
+  auto offer = [&](PlainForm form, int tile, long rows_a, double us) { if (us < best.us) best = {form, tile, rows_a, us}; };
+  // 128 columns over many rows stream the activations at the memory's rate: 256 x 128 tiles fetch each row once (the cut
+  // columns of the 6B shape's FC2, 40960 rows: 277 us, on 128 x 64 ring tiles 315)
+  if (p.Npad == 128 && gm * 2 > cus) return {PLAIN_256x128, 0, 0, ring.us};
+  offer(PLAIN_256x128, 0, 0, one_round_128(p));
+  if (p.Npad % 256 != 0) return best;
+  const long tiles = gm * (p.Npad / 256);
   // A width like 3200 leaves the last 256-wide tile column half used.  When that column is also what
   // spills the launch into a nearly empty last round (at most a quarter of the CUs busy), the residual
   // product is cut by columns: the whole 256-wide tile columns, and the last 128 columns as a launch of
   // their own (weight rows, bias and residual columns are pointer offsets): -4 % on the 6B shape's FC2,
   // +1 % on a SigLIP-shaped batch of 480 slices whose 2560 tiles are ten full rounds anyway.
-  if (residual && p.N > 256 && p.N % 256 != 0 && p.N % 256 <= 128 &&
-      tiles_all >= cus && tiles_all % cus != 0 && (tiles_all % cus) * 4 <= cus) {
-    const int n_a = p.N / 256 * 256;
-    GemmParams a = p, b = p;
-    a.N = n_a; a.Npad = n_a;
-    b.N = p.N - n_a; b.Npad = 128;
-    b.W = p.W + (long)n_a * p.K; b.bias = p.bias + n_a; b.R = p.R + n_a;
-    const hipError_t e = dispatch_plain(a, st);
-    return e != hipSuccess ? e : dispatch_plain(b, st);
-  }
-  double best = launch_256(p);
+  if (residual && p.N > 256 && p.N % 256 != 0 && p.N % 256 <= 128 && tiles >= cus && tiles % cus != 0 && (tiles % cus) * 4 <= cus)
+    return {PLAIN_COLUMNS, 0, 0, 0.0};
+  const long rows_a = cut_rows(p);
+  auto round = [&](double n) { return round_256(n, p.K, p.epi); };
+  if (rows_a == 0) offer(PLAIN_256, 0, 0, rounds_of(tiles, round));
+  else offer(PLAIN_256, best_ring(p.M - (int)(rows_a * BM), p.N, p.K, p.epi).tile, rows_a, rounds_of(rows_a * (p.Npad / 256), round) + behind_cut(p, rows_a));
   // A width of 1152 is four and a half 256-wide tile columns and six 192-wide ones: 240 tiles in one round instead of
-  // 200 for the residual products of the 10-slice SigLIP-shaped request (-8 % on both), but 12 rounds for 10 in a
-  // micro-batch of 128 slices.
-  bool w192 = false;
-  if (residual && persist_res() && tiles_192() && p.N % 192 == 0 && p.N % 256 != 0) {
-    const double t = rounds_of(gm * (p.N / 192), [&](double n) { return round_192(n, p.K); });
-    if (t < 1.04 * best) { best = t; w192 = true; }   // the estimates are no closer than that: 23 slices of 729 tokens, FC2 227 us cut, 225 on 192-wide tiles
-  }
-  if (ring.us < 0.98 * best) return launch_ring(p, ring.tile, st);
-  if (w192) return launch_persist_res<192>(p, st);
+  // 200 for the residual products of the 10-slice SigLIP-shaped request (-8 % on both), but 6 rounds for 5 in 64 slices
+  // (FC2 642 us on 256 x 256 tiles, 677 on these).
+  if (residual && persist_res() && tiles_192() && p.N % 192 == 0 && p.N % 256 != 0)
+    offer(PLAIN_192, 0, 0, rounds_of(gm * (p.N / 192), [&](double n) { return round_192(n, p.K); }));
+  return best;
+}
+
+static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
+  const bool residual = p.epi == EPI_BIAS_RESIDUAL;
+  const Plain c = choose_plain(p);
+  GemmParams a = p, b = p;
   auto wide = [&](const GemmParams& g) {
     if (!residual && p.epi != EPI_BIAS_POS) return dispatch_persist(g, st);
     if (residual && persist_res()) return launch_persist_res(g, st);
     return (a_direct() && g.K >= 2048) ? dispatch<256, 512, 64, 3>(g, st) : dispatch<256, 512, 64, 1>(g, st);
   };
-  const long rows_a = cut_rows(p);
-  if (rows_a == 0) return wide(p);
-  GemmParams a = p, b = p;
-  a.M = (int)(rows_a * BM);
-  b.M = p.M - a.M;
-  b.A = p.A + (long)a.M * p.lda;
-  if (residual) b.R = p.R + (long)a.M * p.ldr;
-  else if (p.epi == EPI_VT) b.VT = p.VT + (long)a.M * p.heads * p.hd_pad;   // whole slices: a.M / n_tok of [heads * hd_pad][n_tok]
-  else if (p.row_map) b.row_map = p.row_map + a.M / p.block_tokens;
-  else b.C = p.C + (long)a.M * p.ldc;
-  const hipError_t e = wide(a);
-  return e != hipSuccess ? e : launch_ring(b, best_ring(b.M, b.Npad, b.K, residual).tile, st);
+  switch (c.form) {
+    case PLAIN_RING: return launch_ring(p, c.tile, st);
+    case PLAIN_256x128: return dispatch<128, 512, 64>(without_padded_columns(p), st);
+    case PLAIN_192: return launch_persist_res<192>(p, st);
+    case PLAIN_256: {
+      if (c.rows_a == 0) return wide(p);
+      a.M = (int)(c.rows_a * BM);
+      b.M = p.M - a.M;
+      b.A = p.A + (long)a.M * p.lda;
+      if (residual) b.R = p.R + (long)a.M * p.ldr;
+      else if (p.epi == EPI_VT) b.VT = p.VT + (long)a.M * p.heads * p.hd_pad;   // whole slices: a.M / n_tok of [heads * hd_pad][n_tok]
+      else if (p.row_map) b.row_map = p.row_map + a.M / p.block_tokens;
+      else b.C = p.C + (long)a.M * p.ldc;
+      const hipError_t e = wide(a);
+      return e != hipSuccess ? e : launch_ring(b, c.tile, st);
+    }
+    case PLAIN_COLUMNS: {
+      const int n_a = p.N / 256 * 256;
+      a.N = n_a; a.Npad = n_a;
+      b.N = p.N - n_a; b.Npad = 128;
+      b.W = p.W + (long)n_a * p.K; b.bias = p.bias + n_a; b.R = p.R + n_a;
+      const hipError_t e = dispatch_plain(a, st);
+      return e != hipSuccess ? e : dispatch_plain(b, st);
+    }
+  }
+  return hipErrorInvalidValue;
+}
+
+// The q/k and the value projection as one launch of ring tiles, where that is estimated to take less than the two
+// launches each in its own best form and the 2.5 us a second launch costs (1024-wide encoder, us per layer: one slice 21.0
+// -> 15.2, five 58.9 -> 45.6, ten 85.5 -> 82.6; 13 slices 98.3 as two launches, 107.6 as one).
+static int pair_columns(const GemmParams& p) { return p.Npad + whole_128(p.n2); }
+bool bf16_gemm_pair_fits(const GemmParams& p) {
+  if (p.cfg != 0 || p.epi != EPI_BIAS || p.n2_pad <= 0 || p.n2_pad % 128 != 0 || p.Npad % 128 != 0 || !ring_has(p)) return false;
+  GemmParams q = p, v = p;
+  q.n2_pad = v.n2_pad = 0; v.epi = EPI_VT; v.N = p.n2; v.Npad = p.n2_pad;
+  return best_ring(p.M, pair_columns(p), p.K, EPI_BIAS).us < choose_plain(q).us + choose_plain(v).us + 2.5;
+}
+
+// For tests: the form choose_plain takes, by its number in GemmParams::cfg (9 / 10 / 7: 256 x 256 tiles by epilogue, 0: the
+// cut by columns); *rows: the rows in front of a row cut, M without one
+int bf16_gemm_choice(const GemmParams& p, long* rows) {
+  const Plain c = choose_plain(p);
+  *rows = c.form == PLAIN_256 && c.rows_a > 0 ? c.rows_a * BM : p.M;
+  switch (c.form) {
+    case PLAIN_RING: return c.tile == RING_64x64 ? 11 : c.tile == RING_128x64 ? 13 : 14;
+    case PLAIN_256x128: return 1;
+    case PLAIN_192: return 12;
+    case PLAIN_256: return p.epi == EPI_BIAS_RESIDUAL ? 10 : p.epi == EPI_BIAS_POS ? 7 : 9;
+    case PLAIN_COLUMNS: return 0;
+  }
+  return -1;
 }
 
 hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
@@ -1711,7 +1755,7 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
   const bool f32_out = p.epi == EPI_BIAS_RESIDUAL || p.epi == EPI_BIAS_POS;
   if (!f32_out && p.epi != EPI_VT && (p.N % 8 != 0 || p.ldc % 8 != 0)) return hipErrorInvalidValue;
   if (p.n2_pad > 0)
-    return bf16_gemm_pair_fits(p) ? launch_ring(p, best_ring(p.M, p.Npad + p.n2_pad, p.K, false).tile, st) : hipErrorInvalidValue;
+    return bf16_gemm_pair_fits(p) ? launch_ring(p, best_ring(p.M, pair_columns(p), p.K, EPI_BIAS).tile, st) : hipErrorInvalidValue;
   switch (p.cfg) {
     case 1: return dispatch<128, 512, 64>(p, st);
     case 2: return ring_has(p) ? launch_ring(p, RING_128x128, st) : dispatch_128_fold<0>(p, st);

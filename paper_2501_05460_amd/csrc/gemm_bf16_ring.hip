@@ -342,8 +342,9 @@ hipError_t launch_ring(const GemmParams& p, hipStream_t st) {
   if (p.Npad % TN != 0 || p.n2_pad % TN != 0) return hipErrorInvalidValue;
   const int gm = (p.M + TM - 1) / TM, gn = (p.Npad + (DUAL ? p.n2_pad : 0)) / TN;
   if (gm * gn == 0) return hipSuccess;
-  // bands of eight tile columns: within 2 % of four at any size, 4 % ahead on average with 128 x 64 tiles
-  k_gemm_bf16_ring<EPI, DUAL, WTM, WTN, RING, OCC><<<dim3(gm * gn), dim3(256), ring_lds<WTM, WTN, RING>(), st>>>(p, gm, gn < 8 ? gn : 8);
+  // bands of up to eight tile columns, equally wide: within 2 % of four at any size, 4 % ahead on average with 128 x 64 tiles
+  const int bands = (gn + 7) / 8;
+  k_gemm_bf16_ring<EPI, DUAL, WTM, WTN, RING, OCC><<<dim3(gm * gn), dim3(256), ring_lds<WTM, WTN, RING>(), st>>>(p, gm, (gn + bands - 1) / bands);
   return hipGetLastError();
 }
 template <int EPI, bool DUAL, int WTM, int WTN, int RING, int OCC>

@@ -86,6 +86,7 @@ bool bf16_gemm_pair_fits(const GemmParams& p);
 enum RingTile { RING_64x64 = 0, RING_128x64 = 1, RING_128x128 = 2 };
 hipError_t bf16_gemm_ring(const GemmParams& p, int tile, hipStream_t st);
 hipError_t bf16_gemm_ring_init();   // part of bf16_gemm_init
+int bf16_gemm_choice(const GemmParams& p, long* rows);   // the form of a product without a folded pre-norm (tests)
 long bf16_gemm_kernel_launches();   // kernels launched by bf16_gemm on the calling host thread so far (a figure for the profiling hooks)
 hipError_t bf16_gemm_init();  // raises the dynamic-LDS limit of the kernels (idempotent: safe from any thread, any number of times)
 
