@@ -1655,7 +1655,10 @@ static Plain choose_plain(const GemmParams& p) {
   const bool residual = p.epi == EPI_BIAS_RESIDUAL;
   const long gm = (p.M + BM - 1) / BM, cus = cu_count();
   const RingPick ring = best_ring(p.M, p.N, p.K, p.epi);
-  Plain best = {PLAIN_RING, ring.tile, 0, ring.us};
+  // Ring tiles are for launches of a few slices.  Past eight 128 x 128 tiles per CU they were never ahead, and there the
+  // stream's rows make them 10 to 25 % slower than estimated (47104 rows of 1152 by K = 1152: 225 us, 177 on 256 x 256 tiles).
+  const bool few = p.Npad % 256 != 0 || (long)((p.M + 127) / 128) * (whole_128(p.N) / 128) <= 8 * cus;
+  Plain best = {PLAIN_RING, ring.tile, 0, few ? ring.us : INFINITY};
   auto offer = [&](PlainForm form, int tile, long rows_a, double us) { if (us < best.us) best = {form, tile, rows_a, us}; };
   // 128 columns over many rows stream the activations at the memory's rate: 256 x 128 tiles fetch each row once (the cut
   // columns of the 6B shape's FC2, 40960 rows: 277 us, on 128 x 64 ring tiles 315)
@@ -1667,8 +1670,10 @@ static Plain choose_plain(const GemmParams& p) {
   // spills the launch into a nearly empty last round (at most a quarter of the CUs busy), the residual
   // product is cut by columns: the whole 256-wide tile columns, and the last 128 columns as a launch of
   // their own (weight rows, bias and residual columns are pointer offsets): -4 % on the 6B shape's FC2,
-  // +1 % on a SigLIP-shaped batch of 480 slices whose 2560 tiles are ten full rounds anyway.
-  if (residual && p.N > 256 && p.N % 256 != 0 && p.N % 256 <= 128 && tiles >= cus && tiles % cus != 0 && (tiles % cus) * 4 <= cus)
+  // +1 % on a SigLIP-shaped batch of 480 slices whose 2560 tiles are ten full rounds anyway.  Not for multiples of 192, which
+  // 256 x 192 tiles take whole (1152 columns, 41216 rows, out-projection and FC2 together: 667 us by columns, 606 on those
+  // tiles; 26624 rows, K = 4352: 314 us by columns, 287 cut by rows).
+  if (residual && p.N > 256 && p.N % 192 != 0 && p.N % 256 != 0 && p.N % 256 <= 128 && tiles >= cus && tiles % cus != 0 && (tiles % cus) * 4 <= cus)
     return {PLAIN_COLUMNS, 0, 0, 0.0};
   const long rows_a = cut_rows(p);
   auto round = [&](double n) { return round_256(n, p.K, p.epi); };
