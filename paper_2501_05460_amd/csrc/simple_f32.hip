@@ -1,8 +1,9 @@
 // fp32 mode of the encode stage: bounds-checked kernels with fp32 storage and
 // fp32 accumulation (the products on the fp32 matrix instruction).  This mode
 // exists for the small fp32 configuration, whose time is the latency chain of
-// some 36 short launches, and as the on-device numerical reference of the bf16
+// its 23 short launches, and as the on-device numerical reference of the bf16
 // MFMA path.
+#include <cmath>
 #include <type_traits>
 
 #include "kernels.h"
@@ -37,29 +38,37 @@ void f32_im2col(const float* tiles, float* A, int T, int S, int p, hipStream_t s
 // ------------------------------------------------------------------ GEMM ----
 // C[M,N] = A[M,K] * W[N,K]^T on v_mfma_f32_16x16x4_f32.  One workgroup per 16 R x 16 R tile; its four waves split K
 // (whole 16-element chunks, a share of ceil(chunks / 4) each) and their partial tiles are added in LDS.
-// The launches of this mode are small: what bounds them is one wave's chain of loads and multiply-adds, so the
-// contraction is cut in four and the tile is 16 x 16 while 32 x 32 tiles would leave CUs idle (M = 256, N = 192,
+// The launches of the small configuration are bound by one wave's chain of loads and multiply-adds, so the
+// contraction is cut in four and the tile is 16 x 16 while larger ones would leave CUs idle (M = 256, N = 192,
 // K = 768, one slice of the tiny configuration: 192 workgroups with chains of 48 instructions; 36 us with one thread's
-// chain of 768 multiply-adds through LDS tiles, 6 us now).  Operands come straight from global memory: lane l holds
+// chain of 768 multiply-adds through LDS tiles, 8 us now).  Large launches are bound by the operand bytes a tile asks its
+// CU's cache for, 64 x 64 tiles for half as many per product as 32 x 32 ones (M = 16384, N = 4096, K = 1024, in us: 3600 |
+// 2040 | 1520 on 16 | 32 | 64-wide tiles, 2640 through LDS tiles of 64 x 64 on the vector unit).  Operands come straight from global memory: lane l holds
 // row l % 16, elements 4 (l / 16) .. + 3 of a chunk (one 16-byte load), and instruction e of a chunk multiplies
 // element e of all four groups, the same four elements of both operands.  An element's sum is ordered by K alone, so its
 // bits do not depend on the tile or the batch.
-constexpr int F32_GROUP = 6;   // chunks loaded ahead as one batch
+constexpr int F32_GROUP = 6;   // most chunks loaded ahead as one batch
 // NORM: the rows of A are normalised on the way in (LayerNorm / RMSNorm over their K elements).  A share of the
 // contraction then has to fit one batch of loads (K <= 64 F32_GROUP): a wave holds its part of the rows, the statistics
 // meet in LDS, twice (mean, then squared deviations), and the normalised row never goes to memory: the launch of its own
-// (5 us of which the work is less than one) is gone.  Bits depend on K alone here too (multiply-adds are written out: both
+// (5 us of which the work is less than one) is gone.  Bits depend on K alone here too (multiply-adds are written out: all
 // tile sizes have to contract alike).
+template <int N, typename F>
+__device__ __forceinline__ void for_const(F f) {
+  if constexpr (N > 0) { for_const<N - 1>(f); f(std::integral_constant<int, N - 1>{}); }
+}
 struct F32Norm { const float* gamma; const float* beta; int rms; float eps; };
 template <int EPI, int R, bool VEC, bool NORM = false>
-__global__ __launch_bounds__(256) void k_f32_gemm(const F32Norm norm, const float* __restrict__ A, int lda,
+__global__ __launch_bounds__(256, R == 4 ? 2 : 1) void k_f32_gemm(const F32Norm norm, const float* __restrict__ A, int lda,
                                                   const float* __restrict__ W,
                                                   const float* __restrict__ bias, float* C, int ldc,
                                                   const float* __restrict__ pos, int n_pos, int M,
                                                   int N, int K, const int* __restrict__ row_map,
                                                   int block_tokens, SliceRows xrows) {
   constexpr int T = 16 * R;
-  __shared__ float part[4][T * T];
+  constexpr int G = R == 4 ? 1 : R == 2 ? 2 : F32_GROUP;   // chunks loaded ahead as one batch: enough products to cover the next one's loads, and two workgroups' registers
+  constexpr int IB = R == 4 ? 1 : R;          // 16-row blocks of the tile whose partial sums meet in LDS at a time
+  __shared__ float part[4][16 * IB * T];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, q = lane >> 4;
   const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
@@ -85,32 +94,40 @@ __global__ __launch_bounds__(256) void k_f32_gemm(const F32Norm norm, const floa
   for (int i = 0; i < R; ++i)
 #pragma unroll
     for (int j = 0; j < R; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  f32x4 a[2][F32_GROUP][R], w[2][F32_GROUP][R];
-  auto fetch = [&](auto set, int c0) {
+  // NORM holds the whole share of its rows, set 0 only
+  f32x4 a[NORM ? 1 : 2][NORM ? F32_GROUP : G][R], w[2][G][R];
+  auto fetch_a = [&](auto set, int c0, int n) {
     constexpr int S = decltype(set)::value;
 #pragma unroll
-    for (int g = 0; g < F32_GROUP; ++g)
+    for (int g = 0; g < (NORM ? F32_GROUP : G); ++g)
 #pragma unroll
-      for (int i = 0; i < R; ++i) {
-        a[S][g][i] = load(A, lda, m0 + 16 * i + r16, M, c0 + g);
-        w[S][g][i] = load(W, K, n0 + 16 * i + r16, N, c0 + g);
-      }
+      for (int i = 0; i < R; ++i)
+        if (g < n) a[S][g][i] = load(A, lda, m0 + 16 * i + r16, M, c0 + g);
   };
-  auto multiply = [&](auto set) {
+  auto fetch_w = [&](auto set, int c0) {
     constexpr int S = decltype(set)::value;
 #pragma unroll
-    for (int g = 0; g < F32_GROUP; ++g)
+    for (int g = 0; g < G; ++g)
+#pragma unroll
+      for (int i = 0; i < R; ++i) w[S][g][i] = load(W, K, n0 + 16 * i + r16, N, c0 + g);
+  };
+  // chunks g0 .. g0 + G - 1 of operand set A against weight set S
+  auto multiply = [&](auto set_a, auto set_w, int g0) {
+    constexpr int SA = decltype(set_a)::value, S = decltype(set_w)::value;
+#pragma unroll
+    for (int g = 0; g < G; ++g)
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int i = 0; i < R; ++i)
 #pragma unroll
           for (int j = 0; j < R; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[S][g][i][e], w[S][g][j][e], acc[i][j], 0, 0, 0);
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[SA][g0 + g][i][e], w[S][g][j][e], acc[i][j], 0, 0, 0);
   };
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
-  fetch(S0{}, c_begin);
+  fetch_a(S0{}, c_begin, F32_GROUP);
+  fetch_w(S0{}, c_begin);
   if constexpr (NORM) {
     __shared__ float red[2][4][T];
     float mean[R], rstd[R];
@@ -163,36 +180,52 @@ __global__ __launch_bounds__(256) void k_f32_gemm(const F32Norm norm, const floa
           for (int e = 0; e < 4; ++e) a[0][g][i][e] = fmaf((a[0][g][i][e] - mean[i]) * rstd[i], gm[e], bt[e]);
       }
   }
-  for (int c = c_begin; c < c_end; c += 2 * F32_GROUP) {   // chunks past the share are zeros
-    fetch(S1{}, c + F32_GROUP);
-    multiply(S0{});
-    if (c + F32_GROUP >= c_end) break;
-    fetch(S0{}, c + 2 * F32_GROUP);
-    multiply(S1{});
+  // chunks past the share are zeros
+  if constexpr (NORM) {
+    static_assert(F32_GROUP % G == 0, "whole batches");
+    for_const<F32_GROUP / G>([&](auto b_) {
+      constexpr int b = decltype(b_)::value;
+      if constexpr ((b + 1) * G < F32_GROUP) fetch_w(std::integral_constant<int, 1 - b % 2>{}, c_begin + (b + 1) * G);
+      multiply(S0{}, std::integral_constant<int, b % 2>{}, b * G);
+    });
+  } else {
+    for (int c = c_begin; c < c_end; c += 2 * G) {
+      fetch_a(S1{}, c + G, G);
+      fetch_w(S1{}, c + G);
+      multiply(S0{}, S0{}, 0);
+      if (c + G >= c_end) break;
+      fetch_a(S0{}, c + 2 * G, G);
+      fetch_w(S0{}, c + 2 * G);
+      multiply(S1{}, S1{}, 0);
+    }
   }
   // result register e of lane l: row 4 (l / 16) + e, column l % 16
 #pragma unroll
-  for (int i = 0; i < R; ++i)
+  for (int ib = 0; ib < R; ib += IB) {
+    if (ib > 0) __syncthreads();
 #pragma unroll
-    for (int j = 0; j < R; ++j)
+    for (int i = 0; i < IB; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) part[wave][(16 * i + 4 * q + e) * T + 16 * j + r16] = acc[i][j][e];
-  __syncthreads();
+      for (int j = 0; j < R; ++j)
 #pragma unroll
-  for (int u = 0; u < R * R; ++u) {
-    const int idx = tid + 256 * u;
-    const int r = m0 + idx / T, c = n0 + idx % T;
-    if (r >= M || c >= N) continue;
-    const float v = ((part[0][idx] + part[1][idx]) + (part[2][idx] + part[3][idx])) + (bias ? bias[c] : 0.f);
-    // paged output: row r of the product lives in block row_map[r / block_tokens]
-    const long orow = row_map ? (long)row_map[r / block_tokens] * block_tokens + r % block_tokens : r;
-    const long o = orow * ldc + c;
-    if (EPI == EPI_BIAS_RESIDUAL) {
-      C[o] += v;
-    } else if (EPI == EPI_BIAS_POS) {
-      C[xrows.row(r) * ldc + c] = v + pos[(long)(r % n_pos) * N + c];   // patch embedding: through the slice layout
-    } else {
-      C[o] = apply_act<EPI>(v);
+        for (int e = 0; e < 4; ++e) part[wave][(16 * i + 4 * q + e) * T + 16 * j + r16] = acc[ib + i][j][e];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < IB * R; ++u) {
+      const int idx = tid + 256 * u;
+      const int r = m0 + 16 * ib + idx / T, c = n0 + idx % T;
+      if (r >= M || c >= N) continue;
+      const float v = ((part[0][idx] + part[1][idx]) + (part[2][idx] + part[3][idx])) + (bias ? bias[c] : 0.f);
+      // paged output: row r of the product lives in block row_map[r / block_tokens]
+      const long orow = row_map ? (long)row_map[r / block_tokens] * block_tokens + r % block_tokens : r;
+      const long o = orow * ldc + c;
+      if (EPI == EPI_BIAS_RESIDUAL) {
+        C[o] += v;
+      } else if (EPI == EPI_BIAS_POS) {
+        C[xrows.row(r) * ldc + c] = v + pos[(long)(r % n_pos) * N + c];   // patch embedding: through the slice layout
+      } else {
+        C[o] = apply_act<EPI>(v);
+      }
     }
   }
 }
@@ -205,6 +238,18 @@ static int f32_cu_count() {
          hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) ? v : 256;
   }
   return n;
+}
+
+// The tile's side in units of 16: the smallest of the times estimated for M rows, N columns and K, in us (fitted to 132
+// launches of M 256 to 16384, K 192 to 4304: the tile taken is 0.7 % behind the fastest on average).  16 x 16 and 32 x 32
+// tiles come in such numbers that the time grows with their count, 64 x 64 tiles in rounds.
+static int f32_tile(int M, int N, int K, bool norm) {
+  const double cus = f32_cu_count(), k = K;
+  const double t32 = (double)((N + 31) / 32) * ((M + 31) / 32) / cus, rounds = ceil((double)((N + 63) / 64) * ((M + 63) / 64) / cus);
+  const double us[3] = {norm ? 4.0 + 0.0078 * k + t32 * (2.0 + 0.0155 * k) : 4.5 + 0.0025 * k + t32 * (1.0 + 0.0145 * k),
+                        norm ? 4.5 + 0.0130 * k + fmax(0.75, t32) * (3.1 + 0.0026 * k) : 6.0 + 0.0030 * k + fmax(0.75, t32) * (0.5 + 0.0088 * k),
+                        norm ? 8.0 + 0.0100 * k + rounds * (9.0 + 0.0100 * k) : 6.0 + rounds * (4.0 + 0.0215 * k)};
+  return us[0] <= us[1] && us[0] <= us[2] ? 1 : us[1] <= us[2] ? 2 : 4;
 }
 
 template <int R, bool VEC>
@@ -225,16 +270,14 @@ void f32_gemm(int epi, const float* A, int lda, const float* W, const float* bia
               const float* pos, int n_pos, int M, int N, int K, hipStream_t st, const int* row_map,
               int block_tokens, SliceRows xrows) {
   if (M == 0 || N == 0) return;
-  const long tiles32 = (long)((N + 31) / 32) * ((M + 31) / 32);
   const bool vec = K % 4 == 0 && lda % 4 == 0 && (((uintptr_t)A | (uintptr_t)W) & 15) == 0;
-  const bool small = tiles32 < 2 * f32_cu_count();   // 16 x 16 tiles until 32 x 32 ones put two workgroups on every CU
-  if (vec) {
-    if (small) f32_gemm_r<1, true>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
-    else f32_gemm_r<2, true>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
-  } else {
-    if (small) f32_gemm_r<1, false>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
-    else f32_gemm_r<2, false>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
-  }
+  const int r = f32_tile(M, N, K, false);
+#define F32_GEMM(VEC)                                                                                                   \
+  if (r == 1) f32_gemm_r<1, VEC>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);       \
+  else if (r == 2) f32_gemm_r<2, VEC>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);  \
+  else f32_gemm_r<4, VEC>(epi, A, lda, W, bias, C, ldc, pos, n_pos, M, N, K, st, row_map, block_tokens, xrows);
+  if (vec) { F32_GEMM(true) } else { F32_GEMM(false) }
+#undef F32_GEMM
 }
 
 bool f32_norm_gemm_fits(int lda, int K, const float* A, const float* W, const float* gamma, const float* beta) {
@@ -246,13 +289,13 @@ void f32_norm_gemm(int epi, int kind, const float* gamma, const float* beta, flo
                    const float* bias, float* C, int ldc, int M, int N, int K, hipStream_t st) {
   if (M == 0 || N == 0) return;
   const F32Norm nm{gamma, beta, kind == 1 ? 1 : 0, eps};
-  const bool small = (long)((N + 31) / 32) * ((M + 31) / 32) < 2 * f32_cu_count();
-  const int t = small ? 16 : 32;
+  const int r = f32_tile(M, N, K, true), t = 16 * r;
   const dim3 grid((N + t - 1) / t, (M + t - 1) / t), block(256);
   const SliceRows xr{0, 0, 0};
 #define F32_NORM_GEMM(EPI)                                                                                              \
-  if (small) k_f32_gemm<EPI, 1, true, true><<<grid, block, 0, st>>>(nm, A, lda, W, bias, C, ldc, nullptr, 1, M, N, K, nullptr, 1, xr); \
-  else k_f32_gemm<EPI, 2, true, true><<<grid, block, 0, st>>>(nm, A, lda, W, bias, C, ldc, nullptr, 1, M, N, K, nullptr, 1, xr);
+  if (r == 1) k_f32_gemm<EPI, 1, true, true><<<grid, block, 0, st>>>(nm, A, lda, W, bias, C, ldc, nullptr, 1, M, N, K, nullptr, 1, xr);      \
+  else if (r == 2) k_f32_gemm<EPI, 2, true, true><<<grid, block, 0, st>>>(nm, A, lda, W, bias, C, ldc, nullptr, 1, M, N, K, nullptr, 1, xr); \
+  else k_f32_gemm<EPI, 4, true, true><<<grid, block, 0, st>>>(nm, A, lda, W, bias, C, ldc, nullptr, 1, M, N, K, nullptr, 1, xr);
   switch (epi) {
     case EPI_BIAS_GELU_ERF: F32_NORM_GEMM(EPI_BIAS_GELU_ERF) break;
     case EPI_BIAS_GELU_TANH: F32_NORM_GEMM(EPI_BIAS_GELU_TANH) break;

@@ -175,6 +175,22 @@ def test_a_slice_alone_has_the_bits_it_has_inside_a_large_batch():
     enc.close()
 
 
+@pytest.mark.parametrize("hidden,heads,patch,tile", [(192, 3, 14, 112), (400, 4, 14, 112), (256, 4, 7, 56)])
+def test_fp32_slice_has_the_same_bits_alone_and_in_batches(hidden, heads, patch, tile):
+    """fp32 products take 16-, 32- or 64-wide tiles by the launch's size, with the pre-norm inside up to 384 columns: one
+    slice (64 rows), six and seventy leave the same bits.  Patches of 7 x 7 are rows of 147 without 16-byte loads."""
+    desc = desc_for(wl.DT_FP32, hidden=hidden, heads=heads, mlp=4 * hidden, patch=patch, tile_size=tile, max_tiles_per_call=72)
+    w = wl.gen_weights(desc, 43, std=0.05)
+    tiles = torch.from_numpy(wl.gen_tiles(desc, 43, 70)).cuda()
+    enc = make_encoder(desc, w)
+    n = enc.tokens_per_tile
+    full = bits(enc.encode(tiles, [0, 70]))
+    for begin, end in ((0, 1), (33, 34), (69, 70), (3, 9)):
+        part = bits(enc.encode(tiles[begin:end].contiguous(), [0, end - begin]))
+        assert np.array_equal(part, full[begin * n:end * n]), (begin, end)
+    enc.close()
+
+
 def test_a_slice_of_nan_pixels_poisons_neither_its_neighbours_nor_later_calls():
     """Class-token shape: 65 tokens in 72 rows, so the last key block of every slice reaches into the next
     slice's rows and values (masked keys, weight exactly zero).  A slice full of NaN must leave the other
