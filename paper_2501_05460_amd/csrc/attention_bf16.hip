@@ -494,11 +494,6 @@ template <int HD, int QT, bool MASK, bool W4 = false>
 hipError_t launch_attn_m(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                          int n_tok, int n_keys, int n_q, int q_shared, int heads, long ld_qk, long ld_o,
                          unsigned char* oq, unsigned* so, long ld_so, hipStream_t st) {
-  // once per instantiation; the initialisation of a function-local static is safe against concurrent callers
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attention_bf16<HD, QT, MASK, W4>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                     (int)AttnSmem<HD>::BYTES);
-  if (attr != hipSuccess) return attr;
   constexpr int BQ = 128 * QT;
   const int n_qb = (n_q + BQ - 1) / BQ, n_pairs = n_slices * heads;
   const long n_wg = (long)((n_pairs + 7) / 8) * 8 * n_qb;
@@ -524,7 +519,27 @@ hipError_t launch_attn(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_
              : launch_attn_m<HD, QT, false>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
 }
 
+template <int HD, bool MASK, bool W4>
+hipError_t set_attr() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attention_bf16<HD, 1, MASK, W4>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)AttnSmem<HD>::BYTES);
+}
+template <int HD>
+hipError_t set_attr_hd() {
+  hipError_t e = set_attr<HD, false, false>();
+  if (e == hipSuccess) e = set_attr<HD, true, false>();
+  if (HD == 64 && e == hipSuccess) e = set_attr<HD, false, HD == 64>();
+  return HD == 64 && e == hipSuccess ? set_attr<HD, true, HD == 64>() : e;
+}
+
 }  // namespace
+
+hipError_t bf16_attention_init() {
+  hipError_t e = set_attr_hd<64>();
+  if (e == hipSuccess) e = set_attr_hd<72>();
+  if (e == hipSuccess) e = set_attr_hd<96>();
+  return e == hipSuccess ? set_attr_hd<128>() : e;
+}
 
 hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                           int n_tok, int n_keys, int n_q, int q_shared, int heads, int hd_pad, long ld_qk,

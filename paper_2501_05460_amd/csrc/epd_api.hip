@@ -421,6 +421,9 @@ epd_status build_ctx(epd_ctx* c, const epd_weights* w, hipStream_t st) {
     c->Kp_k = round_up(x.Kp, 128);
     c->Pin_k = round_up(x.Pin, 128);
     HIP_TRY(c, bf16_gemm_init());
+    HIP_TRY(c, bf16_attention_init());
+  } else {
+    HIP_TRY(c, f32_attention_init());
   }
   const PackMap heads{x.hd, c->hd_pad, x.H};
   if (bf) {
@@ -1488,6 +1491,7 @@ epd_status epd_op_attention_bf16(const void* q, const void* k, const void* vt, v
                                  void* hip_stream) {
   if (!q || !k || !vt || !o) return EPD_ERR_INVALID_ARG;
   if (n_tokens % 64) { set_err(g_err, sizeof(g_err), "epd_op_attention_bf16: n_tokens %% 64 != 0"); return EPD_ERR_UNSUPPORTED; }
+  if (bf16_attention_init() != hipSuccess) return EPD_ERR_HIP;
   hipError_t e = bf16_attention((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)vt, (bf16_t*)o, n_slices,
                                 n_tokens, n_keys, n_tokens, 0, heads, hd_pad, ld_qk, (long)heads * hd_pad, (hipStream_t)hip_stream);
   if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "attention launch failed: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_UNSUPPORTED : EPD_ERR_HIP; }
@@ -1502,6 +1506,7 @@ epd_status epd_op_attention_mx(const void* q, const void* k, const void* vt, voi
     return EPD_ERR_UNSUPPORTED;
   }
   const long rows = (long)n_slices * n_tokens;
+  if (bf16_attention_init() != hipSuccess) return EPD_ERR_HIP;
   hipError_t e = bf16_attention((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)vt, nullptr, n_slices, n_tokens, n_keys,
                                 n_tokens, 0, heads, hd_pad, ld_qk, (long)heads * hd_pad, (hipStream_t)hip_stream,
                                 (unsigned char*)codes, (unsigned*)scales, rows);

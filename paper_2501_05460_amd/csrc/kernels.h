@@ -30,6 +30,7 @@ void f32_norm_gemm(int epi, int kind, const float* gamma, const float* beta, flo
 // Output row t*n_q + i.
 void f32_attention(const float* q, long ld_q, int n_q, int q_shared, const float* k, const float* v, long ld,
                    float* o, long ldo, int T, int N, int H, int hd, float scale, hipStream_t st);
+hipError_t f32_attention_init();   // raises the dynamic-LDS limit on the current device (idempotent); in front of f32_attention
 // out[r][c] = in[r][c] + add[r % add_rows][c], rows of dim floats
 void f32_add_rows(const float* in, const float* add, int add_rows, float* out, long rows, int dim, hipStream_t st);
 void f32_shuffle(const float* in, SliceRows src, float* out, int T, int g, int D, hipStream_t st);
@@ -149,6 +150,7 @@ void bf16_qknorm(bf16_t* buf, long ld, long k_off, const float* gamma_q, const f
 hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                           int n_tok, int n_keys, int n_q, int q_shared, int heads, int hd_pad, long ld_qk,
                           long ld_o, hipStream_t st, unsigned char* oq = nullptr, unsigned* so = nullptr, long ld_so = 0);
+hipError_t bf16_attention_init();   // raises the dynamic-LDS limit on the current device (idempotent); in front of bf16_attention
 
 // W[r][0..cols) *= c (rounded to bf16 again) and b[r] *= c for r < rows: a constant factor of a product's
 // output folded into the rows of its packed weights

@@ -533,23 +533,25 @@ __global__ __launch_bounds__(256) void k_f32_attention_mfma(const float* __restr
   }
 }
 
+// the rows of logits of more than 1020 keys take more than the 64 KiB a launch may ask for by default
+hipError_t f32_attention_init() {
+  constexpr int most = (int)((16 * (F32_ATTN_MAX_KEYS + 4) + 16) * sizeof(float));
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_f32_attention_mfma<4>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, most);
+  return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&k_f32_attention_mfma<0>),
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize, most);
+}
+
 void f32_attention(const float* q, long ld_q, int n_q, int q_shared, const float* k, const float* v, long ld,
                    float* o, long ldo, int T, int N, int H, int hd, float scale, hipStream_t st) {
   if (T == 0) return;
   const bool aligned = ld_q % 4 == 0 && ld % 4 == 0 && (((uintptr_t)q | (uintptr_t)k) & 15) == 0;
   if (hd % 16 == 0 && N <= F32_ATTN_MAX_KEYS && aligned) {
     const size_t smem = (size_t)(16 * ((N + 15) / 16 * 16 + 4) + 16) * sizeof(float);
-    constexpr int most = (int)((16 * (F32_ATTN_MAX_KEYS + 4) + 16) * sizeof(float));
-    static const hipError_t attr4 = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_f32_attention_mfma<4>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    static const hipError_t attr0 = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_f32_attention_mfma<0>),
-                                                        hipFuncAttributeMaxDynamicSharedMemorySize, most);
-    if (attr4 == hipSuccess && attr0 == hipSuccess) {
-      const dim3 grid((n_q + 15) / 16, H, T);
-      if (hd == 64) k_f32_attention_mfma<4><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
-      else k_f32_attention_mfma<0><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
-      return;
-    }
+    const dim3 grid((n_q + 15) / 16, H, T);
+    if (hd == 64) k_f32_attention_mfma<4><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
+    else k_f32_attention_mfma<0><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
+    return;
   }
   const size_t smem = (size_t)(N + hd) * sizeof(float);
   k_f32_attention<<<dim3(n_q, H, T), dim3(128), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, N, hd, scale);

@@ -225,7 +225,7 @@ def test_pre_norms_at_every_register_count_vs_oracle(heads, hd):
     (1, 64, 7, 56, 1, 0),      # 147-element patch vectors (no 16-byte rows), 65 tokens: one past the 64-key group
     (6, 64, 14, 70, 0, 1),     # hidden 384: the longest row normalised inside its product; 25 tokens, 9 past a 16-query block
     (4, 100, 14, 56, 1, 0),    # hidden 400: norm as a launch of its own; head dim no multiple of 16
-    (2, 80, 14, 238, 1, 1),    # 290 tokens: past the 256 keys whose values are fetched ahead; head dim not compiled in
+    (2, 80, 14, 238, 1, 1),    # 290 tokens, head dim not compiled in
 ])
 def test_fp32_products_and_attention_at_their_edges_vs_oracle(heads, hd, patch, tile, cls, norm):
     """fp32 mode where the tiles, the contraction's four shares and the key groups end unevenly.  Bound: the mode's
@@ -233,6 +233,18 @@ def test_fp32_products_and_attention_at_their_edges_vs_oracle(heads, hd, patch, 
     desc = small_desc(wl.DT_FP32, tile_size=tile, patch=patch, hidden=heads * hd, heads=heads, layers=2, norm=norm,
                       class_token=cls, pixel_shuffle=0, proj_prenorm=0)
     got, want = run_case(desc, 61 + hd, 3, [0, 1, 3], std=0.06)
+    assert rel_err(got, want) < tol(desc)
+
+
+@pytest.mark.parametrize("hd,tile,cls", [
+    (64, 266, 1),    # 362 keys, 106 past the 256 whose values are fetched ahead: several waves and blocks take a second turn
+    (64, 448, 1),    # 1025 keys: rows of logits past 64 KiB of LDS
+    (80, 448, 1),    # the same with a head dim that is not compiled in
+])
+def test_fp32_attention_over_many_keys_vs_oracle(hd, tile, cls):
+    """Bound: the mode's 1e-4."""
+    desc = small_desc(wl.DT_FP32, tile_size=tile, hidden=2 * hd, heads=2, layers=1, class_token=cls, max_tiles_per_call=2)
+    got, want = run_case(desc, 71 + hd, 2, [0, 2], std=0.06)
     assert rel_err(got, want) < tol(desc)
 
 
