@@ -183,14 +183,14 @@ void scale_rows(void* W, int w_is_bf16, int rows, int cols, long ld, float* b, c
 
 // Paged multimodal-token cache: copy `n_blocks` blocks of `block_bytes` (multiple of 16) from
 // src_pool[src_ids[i]] to dst_pool[dst_ids[i]]; a null id array means block i (contiguous side).
+void mm_copy_blocks(const void* src_pool, const int* src_ids, void* dst_pool, const int* dst_ids,
+                    int n_blocks, long block_bytes, hipStream_t st);
 // The same with the ids in host memory: they travel in the kernels' arguments (MM_ARG_IDS of them a launch), so that a
 // short list needs no device scratch, no upload in front of the copy and no wait for the upload before it.
 constexpr int MM_ARG_IDS = 896;   // with the other arguments under the 4 KiB a launch may carry
 struct MmIdArgs { int v[MM_ARG_IDS]; };
 void mm_copy_blocks_args(const void* src_pool, const int* src_ids, void* dst_pool, const int* dst_ids,
                          int n_blocks, long block_bytes, hipStream_t st);
-void mm_copy_blocks(const void* src_pool, const int* src_ids, void* dst_pool, const int* dst_ids,
-                    int n_blocks, long block_bytes, hipStream_t st);
 
 // fp32 residual-stream rows <-> rows of a paged cache of fp32 or bf16 tokens of the same width.
 // Patch token r (stream row xr.row(r)) is token r % block_tokens of block row_map[r / block_tokens].

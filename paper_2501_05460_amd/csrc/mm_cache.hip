@@ -153,11 +153,12 @@ bool upload_ids(epd_mm_cache* c, int* d_dst, const int32_t* const* lists, int n_
 }  // namespace
 
 namespace {
-// Lists of up to this many blocks ride in the arguments of the copies (four launches at most for a transfer, two for a
-// gather); longer ones are uploaded once in front of a single launch.  13 slices of the 300M shape (208 blocks), transfer
-// + gather: 46 us with an upload and its event in front of each copy, 36 us with the ids in the arguments while the caller built
-// its lists in 3 x 8 us, 22 us since (the two copies alone are 21).
-constexpr int MM_ARG_BLOCKS = 2 * MM_ARG_IDS;
+// Lists of up to this many blocks ride in the arguments of the copies, two launches at most; longer ones are uploaded once
+// in front of a single launch.  One launch of the copies costs 3 to 5 us, an upload with its event 6 to 9.  In us, ids in the
+// arguments | uploaded: transfer of 896 blocks of 16 x 1152 bf16 15.1 | 18.7, of 16 x 4096 48.7 | 51.5, with three and four
+// launches 1344 blocks of 16 x 3200 61.3 | 59.6, 1664 77.8 | 73.1; gather of 1792 blocks of 16 x 1152 27.3 | 30.5, of 16 x 4096
+// 86.3 | 90.2.  13 slices of the 300M shape (208 blocks), transfer + gather: 46 | 22, the two copies alone are 21.
+constexpr int MM_PAIR_BLOCKS = MM_ARG_IDS, MM_GATHER_BLOCKS = 2 * MM_ARG_IDS;
 // body of the two transfer calls; ids_dev: where the id lists go on the device (null: the static array of
 // the current device, looked up once every argument has passed its checks)
 epd_status transfer_impl(const epd_mm_cache* src, const int32_t* src_blocks, epd_mm_cache* dst,
@@ -176,7 +177,7 @@ epd_status transfer_impl(const epd_mm_cache* src, const int32_t* src_blocks, epd
     return EPD_ERR_OFFSETS;
   }
   if (n_blocks == 0) return EPD_OK;
-  if (n_blocks <= MM_ARG_BLOCKS) {
+  if (n_blocks <= MM_PAIR_BLOCKS) {
     mm_copy_blocks_args(src->pool, src_blocks, dst->pool, dst_blocks, n_blocks, src->block_bytes, st);
     return hipGetLastError() == hipSuccess ? EPD_OK : EPD_ERR_HIP;
   }
@@ -232,7 +233,7 @@ epd_status epd_mm_gather(epd_mm_cache* src, const int32_t* blocks, int32_t n_blo
   }
   if (n_blocks == 0) return EPD_OK;
   hipStream_t st = (hipStream_t)hip_stream;
-  if (n_blocks <= MM_ARG_BLOCKS) {
+  if (n_blocks <= MM_GATHER_BLOCKS) {
     mm_copy_blocks_args(src->pool, blocks, dst_contiguous, nullptr, n_blocks, src->block_bytes, st);
     return hipGetLastError() == hipSuccess ? EPD_OK : EPD_ERR_HIP;
   }
