@@ -162,7 +162,7 @@ def test_paged_encode_leaves_other_blocks_untouched_and_rejects_bad_tables():
 
 @pytest.mark.parametrize("n", [1, 448, 449, 896, 897, 1792, 1793])
 def test_copies_of_lists_around_the_argument_limits(n):
-    """Short id lists ride in the arguments of one or several launches (448 pairs or 896 ids each), longer ones are
+    """Short id lists ride in the arguments of one or two launches (448 pairs or 896 ids each), longer ones are
     uploaded: the same bytes moved on both sides of each limit, held against plain indexing."""
     dim, total = 8, 2000
     src, dst = B.MMCache(total, BT, dim, True), B.MMCache(total, BT, dim, True)

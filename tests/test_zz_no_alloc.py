@@ -46,6 +46,42 @@ def test_noalloc_transfer_matches_the_ordinary_transfer_twice_in_a_row():
         c.close()
 
 
+def test_noalloc_transfer_of_lists_past_the_launch_arguments():
+    """Lists of more than 896 blocks go through the static array: 2500, then 1900 scattered ids (the array still holds
+    the first call's), then 896 of them, which ride in the launch arguments; against plain indexing."""
+    n_src, n_dst = 2600, 2550
+    src, a, b = _pools(n_src, n_dst, 11)
+    a.close()
+    src_ids, b_ids = np.array(src.alloc(n_src * BT)), np.array(b.alloc(n_dst * BT))
+    want = torch.full((n_dst, BT, DIM), -21555, dtype=torch.int16, device="cuda")
+    rng = np.random.default_rng(6)
+    for n in (2500, 1900, 896):
+        s, d = rng.permutation(src_ids)[:n], rng.permutation(b_ids)[:n]
+        src.transfer_to(s.tolist(), b, d.tolist(), noalloc=True)
+        torch.cuda.synchronize()
+        want[torch.from_numpy(d).cuda()] = src.pool_tensor().view(torch.int16)[torch.from_numpy(s).cuda()]
+        assert torch.equal(b.pool_tensor().view(torch.int16), want), n
+    src.close()
+    b.close()
+
+
+@pytest.mark.parametrize("n", [896, 897])
+def test_noalloc_transfer_on_both_sides_of_the_argument_limit(n):
+    src, a, b = _pools(1000, 1000, 13)
+    s, d = src.alloc(1000 * BT), a.alloc(1000 * BT)
+    assert b.alloc(1000 * BT) == d
+    rng = np.random.default_rng(n)
+    pick_s, pick_d = [s[i] for i in rng.permutation(1000)[:n]], [d[i] for i in rng.permutation(1000)[:n]]
+    src.transfer_to(pick_s, a, pick_d)
+    src.transfer_to(pick_s, b, pick_d, noalloc=True)
+    torch.cuda.synchronize()
+    got = b.pool_tensor().view(torch.int16)
+    assert torch.equal(got, a.pool_tensor().view(torch.int16))
+    assert torch.equal(got[torch.tensor(pick_d, device="cuda")], src.pool_tensor().view(torch.int16)[torch.tensor(pick_s, device="cuda")])
+    for c in (src, a, b):
+        c.close()
+
+
 def test_noalloc_transfer_rejects_what_it_cannot_hold_and_bad_ids():
     src, a, b = _pools(8, 8, 9)
     s_ids, b_ids = src.alloc(8 * BT), b.alloc(4 * BT)
