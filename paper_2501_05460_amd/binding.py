@@ -321,14 +321,17 @@ class MMCache:
 
     def pool_tensor(self) -> torch.Tensor:
         """The device pool itself as a tensor [n_blocks, block_tokens, token_dim] (a view of the library's
-        memory, no copy): valid until close()."""
+        memory, no copy): valid until close().  It holds the cache: a tensor that outlives the last other reference to
+        it keeps the pool allocated."""
         base = lib().epd_mm_cache_base(self._h)
         shape = (self.n_blocks, self.block_tokens, self.token_dim)
 
         class _Raw:   # bf16 has no typestr: the pool is exposed as 16-bit integers and viewed as bf16
             __cuda_array_interface__ = {"shape": shape, "typestr": "<i2" if self.bf16 else "<f4",
                                         "data": (int(base), False), "version": 2}
-        t = torch.as_tensor(_Raw(), device="cuda")
+        raw = _Raw()
+        raw.cache = self   # the tensor's storage holds `raw`
+        t = torch.as_tensor(raw, device="cuda")
         return t.view(torch.bfloat16) if self.bf16 else t
 
     def alloc(self, n_tokens: int) -> List[int]:

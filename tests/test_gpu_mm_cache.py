@@ -1,6 +1,9 @@
 """Paged multimodal-token cache on the GPU: the paged encode writes exactly the
 bits of the contiguous encode into the request's blocks, leaves every other
 block alone, and the encode-to-prefill block transfer moves them unchanged."""
+import gc
+import weakref
+
 import numpy as np
 import pytest
 import torch
@@ -117,6 +120,24 @@ def test_raw_pool_holds_the_oracle_index_map(dtype):
     del pool
     cache.close()
     enc.close()
+
+
+@pytest.mark.parametrize("bf16", [True, False])
+def test_a_pool_tensor_keeps_its_cache(bf16):
+    """The pool must not be freed under a view of it that is all the caller has kept."""
+    cache = B.MMCache(4, BT, 8, bf16)
+    alive = weakref.ref(cache)
+    pool = cache.pool_tensor()
+    part = pool[1:2]
+    pool.fill_(3.0)
+    torch.cuda.synchronize()
+    del cache, pool
+    gc.collect()
+    assert alive() is not None
+    assert bool((part == 3.0).all())
+    del part
+    gc.collect()
+    assert alive() is None
 
 
 def test_paged_encode_leaves_other_blocks_untouched_and_rejects_bad_tables():
