@@ -160,3 +160,33 @@ def test_the_three_forms_of_the_pre_norms_agree_with_the_oracle_and_each_other(t
     for a, b in (("classic", "copy"), ("classic", "fold"), ("copy", "fold")):
         assert not np.array_equal(out[a], out[b]), (a, b)          # three different arithmetic paths did run
         assert rel_err(out[a], out[b]) < 1e-2, (a, b)
+
+
+def test_folded_products_of_a_batch_with_a_small_last_round_are_cut(tmp_path):
+    """36 slices of 256 tokens: the 288 tiles of 256 x 256 of FC1 (2048 columns) leave 32 CUs with a second one, so the last
+    1024 rows go as a launch of 256 x 128 tiles.  Two launches are counted, and the first 32 slices carry the bits of a
+    call of their own (one whole round, no cut)."""
+    path = str(tmp_path / "out.npz")
+    code = f"""
+import sys, numpy as np, torch
+sys.path.insert(0, {ROOT!r}); sys.path.insert(0, {os.path.join(ROOT, 'tests')!r})
+import workloads as wl
+from gpu_util import make_encoder
+desc = wl.ModelDesc(dtype=wl.DT_BF16, tile_size=224, patch=14, hidden=256, heads=4, mlp=2048, layers=1, norm=wl.NORM_LAYERNORM,
+                    qk_norm=wl.QKNORM_NONE, act=wl.ACT_GELU_ERF, final_norm=0, pixel_shuffle=1, proj_kind=wl.PROJ_MLP,
+                    proj_prenorm=1, proj_mid=256, proj_out=128, eps=1e-6, max_tiles_per_call=36)
+enc = make_encoder(desc, wl.gen_weights(desc, 79, std=0.06))
+tiles = torch.from_numpy(wl.gen_tiles(desc, 79, 36)).cuda()
+enc.profile_enable(True)
+full = enc.encode(tiles, [0, 36])
+launches = enc.profile_read()["gemm_fc1"]["launches"]
+part = enc.encode(tiles[:32].contiguous(), [0, 32])
+torch.cuda.synchronize()
+np.savez({path!r}, launches=launches, full=full.view(torch.int16).cpu().numpy(), part=part.view(torch.int16).cpu().numpy())
+"""
+    env = dict(os.environ)
+    env["EPD_NORM_MODE"] = "fold"
+    subprocess.run([sys.executable, "-c", code], check=True, env=env, timeout=300)
+    got = np.load(path)
+    assert int(got["launches"]) == 2
+    assert np.array_equal(got["full"][:len(got["part"])], got["part"])
