@@ -32,15 +32,16 @@ epd_status epd_op_gemm_bf16(const void* A, const void* W, const float* bias, voi
 
 /* One launch of the bf16 MFMA GEMM in a chosen form, for tests that hold the forms against each
  * other: epi 0 bias, 1 bias + GELU(erf), 2 bias + GELU(tanh) -> C [M,N] bf16; epi 3 -> R [M,N]
- * fp32 += A W^T + bias (C unused).  form 0 = what the library would pick, 1 = 256x128 tile,
- * 2, 3 (K % 256 == 0) and 14 = 128x128 tile, both operand slabs in an LDS ring, 13 = 128x64 tile of the same kernel, 6 = 256x256 tile with the plain loop, 7 = pipelined loop, 8 = pipelined loop with both operand slabs
+ * fp32 += A W^T + bias (C unused).  form 0 = what the library would pick (W and bias padded as it pads its weights), 1 = 256x128 tile,
+ * 2, 3 (K % 256 == 0) and 14 = 128x128 tile, both operand slabs in an LDS ring (one kernel: 2 and 3 differ in epd_op_norm_gemm_bf16 and
+ * epd_op_gemm_residual_stats only), 13 = 128x64 tile of the same kernel, 6 = 256x256 tile with the plain loop, 7 = pipelined loop, 8 = pipelined loop with both operand slabs
  * loaded straight into LDS, 9 = persistent kernel (not epi 3), 10 = persistent kernel of the residual product (epi 3 only),
  * 11 = 64x64 tile of the ring kernel (11, 13, 14: what the library picks from for launches of a few slices).
  * 12 = the persistent residual product on 256x192 tiles (epi 3 only, N % 192 == 0: what the library picks for a
  * width like 1152, which is six such tile columns and four and a half 256-wide ones).
  * M >= 1 (any), N % 128 == 0 (N % 256 == 0 for forms 6 to 10), K % 128 == 0; bias [N] fp32.
  * A [M,K], C [M,N] and R [M,N] hold exactly M rows; no row past M is written.  (The kernels read whole
- * 256-row tiles; for a ragged M, and for R, the call runs on padded copies it allocates, and synchronises.) */
+ * 256-row tiles; for a ragged M, for R and for padded weights the call runs on copies it allocates, and synchronises.) */
 epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias, void* C, float* R,
                                  int32_t M, int32_t N, int32_t K, int32_t epi, int32_t form,
                                  void* hip_stream);

@@ -1371,9 +1371,16 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
   void* Ap = nullptr;
   float* Rp = nullptr;
   const bool pad_a = Mp != M, pad_r = residual;   // R also needs 256 floats of slack behind its last row
+  // what the library picks (form 0) is picked for weights padded as the library pads them
+  const int Npad = form == 0 ? pad_n(N) : N;
+  const bool pad_w = Npad != N;
+  void* Wp = nullptr;
+  float* bp = nullptr;
   auto fail = [&](epd_status code, const char* what) {
     if (Ap) (void)hipFree(Ap);
     if (Rp) (void)hipFree(Rp);
+    if (Wp) (void)hipFree(Wp);
+    if (bp) (void)hipFree(bp);
     set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_form: %s", what);
     return code;
   };
@@ -1388,17 +1395,26 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
     if (hipMemsetAsync(Rp, 0, bytes, st) != hipSuccess ||
         hipMemcpyAsync(Rp, R, (size_t)M * N * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) return fail(EPD_ERR_HIP, "copy failed");
   }
+  if (pad_w) {
+    if (hipMalloc(&Wp, (size_t)Npad * K * 2) != hipSuccess || hipMalloc((void**)&bp, (size_t)Npad * 4) != hipSuccess)
+      return fail(EPD_ERR_NOMEM, "allocation failed");
+    if (hipMemsetAsync(Wp, 0, (size_t)Npad * K * 2, st) != hipSuccess || hipMemsetAsync(bp, 0, (size_t)Npad * 4, st) != hipSuccess ||
+        hipMemcpyAsync(Wp, W, (size_t)N * K * 2, hipMemcpyDeviceToDevice, st) != hipSuccess ||
+        hipMemcpyAsync(bp, bias, (size_t)N * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) return fail(EPD_ERR_HIP, "copy failed");
+  }
   GemmParams p;
   memset(&p, 0, sizeof(p));
-  p.epi = epi; p.cfg = form; p.A = (const bf16_t*)(pad_a ? Ap : A); p.lda = K; p.W = (const bf16_t*)W; p.bias = bias;
-  p.M = M; p.N = N; p.K = K; p.Npad = N; p.C = (bf16_t*)C; p.ldc = N; p.R = pad_r ? Rp : R; p.ldr = N; p.n_pos = 1;
+  p.epi = epi; p.cfg = form; p.A = (const bf16_t*)(pad_a ? Ap : A); p.lda = K; p.W = (const bf16_t*)(pad_w ? Wp : W); p.bias = pad_w ? bp : bias;
+  p.M = M; p.N = N; p.K = K; p.Npad = Npad; p.C = (bf16_t*)C; p.ldc = N; p.R = pad_r ? Rp : R; p.ldr = N; p.n_pos = 1;
   const hipError_t err = bf16_gemm(p, st);
   if (err != hipSuccess) { fail(EPD_ERR_HIP, hipGetErrorString(err)); return EPD_ERR_HIP; }
   if (pad_r && hipMemcpyAsync(R, Rp, (size_t)M * N * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) return fail(EPD_ERR_HIP, "copy failed");
-  if (pad_a || pad_r) {
+  if (pad_a || pad_r || pad_w) {
     if (hipStreamSynchronize(st) != hipSuccess) return fail(EPD_ERR_HIP, "synchronise failed");
     if (Ap) (void)hipFree(Ap);
     if (Rp) (void)hipFree(Rp);
+    if (Wp) (void)hipFree(Wp);
+    if (bp) (void)hipFree(bp);
   }
   return EPD_OK;
 }

@@ -226,7 +226,7 @@ def test_gemm_forms_agree_bit_for_bit(M, N, K, epi):
         return out.view(torch.int16 if epi != 3 else torch.int32).cpu().numpy()
 
     ref = run(6)
-    forms = [0, 1, 2, 7, 8, 11] + ([3] if K % 256 == 0 else []) + ([9] if epi != 3 else [10])
+    forms = [0, 1, 7, 8, 11, 13, 14] + ([9] if epi != 3 else [10])
     for form in forms:
         assert np.array_equal(run(form), ref), form
     if epi == 0:   # and the value itself, against the oracle
@@ -254,6 +254,34 @@ def test_ring_tiles_agree_bit_for_bit(M, N, K, epi):
     ref = run(1)
     for form in (11, 13, 14, 0):
         assert np.array_equal(run(form), ref), form
+
+
+@pytest.mark.parametrize("epi,M,N,K,form,cut", [
+    (3, 9200, 1152, 256, 12, False),     # 256 x 192 tiles
+    (3, 2600, 1152, 1152, 14, False),    # ring tiles over nine columns of 128, the tenth all padding
+    (3, 3570, 1152, 256, 13, False),     # 128 x 64: eighteen of twenty
+    (3, 14600, 1152, 1152, 10, True),    # whole rounds, the rows behind on ring tiles
+    (3, 6700, 3200, 1152, 10, True),
+    (3, 5000, 3200, 128, 0, False),      # whole 256-wide tile columns, the last 128 columns apart
+    (0, 3000, 2304, 1152, 1, False),     # one round of 256 x 128 tiles
+    (0, 14600, 2304, 128, 9, True),
+    (2, 4800, 3584, 1152, 9, True),
+    (0, 28, 1152, 128, 11, False),
+])
+def test_what_the_library_picks_leaves_the_bits_of_one_form(epi, M, N, K, form, cut):
+    """The dispatch over weights padded as the library pads them (1152 columns to 1280, 3200 to 3328): every kind of choice is
+    reached, and leaves the bits of 256 x 128 tiles over unpadded weights."""
+    taken, rows = B.op_gemm_bf16_choice(M, N, K, epi)
+    assert (taken, rows < M) == (form, cut)
+    rng = np.random.default_rng(M + N + K + epi)
+    A = B.to_device(_bf16_grid(rng, (M, K), 0.5), True)
+    W = B.to_device(_bf16_grid(rng, (N, K), 0.05), True)
+    bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32) * 0.1).cuda()
+    r0 = torch.from_numpy(rng.standard_normal((M, N)).astype(np.float32)).cuda() if epi == 3 else None
+    got, want = (B.op_gemm_bf16_form(A, W, bias, epi, f, None if r0 is None else r0.clone()) for f in (0, 1))
+    torch.cuda.synchronize()
+    as_int = torch.int32 if epi == 3 else torch.int16
+    assert torch.equal(got.view(as_int), want.view(as_int))
 
 
 @pytest.mark.parametrize("M,N,K", [(256, 384, 128), (1000, 1152, 256), (2900, 1152, 1152), (77, 384, 384), (10240, 1152, 128)])
