@@ -280,8 +280,8 @@ class Encoder:
 
 
 def _i32(values: Sequence[int]):
-    """values as a C array of int32.  Lists and tuples go through an `array`: a block list of 208 ids in 9 us, item by
-    item through ctypes 26 us."""
+    """values as a C array of int32.  Lists and tuples go through an `array`: a list of 208 ids in 4 us, item by
+    item through ctypes 13 us."""
     if type(values) in (list, tuple) and values:
         try:
             return (ctypes.c_int32 * len(values)).from_buffer(array("i", values))   # keeps the array alive

@@ -906,7 +906,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
       GemmParams p = gp(EPI_BIAS, Xn, c->D_k, w.qkv, M);
       p.C = QK; p.ldc = ld_qk;
       with_norm(p, w.qkv_cs);
-      // a slice alone: the value projection rides in the same launch (its weights follow the q/k projection's)
+      // few slices: the value projection rides in the same launch (its weights follow the q/k projection's)
       GemmParams pp = p;
       pp.n2 = w.v.N; pp.n2_pad = w.v.Npad; pp.VT = VT; pp.hd_pad = c->hd_pad; pp.heads = x.H; pp.n_tok = x.Ns;
       paired = (const bf16_t*)w.v.W == (const bf16_t*)w.qkv.W + (size_t)w.qkv.Npad * w.qkv.K && w.v.b == w.qkv.b + w.qkv.Npad &&

@@ -74,7 +74,7 @@ struct GemmParams {
   // their statistics pairs to stats_out [M][n_part_out][2] (pair index = column / 128).
   bf16_t* xb; long ldxb;
   float* stats_out; int n_part_out;
-  // A second product over the same A in the same launch (epi EPI_BIAS, small launches only: bf16_gemm_pair_fits):
+  // A second product over the same A in the same launch (epi EPI_BIAS, where bf16_gemm_pair_fits):
   // the value projection next to the q/k projection.  Its packed weights and bias follow the first product's
   // directly (rows Npad .. Npad + n2_pad of W, entries Npad .. of bias); its n2 columns leave through the
   // EPI_VT store (VT, hd_pad, heads, n_tok).  n2_pad == 0: off.
