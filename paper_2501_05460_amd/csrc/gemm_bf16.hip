@@ -1379,7 +1379,7 @@ hipError_t launch_ring(const GemmParams& p, int tile, hipStream_t st) {
 // encoder, each form forced for one product at a time (three shapes, 256 to 65536 rows, K 1024 to 12800, weights cold; half
 // of them within 2-4 %, rms 4-7 %): a workgroup's chain of KT 64-deep slabs plus its fixed cost (first slab, epilogue),
 // times the rounds the launch's tiles make on the CUs, and a part that grows with the tiles alone (the CUs share memory
-// and power).  Of 385 products measured in all forms, the one taken is within 3 % of the fastest for 87 %, within 5 % for 95 %.
+// and power).  Of 697 products measured in all forms, the one taken is within 3 % of the fastest for 87 %, within 5 % for 94 %.
 struct RingPick { int tile; double us; };
 bool f32_rows(int epi) { return epi == EPI_BIAS_RESIDUAL || epi == EPI_BIAS_POS; }   // reads and writes rows of the stream
 bool has_gelu(int epi) { return epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH; }
@@ -1391,8 +1391,8 @@ RingPick best_ring(int M, int n_cols, int K, int epi) {
                         : 5.0 + 0.12 * kt + fmax(1.0, per_cu(64, 64)) * 0.198 * kt;
   RingPick best = {RING_64x64, t0};
   const double r1 = ceil(per_cu(128, 64));   // two workgroups share a CU: a tile alone on its CU takes 3/4 of two
-  const double t1 = f32 ? 6.2 + (r1 == 1.0 ? 0.15 + 0.445 * kt : r1 * (1.2 + 0.33 * kt))
-                        : 5.4 + (r1 == 1.0 ? 0.35 + 0.42 * kt : r1 * (0.27 + 0.315 * kt)) + (has_gelu(epi) ? 0.8 : 0.0);
+  const double t1 = f32 ? 6.2 + (r1 == 1.0 ? 2.15 + 0.445 * kt : r1 * (1.2 + 0.33 * kt))
+                        : 5.4 + (r1 == 1.0 ? 0.35 + 0.42 * kt : r1 * 0.318 * kt) + (has_gelu(epi) ? 0.8 : 0.0);
   if (t1 < best.us) best = {RING_128x64, t1};
   const double r2 = per_cu(128, 128);
   const double t2 = f32 ? 5.5 + ceil(r2) * (4.5 + 0.4 * kt) + r2 * 0.187 * kt
