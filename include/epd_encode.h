@@ -257,11 +257,12 @@ epd_status epd_mm_transfer(const epd_mm_cache* src, const int32_t* src_blocks, e
 
 /* epd_mm_transfer for callers that must not allocate device memory while they run: code under HIP graph
  * capture, tight serving loops, harnesses that forbid it.  Same arguments, same result, same validation;
- * lists of up to 896 blocks travel in the copies' launch arguments, longer ones in a static device array of the library
+ * lists of up to 896 blocks travel in the copies' launch arguments, and so does any list while the stream is being
+ * captured (the graph then carries the ids); other lists go through a static device array of the library
  * (2 x EPD_MM_NOALLOC_MAX_BLOCKS ints, 512 KiB per GPU, held until the process ends) instead of the
  * destination cache's own scratch, and the call allocates and frees nothing.  More than
  * EPD_MM_NOALLOC_MAX_BLOCKS blocks in one call: EPD_ERR_UNSUPPORTED, nothing enqueued (cut the transfer
- * into several calls).  Every call with a longer list shares its GPU's array and keeps the previous such call's ids in
+ * into several calls).  Every call that uses the array shares its GPU's and keeps the previous such call's ids in
  * it: these calls are safe one after the other on one stream; two of them in flight at once on the same
  * GPU (different streams or host threads) race on the array. */
 enum { EPD_MM_NOALLOC_MAX_BLOCKS = 65536 };

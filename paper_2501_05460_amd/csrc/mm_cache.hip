@@ -159,6 +159,14 @@ namespace {
 // launches 1344 blocks of 16 x 3200 61.3 | 59.6, 1664 77.8 | 73.1; gather of 1792 blocks of 16 x 1152 27.3 | 30.5, of 16 x 4096
 // 86.3 | 90.2.  13 slices of the 300M shape (208 blocks), transfer + gather: 46 | 22, the two copies alone are 21.
 constexpr int MM_PAIR_BLOCKS = MM_ARG_IDS, MM_GATHER_BLOCKS = 2 * MM_ARG_IDS;
+// A stream under capture takes lists of any length in the arguments: a recorded upload would read the staging when the
+// graph runs, with the ids of whichever call used it last, and its event cannot be waited for.
+bool ids_in_arguments(int n_blocks, int limit, hipStream_t st) {
+  if (n_blocks <= limit) return true;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &cap) != hipSuccess) { (void)hipGetLastError(); return false; }
+  return cap == hipStreamCaptureStatusActive;
+}
 // body of the two transfer calls; ids_dev: where the id lists go on the device (null: the static array of
 // the current device, looked up once every argument has passed its checks)
 epd_status transfer_impl(const epd_mm_cache* src, const int32_t* src_blocks, epd_mm_cache* dst,
@@ -177,7 +185,7 @@ epd_status transfer_impl(const epd_mm_cache* src, const int32_t* src_blocks, epd
     return EPD_ERR_OFFSETS;
   }
   if (n_blocks == 0) return EPD_OK;
-  if (n_blocks <= MM_PAIR_BLOCKS) {
+  if (ids_in_arguments(n_blocks, MM_PAIR_BLOCKS, st)) {
     mm_copy_blocks_args(src->pool, src_blocks, dst->pool, dst_blocks, n_blocks, src->block_bytes, st);
     return hipGetLastError() == hipSuccess ? EPD_OK : EPD_ERR_HIP;
   }
@@ -233,7 +241,7 @@ epd_status epd_mm_gather(epd_mm_cache* src, const int32_t* blocks, int32_t n_blo
   }
   if (n_blocks == 0) return EPD_OK;
   hipStream_t st = (hipStream_t)hip_stream;
-  if (n_blocks <= MM_GATHER_BLOCKS) {
+  if (ids_in_arguments(n_blocks, MM_GATHER_BLOCKS, st)) {
     mm_copy_blocks_args(src->pool, blocks, dst_contiguous, nullptr, n_blocks, src->block_bytes, st);
     return hipGetLastError() == hipSuccess ? EPD_OK : EPD_ERR_HIP;
   }

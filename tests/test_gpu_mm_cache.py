@@ -203,3 +203,41 @@ def test_copies_of_lists_around_the_argument_limits(n):
     assert torch.equal(got.view(torch.int16).view(n, BT, dim), rows)
     src.close()
     dst.close()
+
+
+@pytest.mark.parametrize("n", [896, 897, 1300, 1793, 2000])
+def test_captured_copies_carry_their_ids(n):
+    """Transfers and a gather recorded into a graph move the blocks of the recorded lists at every replay, with copies of
+    other lists between the replays."""
+    dim, total = 8, 2100
+    src, dst, dst2 = (B.MMCache(total, BT, dim, True) for _ in range(3))
+    g = torch.Generator(device="cuda").manual_seed(n)
+    src.pool_tensor().view(torch.int16).copy_(torch.randint(-32768, 32767, (total, BT, dim), dtype=torch.int16, device="cuda", generator=g))
+    rng = np.random.default_rng(n)
+    s, d = np.array(src.alloc(total * BT)), np.array(dst.alloc(total * BT))
+    assert dst2.alloc(total * BT) == d.tolist()
+    sa, db = rng.permutation(s)[:n], rng.permutation(d)[:n]
+    side = torch.cuda.Stream()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        src.transfer_to(sa.tolist(), dst, db.tolist())
+        src.transfer_to(sa.tolist(), dst2, db.tolist(), noalloc=True)
+        out = src.gather(sa.tolist())
+    torch.cuda.synchronize()
+    rows = src.pool_tensor().view(torch.int16)[torch.from_numpy(sa).cuda()]
+    for rep in range(3):
+        other = rng.permutation(s)
+        for c in (dst, dst2):
+            src.transfer_to(other.tolist(), c, rng.permutation(d).tolist(), noalloc=c is dst2)
+        src.gather(other.tolist())
+        want = dst.pool_tensor().view(torch.int16).clone(), dst2.pool_tensor().view(torch.int16).clone()
+        out.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        for c, w in zip((dst, dst2), want):
+            w[torch.from_numpy(db).cuda()] = rows
+            assert torch.equal(c.pool_tensor().view(torch.int16), w), rep
+        assert torch.equal(out.view(torch.int16).view(n, BT, dim), rows), rep
+    for c in (src, dst, dst2):
+        c.close()
