@@ -967,13 +967,14 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
       continue;
     }
     norm_kernel(w.n2_g, w.n2_b, !copy);
+    GemmParams p2 = gp(EPI_BIAS_RESIDUAL, Hd, c->F_k, w.fc2, M);
     { ProfScope ps(c, 7, st);
       GemmParams p = gp(act_epi, Xn, c->D_k, w.fc1, M);
       p.C = Hd; p.ldc = c->F_k;
+      p.c_cached = bf16_gemm_on_64x64(p2);
       with_norm(p, w.fc1_cs);
       HIP_TRY(c, bf16_gemm(p, st)); }
     { ProfScope ps(c, 8, st);
-      GemmParams p2 = gp(EPI_BIAS_RESIDUAL, Hd, c->F_k, w.fc2, M);
       p2.R = X; p2.ldr = x.D;
       with_emit(p2, l + 1 < n_layers);   // the next layer's first norm; nothing reads it after the last layer
       HIP_TRY(c, bf16_gemm(p2, st)); }

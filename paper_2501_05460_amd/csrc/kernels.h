@@ -53,6 +53,10 @@ struct GemmParams {
   const float* bias;          // [Npad]
   int M, N, K, Npad;
   bf16_t* C; long ldc;        // bf16 output (BIAS, GELU_*)
+  // 1: 256 x 128 tiles store C without the streaming hint (one round of them writes at most 17 MB, which the caches keep),
+  // for a reader on 64 x 64 ring tiles, which wait for their rows in several rounds.  Rows of the 1024-wide encoder, us:
+  // 1728, FC1 25.0 -> 26.6 and FC2 behind it on 64 x 64 tiles 34 -> 29; 2048, 26.3 -> 27.6 and on 128 x 64 tiles 34.0 | 34.0.
+  int c_cached;
   const int* row_map;         // optional paged output: row r -> row_map[r / block_tokens] * block_tokens + r % block_tokens
   int block_tokens;
   float* R; long ldr;         // fp32 residual stream (RESIDUAL, POS); RESIDUAL reads whole tiles: R must hold
@@ -81,6 +85,7 @@ struct GemmParams {
   int n2, n2_pad;
 };
 hipError_t bf16_gemm(const GemmParams& p, hipStream_t st);
+bool bf16_gemm_on_64x64(const GemmParams& p);   // whether p, without a folded pre-norm, takes 64 x 64 ring tiles
 // true: bf16_gemm runs p with its second product (n2_pad > 0) as one launch; false: the caller issues two products
 bool bf16_gemm_pair_fits(const GemmParams& p);
 // the product on the ring kernel's tiles (gemm_bf16_ring.hip: launches of a few slices), any epilogue, n2_pad included
