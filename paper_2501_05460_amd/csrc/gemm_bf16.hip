@@ -694,17 +694,6 @@ __global__ __launch_bounds__(NTHREADS, BM_ == 128 && PIPE == 0 ? 2 : 1) void k_g
       }
     }
   __syncthreads();
-  if constexpr (BN == 128 && (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH)) {
-    if (p.c_cached) {   // a loop of its own: the choice inside the loop below cost a launch without it 3 % (FC1 of 2048 rows, 26.3 us)
-#pragma unroll
-      for (int i = 0; i < PER_T; ++i) {
-        const int q = tid + NTHREADS * i, r = q / NCH, c = q % NCH, row = m0 + r, col = n0 + c * 8;
-        if (row < p.M && col < p.N)
-          *reinterpret_cast<u32x4*>(p.C + (long)row * p.ldc + col) = *reinterpret_cast<const u32x4*>(stage + r * ROWB + ((c ^ (r & 15)) << 4));
-      }
-      return;
-    }
-  }
 #pragma unroll
   for (int i = 0; i < PER_T; ++i) {
     const int q = tid + NTHREADS * i;
@@ -739,9 +728,8 @@ __global__ __launch_bounds__(NTHREADS, BM_ == 128 && PIPE == 0 ? 2 : 1) void k_g
 // rows: the next tile's main loop starts right behind the last store, without
 // the launch gap and the exposed first-slab latency a fresh workgroup pays.
 // ---------------------------------------------------------------------------
-// ADIR: the activation slab also goes from global memory straight into LDS (one slab ahead, like the weight
-// slab) instead of through registers two slabs ahead.
-template <int EPI, bool FOLD, bool ADIR = false>
+// For products with a folded pre-norm; the others run on gemm_bf16_wide.hip.
+template <int EPI>
 __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p, const int gm_, const int gw,
                                                               const int n_tiles) {
   constexpr int BN = 256, NTHREADS = 512, WN = 64, WAVES_N = 4, WM = 128, TM = 4, TN = 2;
@@ -756,7 +744,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
   float* sCol = sBias + BN;   // column sums of the weights, mean and rstd of the tile's rows (folded pre-norm)
   float* sMu = sCol + BN;
   float* sRs = sMu + BM;
-  constexpr bool fold = FOLD;
+  constexpr bool fold = true;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
@@ -837,19 +825,6 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
     for (int i = 0; i < A_LD; ++i)
       *reinterpret_cast<u32x4*>(sA + buf * BM * BK + ROWS_PER_LD * i * BK + st_off) = ra[S][i];
   };
-  // ADIR: activation slab kt of the tile rows mrow0 .. -> LDS, the swizzle applied on the global side as for the
-  // weights (LDS-DMA reaches the whole LDS through M0 on gfx950, so the activation buffers above 64 KiB are fine)
-  const unsigned ad_voff = ((unsigned)ld_row * (unsigned)p.lda + ((ld_c ^ SWZ(ld_row)) * 8)) * 2;
-  auto aload = [&](int buf, int mrow0, int kt) {
-#pragma unroll
-    for (int i = 0; i < A_LD; ++i) {
-      const bf16_t* g = p.A + (long)(mrow0 + ROWS_PER_LD * i) * p.lda + kt * BK;   // uniform
-      bf16_t* l = sA + buf * BM * BK + (wave_u * 64 + NTHREADS * i) * 8;
-      const unsigned lds_addr = (unsigned)(size_t)(__attribute__((address_space(3))) void*)l;
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                   :: "v"(ad_voff), "s"(g), "s"(lds_addr) : "memory", "m0");
-    }
-  };
   auto wait_vm = [&](auto n) {
     constexpr int N = decltype(n)::value;
     __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | (0x7 << 4) | (0xf << 8));
@@ -894,17 +869,11 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
     stats_load(tid, rp0, m0);
     tile_scalars(tid, rp0, m0, n0);
   }
-  using VM_0 = std::integral_constant<int, 0>;
   bload(0, n0, 0);
-  if constexpr (ADIR) {
-    aload(0, m0, 0);
-    wait_vm(VM_0{});
-  } else {
-    gload(S0{}, m0, 0);
-    gload(S1{}, m0, 1);
-    sstore(S0{}, 0);
-    wait_vm(VM_A{});   // loads complete in order: all but slab 1's are done, weight slab 0 has landed
-  }
+  gload(S0{}, m0, 0);
+  gload(S1{}, m0, 1);
+  sstore(S0{}, 0);
+  wait_vm(VM_A{});   // loads complete in order: all but slab 1's are done, weight slab 0 has landed
   __syncthreads();
 
   for (;;) {
@@ -924,19 +893,14 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
     auto slab = [&](auto lset, auto sset, int buf, int kt) {
       const bool w_own = kt + 1 < KT_, a_own = kt + 2 < KT_;
       bload(buf ^ 1, w_own ? n0 : n0n, w_own ? kt + 1 : kt + 1 - KT_);
-      if constexpr (ADIR) aload(buf ^ 1, w_own ? m0 : m0n, w_own ? kt + 1 : kt + 1 - KT_);
-      else gload(lset, a_own ? m0 : m0n, a_own ? kt + 2 : kt + 2 - KT_);
+      gload(lset, a_own ? m0 : m0n, a_own ? kt + 2 : kt + 2 - KT_);
       __builtin_amdgcn_sched_barrier(0);
       ldfrag(S1{}, buf, 1); mma(S0{}); interleave();
       ldfrag(S0{}, buf, 2); mma(S1{}); interleave();
       ldfrag(S1{}, buf, 3); mma(S0{}); interleave();
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (ADIR) {
-        wait_vm(VM_0{});        // both slabs have landed in the other buffer
-      } else {
-        sstore(sset, buf ^ 1);
-        wait_vm(VM_A{});
-      }
+      sstore(sset, buf ^ 1);
+      wait_vm(VM_A{});
       __syncthreads();
       ldfrag(S0{}, buf ^ 1, 0); mma(S1{}); interleave();
     };
@@ -1063,262 +1027,6 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
         }
       }
     }
-    }
-    if (!has_next) break;
-    __syncthreads();   // buffer 1 has been read out: the next tile's first hand-over may fill it
-    pos = nxt; m0 = m0n; n0 = n0n;
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Persistent form of the residual product, R += A W^T + bias on the fp32 stream: the tile walk and the main loop
-// of the persistent kernel above (both operand slabs straight into LDS, the loads past a tile's last slab fetch
-// the next tile's first slab into buffer 0), and the four-pass fp32 read-modify-write epilogue staged through
-// LDS buffer 1 only.  A pass holds sub-tile row group i = pass of all eight waves (rows wm * 128 + 32 pass ..
-// + 31 of both wave rows: staging row r = 32 wm + row), so every wave stages in every pass.  The stream rows of
-// the first two passes are fetched while the last two slabs are multiplied, those of pass p + 2 behind pass p.
-//
-// BN = 192 (tile 256 x 192) is for output widths that are whole multiples of 192 and not of 256 (1152 = 6 x 192
-// = 4.5 x 256: every fifth 256-wide tile column would be half empty).  Its waves stand 4 x 2, each on 64 x 96
-// (2 x 3 MFMA blocks; the k-steps of an element are summed in the same order, so the bits are those of every
-// other form).  The 64 staging rows of a pass then hold sub-tile row group pass / 2 of wave rows 2 (pass % 2)
-// and 2 (pass % 2) + 1, so half of the waves stage in a pass, and a staging row's 48 chunks no longer match a
-// wave: thread t reads chunks t, t + 512, .. of the 3072 a pass has, row and column per lane.
-// ---------------------------------------------------------------------------
-template <int BN>
-__global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist_res(const GemmParams p, const int gm_, const int gw,
-                                                                  const int n_tiles) {
-  static_assert(BN == 256 || BN == 192, "tile widths compiled");
-  constexpr bool WIDE = BN == 256;
-  constexpr int NTHREADS = 512, WAVES_N = WIDE ? 4 : 2, WN = BN / WAVES_N, WM = BM / (8 / WAVES_N), TM = WM / 32, TN = WN / 32;
-  constexpr int A_LD = 4, B_LD = BN / 64, ROWS_PER_LD = 64;
-  constexpr int XNCH = BN * 4 / 16;                // 16-byte chunks per staging row (BN = 256: one wave reads one row)
-  constexpr int XSTEP = NTHREADS / XNCH;           // BN = 256: 8 staging rows between a thread's chunks
-  constexpr int XPER_T = 64 * XNCH / NTHREADS;     // 8 (6) chunks per thread and pass
-  constexpr int ROWB = BN * 4;
-
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  bf16_t* sB = reinterpret_cast<bf16_t*>(smem);  // [2][BN][64]: bytes 0 .. 64 Ki
-  bf16_t* sA = sB + 2 * BN * BK;                 // [2][BM][64]: bytes 64 Ki .. 128 Ki
-  float* sBias = reinterpret_cast<float*>(smem + smem_main_bytes<BN, NTHREADS>());
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-  const int l32 = lane & 31, lh = lane >> 5;
-  const int KT_ = p.K / BK;  // even
-  const int gn = WIDE ? p.Npad / BN : p.N / BN;
-
-  auto tile_of = [&](int pos, int& m0, int& n0) {
-    const int x = pos & 7, slot = pos >> 3;
-    const int q = n_tiles >> 3, r = n_tiles & 7;
-    const int id = x * q + (x < r ? x : r) + slot;
-    const int band_tiles = gm_ * gw;
-    const int full_bands = gn / gw;
-    int band = id / band_tiles, in_band = id % band_tiles, bw = gw;
-    if (band >= full_bands) { band = full_bands; in_band = id - full_bands * band_tiles; bw = gn - full_bands * gw; }
-    m0 = (in_band / bw) * BM;
-    n0 = (band * gw + in_band % bw) * BN;
-  };
-
-  const int ld_row = tid >> 3, ld_c = tid & 7;
-  const unsigned ad_voff = ((unsigned)ld_row * (unsigned)p.lda + ((ld_c ^ SWZ(ld_row)) * 8)) * 2;
-  const unsigned bd_voff = ((unsigned)ld_row * (unsigned)p.K + ((ld_c ^ SWZ(ld_row)) * 8)) * 2;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  auto dma = [&](const bf16_t* g, bf16_t* l, unsigned voff) {
-    const unsigned lds_addr = (unsigned)(size_t)(__attribute__((address_space(3))) void*)l;
-    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                 :: "v"(voff), "s"(g), "s"(lds_addr) : "memory", "m0");
-  };
-  auto bload = [&](int buf, int ncol0, int kt) {
-#pragma unroll
-    for (int i = 0; i < B_LD; ++i)
-      dma(p.W + (long)(ncol0 + ROWS_PER_LD * i) * p.K + kt * BK, sB + buf * BN * BK + (wave_u * 64 + NTHREADS * i) * 8, bd_voff);
-  };
-  auto aload = [&](int buf, int mrow0, int kt) {
-#pragma unroll
-    for (int i = 0; i < A_LD; ++i)
-      dma(p.A + (long)(mrow0 + ROWS_PER_LD * i) * p.lda + kt * BK, sA + buf * BM * BK + (wave_u * 64 + NTHREADS * i) * 8, ad_voff);
-  };
-  auto wait_vm = [&](auto n) {
-    constexpr int N = decltype(n)::value;
-    __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | (0x7 << 4) | (0xf << 8));
-  };
-
-  f32x16 acc[TM][TN];
-  bf16x8 fa[2][TM], fb[2][TN];
-  const int frag_sw = SWZ(l32);
-  auto ldfrag = [&](auto set, int buf, int kk) {
-    constexpr int S = decltype(set)::value;
-    const bf16_t* a_s = sA + buf * BM * BK + (wm * WM + l32) * BK;
-    const bf16_t* b_s = sB + buf * BN * BK + (wn * WN + l32) * BK;
-    const int coff = (((2 * kk + lh) ^ frag_sw) * 8);
-#pragma unroll
-    for (int i = 0; i < TM; ++i) fa[S][i] = *reinterpret_cast<const bf16x8*>(a_s + i * 32 * BK + coff);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) fb[S][j] = *reinterpret_cast<const bf16x8*>(b_s + j * 32 * BK + coff);
-  };
-  auto mma = [&](auto set) {
-    constexpr int S = decltype(set)::value;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j) acc[i][j] = mfma32(fb[S][j], fa[S][i], acc[i][j]);
-  };
-  auto interleave = [&]() {
-#pragma unroll
-    for (int i = 0; i < TM + TN; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-    }
-  };
-  using S0 = std::integral_constant<int, 0>;
-  using S1 = std::integral_constant<int, 1>;
-  using VM_0 = std::integral_constant<int, 0>;
-  using VM_X = std::integral_constant<int, XPER_T>;
-
-  // Stream rows of an epilogue pass through a buffer descriptor: every lane of every wave issues exactly XPER_T
-  // loads whatever the tile's position, so a wait can count them.  BN = 256: the row is a scalar offset, outside
-  // the descriptor's range check (rows past M are read like any other: R holds whole tiles); columns past N fall
-  // outside the range and come back as zero.  BN = 192: row and column are the lane offset; a row past M comes
-  // back as zero.
-  __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
-      p.R, 0, (int)(unsigned)(((long)(p.M - 1) * p.ldr + p.N) * 4), 0x00020000);
-  f32x4 xr[2][XPER_T];
-  // staging row r of a pass <-> tile row: BN = 256: (r / 32) * 128 + 32 pass + r % 32;
-  // BN = 192: (2 (pass % 2) + r / 32) * 64 + 32 (pass / 2) + r % 32
-  auto tile_row = [&](int pass, int r) {
-    return WIDE ? (r >> 5) * 128 + pass * 32 + (r & 31) : (2 * (pass & 1) + (r >> 5)) * 64 + (pass >> 1) * 32 + (r & 31);
-  };
-  // BN = 192: chunk i of this thread in a pass: staging row and chunk column
-  auto x_r = [&](int i) { return (tid + NTHREADS * i) / XNCH; };
-  auto x_c = [&](int i) { return (tid + NTHREADS * i) % XNCH; };
-
-  int pos = blockIdx.x, m0, n0, m0n, n0n;
-  tile_of(pos, m0, n0);
-  if (tid < BN) sBias[tid] = p.bias[n0 + tid];
-  bload(0, n0, 0);
-  aload(0, m0, 0);
-  wait_vm(VM_0{});
-  __syncthreads();
-
-  for (;;) {
-    ldfrag(S0{}, 0, 0);
-    const int nxt = pos + (int)gridDim.x;
-    const bool has_next = nxt < n_tiles;
-    if (has_next) tile_of(nxt, m0n, n0n); else { m0n = m0; n0n = n0; }   // no next tile: harmless re-reads
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-    // the thread's chunk of the stream: column n0 + 4 (tid % 64), rows given by the pass
-    const int x_col = n0 + (tid % XNCH) * 4;
-    const bool x_col_ok = x_col < p.N;
-    auto xload = [&](auto set, int pass) {
-      constexpr int S = decltype(set)::value;
-#pragma unroll
-      for (int i = 0; i < XPER_T; ++i)
-        if constexpr (WIDE)
-          xr[S][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-              rsrc_x, (unsigned)x_col * 4u, (unsigned)(m0 + tile_row(pass, wave_u + XSTEP * i)) * (unsigned)p.ldr * 4u, 2));
-        else
-          xr[S][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-              rsrc_x, ((unsigned)(m0 + tile_row(pass, x_r(i))) * (unsigned)p.ldr + (unsigned)(n0 + x_c(i) * 4)) * 4u, 0, 2));
-    };
-    // PHASE 0: a slab in the middle of the tile; 1: the slab before the last (also starts the stream rows of pass 0,
-    // which its wait leaves in flight); 2: the last slab (fetches the next tile's first slab, starts pass 1's rows)
-    auto slab = [&](int buf, int kt, auto phase) {
-      constexpr int PHASE = decltype(phase)::value;
-      const bool own = kt + 1 < KT_;
-      bload(buf ^ 1, own ? n0 : n0n, own ? kt + 1 : 0);
-      aload(buf ^ 1, own ? m0 : m0n, own ? kt + 1 : 0);
-      if constexpr (PHASE == 1) xload(S0{}, 0);
-      if constexpr (PHASE == 2) xload(S1{}, 1);
-      __builtin_amdgcn_sched_barrier(0);
-      ldfrag(S1{}, buf, 1); mma(S0{}); interleave();
-      ldfrag(S0{}, buf, 2); mma(S1{}); interleave();
-      ldfrag(S1{}, buf, 3); mma(S0{}); interleave();
-      __builtin_amdgcn_sched_barrier(0);
-      // loads complete in order: everything but the newest stream rows has landed
-      if constexpr (PHASE == 0) wait_vm(VM_0{}); else wait_vm(VM_X{});
-      __syncthreads();
-      if constexpr (PHASE < 2) { ldfrag(S0{}, buf ^ 1, 0); mma(S1{}); interleave(); }
-      else mma(S1{});
-    };
-    for (int kt = 0; kt < KT_ - 2; kt += 2) {
-      slab(0, kt, std::integral_constant<int, 0>{});
-      slab(1, kt + 1, std::integral_constant<int, 0>{});
-    }
-    slab(0, KT_ - 2, std::integral_constant<int, 1>{});
-    slab(1, KT_ - 1, std::integral_constant<int, 2>{});
-    // LDS buffer 0 now holds slab 0 of the next tile; nobody reads buffer 1 any more.
-
-    // ---- epilogue through LDS buffer 1: staging rows 0..31 in sB[1], 32..63 in sA[1], [row][256] floats ----
-    {
-      // addresses from an opaque copy of the thread index, made anew per tile (see the persistent kernel above)
-      int tid_opaque = threadIdx.x;
-      asm volatile("" : "+v"(tid_opaque));
-      const int tid = tid_opaque, lane = tid & 63, wave = tid >> 6;
-      const int wm = wave / WAVES_N, wn = wave % WAVES_N;
-      const int l32 = lane & 31, lh = lane >> 5;
-      const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-      auto stage_row = [&](int r) -> unsigned char* {
-        return reinterpret_cast<unsigned char*>(r < 32 ? sB + BN * BK : sA + BM * BK) + (r & 31) * ROWB;
-      };
-      auto fp32_pass = [&](auto set, auto pass_) {
-        constexpr int S = decltype(set)::value;
-        constexpr int pass = decltype(pass_)::value;
-        constexpr int sub = WIDE ? pass : pass >> 1;     // sub-tile row group of a wave that goes through this pass
-        if (pass > 0) __syncthreads();   // the previous pass has been read out
-        if (WIDE || (wm >> 1) == (pass & 1)) {           // wave-uniform
-          const int r = (WIDE ? wm : wm & 1) * 32 + l32;   // this lane's staging row
-          unsigned char* srow = stage_row(r);
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int gi = 0; gi < 4; ++gi) {
-              const int cl = wn * WN + j * 32 + gi * 8 + lh * 4;
-              const f32x4 b4 = *reinterpret_cast<const f32x4*>(sBias + cl);
-              f32x4 v;
-#pragma unroll
-              for (int e = 0; e < 4; ++e) v[e] = acc[sub][j][gi * 4 + e] + b4[e];
-              *reinterpret_cast<f32x4*>(srow + (((cl >> 2) ^ (r & 15)) << 4)) = v;
-            }
-        }
-        __syncthreads();
-        if (pass == 3 && has_next && tid < BN) sBias[tid] = p.bias[n0n + tid];   // every bias read is behind us
-        if constexpr (WIDE) {
-          if (x_col_ok) {
-            const int c = tid % XNCH;
-#pragma unroll
-            for (int i = 0; i < XPER_T; ++i) {
-              const int r = wave_u + XSTEP * i;
-              const int row = m0 + tile_row(pass, r);              // uniform
-              if (row < p.M) {
-                const f32x4 v = *reinterpret_cast<const f32x4*>(stage_row(r) + ((c ^ (r & 15)) << 4));
-                __builtin_nontemporal_store(xr[S][i] + v, reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + x_col));
-              }
-            }
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < XPER_T; ++i) {
-            const int r = x_r(i), c = x_c(i);
-            const int row = m0 + tile_row(pass, r), col = n0 + c * 4;
-            if (row < p.M && col < p.N) {
-              const f32x4 v = *reinterpret_cast<const f32x4*>(stage_row(r) + ((c ^ (r & 15)) << 4));
-              __builtin_nontemporal_store(xr[S][i] + v, reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + col));
-            }
-          }
-        }
-        if (pass + 2 < 4) xload(set, pass + 2);
-      };
-      fp32_pass(S0{}, std::integral_constant<int, 0>{});
-      fp32_pass(S1{}, std::integral_constant<int, 1>{});
-      fp32_pass(S0{}, std::integral_constant<int, 2>{});
-      fp32_pass(S1{}, std::integral_constant<int, 3>{});
     }
     if (!has_next) break;
     __syncthreads();   // buffer 1 has been read out: the next tile's first hand-over may fill it
@@ -1473,7 +1181,7 @@ bool a_direct() {
   return on;
 }
 
-template <int EPI, bool FOLD>
+template <int EPI>
 hipError_t launch_persist(const GemmParams& p, hipStream_t st) {
   const int gm = (p.M + BM - 1) / BM, gn = p.Npad / 256;
   const int n_tiles = gm * gn;
@@ -1488,8 +1196,7 @@ hipError_t launch_persist(const GemmParams& p, hipStream_t st) {
   }
   if (p.band > 0 && p.band <= gn) gw = p.band;
   const int grid = n_tiles < cu_count() ? n_tiles : cu_count();
-  if (!FOLD && a_direct()) k_gemm_bf16_persist<EPI, false, true><<<dim3(grid), dim3(512), smem_bytes<256, 512>(), st>>>(p, gm, gw, n_tiles);
-  else k_gemm_bf16_persist<EPI, FOLD><<<dim3(grid), dim3(512), smem_bytes<256, 512>(), st>>>(p, gm, gw, n_tiles);
+  k_gemm_bf16_persist<EPI><<<dim3(grid), dim3(512), smem_bytes<256, 512>(), st>>>(p, gm, gw, n_tiles);
   ++g_kernel_launches;
   return hipGetLastError();
 }
@@ -1499,27 +1206,9 @@ bool persist_res() {   // EPD_PERSIST_RES=0: the residual products stay on the o
   return on;
 }
 
-// residual product on the persistent kernel (whole 256 x BN tiles; no bf16 rows / statistics emitted);
-// BN = 192 wants N % 192 == 0
-template <int BN = 256>
-hipError_t launch_persist_res(const GemmParams& p, hipStream_t st) {
-  if (BN != 256 && p.N % BN != 0) return hipErrorInvalidValue;
-  const int gm = (p.M + BM - 1) / BM, gn = BN == 256 ? p.Npad / 256 : p.N / BN;
-  const int n_tiles = gm * gn;
-  if (n_tiles == 0) return hipSuccess;
-  const double panel = (double)BN * p.K * sizeof(bf16_t);
-  int gw = 1;
-  double best = 1e30;
-  for (int c = 1; c <= gn && c <= 32; ++c) {
-    const bool resident = c * panel <= 2.5 * (1 << 20);
-    const double cost = (32.0 / c) * panel + (resident ? 0.0 : c * panel);
-    if (cost < best * 0.999) { best = cost; gw = c; }
-  }
-  if (p.band > 0 && p.band <= gn) gw = p.band;
-  const int grid = n_tiles < cu_count() ? n_tiles : cu_count();
-  k_gemm_bf16_persist_res<BN><<<dim3(grid), dim3(512), smem_bytes<BN, 512>(), st>>>(p, gm, gw, n_tiles);
+hipError_t launch_wide(const GemmParams& p, int tile, hipStream_t st) {
   ++g_kernel_launches;
-  return hipGetLastError();
+  return bf16_gemm_wide(p, tile, cu_count(), st);
 }
 
 bool tiles_192() {   // EPD_TILES_192=0: widths like 1152 stay on the 256-wide tiles
@@ -1527,28 +1216,20 @@ bool tiles_192() {   // EPD_TILES_192=0: widths like 1152 stay on the 256-wide t
   return on;
 }
 
-template <bool FOLD>
-hipError_t dispatch_persist_f(const GemmParams& p, hipStream_t st) {
+hipError_t dispatch_persist(const GemmParams& p, hipStream_t st) {   // bf16-output epilogues on 256 x 256 tiles
+  if (!p.stats) return launch_wide(p, WIDE_256, st);
   switch (p.epi) {
-    case EPI_BIAS: return launch_persist<EPI_BIAS, FOLD>(p, st);
-    case EPI_BIAS_GELU_ERF: return launch_persist<EPI_BIAS_GELU_ERF, FOLD>(p, st);
-    case EPI_BIAS_GELU_TANH: return launch_persist<EPI_BIAS_GELU_TANH, FOLD>(p, st);
-    case EPI_VT: return launch_persist<EPI_VT, FOLD>(p, st);
+    case EPI_BIAS: return launch_persist<EPI_BIAS>(p, st);
+    case EPI_BIAS_GELU_ERF: return launch_persist<EPI_BIAS_GELU_ERF>(p, st);
+    case EPI_BIAS_GELU_TANH: return launch_persist<EPI_BIAS_GELU_TANH>(p, st);
+    case EPI_VT: return launch_persist<EPI_VT>(p, st);
   }
   return hipErrorInvalidValue;
 }
-hipError_t dispatch_persist(const GemmParams& p, hipStream_t st) {
-  return p.stats ? dispatch_persist_f<true>(p, st) : dispatch_persist_f<false>(p, st);
-}
 
-template <int EPI, bool FOLD>
+template <int EPI>
 hipError_t set_attr_persist() {
-  if (!FOLD) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_persist<EPI, false, true>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_bytes<256, 512>());
-    if (e != hipSuccess) return e;
-  }
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_persist<EPI, FOLD>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_persist<EPI>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_bytes<256, 512>());
 }
 
@@ -1568,13 +1249,15 @@ hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     return p.stats_out ? launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_, 2>(p, st)
                        : launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_, 1>(p, st);
   }
-  switch (p.epi) {
-    case EPI_BIAS: return launch<BN, NT, WN, EPI_BIAS, PIPE, BM_>(p, st);
-    case EPI_BIAS_GELU_ERF: return launch<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>(p, st);
-    case EPI_BIAS_GELU_TANH: return launch<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>(p, st);
-    case EPI_BIAS_RESIDUAL: return launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>(p, st);
-    case EPI_BIAS_POS: return launch<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>(p, st);
-    case EPI_VT: return launch<BN, NT, WN, EPI_VT, PIPE, BM_>(p, st);
+  if constexpr (BN == 256) {   // (256 x 128 tiles of plain products: gemm_bf16_wide.hip)
+    switch (p.epi) {
+      case EPI_BIAS: return launch<BN, NT, WN, EPI_BIAS, PIPE, BM_>(p, st);
+      case EPI_BIAS_GELU_ERF: return launch<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>(p, st);
+      case EPI_BIAS_GELU_TANH: return launch<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>(p, st);
+      case EPI_BIAS_RESIDUAL: return launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>(p, st);
+      case EPI_BIAS_POS: return launch<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>(p, st);
+      case EPI_VT: return launch<BN, NT, WN, EPI_VT, PIPE, BM_>(p, st);
+    }
   }
   return hipErrorInvalidValue;
 }
@@ -1605,12 +1288,14 @@ hipError_t set_attr() {
 template <int BN, int NT, int WN, int PIPE = 0, int BM_ = BM>
 hipError_t set_attr_all() {
   hipError_t e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_VT, PIPE, BM_>()) != hipSuccess) return e;
+  if constexpr (BN == 256) {
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_VT, PIPE, BM_>()) != hipSuccess) return e;
+  }
   if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_, 2>()) != hipSuccess) return e;
   if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_, 2>()) != hipSuccess) return e;
   if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_, 2>()) != hipSuccess) return e;
@@ -1639,18 +1324,11 @@ hipError_t bf16_gemm_init() {
   if (e != hipSuccess) return e;
   if ((e = set_attr_all<256, 512, 64, 1>()) != hipSuccess) return e;
   if ((e = set_attr_all<256, 512, 64, 3>()) != hipSuccess) return e;
-  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_persist_res<256>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_bytes<256, 512>())) != hipSuccess) return e;
-  if ((e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_persist_res<192>),
-                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem_bytes<192, 512>())) != hipSuccess) return e;
-  if ((e = set_attr_persist<EPI_BIAS, false>()) != hipSuccess) return e;
-  if ((e = set_attr_persist<EPI_BIAS_GELU_ERF, false>()) != hipSuccess) return e;
-  if ((e = set_attr_persist<EPI_BIAS_GELU_TANH, false>()) != hipSuccess) return e;
-  if ((e = set_attr_persist<EPI_VT, false>()) != hipSuccess) return e;
-  if ((e = set_attr_persist<EPI_BIAS, true>()) != hipSuccess) return e;
-  if ((e = set_attr_persist<EPI_BIAS_GELU_ERF, true>()) != hipSuccess) return e;
-  if ((e = set_attr_persist<EPI_BIAS_GELU_TANH, true>()) != hipSuccess) return e;
-  if ((e = set_attr_persist<EPI_VT, true>()) != hipSuccess) return e;
+  if ((e = set_attr_persist<EPI_BIAS>()) != hipSuccess) return e;
+  if ((e = set_attr_persist<EPI_BIAS_GELU_ERF>()) != hipSuccess) return e;
+  if ((e = set_attr_persist<EPI_BIAS_GELU_TANH>()) != hipSuccess) return e;
+  if ((e = set_attr_persist<EPI_VT>()) != hipSuccess) return e;
+  if ((e = bf16_gemm_wide_init()) != hipSuccess) return e;
   if ((e = set_attr_all<128, 512, 64>()) != hipSuccess) return e;
   if ((e = set_attr_128_fold<0>()) != hipSuccess) return e;
   if ((e = set_attr_128_fold<2>()) != hipSuccess) return e;
@@ -1703,14 +1381,13 @@ static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
   const Plain c = choose_plain(p);
   GemmParams a = p, b = p;
   auto wide = [&](const GemmParams& g) {
-    if (!residual && p.epi != EPI_BIAS_POS) return dispatch_persist(g, st);
-    if (residual && persist_res()) return launch_persist_res(g, st);
+    if (!residual || persist_res()) return launch_wide(g, WIDE_256, st);
     return (a_direct() && g.K >= 2048) ? dispatch<256, 512, 64, 3>(g, st) : dispatch<256, 512, 64, 1>(g, st);
   };
   switch (c.form) {
     case PLAIN_RING: return launch_ring(p, c.tile, st);
-    case PLAIN_256x128: return dispatch<128, 512, 64>(without_padded_columns(p), st);
-    case PLAIN_192: return launch_persist_res<192>(p, st);
+    case PLAIN_256x128: return launch_wide(p, WIDE_128, st);
+    case PLAIN_192: return launch_wide(p, WIDE_192, st);
     case PLAIN_256: {
       if (c.rows_a == 0) return wide(p);
       a.M = (int)(c.rows_a * BM);
@@ -1778,18 +1455,18 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
   if (p.n2_pad > 0)
     return bf16_gemm_pair_fits(p) ? launch_ring(p, best_ring(p.M, pair_columns(p), p.K, EPI_BIAS).tile, st) : hipErrorInvalidValue;
   switch (p.cfg) {
-    case 1: return dispatch<128, 512, 64>(p, st);
+    case 1: return ring_has(p) ? launch_wide(p, WIDE_128, st) : dispatch<128, 512, 64>(p, st);
     case 2: return ring_has(p) ? launch_ring(p, RING_128x128, st) : dispatch_128_fold<0>(p, st);
     case 3: if (!ring_has(p)) { if (p.K % 256 == 0) return dispatch_128_fold<2>(p, st); break; } return launch_ring(p, RING_128x128, st);
     case 6: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 0>(p, st); break;
     case 7: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 1>(p, st); break;
     case 8: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 3>(p, st); break;
     case 9: if (p.Npad % 256 == 0 && p.epi != EPI_BIAS_RESIDUAL && p.epi != EPI_BIAS_POS) return dispatch_persist(p, st); break;
-    case 10: if (p.Npad % 256 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_persist_res(p, st); break;
+    case 10: if (p.Npad % 256 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_wide(p, WIDE_256, st); break;
     case 11: if (ring_has(p)) return launch_ring(p, RING_64x64, st); break;
     case 13: if (ring_has(p)) return launch_ring(p, RING_128x64, st); break;
     case 14: if (ring_has(p)) return launch_ring(p, RING_128x128, st); break;
-    case 12: if (p.N % 192 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_persist_res<192>(p, st); break;
+    case 12: if (p.N % 192 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_wide(p, WIDE_192, st); break;
   }
   if (ring_has(p)) return dispatch_plain(p, st);
   // from here on: products with a folded pre-norm or an emitting residual epilogue (EPD_NORM_MODE)

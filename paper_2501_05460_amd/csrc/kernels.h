@@ -92,6 +92,10 @@ bool bf16_gemm_pair_fits(const GemmParams& p);
 enum RingTile { RING_64x64 = 0, RING_128x64 = 1, RING_128x128 = 2 };
 hipError_t bf16_gemm_ring(const GemmParams& p, int tile, hipStream_t st);
 hipError_t bf16_gemm_ring_init();   // part of bf16_gemm_init
+// the product on large tiles with persistent workgroups (gemm_bf16_wide.hip), any epilogue without n2_pad; WIDE_192: RESIDUAL only
+enum WideTile { WIDE_256 = 0, WIDE_192 = 1, WIDE_128 = 2 };
+hipError_t bf16_gemm_wide(const GemmParams& p, int tile, int cus, hipStream_t st);
+hipError_t bf16_gemm_wide_init();   // part of bf16_gemm_init
 int bf16_gemm_choice(const GemmParams& p, long* rows);   // the form of a product without a folded pre-norm (tests)
 long bf16_gemm_kernel_launches();   // kernels launched by bf16_gemm on the calling host thread so far (a figure for the profiling hooks)
 hipError_t bf16_gemm_init();  // raises the dynamic-LDS limit of the kernels (idempotent: safe from any thread, any number of times)
