@@ -14,7 +14,8 @@
 //   * What the epilogue reads (bias, residual rows) is fetched in front of the main loop.
 //   * Four waves (2 x 2) of 32 WTM x 32 WTN each: a 64 x 64 wave tile reads half as many LDS bytes per flop as the
 //     32 x 64 wave tiles of an eight-wave 128 x 128 tile.
-// An element's k-steps are added in the order of every other form (same instruction, k ascending): same bits.
+//   * v_mfma_f32_16x16x32_bf16, for the reason given in gemm_bf16_wide.hip.
+// An element's k-steps are added in the order of every other form (k ascending): same bits.
 // Measured stand-alone, K = 4096, N = 1024: 1024 rows 21.8 us with the 64 x 64 form this replaces, 15.4 now; 3096 rows
 // 56.4 us with eight-wave 128 x 128 tiles, 30.5 now.  In the running encoder, weights cold: 24.4 -> 22.9, 55.8 -> 41.5.
 // A deeper ring (8 / 6 / 5 stages, one workgroup per CU) changed nothing in the encoder.
@@ -33,8 +34,12 @@ namespace {
 constexpr int BK = 64;
 #define SWZ(row) (((row) >> 1) & 7)
 
-__device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+
+// acc += a b with the accumulator kept in place (the compiler's form moves it from register to register).  The compiler does
+// not see the wait states around it: nothing but MFMAs may touch an accumulator between the zeros in front of the main loop
+// and the pause behind it.
+__device__ __forceinline__ void mfma_in_place(bf16x8 a, bf16x8 b, f32x4& c) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(c) : "v"(a), "v"(b));
 }
 
 template <int WTM, int WTN>
@@ -72,7 +77,8 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave >> 1, wn = wave & 1;
-  const int l32 = lane & 31, lh = lane >> 5;
+  const int l16 = lane & 15, lg = lane >> 4;
+  constexpr int BM = 2 * WTM, BN = 2 * WTN;   // 16 x 16 blocks of a wave
   const int ld_row = tid >> 3, ld_c = tid & 7;
   // the lane that lands on physical chunk ld_c of its LDS row fetches logical chunk ld_c ^ SWZ(row).  One scalar base per
   // operand walks along K; where a load's 32 rows lie relative to it is a lane offset fixed for the whole kernel.
@@ -104,27 +110,21 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
     __builtin_amdgcn_s_waitcnt((N & 0xf) | ((N >> 4) << 14) | (0x7 << 4) | (0xf << 8));
   };
 
-  f32x16 acc[WTM][WTN];
-#pragma unroll
-  for (int i = 0; i < WTM; ++i)
-#pragma unroll
-    for (int j = 0; j < WTN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  f32x4 acc[BM][BN];
 
-  // byte offsets of the fragments inside a stage; k-step kk sits at chunk (2 kk + lh) ^ swizzle = chunk 0's ^ 2 kk
-  const unsigned fa0 = (unsigned)(((wm * 32 * WTM + l32) * BK + ((lh ^ SWZ(l32)) * 8)) * 2);
-  const unsigned fb0 = (unsigned)((TM * BK + (wn * 32 * WTN + l32) * BK + ((lh ^ SWZ(l32)) * 8)) * 2);
-  bf16x8 fa[2][4][WTM], fb[2][4][WTN];
-  constexpr int RPK = WTM + WTN, NRD = 4 * RPK;   // fragment reads per k-step and per slab
+  // byte offsets of the fragments inside a stage; k-step kk (32 deep) sits at chunk (4 kk + lg) ^ swizzle = chunk 0's ^ 4 kk
+  const unsigned fa0 = (unsigned)(((wm * 32 * WTM + l16) * BK + ((lg ^ SWZ(l16)) * 8)) * 2);
+  const unsigned fb0 = (unsigned)((TM * BK + (wn * 32 * WTN + l16) * BK + ((lg ^ SWZ(l16)) * 8)) * 2);
+  bf16x8 fa[2][2][BM], fb[2][2][BN];
+  constexpr int RPK = BM + BN, NRD = 2 * RPK;   // fragment reads per k-step and per slab
   auto read_some = [&](auto set, unsigned so, int from, int to) {
     constexpr int S = decltype(set)::value;
 #pragma unroll
     for (int r = 0; r < NRD; ++r) {
       if (r < from || r >= to) continue;
       const int kk = r / RPK, x = r % RPK;
-      if (x < WTM) fa[S][kk][x < WTM ? x : 0] = *reinterpret_cast<const bf16x8*>(smem + ((fa0 ^ (32u * kk)) + so) + x * 32 * BK * 2);
-      else fb[S][kk][x < WTM ? 0 : x - WTM] = *reinterpret_cast<const bf16x8*>(smem + ((fb0 ^ (32u * kk)) + so) + (x - WTM) * 32 * BK * 2);
+      if (x < BM) fa[S][kk][x < BM ? x : 0] = *reinterpret_cast<const bf16x8*>(smem + ((fa0 ^ (64u * kk)) + so) + x * 16 * BK * 2);
+      else fb[S][kk][x < BM ? 0 : x - BM] = *reinterpret_cast<const bf16x8*>(smem + ((fb0 ^ (64u * kk)) + so) + (x - BM) * 16 * BK * 2);
     }
   };
 
@@ -176,6 +176,15 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
   epilogue_loads();
   auto main_loop = [&](auto tm) {
     constexpr bool TOKM = decltype(tm)::value;
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+      for (int j = 0; j < BN; ++j) {
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        asm volatile("" : "+v"(acc[i][j]));   // the zeros are in their registers here (see mfma_in_place)
+      }
+    asm volatile("s_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
     unsigned so = 0;   // stage of the slab being multiplied, as a byte offset
     // One slab: its fragments are in register set `cur`; slab kt + 1 moves into the other set and slab kt + RING into
     // the stage slab kt has left.  AHEAD: slabs issued behind slab kt + 1 (loads complete in order, so it has landed
@@ -192,11 +201,13 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
       // A wave issues in order: a fragment read waits for its turn in LDS, a direct load for its turn in the address
       // unit.  Each goes between two MFMAs and passes under the one in front of it: the reads, which the next slab
       // waits for, in the first half, the loads that refill the stage in the second.
-      constexpr int MM = 4 * WTM * WTN, HALF = MM / 2;
+      // (Blocks in serpentine order: consecutive MFMAs share a fragment, which saves power.)
+      constexpr int MM = 2 * BM * BN, HALF = MM / 2;
 #pragma unroll
       for (int m = 0; m < MM; ++m) {
-        const int kk = m / (WTM * WTN), i = m / WTN % WTM, j = m % WTN;
-        acc[i][j] = TOKM ? mfma32(fa[S][kk][i], fb[S][kk][j], acc[i][j]) : mfma32(fb[S][kk][j], fa[S][kk][i], acc[i][j]);
+        const int kk = m / (BM * BN), i = m / BN % BM, j = i % 2 ? BN - 1 - m % BN : m % BN;
+        const bf16x8 l = TOKM ? fa[S][kk][i] : fb[S][kk][j], r = TOKM ? fb[S][kk][j] : fa[S][kk][i];
+        mfma_in_place(l, r, acc[i][j]);
         if constexpr (NEXT) {
           __builtin_amdgcn_sched_barrier(0);
           if (m < HALF) read_some(nxt, son, m * NRD / HALF, (m + 1) * NRD / HALF);
@@ -210,20 +221,13 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
     using AH = std::integral_constant<int, RING - 2>;
     using YES = std::true_type;
     using NO = std::false_type;
-    // the last N slabs: slab KT - N + t has slab kt + RING behind it only while t + RING < N
-    auto tail = [&](auto n) {
-      constexpr int N = decltype(n)::value;
-      auto one = [&](auto t_) {
-        constexpr int t = decltype(t_)::value;
-        if constexpr (t < N) {
-          constexpr int behind = N - 2 - t < RING - 2 ? N - 2 - t : RING - 2;
-          step(std::integral_constant<int, t % 2>{}, std::integral_constant<int, 1 - t % 2>{},
-               std::integral_constant<int, (behind > 0 ? behind : 0)>{}, std::integral_constant<bool, (t + RING < N)>{},
-               std::integral_constant<bool, (t + 1 < N)>{});
-        }
-      };
-      one(std::integral_constant<int, 0>{}); one(std::integral_constant<int, 1>{});
-      one(std::integral_constant<int, 2>{}); one(std::integral_constant<int, 3>{});
+    // slab KT - TAIL + t of the last ones: slab kt + RING is behind it only while t + RING < TAIL
+    auto last = [&](auto t_) {
+      constexpr int t = decltype(t_)::value;
+      constexpr int behind = TAIL - 2 - t < RING - 2 ? TAIL - 2 - t : RING - 2;
+      step(std::integral_constant<int, t % 2>{}, std::integral_constant<int, 1 - t % 2>{},
+           std::integral_constant<int, (behind > 0 ? behind : 0)>{}, std::integral_constant<bool, (t + RING < TAIL)>{},
+           std::integral_constant<bool, (t + 1 < TAIL)>{});
     };
     static_assert(TAIL == 4, "the tail is unrolled that far");
     wait_vm(std::integral_constant<int, LPS>{});   // slab 0 (slab 1 and the epilogue's loads are newer)
@@ -237,8 +241,19 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
       step(S0{}, S1{}, AH{}, YES{}, YES{});
       step(S1{}, S0{}, AH{}, YES{}, YES{});
     }
-    if (KT >= TAIL) tail(std::integral_constant<int, TAIL>{});
-    else tail(std::integral_constant<int, 2>{});   // K = 128: two slabs
+    if (KT >= TAIL) {   // K = 128: two slabs
+      last(std::integral_constant<int, 0>{});
+      last(std::integral_constant<int, 1>{});
+    }
+    last(std::integral_constant<int, 2>{});
+    last(std::integral_constant<int, 3>{});
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 7" ::: "memory");   // the last MFMAs have written
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+      for (int j = 0; j < BN; ++j) asm volatile("" : "+v"(acc[i][j]));
   };
   if (DUAL && vt_tile) main_loop(std::true_type{});
   else main_loop(std::integral_constant<bool, tok_major>{});
@@ -258,11 +273,10 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
 #pragma unroll
     for (int j = 0; j < WTN; ++j) {
 #pragma unroll
-      for (int i = 0; i < WTM; ++i)
+      for (int j2 = 0; j2 < 2; ++j2)
 #pragma unroll
-        for (int g = 0; g < 4; ++g)
-          *reinterpret_cast<f32x4*>(stg + l32 * ROWF + i * 32 + 8 * g + 4 * lh) =
-              f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+        for (int i = 0; i < BM; ++i)
+          *reinterpret_cast<f32x4*>(stg + (j2 * 16 + l16) * ROWF + i * 16 + 4 * lg) = acc[i][2 * j + j2];
       wave_sync();
 #pragma unroll
       for (int u = 0; u < VU; ++u) {
@@ -286,11 +300,10 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
   float* stg = reinterpret_cast<float*>(smem) + wave * 32 * ROWF;
   auto stage_rows = [&](int i) {
 #pragma unroll
-    for (int j = 0; j < WTN; ++j)
+    for (int i2 = 0; i2 < 2; ++i2)
 #pragma unroll
-      for (int g = 0; g < 4; ++g)
-        *reinterpret_cast<f32x4*>(stg + l32 * ROWF + j * 32 + 8 * g + 4 * lh) =
-            f32x4{acc[i][j][4 * g], acc[i][j][4 * g + 1], acc[i][j][4 * g + 2], acc[i][j][4 * g + 3]};
+      for (int j = 0; j < BN; ++j)
+        *reinterpret_cast<f32x4*>(stg + (i2 * 16 + l16) * ROWF + j * 16 + 4 * lg) = acc[2 * i + i2][j];
     wave_sync();
   };
   if constexpr (F32_OUT) {
