@@ -133,6 +133,40 @@ def test_attention_bf16_ignores_rows_past_n_keys(n_tok, n_keys, heads, hd, hd_pa
         assert rel_err(got[r], want) < 1.5e-2, s
 
 
+@pytest.mark.parametrize("hd", [64, 72, 96, 128])
+@pytest.mark.parametrize("n_tok,n_keys", [(1024, 1024), (1088, 1025), (1024, 1000), (128, 33), (64, 32), (192, 129)])
+def test_attention_bf16_of_few_and_many_slices_agrees_bit_for_bit(n_tok, n_keys, hd):
+    """Up to 512 workgroups of 128 queries the kernel runs 16 queries per wave, above them 32: the same bits either way,
+    with reference moves (logits of up to about 30) in both.  Padding rows hold large values and NaN."""
+    g = torch.Generator().manual_seed(n_tok * 131 + n_keys + hd)
+    heads = 8
+    many = 512 // (heads * ((n_tok + 127) // 128)) + 1
+    D = heads * hd
+    qk = torch.randn(many, n_tok, 2 * D, generator=g)
+    qk[:, :, :D] *= 6.0 * hd ** -0.5
+    vt = torch.randn(many, D, n_tok, generator=g)
+    qk[:, n_keys:, D:] = 1e4
+    vt[:, :, n_keys:] = float("nan")
+    # a last block reaches past the slice: rows and elements behind it belong to the buffers
+    qk_d = torch.zeros(many * n_tok + 64, 2 * D, dtype=torch.bfloat16, device="cuda")
+    qk_d[:many * n_tok] = qk.reshape(-1, 2 * D).to("cuda", torch.bfloat16)
+    vt_d = torch.zeros(many * D * n_tok + 64, dtype=torch.bfloat16, device="cuda")
+    vt_d[:many * D * n_tok] = vt.reshape(-1).to("cuda", torch.bfloat16)
+    whole = B.op_attention_bf16(qk_d, qk_d[:, D:], vt_d, many, n_tok, heads, hd, 2 * D, n_keys=n_keys)
+    whole = whole.view(many, n_tok, D)[:, :n_keys]
+    assert torch.isfinite(whole.float()).all()
+    for t in (0, many - 1):
+        one = B.op_attention_bf16(qk_d[t * n_tok:], qk_d[t * n_tok:, D:], vt_d[t * D * n_tok:], 1, n_tok, heads, hd, 2 * D,
+                                  n_keys=n_keys)
+        assert torch.equal(one[:n_keys], whole[t])
+    # and the values are the softmax's: bf16 weights and outputs, 2^-9 each on a handful of effective keys
+    q, k = qk_d[:n_keys, :hd].double().cpu(), qk_d[:n_keys, D:D + hd].double().cpu()
+    v = vt_d[:hd * n_tok].view(hd, n_tok)[:, :n_keys].double().cpu()
+    want = torch.softmax(q @ k.T * np.log(2.0), -1) @ v.T
+    got = whole[0, :, :hd].double().cpu()
+    assert float((got - want).norm() / want.norm()) < 6e-3
+
+
 def _attention_run(q, k, v, n_slices, n_tok, heads, hd):
     """q, k, v [M, heads * hd] on the bf16 grid -> kernel output and oracle output, both [M, heads * hd]."""
     M, D = q.shape
