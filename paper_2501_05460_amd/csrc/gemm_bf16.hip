@@ -1064,6 +1064,7 @@ hipError_t launch(const GemmParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
+}  // namespace
 int cu_count() {
   static int n = 0;
   if (n == 0) {
@@ -1076,6 +1077,7 @@ int cu_count() {
   }
   return n;
 }
+namespace {
 
 // the ring kernel has neither the folded pre-norm nor the bf16 copy of the residual rows
 bool ring_has(const GemmParams& p) { return !p.stats && !p.xb; }

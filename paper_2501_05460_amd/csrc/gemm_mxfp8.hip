@@ -9,15 +9,20 @@
 // the four scale bytes of row r's blocks 4 s .. 4 s + 3 (byte b = block 4 s + b): one K slab of 128 elements
 // of a 256-row tile reads 256 consecutive words.
 //
-// Product: C[M,N] = A[M,K] W[N,K]^T with v_mfma_scale_f32_32x32x64_f8f6f4, which takes the block scales as
-// operands and applies them inside the instruction: lane l supplies row l % 32 of its 32 x 64 operand; its
-// registers 0-3 hold k = 16 (l / 32) .. + 15 and its registers 4-7 hold k = 32 + 16 (l / 32) .. + 15, so a block
-// (k 0..31 or 32..63) is shared by lanes l and l + 32, and the scale register of lanes 0-31 carries the scale
-// byte of the row's first block, that of lanes 32-63 the second's; result register i of lane l is
-// D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32] (the layout of the 32x32 bf16 instruction).  All of this is what
-// the operand-layout test holds on the device.  Block tile 256 x 256 x 128, 8 waves of 128 x 64, both operand
-// slabs and their scale words go from global memory straight into LDS one slab ahead (LDS-DMA); LDS rows of
-// 128 bytes with the 16-byte chunks XOR-swizzled by (row >> 1) & 7, as in the bf16 kernel.
+// Product: C[M,N] = A[M,K] W[N,K]^T with v_mfma_scale_f32_16x16x128_f8f6f4, which takes the block scales as operands and
+// applies them inside the instruction: lane l supplies row l % 16 of its 16 x 128 operand; its registers 0-3 hold k =
+// 16 (l / 16) .. + 15 and its registers 4-7 k = 64 + 16 (l / 16) .. + 15, its scale register carries the scale byte of the
+// row's block l / 16 (k = 32 (l / 16) .. + 31); result register e of lane l is D[4 (l / 16) + e][l % 16].  (The same bits as two
+// v_mfma_scale_f32_32x32x64_f8f6f4 steps; a register-resident loop runs 4.6 PFLOP/s with it and 4.25 with those.)
+//
+// What bounds it: at the depths of an encoder layer (8 to 32 slabs) as much the epilogue and the fill of the chip as the
+// products, hence persistent workgroups (the slabs past a tile's last are the next tile's), staging wave by wave without a
+// workgroup barrier, and small tiles, two workgroups per CU, where large ones leave CUs idle or would all reach their fp32
+// epilogue at once.  Slabs of 128 go from global memory straight into one of two LDS buffers (rows of 128 bytes, 16-byte chunks
+// XOR-swizzled by (row >> 1) & 7), two slabs ahead; the fragments of a slab are read between its products and one barrier a
+// slab frees the buffer.  us, one workgroup per tile on 32x32x64 -> this: 1024 rows, 2048 x 1024 16.3 -> 8.2, 4096 x 1024 with
+// GELU 21.3 -> 10.4, 1024 x 4096 residual 46.7 -> 26.6; 26624 rows 74.7 -> 58.7, 151 -> 137, 128 -> 124, 1024 x 1024 residual
+// 63.4 -> 54.7; 53248 rows 128 -> 105, 281 -> 255, 246 -> 244, 116 -> 103.
 #include <cstring>
 #include <type_traits>
 
@@ -30,14 +35,22 @@ namespace {
 typedef int i32x8 __attribute__((ext_vector_type(8)));
 typedef unsigned char u8;
 
-constexpr int BM = 256, BN = 256;
 constexpr int BKB = 128;               // K elements (= bytes) per slab
-constexpr int WM = 128, WN = 64;       // wave tile
-constexpr int TM = WM / 32, TN = WN / 32;
-constexpr int NT = 512;
-constexpr size_t SMEM_OPERANDS = (size_t)2 * (BM + BN) * BKB;           // 128 KiB: two slab buffers per operand
-constexpr size_t SMEM_SCALES = (size_t)2 * (BM + BN) * sizeof(unsigned);  // per buffer: 256 words of A rows, 256 of W rows
-constexpr size_t SMEM_TOTAL = SMEM_OPERANDS + SMEM_SCALES + 2 * BN * sizeof(float);
+constexpr int TN = 4;                  // a wave's blocks of 16 columns
+
+// Waves stand WAVES_M x WAVES_N, each on TM x TN blocks of 16 x 16.
+template <int TM, int WAVES_M, int WAVES_N>
+struct MxTile {
+  static constexpr int NT = 64 * WAVES_M * WAVES_N, WM = 16 * TM, WN = 16 * TN, BM = WM * WAVES_M, BN = WN * WAVES_N;
+  static constexpr unsigned SLAB = (BM + BN) * BKB;                // bytes of a slab of both operands,
+  static constexpr unsigned SCALES = (BM + BN) * sizeof(unsigned); // of its scale words: one per row of A and of W,
+  static constexpr unsigned STAGE = 2048;                          // of a wave's staging space
+  static constexpr size_t LDS = 2 * (size_t)SLAB + 2 * SCALES + NT / 64 * STAGE;
+  static_assert(LDS <= 160 * 1024, "LDS of a CU");
+  static_assert((SLAB & (SLAB - 1)) == 0 && (SCALES & (SCALES - 1)) == 0, "the buffers are told apart by one bit");
+  static_assert(SCALES == NT * 4 && BM % 64 == 0, "a wave loads 64 scale words, of A or of W");
+  static_assert(TM % 4 == 0, "fragment slots");
+};
 
 #define SWZ(row) (((row) >> 1) & 7)
 
@@ -162,302 +175,352 @@ __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
 }
 
 // ---- product ------------------------------------------------------------------------------------------------
-template <int EPI>
-__global__ __launch_bounds__(NT, 1) void k_gemm_mxfp8(const MxGemmParams p, const int gm_, const int gw) {
-  constexpr bool tok_major = EPI == EPI_VT;
-  constexpr bool MX_OUT = EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH;
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  u8* sB = smem;                            // [2][BN][128]
-  u8* sA = smem + 2 * BN * BKB;             // [2][BM][128]
-  unsigned* sS = reinterpret_cast<unsigned*>(smem + SMEM_OPERANDS);   // [2][A rows 0..255 | W rows 0..255]
-  float* sBias = reinterpret_cast<float*>(smem + SMEM_OPERANDS + SMEM_SCALES);   // [BN]
-  float* sCs = sBias + BN;                                                        // [BN] per-column factor
-
-  // Workgroups are dealt round-robin to the 8 XCDs; XCD x takes a contiguous run of the tile sequence, which
-  // walks a band of gw tile columns top to bottom before the next band (weight panel of the band L2-resident).
-  const int gn = p.Npad / BN;
-  int id = blockIdx.x;
-  {
-    const int nb = gridDim.x;
-    const int x = id & 7, slot = id >> 3;
-    const int q = nb >> 3, r = nb & 7;
-    id = x * q + (x < r ? x : r) + slot;
+template <int N, int I = 0, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<N, I + 1>(f);
   }
-  const int band_tiles = gm_ * gw;
-  const int full_bands = gn / gw;
-  int band = id / band_tiles, in_band = id % band_tiles, bw = gw;
-  if (band >= full_bands) { band = full_bands; in_band = id - full_bands * band_tiles; bw = gn - full_bands * gw; }
-  const int m0 = (in_band / bw) * BM;
-  const int n0 = (band * gw + in_band % bw) * BN;
+}
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-  const int wm = wave >> 2, wn = wave & 3;
-  const int l32 = lane & 31, lh = lane >> 5;
+template <int EPI, int TM, int WAVES_M, int WAVES_N>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES_N)) void k_gemm_mxfp8(const MxGemmParams p, const int gm, const int gw, const int gn, const int n_tiles) {
+  using T = MxTile<TM, WAVES_M, WAVES_N>;
+  constexpr int NT = T::NT, WM = T::WM, WN = T::WN, BM = T::BM, BN = T::BN;
+  constexpr unsigned SLAB = T::SLAB, SCALES = T::SCALES, STAGE = T::STAGE;
+  constexpr bool TOK = EPI == EPI_VT;
+  constexpr bool MX_OUT = EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH;
+  constexpr bool F32_OUT = EPI == EPI_BIAS_RESIDUAL;
+  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // slab buffers 0, 1 | scale words 0, 1 | staging by wave
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave / WAVES_N, wn = wave % WAVES_N;
+  const int l16 = lane & 15, lg = lane >> 4;
   const int KT = p.K / BKB;
 
-  if (tid < BN) {
-    sBias[tid] = p.bias[n0 + tid];
-    sCs[tid] = p.cscale ? p.cscale[n0 + tid] : 1.0f;
-  }
+  // position in the launch order -> tile: XCD x (workgroups are dealt round-robin; a workgroup keeps pos % 8) takes a
+  // contiguous run of the tile sequence, which walks bands of gw tile columns top to bottom
+  auto tile_of = [&](int pos, int& m0, int& n0) {
+    const int x = pos & 7, slot = pos >> 3;
+    const int q = n_tiles >> 3, r = n_tiles & 7;
+    const int id = x * q + (x < r ? x : r) + slot;
+    const int band_tiles = gm * gw;
+    const int full_bands = gn / gw;
+    int band = id / band_tiles, in_band = id % band_tiles, bw = gw;
+    if (band >= full_bands) { band = full_bands; in_band = id - full_bands * band_tiles; bw = gn - full_bands * gw; }
+    m0 = (in_band / bw) * BM;
+    n0 = (band * gw + in_band % bw) * BN;
+  };
 
-  // LDS-DMA: lane l of a wave lands on 16 bytes at (wave-uniform LDS base) + 16 l, i.e. a wave fills 8 slab rows
-  // linearly; the swizzle is applied on the global side: the lane that lands on physical chunk c of its row
-  // fetches logical chunk c ^ SWZ(row).
+  // Direct loads: a wave fills 8 slab rows of 128 bytes linearly; the lane that lands on physical chunk ld_c of its row
+  // fetches logical chunk ld_c ^ SWZ(row).  The first BM / 64 waves fetch the scale words of A rows, the
+  // others those of W rows.
   const int ld_row = tid >> 3, ld_c = tid & 7;
   const unsigned a_voff = (unsigned)ld_row * (unsigned)p.lda + (unsigned)((ld_c ^ SWZ(ld_row)) * 16);
   const unsigned b_voff = (unsigned)ld_row * (unsigned)p.K + (unsigned)((ld_c ^ SWZ(ld_row)) * 16);
   const unsigned s_voff = (unsigned)lane * 4u;
-  auto issue = [&](int buf, int kt) {
-#pragma unroll
-    for (int i = 0; i < BN * 8 / NT; ++i) {
-      const u8* g = p.W + (long)(n0 + 64 * i) * p.K + (long)kt * BKB;   // uniform
-      const unsigned lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(sB + buf * BN * BKB + (wave_u * 64 + NT * i) * 16);
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(b_voff), "s"(g), "s"(lds) : "memory", "m0");
-    }
-#pragma unroll
-    for (int i = 0; i < BM * 8 / NT; ++i) {
-      const u8* g = p.A + (long)(m0 + 64 * i) * p.lda + (long)kt * BKB;
-      const unsigned lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(sA + buf * BM * BKB + (wave_u * 64 + NT * i) * 16);
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" :: "v"(a_voff), "s"(g), "s"(lds) : "memory", "m0");
-    }
-    {
-      // scale words of the slab: waves 0-3 fetch the tile's 256 A rows, waves 4-7 its 256 W rows, 64 words each
-      const unsigned* g = wave_u < 4 ? p.SA + (long)kt * p.sa_ld + m0 + 64 * wave_u
-                                     : p.SW + (long)kt * p.Npad + n0 + 64 * (wave_u - 4);
-      const unsigned lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)(sS + buf * (BM + BN) + 64 * wave_u);
-      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" :: "v"(s_voff), "s"(g), "s"(lds) : "memory", "m0");
+  const long a_step = (long)(NT / 8) * p.lda, b_step = (long)(NT / 8) * p.K;
+  constexpr int SA_WAVES = BM / 64;
+  const long s_step = (wave < SA_WAVES ? p.sa_ld : (long)p.Npad) * 4;
+  constexpr int LA = BM * 8 / NT, LPS = LA + BN * 8 / NT + 1;
+  const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
+  // the slab to fetch next: its position, its index in the tile, its first rows
+  int lpos = blockIdx.x, lk = 0;
+  unsigned lbuf = 0;
+  const u8 *ga, *gb, *gs;
+  auto aim = [&]() {
+    int m, n;
+    tile_of(lpos, m, n);
+    ga = p.A + (long)m * p.lda;
+    gb = p.W + (long)n * p.K;
+    gs = reinterpret_cast<const u8*>(wave < SA_WAVES ? p.SA + m + 64 * wave : p.SW + n + 64 * (wave - SA_WAVES));
+  };
+  auto issue = [&](int i) {
+    if (i < LPS - 1) {
+      const u8* g = i < LA ? ga + i * a_step : gb + (i - LA) * b_step;
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+                   :: "v"(i < LA ? a_voff : b_voff), "s"(g), "s"(lds0 + lbuf * SLAB + wave * 1024 + i * (NT * 16)) : "memory", "m0");
+    } else {
+      asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                   :: "v"(s_voff), "s"(gs), "s"(lds0 + 2 * SLAB + lbuf * SCALES + wave * 256) : "memory", "m0");
     }
   };
-  auto wait_all_vm = [&]() { __builtin_amdgcn_s_waitcnt((0x7 << 4) | (0xf << 8)); };   // vmcnt(0), other counters untouched
-
-  f32x16 acc[TM][TN];
-#pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
-
-  const int frag_sw = SWZ(l32);
-  auto compute = [&](int buf) {
-    const u8* a_s = sA + buf * BM * BKB + (wm * WM + l32) * BKB;
-    const u8* b_s = sB + buf * BN * BKB + (wn * WN + l32) * BKB;
-    const unsigned* s_a = sS + buf * (BM + BN) + wm * WM + l32;
-    const unsigned* s_b = sS + buf * (BM + BN) + BM + wn * WN + l32;
-    // a lane carries the scale of block 2 kk + lh of the slab into k-step kk: that byte is brought to byte 2 kk of
-    // the register once (shift by 8 lh), and the instruction's byte select (0 or 2) does the rest
-    int sa[TM], sb[TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i) sa[i] = (int)(s_a[i * 32] >> (8 * lh));
-#pragma unroll
-    for (int j = 0; j < TN; ++j) sb[j] = (int)(s_b[j * 32] >> (8 * lh));
-#pragma unroll
-    for (int kk = 0; kk < BKB / 64; ++kk) {
-      // 16-byte chunks lh and 2 + lh of the k-step's four: k = 16 lh .. + 15 and 32 + 16 lh .. + 15
-      const int c0 = 4 * kk + lh;
-      const int o0 = ((c0 ^ frag_sw) * 16), o1 = (((c0 + 2) ^ frag_sw) * 16);
-      i32x8 fa[TM], fb[TN];
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const u32x4 lo = *reinterpret_cast<const u32x4*>(a_s + i * 32 * BKB + o0);
-        const u32x4 hi = *reinterpret_cast<const u32x4*>(a_s + i * 32 * BKB + o1);
-        fa[i] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-      }
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        const u32x4 lo = *reinterpret_cast<const u32x4*>(b_s + j * 32 * BKB + o0);
-        const u32x4 hi = *reinterpret_cast<const u32x4*>(b_s + j * 32 * BKB + o1);
-        fb[j] = i32x8{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-      }
-#pragma unroll
-      for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-          // the weight fragment is the LEFT operand (a lane then owns one token and four consecutive features
-          // per register group), except for the transposed value store
-          if (kk == 0)
-            acc[i][j] = tok_major ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i], fb[j], acc[i][j], 0, 0, 0, sa[i], 0, sb[j])
-                                  : __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j], fa[i], acc[i][j], 0, 0, 0, sb[j], 0, sa[i]);
-          else
-            acc[i][j] = tok_major ? __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa[i], fb[j], acc[i][j], 0, 0, 2, sa[i], 2, sb[j])
-                                  : __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fb[j], fa[i], acc[i][j], 0, 0, 2, sb[j], 2, sa[i]);
-        }
+  auto advance = [&]() {
+    lbuf ^= 1;
+    ga += BKB; gb += BKB; gs += s_step;
+    if (++lk == KT) {
+      lk = 0;
+      lpos += (int)gridDim.x;
+      if (lpos < n_tiles) aim();
     }
   };
+  auto wait_all = [&]() { __builtin_amdgcn_s_waitcnt(0x7 << 4); };   // vmcnt(0), lgkmcnt(0)
 
-  issue(0, 0);
-  wait_all_vm();
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < KT) issue(buf ^ 1, kt + 1);   // the other buffer is free since the barrier that ended slab kt - 1
-    compute(buf);
-    wait_all_vm();        // this wave's share of slab kt + 1 has landed
-    __syncthreads();      // ... everyone's has, and everyone is done reading slab kt
+  // Fragments: 16-byte chunks lg and 4 + lg of a row (k = 16 lg .. + 15 and 64 + 16 lg .. + 15), byte lg of its scale word.
+  // Addresses of fragment 0 in the buffer of the slab at hand; the buffers lie a power of two apart.
+  unsigned a_lo = (unsigned)((wm * WM + l16) * BKB + ((lg ^ SWZ(l16)) * 16)), a_hi = a_lo ^ 64u;
+  unsigned b_lo = (unsigned)(BM * BKB + (wn * WN + l16) * BKB + ((lg ^ SWZ(l16)) * 16)), b_hi = b_lo ^ 64u;
+  unsigned sc_a = (unsigned)(2 * SLAB + (wm * WM + l16) * 4 + lg), sc_b = (unsigned)(2 * SLAB + (BM + wn * WN + l16) * 4 + lg);
+  auto other_buffer = [&]() { a_lo ^= SLAB; a_hi ^= SLAB; b_lo ^= SLAB; b_hi ^= SLAB; sc_a ^= SCALES; sc_b ^= SCALES; };
+  auto frag = [&](unsigned lo, unsigned hi, int r) {
+    const u32x4 x = *reinterpret_cast<const u32x4*>(smem + lo + r * (16 * BKB)), y = *reinterpret_cast<const u32x4*>(smem + hi + r * (16 * BKB));
+    return __builtin_bit_cast(i32x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
+  };
+  f32x4 acc[TM][TN];
+  i32x8 fa[4], fb[TN];   // fragment i of A in slot i % 4
+  int sa[4], sb[TN];
+  auto read_a = [&](int i) { fa[i % 4] = frag(a_lo, a_hi, i); sa[i % 4] = smem[sc_a + i * 64]; };
+  auto read_b = [&](int j) { fb[j] = frag(b_lo, b_hi, j); sb[j] = smem[sc_b + j * 64]; };
+  // In place, as assembly: the compiler's form moves accumulators from register to register, and spills.  It does not see
+  // the wait states behind such an instruction: nothing but products touches an accumulator between the zeros in front of a
+  // tile and the nops behind it.
+  auto mma = [&](auto i, auto j) {
+    constexpr int I = decltype(i)::value, J = decltype(j)::value;
+    if constexpr (TOK)
+      asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fa[I % 4]), "v"(fb[J]), "v"(sa[I % 4]), "v"(sb[J]));
+    else
+      asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fb[J]), "v"(fa[I % 4]), "v"(sb[J]), "v"(sa[I % 4]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+
+  // fp32 epilogue: pass q adds rows 16 (q / 2) .. + 15, columns 32 (q % 2) .. + 31 of the wave's tile; the rows of four passes
+  // are on their way
+  constexpr int XAHEAD = 4, PASSES = 2 * TM;
+  __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
+      p.R, 0, F32_OUT ? (int)(unsigned)(((long)(p.M - 1) * p.ldr + p.N) * 4) : 0, 0x00020000);
+
+  aim();
+#pragma unroll
+  for (int i = 0; i < LPS; ++i) issue(i);
+  advance();
+  if (lpos < n_tiles) {
+#pragma unroll
+    for (int i = 0; i < LPS; ++i) issue(i);
+    advance();
   }
+  wait_all();
+  __syncthreads();
 
-  // ------------------------------------------------------------------ epilogue ----
-  // through LDS (the operand buffers are idle), so that global memory sees 16-byte chunks of whole rows
-  u8* stage = smem;
-  if constexpr (EPI == EPI_BIAS_RESIDUAL) {
-    // R[row][col] += acc * cscale + bias on the fp32 stream, four passes of 64 token rows: [64][BN] floats.  The
-    // stream rows of a pass wait in registers, fetched two passes ahead (those of the first two passes in one batch
-    // in front of the first staging), through a buffer descriptor: one lane offset for all of a thread's chunks, the
-    // row part of the address in scalar registers, so the 16 loads in flight cost 64 data registers and no more.
-    // (The descriptor's range check covers the lane offset only: R holds round_up(M, 256) rows, rows past M are
-    // read like any other and never written.)
-    constexpr int XROWS = 64, ROWB = BN * 4, XNCH = ROWB / 16, PER_T = XROWS * XNCH / NT, XSTEP = NT / XNCH;
-    int et = tid;
-    asm volatile("" : "+v"(et));   // opaque copy: what the epilogue derives from it is not hoisted above the main loop
-    const int x_r0 = et / XNCH, x_c = et % XNCH;
-    const int x_col = n0 + x_c * 4;
-    const bool col_ok = x_col < p.N;
-    __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(p.R, 0, (int)0x7fffffff, 0x00020000);
-    const unsigned x_voff = ((unsigned)x_r0 * (unsigned)p.ldr + (unsigned)x_col) * 4u;
-    f32x4 xr[2][PER_T];
-    auto xload = [&](auto set, int pass) {
-      constexpr int S = decltype(set)::value;
+  for (int pos = blockIdx.x;;) {
+    int m0, n0;
+    tile_of(pos, m0, n0);
 #pragma unroll
-      for (int i = 0; i < PER_T; ++i)
-        xr[S][i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-            rsrc_x, x_voff, (unsigned)(m0 + pass * XROWS + XSTEP * i) * (unsigned)p.ldr * 4u, 2));
-    };
-    auto one_pass = [&](auto set, int pass) {
-      constexpr int S = decltype(set)::value;
-      if (pass > 0) __syncthreads();
-#pragma unroll
-      for (int i = 0; i < TM; ++i) {
-        const int base = wm * WM + i * 32;
-        if (base / XROWS != pass) continue;   // wave-uniform
-        const int r = base % XROWS + l32;
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-          for (int gi = 0; gi < 4; ++gi) {
-            const int cl = wn * WN + j * 32 + gi * 8 + lh * 4;
-            const f32x4 b4 = *reinterpret_cast<const f32x4*>(sBias + cl), c4 = *reinterpret_cast<const f32x4*>(sCs + cl);
-            f32x4 v;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(acc[i][j][gi * 4 + e], c4[e], b4[e]);
-            *reinterpret_cast<f32x4*>(stage + r * ROWB + (((cl >> 2) ^ (r & 15)) << 4)) = v;
-          }
-      }
-      __syncthreads();
-#pragma unroll
-      for (int i = 0; i < PER_T; ++i) {
-        const int r = x_r0 + XSTEP * i;
-        const int row = m0 + pass * XROWS + r;
-        if (row < p.M && col_ok) {
-          const f32x4 v = *reinterpret_cast<const f32x4*>(stage + r * ROWB + ((x_c ^ (r & 15)) << 4));
-          __builtin_nontemporal_store(xr[S][i] + v, reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + x_col));
-        }
-      }
-      if (pass + 2 < BM / XROWS) xload(set, pass + 2);
-    };
-    using X0 = std::integral_constant<int, 0>;
-    using X1 = std::integral_constant<int, 1>;
-    xload(X0{}, 0);
-    xload(X1{}, 1);
-    one_pass(X0{}, 0);
-    one_pass(X1{}, 1);
-    one_pass(X0{}, 2);
-    one_pass(X1{}, 3);
-  } else if constexpr (MX_OUT) {
-    // act(acc * cscale + bias) converted to MXFP8 along the output features (the contraction dimension of the
-    // next product).  A lane and its partner lane ^ 32 together hold the 32 features of one block of one token:
-    // 16 each (register group gi -> features 8 gi + 4 lh .. + 3).  Codes are staged as [256 rows][256 bytes]
-    // (16-byte chunk c of row r at chunk c ^ (r & 15)), scale bytes as [256 rows][8].
-    u8* sScale = smem + BM * BN;   // behind the code tile
-#pragma unroll
-    for (int i = 0; i < TM; ++i) {
-      const int r = wm * WM + i * 32 + l32;
-#pragma unroll
-      for (int j = 0; j < TN; ++j) {
-        float v[16];
-        float amax = 0.f;
-#pragma unroll
-        for (int gi = 0; gi < 4; ++gi) {
-          const int cl = wn * WN + j * 32 + gi * 8 + lh * 4;
-          const f32x4 b4 = *reinterpret_cast<const f32x4*>(sBias + cl), c4 = *reinterpret_cast<const f32x4*>(sCs + cl);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            v[gi * 4 + e] = apply_act_fast<EPI>(__builtin_fmaf(acc[i][j][gi * 4 + e], c4[e], b4[e]));
-            amax = fmaxf(amax, fabsf(v[gi * 4 + e]));
-          }
-        }
-        amax = fmaxf(amax, __shfl_xor(amax, 32, 64));
-        const unsigned byte = mx_scale_byte(amax);
-        const float inv = mx_inv_scale(byte);
-#pragma unroll
-        for (int gi = 0; gi < 4; ++gi) {
-          const int cb = wn * WN + j * 32 + gi * 8 + lh * 4;   // byte column inside the tile
-          *reinterpret_cast<unsigned*>(stage + r * BN + (((cb >> 4) ^ (r & 15)) << 4) + (cb & 15)) =
-              mx_pack4(v[gi * 4] * inv, v[gi * 4 + 1] * inv, v[gi * 4 + 2] * inv, v[gi * 4 + 3] * inv);
-        }
-        if (lh == 0) sScale[r * 8 + wn * 2 + j] = (u8)byte;
-      }
-    }
-    __syncthreads();
-    constexpr int NCH = BN / 16, PER_T = BM * NCH / NT;
-#pragma unroll
-    for (int i = 0; i < PER_T; ++i) {
-      const int q = tid + NT * i;
-      const int r = q / NCH, c = q % NCH;
-      const int row = m0 + r, col = n0 + c * 16;
-      if (row < p.M && col < p.ncq)
-        __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(stage + r * BN + ((c ^ (r & 15)) << 4)),
-                                    reinterpret_cast<u32x4*>(p.Cq + (long)row * p.ldcq + col));
-    }
-    {
-      const int r = tid & (BM - 1), half = tid >> 8;    // 256 rows x 2 slabs of 128 features
-      const int slab = n0 / BKB + half;
-      if (m0 + r < p.M && slab * BKB < p.ncq)
-        p.SC[(long)slab * p.sc_ld + m0 + r] = *reinterpret_cast<const unsigned*>(sScale + r * 8 + half * 4);
-    }
-  } else {
-    // bf16 staging of the whole tile: rows = the MFMA lane dimension (tokens; features for the transposed store)
-    constexpr int SROWS = tok_major ? BN : BM, SCOLS = tok_major ? BM : BN;
-    constexpr int ROWB = SCOLS * 2, NCH = ROWB / 16, PER_T = SROWS * NCH / NT;
+    for (int j = 0; j < TN; ++j) read_b(j);
+    read_a(0);
+    read_a(1);
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j) {
-        const int r = tok_major ? (wn * WN + j * 32 + l32) : (wm * WM + i * 32 + l32);
-        const float bl = tok_major ? sBias[r] : 0.f, cs = tok_major ? sCs[r] : 1.f;
+        acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        asm volatile("" : "+v"(acc[i][j]));   // the zeros are in their registers here, not in front of their first use
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 7" ::: "memory");     // wait states between them and the first product
+    __builtin_amdgcn_sched_barrier(0);
+
+    f32x4 xr[F32_OUT ? XAHEAD : 1][2];
+    auto xload = [&](int lane, int q) {
+      if constexpr (F32_OUT) {
 #pragma unroll
-        for (int gi = 0; gi < 4; ++gi) {
-          const int cl = (tok_major ? (wm * WM + i * 32) : (wn * WN + j * 32)) + gi * 8 + lh * 4;
-          bf16x4 o;
-          if (tok_major) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16_t)__builtin_fmaf(acc[i][j][gi * 4 + e], cs, bl);
-          } else {
-            const f32x4 b4 = *reinterpret_cast<const f32x4*>(sBias + cl), c4 = *reinterpret_cast<const f32x4*>(sCs + cl);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) o[e] = (bf16_t)__builtin_fmaf(acc[i][j][gi * 4 + e], c4[e], b4[e]);
-          }
-          *reinterpret_cast<bf16x4*>(stage + r * ROWB + (((cl >> 3) ^ (r & 15)) << 4) + ((cl & 4) << 1)) = o;
+        for (int u = 0; u < 2; ++u) {
+          const int r = (lane + 64 * u) / 8, c = lane % 8;
+          const int row = m0 + wm * WM + (q / 2) * 16 + r, col = n0 + wn * WN + (q % 2) * 32 + c * 4;
+          xr[q % XAHEAD][u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(   // rows past M come back as zero
+              rsrc_x, ((unsigned)row * (unsigned)p.ldr + (unsigned)col) * 4u, 0, 2));
         }
       }
-    __syncthreads();
+    };
+    // One slab.  Rows 0 .. 5 of blocks with the fragments of row i + 2 read meanwhile; then everyone holds what it needs of the
+    // slab: behind the barrier the slab after the next is fetched into its buffer, and rows 6 and 7 run column by column,
+    // each column's fragment of the next slab read into the registers the column has left.
+    auto slab = [&](auto last) {
+      constexpr bool LAST = decltype(last)::value;
+      static_for<TM - 2>([&](auto i) {
+        static_for<TN>([&](auto jj) {
+          constexpr int J = i % 2 ? TN - 1 - jj : jj;
+          mma(i, std::integral_constant<int, J>{});
+          if constexpr (jj == 0 && i < TM - 3) read_a(i + 2);
+          if constexpr (jj == 2 && i == TM - 4) read_a(TM - 1);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+      });
+      wait_all();        // the wave's part of the next slab has landed, its fragments of this one are in registers
+      __syncthreads();   // everyone's has, and everyone holds this slab's fragments: its buffer is free
+      other_buffer();
+      if constexpr (LAST) {
 #pragma unroll
-    for (int i = 0; i < PER_T; ++i) {
-      const int q = tid + NT * i;
-      const int r = q / NCH, c = q % NCH;
-      const u32x4 v = *reinterpret_cast<const u32x4*>(stage + r * ROWB + ((c ^ (r & 15)) << 4));
-      if (tok_major) {
-        const int f = n0 + r, tok = m0 + c * 8;
-        if (f < p.N && tok < p.M) {
-          const int h = f / p.hd_pad, d = f % p.hd_pad;
-          const int t = tok / p.n_tok, n = tok % p.n_tok;
-          __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + (((long)t * p.heads + h) * p.hd_pad + d) * p.n_tok + n));
+        for (int q = 0; q < 2; ++q) xload(lane, q);
+      } else {
+        read_a(0);
+        read_a(1);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      const bool more = lpos < n_tiles;
+      static_for<TN>([&](auto j) {
+        constexpr int FIRST = j % 2 ? TM - 1 : TM - 2;
+        mma(std::integral_constant<int, FIRST>{}, j);
+        if (more) { issue(2 * j); issue(2 * j + 1); }
+        mma(std::integral_constant<int, 2 * TM - 3 - FIRST>{}, j);
+        if constexpr (!LAST) read_b(j);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      if (more) { issue(LPS - 1); advance(); }
+    };
+#pragma clang loop unroll(disable)
+    for (int kt = 0; kt < KT - 1; ++kt) slab(std::false_type{});
+    slab(std::true_type{});
+    asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j) asm volatile("" : "+v"(acc[i][j]));
+    __builtin_amdgcn_sched_barrier(0);
+
+    {
+      // The epilogue's addresses derive from an opaque copy of the thread index, made anew for every tile: computed in
+      // front of the tile loop they would occupy registers through the main loop.
+      int tid_opaque = threadIdx.x;
+      asm volatile("" : "+v"(tid_opaque));
+      const int lane = tid_opaque & 63, l16 = lane & 15, lg = lane >> 4;
+      u8* stg = smem + 2 * SLAB + 2 * SCALES + wave * STAGE;
+      auto wave_sync = [&]() {   // LDS written by one lane, read by another of the same wave
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      };
+      auto at = [&](int r, int c) { return stg + r * 128 + ((c ^ SWZ(r)) << 4); };   // 16 rows of eight 16-byte chunks
+      // per-column factor and bias: of feature l16 of block j (transposed store), of features 4 lg .. + 3 otherwise
+      f32x4 c4[TOK ? 1 : TN], b4[TOK ? 1 : TN];
+      float c1[TOK ? TN : 1], b1[TOK ? TN : 1];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int col = n0 + wn * WN + j * 16;
+        if constexpr (TOK) {
+          b1[j] = p.bias[col + l16];
+          c1[j] = p.cscale ? p.cscale[col + l16] : 1.0f;
+        } else {
+          b4[j] = *reinterpret_cast<const f32x4*>(p.bias + col + lg * 4);
+          c4[j] = p.cscale ? *reinterpret_cast<const f32x4*>(p.cscale + col + lg * 4) : f32x4{1.f, 1.f, 1.f, 1.f};
+        }
+      }
+      if constexpr (F32_OUT) {
+#pragma unroll
+        for (int q = 2; q < XAHEAD; ++q) xload(lane, q);
+#pragma unroll
+        for (int q = 0; q < PASSES; ++q) {
+#pragma unroll
+          for (int jj = 0; jj < 2; ++jj) {
+            const int j = (q % 2) * 2 + jj;
+            f32x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(acc[q / 2][j][e], c4[j][e], b4[j][e]);
+            *reinterpret_cast<f32x4*>(at(l16, jj * 4 + lg)) = v;
+          }
+          wave_sync();
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int r = (lane + 64 * u) / 8, c = lane % 8;
+            const int row = m0 + wm * WM + (q / 2) * 16 + r, col = n0 + wn * WN + (q % 2) * 32 + c * 4;
+            const f32x4 v = *reinterpret_cast<const f32x4*>(at(r, c));
+            if (row < p.M && col < p.N)   // streamed: read next by a row kernel, not by this launch
+              __builtin_nontemporal_store(xr[q % XAHEAD][u] + v, reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + col));
+          }
+          wave_sync();
+          if (q + XAHEAD < PASSES) xload(lane, q + XAHEAD);
+        }
+      } else if constexpr (TOK) {
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+          for (int h = 0; h < TM / 4; ++h) {   // 64 tokens each
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              bf16x4 o;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) o[e] = (bf16_t)__builtin_fmaf(acc[h * 4 + i][j][e], c1[j], b1[j]);
+              *reinterpret_cast<bf16x4*>(at(l16, i * 2 + (lg >> 1)) + ((lg & 1) << 3)) = o;
+            }
+            wave_sync();
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const int r = (lane + 64 * u) / 8, c = lane % 8;
+              const int f = n0 + wn * WN + j * 16 + r, tok = m0 + wm * WM + h * 64 + c * 8;   // n_tok % 8 == 0: the eight tokens share a slice
+              if (f < p.N && tok < p.M) {
+                const u32x4 v = *reinterpret_cast<const u32x4*>(at(r, c));
+                const int t = tok / p.n_tok, n = tok % p.n_tok;
+                __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n));
+              }
+            }
+            wave_sync();
+          }
+      } else if constexpr (MX_OUT) {
+        // act(acc * cscale + bias) converted to MXFP8 along the output features (the contraction dimension of the next
+        // product).  Blocks 2 b and 2 b + 1 of a token's four lanes are one block of 32 features, eight in each lane.  Codes of
+        // 32 rows are staged as rows of 64 bytes, 16-byte chunk c of row r at c ^ (r / 4) % 4.
+        auto code_at = [&](int r, int c) { return stg + r * 64 + ((c ^ ((r >> 2) & 3)) << 4); };
+#pragma unroll
+        for (int i2 = 0; i2 < TM; i2 += 2) {
+#pragma unroll
+          for (int i = i2; i < i2 + 2; ++i) {
+            unsigned bytes[2];
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+              float v[8], amax = 0.f;
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                const int j = 2 * b + (e >> 2);
+                v[e] = apply_act_fast<EPI>(__builtin_fmaf(acc[i][j][e & 3], c4[j][e & 3], b4[j][e & 3]));
+                amax = fmaxf(amax, fabsf(v[e]));
+              }
+              amax = fmaxf(amax, __shfl_xor(amax, 16, 64));
+              amax = fmaxf(amax, __shfl_xor(amax, 32, 64));
+              bytes[b] = mx_scale_byte(amax);
+              const float inv = mx_inv_scale(bytes[b]);
+#pragma unroll
+              for (int x = 0; x < 2; ++x)
+                *reinterpret_cast<unsigned*>(code_at((i - i2) * 16 + l16, 2 * b + x) + lg * 4) =
+                    mx_pack4(v[4 * x] * inv, v[4 * x + 1] * inv, v[4 * x + 2] * inv, v[4 * x + 3] * inv);
+            }
+            // the wave's 64 features are half of a scale word
+            const int row = m0 + wm * WM + i * 16 + l16, col = n0 + wn * WN;
+            if (lg == 0 && row < p.M && col < p.ncq)
+              reinterpret_cast<unsigned short*>(p.SC + (long)(col / BKB) * p.sc_ld + row)[wn & 1] = (unsigned short)(bytes[0] | bytes[1] << 8);
+          }
+          wave_sync();
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int r = (lane + 64 * u) / 4, c = lane % 4;
+            const int row = m0 + wm * WM + i2 * 16 + r, col = n0 + wn * WN + c * 16;
+            if (row < p.M && col < p.ncq)
+              __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(code_at(r, c)), reinterpret_cast<u32x4*>(p.Cq + (long)row * p.ldcq + col));
+          }
+          wave_sync();
         }
       } else {
-        const int row = m0 + r, col = n0 + c * 8;
-        if (row < p.M && col < p.N) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.C + (long)row * p.ldc + col));
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (bf16_t)__builtin_fmaf(acc[i][j][e], c4[j][e], b4[j][e]);
+            *reinterpret_cast<bf16x4*>(at(l16, j * 2 + (lg >> 1)) + ((lg & 1) << 3)) = o;
+          }
+          wave_sync();
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int r = (lane + 64 * u) / 8, c = lane % 8;
+            const int row = m0 + wm * WM + i * 16 + r, col = n0 + wn * WN + c * 8;
+            if (row < p.M && col < p.N)
+              __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(at(r, c)), reinterpret_cast<u32x4*>(p.C + (long)row * p.ldc + col));
+          }
+          wave_sync();
+        }
       }
     }
+    pos += (int)gridDim.x;
+    if (pos >= n_tiles) break;
   }
 }
 
@@ -476,18 +539,44 @@ __global__ __launch_bounds__(64) void k_mx_mfma_probe(const int* a, const int* b
   for (int e = 0; e < 16; ++e) d[l * 16 + e] = acc[e];
 }
 
-template <int EPI>
-hipError_t launch(const MxGemmParams& p, hipStream_t st) {
-  const int gm = (p.M + BM - 1) / BM, gn = p.Npad / BN;
-  const int gw = gn <= 4 ? gn : 4;
-  k_gemm_mxfp8<EPI><<<dim3((unsigned)(gm * gn)), dim3(NT), SMEM_TOTAL, st>>>(p, gm, gw);
+template <int EPI, int TM, int WAVES_M, int WAVES_N>
+hipError_t launch_tile(const MxGemmParams& p, int cols, hipStream_t st) {
+  using T = MxTile<TM, WAVES_M, WAVES_N>;
+  const int gm = (p.M + T::BM - 1) / T::BM, gn = (cols + T::BN - 1) / T::BN, n_tiles = gm * gn, slots = cu_count() * (512 / T::NT);
+  const int gw = gn <= 1024 / T::BN ? gn : 1024 / T::BN;
+  if (gn * T::BN > p.Npad) return hipErrorInvalidValue;
+  k_gemm_mxfp8<EPI, TM, WAVES_M, WAVES_N><<<dim3((unsigned)(n_tiles < slots ? n_tiles : slots)), dim3(T::NT), T::LDS, st>>>(p, gm, gw, gn, n_tiles);
   return hipGetLastError();
 }
 
 template <int EPI>
+hipError_t launch(const MxGemmParams& p, hipStream_t st) {
+  // tile columns that hold nothing but padding are not launched (the weights are packed to 256 rows)
+  const int cols = (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH) && p.ncq > p.N ? p.ncq : p.N;
+  // 256 x 256 tiles, a workgroup of eight waves per CU, or 128 x 128 ones, two of four waves: whichever is estimated to take
+  // less.  A round of either: a fixed part by epilogue and a part per slab, us, fitted to 50 products (1024 to 53248 rows,
+  // 1024 to 4352 columns, K 1024 to 12800; the other form was faster by more than 3 % for two of them); the small tiles'
+  // last round counts 0.7 while one per CU holds it.  us, 256 x 256 | 128 x 128: 1024 rows, 2048 x 1024 14.6 | 8.2, 1024 x 4096
+  // residual 43.9 | 26.6; 5120 rows, 4096 x 1024 39.6 | 28.6; 26624 rows, 4096 x 1024 137 | 150, 1024 x 1024 residual 63.9 | 54.7.
+  constexpr bool MX = EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH, RES = EPI == EPI_BIAS_RESIDUAL;
+  const long cus = cu_count(), kt = p.K / BKB;
+  const long big = ((p.M + 255) / 256) * (long)((cols + 255) / 256), small = ((p.M + 127) / 128) * (long)((cols + 127) / 128);
+  const long full = small / (2 * cus), rem = small % (2 * cus);
+  const double us_big = ((big + cus - 1) / cus) * ((RES ? 21.0 : MX ? 9.7 : 5.3) + 1.25 * kt);
+  const double us_small = 2.0 + (full + (rem == 0 ? 0.0 : rem <= cus ? 0.7 : 1.0)) * ((RES ? 6.3 : MX ? 3.9 : 0.8) + 0.93 * kt);
+  if (us_small < us_big) return launch_tile<EPI, 4, 2, 2>(p, cols, st);
+  return launch_tile<EPI, 8, 2, 4>(p, cols, st);
+}
+
+template <int EPI, int TM, int WAVES_M, int WAVES_N>
+hipError_t set_attr_tile() {
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mxfp8<EPI, TM, WAVES_M, WAVES_N>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)MxTile<TM, WAVES_M, WAVES_N>::LDS);
+}
+template <int EPI>
 hipError_t set_attr() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mxfp8<EPI>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)SMEM_TOTAL);
+  const hipError_t e = set_attr_tile<EPI, 8, 2, 4>();
+  return e != hipSuccess ? e : set_attr_tile<EPI, 4, 2, 2>();
 }
 
 }  // namespace
@@ -505,7 +594,8 @@ hipError_t mx_gemm_init() {
 }
 
 hipError_t mx_gemm(const MxGemmParams& p, hipStream_t st) {
-  // what the kernel assumes, checked where the launch is made
+  // what the kernel assumes, checked where the launch is made (buffers hold whole 256-row tiles)
+  constexpr int BM = 256, BN = 256;
   const long a_extent = ((long)(p.M + BM - 1) / BM * BM) * p.lda;
   if (p.M <= 0 || p.K <= 0 || p.K % BKB || p.Npad <= 0 || p.Npad % BN || p.N > p.Npad || p.lda < p.K || p.lda % 16 ||
       p.sa_ld < (long)(p.M + BM - 1) / BM * BM || a_extent >= (1L << 32) || (long)p.Npad * p.K >= (1L << 32) ||

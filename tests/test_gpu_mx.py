@@ -436,3 +436,39 @@ def test_attention_output_converted_in_the_kernel(n_tok, n_keys, heads, hd):
     same = (got_bytes == exact_bytes).repeat(32, axis=1) & (got_codes == exact_codes)
     print(f"attention -> MXFP8: {same.mean():.4f} of the codes are the oracle's")
     assert same.mean() > 0.9
+
+
+@pytest.mark.parametrize("epi", [0, 1, 3, 5])
+@pytest.mark.parametrize("K", [128, 384, 1024])
+def test_product_tiles_agree_bit_for_bit(epi, K):
+    """The first rows of a product of many rows (256 x 256 tiles, several of a workgroup, where the estimate takes them)
+    and the product of those rows alone (128 x 128 tiles): the same bits; K of one, three and eight slabs, so that slab
+    buffers change over at tiles of odd depth; and both against fp64 on the codes."""
+    g = torch.Generator().manual_seed(1000 * epi + K)
+    N, few, many, n_tok, heads, hd = 1024, 512, 26624, 512, 16, 64
+    code = lambda r: (torch.randint(0x28, 0x40, (r, K), generator=g) | torch.randint(0, 2, (r, K), generator=g) << 7).to(torch.uint8).cuda()
+    scale = lambda r: torch.from_numpy(pack_scale_words(torch.randint(122, 127, (r, K // 32), generator=g).numpy())).cuda()
+    A, W, SA, SW = code(many), code(N), scale(many), scale(N)
+    bias, cs = torch.randn(N, generator=g).cuda(), torch.rand(N, generator=g).cuda() + 0.5
+    R = torch.randn(many, N, generator=g).cuda() if epi == 3 else None
+
+    def product(rows):
+        r = R[:rows].clone() if R is not None else None
+        return B.op_mx_gemm(epi, A[:rows].contiguous(), SA[:, :rows].contiguous(), W, SW, bias, cs, r,
+                            n_tok if epi == 5 else 0, heads if epi == 5 else 0, hd if epi == 5 else 0)
+
+    whole, part = product(many), product(few)
+    if epi == 1:
+        assert torch.equal(whole[0][:few], part[0]) and torch.equal(whole[1][:, :few], part[1])
+        return   # the values: test_product_with_activation_and_converted_output
+    assert torch.equal(whole[:part.shape[0]], part)
+    value = lambda c, s: torch.from_numpy(O.mx_dequantize(c.cpu().numpy(), unpack_scale_words(s.cpu().numpy())))
+    last = slice(many - few, many)
+    want = value(A[last], SA[:, last]) @ value(W, SW).T * cs.double().cpu() + bias.double().cpu()
+    got = whole[-1:] if epi == 5 else whole[last]
+    if epi == 5:
+        got = got.permute(0, 3, 1, 2).reshape(n_tok, N)
+    if epi == 3:
+        got = got - R[last]
+    # bf16 output 2^-9; fp32 the bound of the products on given codes
+    assert float((got.double().cpu() - want).norm() / want.norm()) < (TOL_PRODUCT if epi == 3 else 4e-3)
