@@ -73,8 +73,14 @@ struct AttnSmem {
   static constexpr int V_ELEMS = V_ROWS * BKEY;
   static constexpr size_t BYTES = (size_t)2 * (K_ELEMS + V_ELEMS) * sizeof(bf16_t) + (ONES ? 16 : 0);
   // Rows are unpadded (a load puts 64 lanes' chunks next to each other): the 16 rows of a read of one logical 16-byte chunk
-  // are spread over the 64 banks by where the chunk sits in its row.  Key rows are read as {0-3, 8-11, 16-19, 24-27} + 4 b.
+  // are spread over the 64 banks by where the chunk sits in its row.  Key rows are read as {0-3, 8-11, 16-19, 24-27} + 4 b,
+  // in the PAIRED order as {0-7, 16-23} + 8 b.
+  template <bool PAIRED>
   static __device__ __forceinline__ int k_chunk(int row, int c) {
+    if (PAIRED) {
+      const int a = (row >> 4) & 1;
+      return HD == 64 ? c ^ (a << 2 | ((row >> 1) & 3)) : HD == 96 ? c ^ (a << 1 | ((row >> 2) & 1)) : HD == 128 ? c ^ (a << 3 | (row & 7)) : c < 8 ? c ^ a : c;
+    }
     const int a = (row >> 3) & 3;
     return HD == 64 ? c ^ (a << 1 | ((row >> 1) & 1)) : HD == 96 ? c ^ a : HD == 128 ? c ^ (a << 2 | (row & 3)) : c < 8 ? c ^ ((a >> 1) << 2) : c;
   }
@@ -160,9 +166,13 @@ __device__ __forceinline__ void static_for(F&& f) {
 // LEAN: one step's S^T registers and weights only, no step issued ahead, so that four (head dim 64), three (72, 96) workgroups
 // share a CU (112, 139, 150 registers); at head dim 128, where LDS holds two, the S^T product of step i + 1 is issued ahead
 // of the softmax of step i.
+// PAIRED: a lane's eight keys of a step are 16 (l / 32) + 4 (l / 16 % 2) + {0..3, 8..11}, V^T fragments are two 8-byte halves, and
+// the row sum on the VALU runs over a lane pair's sixteen weights in a row: the order of summation of a kernel on
+// v_mfma_f32_32x32x16_bf16, whose bits this gives.  For calls whose output is converted to MXFP8: there a change of the last
+// bit anywhere re-draws the conversion's rounding in all that follows (6 % of an encoder's output).
 // MASK: the slices carry rows past n_keys (compiled apart: the unmasked kernel keeps its registers and its step free of
 // the key-index compare).
-template <int HD, int QT, bool MASK>
+template <int HD, int QT, bool MASK, bool PAIRED>
 __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 96 ? 3 : 2) void k_attention_bf16(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                         const bf16_t* __restrict__ vt,
                                                         bf16_t* __restrict__ o, int n_tok, int n_keys, int n_q,
@@ -231,7 +241,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
   for (int i = 0; i < (K_RIGID ? 1 : K_LOADS); ++i) {
     const int c = tid + 256 * i < K_TOTAL ? tid + 256 * i : 0;   // (waves past the block's end load nothing)
     const int row = c / KCH;
-    koff[i] = (unsigned)(((long)row * ld_qk + SM::k_chunk(row, c % KCH) * 8) * 2);
+    koff[i] = (unsigned)(((long)row * ld_qk + SM::template k_chunk<PAIRED>(row, c % KCH) * 8) * 2);
   }
   const unsigned voff = (unsigned)(((long)(tid >> 3) * n_tok + SM::v_chunk(tid >> 3, tid & 7) * 8) * 2);   // 32 rows a load
   const unsigned ldsk = (unsigned)(size_t)(__attribute__((address_space(3))) void*)sK + wave * 1024;
@@ -297,10 +307,10 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
   // S^T of one 32-key step for all sub-tiles: row i of key block b is key 8 (i / 4) + 4 b + i % 4, so that s[u][b] holds keys
   // 8 lg + 4 b + 0..3 of query l16, and the exponentials of both are the second product's operand as they stand: keys
   // 8 lg .. + 7.  (Fragment addresses: the swizzle depends on l16 alone.)
-  const int krow = 8 * (l16 >> 2) + (l16 & 3);
+  const int krow = PAIRED ? 16 * (l16 >> 3) + (l16 & 7) : 8 * (l16 >> 2) + (l16 & 3);
   unsigned kfo[KS];
 #pragma unroll
-  for (int st = 0; st < KS; ++st) kfo[st] = (unsigned)(krow * HD + SM::k_chunk(krow, (st * 4 + lg) % KCH) * 8);
+  for (int st = 0; st < KS; ++st) kfo[st] = (unsigned)(krow * HD + SM::template k_chunk<PAIRED>(krow, (st * 4 + lg) % KCH) * 8);
   auto issue_s = [&](f32x4 (&s)[QT][2], int buf, int kt) {
     const bf16_t* ks = sK + buf * SM::K_ELEMS;
     // fragments two k-steps ahead: the LDS latency is paid once per step, in front of it
@@ -308,7 +318,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
     auto read_k = [&](int st) {
 #pragma unroll
       for (int b = 0; b < 2; ++b) {
-        const bf16_t* a = ks + kfo[st] + (kt * 32 + b * 4) * HD;
+        const bf16_t* a = ks + kfo[st] + (kt * 32 + b * (PAIRED ? 8 : 4)) * HD;
         if (SM::ONES && st == KS - 1) a = lg == 0 ? a : sV + 2 * SM::V_ELEMS;   // past the head dim: the zeros behind V^T
         kf[st & 1][b] = *reinterpret_cast<const bf16x8*>(a);
       }
@@ -338,10 +348,18 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
     psum = 0.f;
     if (!SUM_MFMA) {
       const bf16x2 ones = {(bf16_t)1.0f, (bf16_t)1.0f};
-      psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 0, 1), ones, psum, false);
-      psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 2, 3), ones, psum, false);
-      psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 4, 5), ones, psum, false);
-      psum = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 6, 7), ones, psum, false);
+      auto add = [&](float x) {
+        x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 0, 1), ones, x, false);
+        x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 2, 3), ones, x, false);
+        x = __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 4, 5), ones, x, false);
+        return __builtin_amdgcn_fdot2_f32_bf16(__builtin_shufflevector(pv, pv, 6, 7), ones, x, false);
+      };
+      psum = add(0.f);
+      if (PAIRED) {   // lanes 32 .. 63 go on from the sums of lanes 0 .. 31 and hold the sixteen weights', the others their own eight's
+        const unsigned z = __float_as_uint(psum);
+        const auto r = __builtin_amdgcn_permlane32_swap(0u, z, false, false);   // r[0]: 0 | the low lanes' sums
+        psum = add(__uint_as_float(r[0]));
+      }
     }
   };
   // Online softmax of one step, one query of each sub-tile per lane (shared with three others).  `force`: the first
@@ -354,7 +372,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
       for (int u = 0; u < QT; ++u)
 #pragma unroll
         for (int e = 0; e < 8; ++e)
-          if (key0 + 8 * lg + e >= n_keys) s[u][e >> 2][e & 3] = -INFINITY;
+          if (key0 + (PAIRED ? 16 * (lg >> 1) + 8 * (e >> 2) + 4 * (lg & 1) + (e & 3) : 8 * lg + e) >= n_keys) s[u][e >> 2][e & 3] = -INFINITY;
     }
     // logits relative to the reference as it stands (log2 domain already: q carries the scale)
     if (shifted) {
@@ -410,6 +428,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
         // nothing has been accumulated before the first step (and the factor would overflow for a
         // first maximum below -127)
         alpha[u] = force ? 1.0f : __builtin_amdgcn_exp2f(-d);
+        l_run[u] *= alpha[u];
 #pragma unroll
         for (int e = 0; e < 8; ++e) s[u][e >> 2][e & 3] -= d;
         m_ref[u] += d;
@@ -419,7 +438,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
       if (SUM_MFMA) weights(s[u], pf[u], psum[u]);
-      else l_run[u] = __builtin_fmaf(l_run[u], alpha[u], psum[u]);
+      else l_run[u] += psum[u];
     }
     static_for<QT>([&](auto u) { acc_scale<u>(oacc[u], moved, alpha[u]); });
   };
@@ -429,12 +448,19 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
   unsigned vfo[2], vfo_last[2];   // by step of the block
 #pragma unroll
   for (int kt = 0; kt < 2; ++kt) {
-    vfo[kt] = (unsigned)(l16 * BKEY + SM::v_chunk(l16, kt * 4 + lg) * 8);
+    vfo[kt] = (unsigned)(l16 * BKEY + SM::v_chunk(l16, kt * 4 + (PAIRED ? lg & 2 : lg)) * 8 + (PAIRED ? (lg & 1) * 4 : 0));
     vfo_last[kt] = SM::ONES && l16 > HD % 16 ? (unsigned)(HD % 16 * BKEY) : vfo[kt];
   }
   bf16x8 vf[PRE];
   auto read_v = [&](int buf, int kt, int b) {
-    vf[b % PRE] = *reinterpret_cast<const bf16x8*>(sV + buf * SM::V_ELEMS + (b == OB - 1 ? vfo_last[kt] : vfo[kt]) + b * 16 * BKEY);
+    const unsigned o = b == OB - 1 ? vfo_last[kt] : vfo[kt];
+    const bf16_t* v = sV + buf * SM::V_ELEMS + b * 16 * BKEY;
+    if constexpr (PAIRED) {   // the other half of the keys: the neighbouring chunk, which the swizzle keeps in the pair
+      const bf16x4 x = *reinterpret_cast<const bf16x4*>(v + o), y = *reinterpret_cast<const bf16x4*>(v + (o ^ 8u));
+      vf[b % PRE] = __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+      vf[b % PRE] = *reinterpret_cast<const bf16x8*>(v + o);
+    }
   };
   auto pre_pv = [&](int buf, int kt) {
 #pragma unroll
@@ -548,7 +574,8 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
       l_tot = __shfl(oacc[u][OB - 1][0], (HD % 16 / 4) * 16 + l16, 64);
     } else {
       l_tot = l_run[u] + __shfl_xor(l_run[u], 16, 64);
-      l_tot += __shfl_xor(l_tot, 32, 64);
+      if (PAIRED) l_tot = __shfl(l_tot, lane | 32, 64);   // whole in the upper lanes
+      else l_tot += __shfl_xor(l_tot, 32, 64);
     }
     if (q0 + u * 16 + l16 >= n_q) continue;   // the slice's queries need not fill its last sub-tile (nor its rows a wave)
     const float inv = 1.0f / l_tot;
@@ -591,7 +618,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
   }
 }
 
-template <int HD, int QT, bool MASK>
+template <int HD, int QT, bool MASK, bool PAIRED>
 hipError_t launch_attn_m(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                          int n_tok, int n_keys, int n_q, int q_shared, int heads, long ld_qk, long ld_o,
                          unsigned char* oq, unsigned* so, long ld_so, hipStream_t st) {
@@ -599,12 +626,12 @@ hipError_t launch_attn_m(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf1
   const int n_qb = (n_q + BQ - 1) / BQ, n_pairs = n_slices * heads;
   const long n_wg = (long)((n_pairs + 7) / 8) * 8 * n_qb;
   if (n_wg > 0x7fffffffL) return hipErrorInvalidValue;
-  k_attention_bf16<HD, QT, MASK><<<dim3((unsigned)n_wg), dim3(256), AttnSmem<HD>::BYTES, st>>>(
+  k_attention_bf16<HD, QT, MASK, PAIRED><<<dim3((unsigned)n_wg), dim3(256), AttnSmem<HD>::BYTES, st>>>(
       q, k, vt, o, n_tok, n_keys, n_q, q_shared, heads, n_pairs, ld_qk, ld_o, oq, so, ld_so);
   return hipGetLastError();
 }
 
-template <int HD>
+template <int HD, bool PAIRED>
 hipError_t launch_attn(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                        int n_tok, int n_keys, int n_q, int q_shared, int heads, long ld_qk, long ld_o,
                        unsigned char* oq, unsigned* so, long ld_so, hipStream_t st) {
@@ -614,23 +641,27 @@ hipError_t launch_attn(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_
   // (us, 32 | 16 queries per wave: 128 workgroups of head dim 64 19.1 | 14.0, 384 25.1 | 21.0, 640 33.7 | 36.1; of head dim 72
   // 128 21.0 | 16.1, 384 28.9 | 25.9, 1280 62.9 | 74.4; of 128 200 25.8 | 23.5, 600 56.5 | 57.6).  A query's bits are the same.
   if (wgs <= 512)
-    return mask ? launch_attn_m<HD, 1, true>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
-                : launch_attn_m<HD, 1, false>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
-  return mask ? launch_attn_m<HD, 2, true>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
-              : launch_attn_m<HD, 2, false>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
+    return mask ? launch_attn_m<HD, 1, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
+                : launch_attn_m<HD, 1, false, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
+  return mask ? launch_attn_m<HD, 2, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
+              : launch_attn_m<HD, 2, false, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
 }
 
-template <int HD, int QT, bool MASK>
+template <int HD, int QT, bool MASK, bool PAIRED>
 hipError_t set_attr() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attention_bf16<HD, QT, MASK>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_attention_bf16<HD, QT, MASK, PAIRED>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)AttnSmem<HD>::BYTES);
 }
 template <int HD>
 hipError_t set_attr_hd() {
-  hipError_t e = set_attr<HD, 1, false>();
-  if (e == hipSuccess) e = set_attr<HD, 1, true>();
-  if (e == hipSuccess) e = set_attr<HD, 2, false>();
-  return e == hipSuccess ? set_attr<HD, 2, true>() : e;
+  hipError_t e = set_attr<HD, 1, false, false>();
+  if (e == hipSuccess) e = set_attr<HD, 1, true, false>();
+  if (e == hipSuccess) e = set_attr<HD, 2, false, false>();
+  if (e == hipSuccess) e = set_attr<HD, 2, true, false>();
+  if (e == hipSuccess) e = set_attr<HD, 1, false, true>();
+  if (e == hipSuccess) e = set_attr<HD, 1, true, true>();
+  if (e == hipSuccess) e = set_attr<HD, 2, false, true>();
+  return e == hipSuccess ? set_attr<HD, 2, true, true>() : e;
 }
 
 }  // namespace
@@ -644,7 +675,7 @@ hipError_t bf16_attention_init() {
 
 hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                           int n_tok, int n_keys, int n_q, int q_shared, int heads, int hd_pad, long ld_qk,
-                          long ld_o, hipStream_t st, unsigned char* oq, unsigned* so, long ld_so) {
+                          long ld_o, hipStream_t st, unsigned char* oq, unsigned* so, long ld_so, bool paired) {
   if (n_slices == 0) return hipSuccess;
   // MXFP8 output: whole blocks of 32 per head only, rows of at least heads * hd_pad bytes, 4-byte pieces
   if (oq && (hd_pad % 32 != 0 || !so || ld_o % 4 != 0 || ld_o < (long)heads * hd_pad || ld_so < (long)n_slices * n_q)) return hipErrorInvalidValue;
@@ -652,12 +683,16 @@ hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf
   // read up to 63 rows (q, k) / 63 elements (v^T) past its end: the caller's buffers must reach that far.
   if (n_tok % 8 != 0 || n_tok <= 0 || n_keys < 1 || n_keys > n_tok || n_q < 1) return hipErrorInvalidValue;
   if (!q_shared && n_q != n_tok) return hipErrorInvalidValue;   // a slice's own rows: one query per row
+#define LAUNCH(HD)                                                                                                       \
+  return paired || oq ? launch_attn<HD, true>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st) \
+                      : launch_attn<HD, false>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
   switch (hd_pad) {
-    case 64: return launch_attn<64>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
-    case 72: return launch_attn<72>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
-    case 96: return launch_attn<96>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
-    case 128: return launch_attn<128>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
+    case 64: LAUNCH(64);
+    case 72: LAUNCH(72);
+    case 96: LAUNCH(96);
+    case 128: LAUNCH(128);
   }
+#undef LAUNCH
   return hipErrorInvalidValue;
 }
 

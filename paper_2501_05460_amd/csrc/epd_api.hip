@@ -932,7 +932,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
       const bool fused = c->hd_pad % 32 == 0;
       { ProfScope ps(c, 3, st);
         HIP_TRY(c, bf16_attention(QK, QK + c->Dq, VT, O, T, x.Ns, x.Nt, x.Ns, 0, x.H, c->hd_pad, ld_qk, c->Dq_k, st,
-                                  fused ? OQ : nullptr, fused ? SO : nullptr, c->Mp));
+                                  fused ? OQ : nullptr, fused ? SO : nullptr, c->Mp, true));
         if (!fused) {
           MxRowParams r;
           memset(&r, 0, sizeof(r));
@@ -946,7 +946,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
         HIP_TRY(c, mx_gemm(p, st)); }
     } else {
     { ProfScope ps(c, 3, st);
-      HIP_TRY(c, bf16_attention(QK, QK + c->Dq, VT, O, T, x.Ns, x.Nt, x.Ns, 0, x.H, c->hd_pad, ld_qk, c->Dq_k, st)); }
+      HIP_TRY(c, bf16_attention(QK, QK + c->Dq, VT, O, T, x.Ns, x.Nt, x.Ns, 0, x.H, c->hd_pad, ld_qk, c->Dq_k, st, nullptr, nullptr, 0, d.mx_fp8 != 0)); }
     { ProfScope ps(c, 6, st);
       GemmParams p = gp(EPI_BIAS_RESIDUAL, O, c->Dq_k, w.o, M);
       p.R = X; p.ldr = x.D;
@@ -1008,7 +1008,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
       pv.VT = (bf16_t*)r.V; pv.hd_pad = r.hd_pad; pv.heads = r.H; pv.n_tok = x.N;
       HIP_TRY(c, bf16_gemm(pv, st)); }
     { ProfScope ps(c, 3, st);
-      HIP_TRY(c, bf16_attention((const bf16_t*)r.qp, K, (const bf16_t*)r.V, Oq, T, x.N, x.N, r.Q, 1, r.H, r.hd_pad, r.Eq_k, r.Eq_k, st)); }
+      HIP_TRY(c, bf16_attention((const bf16_t*)r.qp, K, (const bf16_t*)r.V, Oq, T, x.N, x.N, r.Q, 1, r.H, r.hd_pad, r.Eq_k, r.Eq_k, st, nullptr, nullptr, 0, d.mx_fp8 != 0)); }
     { ProfScope ps(c, 9, st);
       GemmParams p = gp(EPI_BIAS, Oq, r.Eq_k, r.o, Mo);
       p.C = o2; p.ldc = r.E_k;
