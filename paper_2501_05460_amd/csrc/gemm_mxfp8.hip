@@ -273,14 +273,17 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   auto read_a = [&](int i) { fa[i % 4] = frag(a_lo, a_hi, i); sa[i % 4] = smem[sc_a + i * 64]; };
   auto read_b = [&](int j) { fb[j] = frag(b_lo, b_hi, j); sb[j] = smem[sc_b + j * 64]; };
   // In place, as assembly: the compiler's form moves accumulators from register to register, and spills.  It does not see
-  // the wait states behind such an instruction: nothing but products touches an accumulator between the zeros in front of a
-  // tile and the nops behind it.
+  // the wait states such an instruction needs.  Behind it: nothing but products touches an accumulator between the zeros in
+  // front of a tile and the nops behind it.  In front of it: an operand that a vector instruction wrote is read two wait
+  // states later at the earliest.  The codes come from LDS as they are, but the compiler widens a scale byte wherever it
+  // likes, also next to the product: hence the s_nop of every product.  It costs nothing (a product holds the matrix core
+  // for eight wait states; 50 products with it in front of all and of two products a slab: equal to within two runs of one).
   auto mma = [&](auto i, auto j) {
     constexpr int I = decltype(i)::value, J = decltype(j)::value;
     if constexpr (TOK)
-      asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fa[I % 4]), "v"(fb[J]), "v"(sa[I % 4]), "v"(sb[J]));
+      asm volatile("s_nop 1\n\tv_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fa[I % 4]), "v"(fb[J]), "v"(sa[I % 4]), "v"(sb[J]));
     else
-      asm volatile("v_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fb[J]), "v"(fa[I % 4]), "v"(sb[J]), "v"(sa[I % 4]));
+      asm volatile("s_nop 1\n\tv_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fb[J]), "v"(fa[I % 4]), "v"(sb[J]), "v"(sa[I % 4]));
     __builtin_amdgcn_sched_barrier(0);
   };
 
