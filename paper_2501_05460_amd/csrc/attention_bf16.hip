@@ -341,6 +341,19 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
       }
     }
   };
+  // Where the softmax of a step follows its S^T product directly.  The compiler keeps the eight wait states behind a product
+  // on the way through the rare shift of the logits, but not past it: its search does not look at the direct way, and
+  // the first exponential stood three behind.  (Everywhere else a second product or the next S^T product lies in between.)
+  // us with 8 | 5 wait states here: one slice of 16 heads of 64 14.4 | 14.3, 13 68.3 | 68.4, 104 529.6 | 526.1; of 72 10 64.4 | 64.4.
+  auto settle = [&](f32x4 (&s)[QT][2]) {
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int u = 0; u < QT; ++u) asm volatile("" : "+v"(s[u][0]), "+v"(s[u][1]));
+    asm volatile("s_nop 7" ::: "memory");
+#pragma unroll
+    for (int u = 0; u < QT; ++u) asm volatile("" : "+v"(s[u][0]), "+v"(s[u][1]));
+    __builtin_amdgcn_sched_barrier(0);
+  };
   // weights of one step from its shifted logits, and (unless the second product sums them) their
   // sum over the rounded values that product uses, two per instruction
   auto weights = [&](const f32x4 (&sv)[2], bf16x8& pv, float& psum) {
@@ -511,6 +524,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
       const bool more = kb + 1 < NB;
       if (more) gload(buf ^ 1, kb + 1);   // the other buffer: nobody reads it after the previous barrier
       issue_s(s0, buf, 0);
+      settle(s0);
       softmax(s0, p0, kb * BKEY, first);
       first = 0;
       pre_pv(buf, 0);
@@ -528,6 +542,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
 #pragma clang loop unroll(disable)
     for (int kb = NF; kb < NB; ++kb) {
       issue_s(s0, kb & 1, 0);
+      settle(s0);
       softmax(s0, p0, kb * BKEY, first);
       pre_pv(kb & 1, 0);
       issue_pv(p0, kb & 1, 0);
@@ -560,6 +575,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
 #pragma clang loop unroll(disable)
     for (int kb = NF; kb < NB; ++kb) {
       pre_pv(kb & 1, 0);
+      settle(s0);
       softmax(s0, p0, kb * BKEY, first);
       issue_pv(p0, kb & 1, 0);
     }

@@ -277,7 +277,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   // front of a tile and the nops behind it.  In front of it: an operand that a vector instruction wrote is read two wait
   // states later at the earliest.  The codes come from LDS as they are, but the compiler widens a scale byte wherever it
   // likes, also next to the product: hence the s_nop of every product.  It costs nothing (a product holds the matrix core
-  // for eight wait states; 50 products with it in front of all and of two products a slab: equal to within two runs of one).
+  // for eight wait states; 40 products with it in front of all and of two products a slab: equal to within two runs of one).
   auto mma = [&](auto i, auto j) {
     constexpr int I = decltype(i)::value, J = decltype(j)::value;
     if constexpr (TOK)

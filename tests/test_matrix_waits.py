@@ -3,9 +3,11 @@
 Much of the matrix work is inline assembly, and the compiler puts no wait states around instructions it does not see.
 This follows every path of every kernel that holds a matrix instruction and counts, as the compiler's own forms do: an
 instruction is one wait state, s_nop n is n + 1.  The rules (CDNA3 ISA guide, tables of manually inserted wait states and of
-required independent instructions):
+required independent instructions; the compiler's own figures for gfx950):
   * a VGPR a vector instruction has written is read by a matrix instruction (any operand, scales included) no earlier
     than 2 wait states behind it;
+  * the result of a matrix instruction of p passes is touched by anything but a matrix instruction that adds to exactly
+    these registers no earlier than p + 4 wait states behind it (fp32 operands: p + 2);
   * an SGPR a vector instruction has written is read by a memory instruction no earlier than 5 wait states behind it.
 """
 import functools
@@ -19,6 +21,7 @@ import pytest
 from paper_2501_05460_amd import binding as B
 
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
+PASSES = {"4x4x4": 2, "16x16x4": 8, "16x16x16": 4, "16x16x32": 4, "16x16x128": 8, "32x32x2": 16, "32x32x16": 8, "32x32x64": 16}
 REG = re.compile(r"(?<![\w.])([vas])(?:(\d+)|\[(\d+):(\d+)\])(?!\w)|\b(vcc)\b")
 
 
@@ -73,6 +76,10 @@ class Inst:
         elif "store" in name or "atomic" in name or "lds" in name or name.startswith("ds_write") or name.startswith("s_cmp"):
             self.writes, self.reads = frozenset(), first | rest
         self.mfma = name.startswith("v_mfma")
+        if self.mfma:
+            fp32 = name.endswith("_f32") and name.count("f32") == 2
+            self.result_wait = PASSES[re.search(r"\d+x\d+x\d+", name).group()] + (2 if fp32 else 4)
+            self.c, self.factors = ops[3], frozenset().union(ops[1], ops[2], *ops[4:])
 
 
 def kernels(listing):
@@ -126,6 +133,19 @@ def operand_faults(order):
                 yield "scalar register of a memory instruction", inst, at, gap
 
 
+def result_faults(order):
+    for inst in order:
+        if not inst.mfma:
+            continue
+        for at, gap in reached(inst, inst.result_wait):
+            if at.mfma:
+                touched = at.factors & inst.writes or (at.c & inst.writes and at.c != inst.writes)
+            else:
+                touched = at.reads & inst.writes or (is_vector(at.name) and at.writes & inst.writes)
+            if touched:
+                yield "result of a matrix instruction", inst, at, gap
+
+
 @pytest.fixture(scope="module")
 def built_kernels(tmp_path_factory):
     if not os.path.exists(B.LIB_PATH) or not os.path.exists(OBJDUMP):
@@ -146,3 +166,7 @@ def check(built, faults):
 
 def test_operands_are_written_early_enough(built_kernels):
     check(built_kernels, operand_faults)
+
+
+def test_results_are_touched_late_enough(built_kernels):
+    check(built_kernels, result_faults)
