@@ -47,8 +47,8 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
                                  void* hip_stream);
 
 /* Which form the library takes for a product of M rows, N columns (padded as the library pads its weights) and K, by
- * epilogue as above and 4 = patch embedding, 5 = value projection (slices of n_tok rows each): *form as above (9 / 10 / 7
- * for 256x256 tiles, 0: whole 256-wide tile columns and the rest apart); *rows: the rows in front of a row cut, M
+ * epilogue as above and 4 = patch embedding, 5 = value projection (slices of n_tok rows each): *form as above (10 / 9
+ * for 256x256 tiles of residual / other products, 0: whole 256-wide tile columns and the rest apart); *rows: the rows in front of a row cut, M
  * without one.  Host only: launches nothing, and counts 256 CUs where there is no device. */
 epd_status epd_op_gemm_bf16_choice(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t n_tok, int32_t* form, int32_t* rows);
 

@@ -1218,7 +1218,7 @@ bool tiles_192() {   // EPD_TILES_192=0: widths like 1152 stay on the 256-wide t
   return on;
 }
 
-hipError_t dispatch_persist(const GemmParams& p, hipStream_t st) {   // bf16-output epilogues on 256 x 256 tiles
+hipError_t dispatch_persist(const GemmParams& p, hipStream_t st) {   // all but the residual epilogue, on 256 x 256 tiles
   if (!p.stats) return launch_wide(p, WIDE_256, st);
   switch (p.epi) {
     case EPI_BIAS: return launch_persist<EPI_BIAS>(p, st);
@@ -1430,8 +1430,8 @@ bool bf16_gemm_on_64x64(const GemmParams& p) {
   return c.form == PLAIN_RING && c.tile == RING_64x64;
 }
 
-// For tests: the form choose_plain takes, by its number in GemmParams::cfg (9 / 10 / 7: 256 x 256 tiles by epilogue, 0: the
-// cut by columns); *rows: the rows in front of a row cut, M without one
+// For tests: the form choose_plain takes, by its number in GemmParams::cfg (10 / 9: 256 x 256 tiles of residual / other
+// products, 0: the cut by columns); *rows: the rows in front of a row cut, M without one
 int bf16_gemm_choice(const GemmParams& p, long* rows) {
   const Plain c = choose_plain(p);
   *rows = c.form == PLAIN_256 && c.rows_a > 0 ? c.rows_a * BM : p.M;
@@ -1439,7 +1439,7 @@ int bf16_gemm_choice(const GemmParams& p, long* rows) {
     case PLAIN_RING: return c.tile == RING_64x64 ? 11 : c.tile == RING_128x64 ? 13 : 14;
     case PLAIN_256x128: return 1;
     case PLAIN_192: return 12;
-    case PLAIN_256: return p.epi == EPI_BIAS_RESIDUAL ? 10 : p.epi == EPI_BIAS_POS ? 7 : 9;
+    case PLAIN_256: return p.epi == EPI_BIAS_RESIDUAL ? 10 : 9;
     case PLAIN_COLUMNS: return 0;
   }
   return -1;
@@ -1463,7 +1463,7 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
     case 6: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 0>(p, st); break;
     case 7: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 1>(p, st); break;
     case 8: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 3>(p, st); break;
-    case 9: if (p.Npad % 256 == 0 && p.epi != EPI_BIAS_RESIDUAL && p.epi != EPI_BIAS_POS) return dispatch_persist(p, st); break;
+    case 9: if (p.Npad % 256 == 0 && p.epi != EPI_BIAS_RESIDUAL) return dispatch_persist(p, st); break;
     case 10: if (p.Npad % 256 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_wide(p, WIDE_256, st); break;
     case 11: if (ring_has(p)) return launch_ring(p, RING_64x64, st); break;
     case 13: if (ring_has(p)) return launch_ring(p, RING_128x64, st); break;

@@ -45,6 +45,14 @@ def test_the_form_taken_is_among_the_fastest(epi, M, N, K, n_tok, us):
     assert us[taken] <= 1.09 * min(us.values()), (taken, us)
 
 
+@pytest.mark.parametrize("M,N,K", [(1024, 1024, 640), (13312, 1024, 640), (106496, 1024, 640), (40960, 3200, 640), (65536, 1152, 640)])
+def test_the_patch_embedding_is_reported_by_the_kernel_that_runs(M, N, K):
+    """Its forms are the ring tiles, 256 x 128 tiles and the persistent 256 x 256 tiles (9), as for the other products."""
+    form, rows = B.op_gemm_bf16_choice(M, N, K, 4)
+    assert form in (1, 9, 11, 13, 14) and rows == M
+    assert (form == 9) == (M > 1024)
+
+
 def test_choice_rejects_what_the_products_do_not_take():
     for args in ((0, 128, 128, 0), (1, 126, 128, 0), (1, 128, 64, 0), (1, 128, 128, 6), (1, 128, 128, 5, 0)):
         with pytest.raises(B.EpdError):
