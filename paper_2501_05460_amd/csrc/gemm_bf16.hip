@@ -1065,16 +1065,15 @@ hipError_t launch(const GemmParams& p, hipStream_t st) {
 }
 
 }  // namespace
+// The calling thread's device when first asked, for good: every GPU this code runs on is of one kind.  A function-local
+// constant, so that threads that ask at once wait for one answer.
 int cu_count() {
-  static int n = 0;
-  if (n == 0) {
+  static const int n = [] {
     int dev = 0, v = 0;
-    if (hipGetDevice(&dev) == hipSuccess &&
-        hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0)
-      n = v;
-    else
-      n = 256;
-  }
+    const bool ok = hipGetDevice(&dev) == hipSuccess &&
+                    hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0;
+    return ok ? v : 256;
+  }();
   return n;
 }
 namespace {

@@ -250,7 +250,7 @@ struct MxGemmParams {
   unsigned char* Cq; long ldcq; int ncq;
   unsigned* SC; long sc_ld;
 };
-int cu_count();   // compute units of the current device
+int cu_count();   // compute units of the device (see gemm_bf16.hip)
 hipError_t mx_gemm(const MxGemmParams& p, hipStream_t st);
 hipError_t mx_gemm_init();   // raises the dynamic-LDS limit of the kernels (idempotent)
 // one v_mfma_scale_f32_32x32x64_f8f6f4 on caller-supplied registers (operand-layout test): a, b [64][8], sa, sb [64], d [64][16]
