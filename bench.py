@@ -42,11 +42,13 @@ def traffic_from_profile(workload: str):
 
 def roof_report(B, torch):
     """Measured ceilings of this machine, one JSON line: register-resident MFMA loop (random and constant
-    operands), streaming copy, and the vendor BLAS (through torch.matmul) next to this library's plain
+    operands, either bf16 instruction), streaming copy, and the vendor BLAS (through torch.matmul) next to this library's plain
     bias-epilogue product on the four per-layer shapes of the C3 workload and a large cube, ten launches
     back to back each, random operands."""
-    out = {"mfma_loop_tflops_random_operands": round(B.op_mfma_peak(True), 1),
-           "mfma_loop_tflops_constant_operands": round(B.op_mfma_peak(False), 1),
+    out = {"mfma_loop_tflops_random_operands": {"32x32x16": round(B.op_mfma_peak(True), 1),
+                                                "16x16x32": round(B.op_mfma_peak(True, shape=16), 1)},
+           "mfma_loop_tflops_constant_operands": {"32x32x16": round(B.op_mfma_peak(False), 1),
+                                                  "16x16x32": round(B.op_mfma_peak(False, shape=16), 1)},
            "copy_GBps_read_plus_write_1GiB": round(B.op_copy_peak(), 1), "gemm": []}
     # issue port of a SIMD: a wave of MFMAs and a wave of exp + fma pairs, each alone and both together (three rounds)
     co = []
@@ -239,7 +241,7 @@ def main():
         "bound": "mfma", "kernel": ("k_gemm_mxfp8 (q/k/v, out-proj, FC1, FC2) + k_gemm_bf16 (the rest)" if args.mx_fp8 else "k_gemm_bf16 (all epilogue variants)") if bf16 else "k_f32_gemm",
         "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
         # what a register-resident MFMA loop reaches on this machine right now (random operands; no memory, no LDS)
-        "achievable_peak": round(B.op_mfma_peak(True), 1) if bf16 else None,
+        "achievable_peak": round(max(B.op_mfma_peak(True), B.op_mfma_peak(True, shape=16)), 1) if bf16 else None,
         "traffic": traffic, "traffic_source": traffic_source,
         "flops_per_launch": gemm_flops / max(gemm_launches, 1),
         "avg_launch_ms": gemm_ms / max(gemm_launches, 1),

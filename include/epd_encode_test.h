@@ -32,18 +32,19 @@ epd_status epd_op_gemm_bf16(const void* A, const void* W, const float* bias, voi
 
 /* One launch of the bf16 MFMA GEMM in a chosen form, for tests that hold the forms against each
  * other: epi 0 bias, 1 bias + GELU(erf), 2 bias + GELU(tanh) -> C [M,N] bf16; epi 3 -> R [M,N]
- * fp32 += A W^T + bias (C unused).  form 0 = what the library would pick (W and bias padded as it pads its weights), 1 = 256x128 tile,
+ * fp32 += A W^T + bias (C unused); epi 4 -> R [M,N] = A W^T + bias + pos[row % n_tok] (pos [n_tok,N] fp32); epi 5 -> C bf16
+ * transposed per slice of n_tok rows, [M / n_tok, N, n_tok] (n_tok % 8 == 0, M % n_tok == 0).  form 0 = what the library would pick (W and bias padded as it pads its weights), 1 = 256x128 tile,
  * 2, 3 (K % 256 == 0) and 14 = 128x128 tile, both operand slabs in an LDS ring (one kernel: 2 and 3 differ in epd_op_norm_gemm_bf16 and
  * epd_op_gemm_residual_stats only), 13 = 128x64 tile of the same kernel, 6 = 256x256 tile with the plain loop, 7 = pipelined loop, 8 = pipelined loop with both operand slabs
- * loaded straight into LDS, 9 = persistent kernel (not epi 3), 10 = persistent kernel of the residual product (epi 3 only),
+ * loaded straight into LDS, 9 = persistent kernel on 256x256 tiles (not epi 3), 10 = persistent kernel of the residual product (epi 3 only),
  * 11 = 64x64 tile of the ring kernel (11, 13, 14: what the library picks from for launches of a few slices).
  * 12 = the persistent residual product on 256x192 tiles (epi 3 only, N % 192 == 0: what the library picks for a
  * width like 1152, which is six such tile columns and four and a half 256-wide ones).
  * M >= 1 (any), N % 128 == 0 (N % 256 == 0 for forms 6 to 10), K % 128 == 0; bias [N] fp32.
  * A [M,K], C [M,N] and R [M,N] hold exactly M rows; no row past M is written.  (The kernels read whole
  * 256-row tiles; for a ragged M, for R and for padded weights the call runs on copies it allocates, and synchronises.) */
-epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias, void* C, float* R,
-                                 int32_t M, int32_t N, int32_t K, int32_t epi, int32_t form,
+epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias, void* C, float* R, const float* pos,
+                                 int32_t M, int32_t N, int32_t K, int32_t n_tok, int32_t epi, int32_t form,
                                  void* hip_stream);
 
 /* Which form the library takes for a product of M rows, N columns (padded as the library pads its weights) and K, by
@@ -79,10 +80,11 @@ epd_status epd_op_norm_gemm_bf16(const float* x, const float* gamma, const float
  * with row stride ld_qk elements; vt dev bf16 [T, H, hd_pad, n_tokens] (values transposed); o dev
  * bf16 [T * n_tokens, H * hd_pad].  hd_pad in {64, 72, 96, 128}, n_tokens % 64 == 0.
  * Only the first n_keys (1 .. n_tokens) rows of a slice are tokens:
- * the others are left out of every softmax as keys, and their rows of o hold unused values. */
+ * the others are left out of every softmax as keys, and their rows of o hold unused values.
+ * paired: the order of summation of calls of the MXFP8 option. */
 epd_status epd_op_attention_bf16(const void* q, const void* k, const void* vt, void* o,
                                  int32_t n_slices, int32_t n_tokens, int32_t n_keys, int32_t heads,
-                                 int32_t hd_pad, int32_t ld_qk, void* hip_stream);
+                                 int32_t hd_pad, int32_t ld_qk, int32_t paired, void* hip_stream);
 
 /* The same attention with its output leaving as MXFP8 (the out-projection's operand under epd_model_desc::mx_fp8),
  * converted from the kernel's fp32 accumulators: codes dev uint8 [T * n_tokens, H * hd_pad], scales dev uint32
@@ -101,15 +103,15 @@ epd_status epd_op_mfma_probe(const void* A, const void* B, float* D, void* hip_s
  * = the scale bytes of blocks 4 s .. 4 s + 3 of row r, block 4 s + b in byte b.
  * epd_op_mx_rows: conversion of `rows` rows of `dim` elements (dim % 128 == 0; fp32, or bf16 if in_bf16), after
  *   a LayerNorm (kind 0, gamma / beta [dim] fp32), an RMSNorm (kind 1, gamma) or as they are (kind 2).
- * epd_op_mx_gemm: out = (A W^T) * cscale[n] + bias[n] on such operands (A [M, K], W [N, K]; M % 256 == 0,
- *   N % 256 == 0, K % 128 == 0; cscale may be null); epi 0 -> C bf16 [M, N]; epi 5 -> C bf16 transposed per
+ * epd_op_mx_gemm: out = (A W^T) * cscale[n] + bias[n] on such operands (A [M, K], W [N, K]; N % 256 == 0, K % 128 == 0; A, SA
+ *   and SC hold M rounded up to 256 rows; cscale may be null; tile 0 = as the library picks, 1 = 256x256, 2 = 128x128); epi 0 -> C bf16 [M, N]; epi 5 -> C bf16 transposed per
  *   slice and head, [M / n_tok, heads, hd_pad, n_tok] with N = heads * hd_pad; epi 1 / 2 -> GELU (erf / tanh form),
  *   then converted: codes Cq [M, N], scales SC [N / 128, M]; epi 3 -> R fp32 [M, N] += out.
- * epd_op_mx_mfma_probe: one v_mfma_scale_f32_32x32x64_f8f6f4 on caller-supplied registers (a, b: int32 [64][8],
- *   sa, sb: int32 [64], scale byte 0 used; d: fp32 [64][16]), for the operand-layout test.  All pointers dev. */
+ * epd_op_mx_mfma_probe: one v_mfma_scale_f32_16x16x128_f8f6f4 on caller-supplied registers (a, b: int32 [64][8],
+ *   sa, sb: int32 [64], scale byte 0 used; d: fp32 [64][4]), for the operand-layout test.  All pointers dev. */
 epd_status epd_op_mx_rows(const void* in, int32_t in_bf16, int64_t rows, int32_t dim, int32_t kind, const float* gamma,
                           const float* beta, float eps, void* codes, void* scales, void* hip_stream);
-epd_status epd_op_mx_gemm(int32_t epi, const void* A, const void* SA, const void* W, const void* SW, const float* bias,
+epd_status epd_op_mx_gemm(int32_t epi, int32_t tile, const void* A, const void* SA, const void* W, const void* SW, const float* bias,
                           const float* cscale, int32_t M, int32_t N, int32_t K, void* C, float* R, void* Cq, void* SC,
                           int32_t n_tok, int32_t heads, int32_t hd_pad, void* hip_stream);
 epd_status epd_op_mx_mfma_probe(const void* a, const void* b, const void* sa, const void* sb, float* d, void* hip_stream);
@@ -128,8 +130,8 @@ epd_status epd_profile_enable(epd_ctx* ctx, int32_t on);
 epd_status epd_profile_read(epd_ctx* ctx, float* ms /*host [10]*/, int32_t* launches /*host [10]*/);
 
 /* Measured ceilings next to the nominal ones (the roofline figures of the benchmark).
- * epd_op_mfma_peak: a register-resident loop of v_mfma_f32_32x32x16_bf16 on every CU (two waves per SIMD,
- * eight independent accumulators, eight rotating operand fragment pairs, no LDS or memory traffic inside
+ * epd_op_mfma_peak: a register-resident loop of v_mfma_f32_32x32x16_bf16 (shape 32) or v_mfma_f32_16x16x32_bf16 (shape 16,
+ * what the products and attention run on) on every CU (two waves per SIMD, eight independent accumulators, eight rotating operand fragment pairs, no LDS or memory traffic inside
  * the loop); *tflops = dense bf16 rate over `reps` launches of `iters` loop trips.  operands: dev, 16 KiB of
  * bf16 the fragments are loaded from (random values: the operand buses toggle as in a real product), or
  * null for constant ones (the chip clocks higher on those).  sink: dev, 4 bytes per launched thread
@@ -141,7 +143,7 @@ epd_status epd_profile_read(epd_ctx* ctx, float* ms /*host [10]*/, int32_t* laun
  * other four iters_valu x 32 pairs of v_exp_f32 + fma; which = 1 the matrix waves alone, 2 the vector waves alone,
  * 3 both together.  *ms_per_launch over `reps` launches.  operands: dev, 8 KiB of bf16; sink: dev, 4 bytes per
  * launched thread (CUs * 512 floats). */
-epd_status epd_op_mfma_peak(const void* operands, int32_t iters, int32_t reps, float* sink, float* tflops,
+epd_status epd_op_mfma_peak(int32_t shape, const void* operands, int32_t iters, int32_t reps, float* sink, float* tflops,
                             void* hip_stream);
 epd_status epd_op_copy_peak(const void* src, void* dst, int64_t bytes, int32_t reps, float* gbps, void* hip_stream);
 epd_status epd_op_coissue(const void* operands, int32_t iters_mfma, int32_t iters_valu, int32_t which, int32_t reps,

@@ -98,11 +98,11 @@ def lib() -> ctypes.CDLL:
         L.epd_debug_read_stream.restype = i32
         L.epd_op_gemm_bf16.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, ctypes.POINTER(ctypes.c_float), vp]
         L.epd_op_gemm_bf16.restype = i32
-        L.epd_op_gemm_bf16_form.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp]
+        L.epd_op_gemm_bf16_form.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
         L.epd_op_gemm_bf16_form.restype = i32
         L.epd_op_gemm_bf16_choice.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.epd_op_gemm_bf16_choice.restype = i32
-        L.epd_op_attention_bf16.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
+        L.epd_op_attention_bf16.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp]
         L.epd_op_attention_bf16.restype = i32
         L.epd_op_mfma_probe.argtypes = [vp, vp, vp, vp]
         L.epd_op_mfma_probe.restype = i32
@@ -110,7 +110,7 @@ def lib() -> ctypes.CDLL:
         L.epd_profile_enable.restype = i32
         L.epd_profile_read.argtypes = [vp, ctypes.POINTER(ctypes.c_float), ctypes.POINTER(i32)]
         L.epd_profile_read.restype = i32
-        L.epd_op_mfma_peak.argtypes = [vp, i32, i32, vp, ctypes.POINTER(ctypes.c_float), vp]
+        L.epd_op_mfma_peak.argtypes = [i32, vp, i32, i32, vp, ctypes.POINTER(ctypes.c_float), vp]
         L.epd_op_mfma_peak.restype = i32
         L.epd_op_copy_peak.argtypes = [vp, vp, i64, i32, ctypes.POINTER(ctypes.c_float), vp]
         L.epd_op_copy_peak.restype = i32
@@ -124,7 +124,7 @@ def lib() -> ctypes.CDLL:
         L.epd_op_norm_gemm_bf16.restype = i32
         L.epd_op_mx_rows.argtypes = [vp, i32, i64, i32, i32, vp, vp, ctypes.c_float, vp, vp, vp]
         L.epd_op_mx_rows.restype = i32
-        L.epd_op_mx_gemm.argtypes = [i32, vp, vp, vp, vp, vp, vp, i32, i32, i32, vp, vp, vp, vp, i32, i32, i32, vp]
+        L.epd_op_mx_gemm.argtypes = [i32, i32, vp, vp, vp, vp, vp, vp, i32, i32, i32, vp, vp, vp, vp, i32, i32, i32, vp]
         L.epd_op_mx_gemm.restype = i32
         L.epd_op_attention_mx.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
         L.epd_op_attention_mx.restype = i32
@@ -420,39 +420,43 @@ def op_gemm_bf16_choice(M: int, N: int, K: int, epi: int, n_tok: int = 1):
 
 
 def op_gemm_bf16_form(A: torch.Tensor, W: torch.Tensor, bias: torch.Tensor, epi: int, form: int,
-                      R: Optional[torch.Tensor] = None) -> torch.Tensor:
-    """One GEMM launch in the given form; returns C (bf16) or, for epi 3, the updated R (fp32, in place).
+                      R: Optional[torch.Tensor] = None, pos: Optional[torch.Tensor] = None, n_tok: int = 0) -> torch.Tensor:
+    """One GEMM launch in the given form; returns C (bf16), for epi 3 the updated R (fp32, in place), for epi 4 the embedded
+    rows (fp32; pos [n_tok, N]), for epi 5 C transposed per slice [M / n_tok, N, n_tok].
 
     The output buffer carries guard rows behind row M; a call that writes any of them raises."""
     M, K = A.shape
     N = W.shape[0]
     guard = 12345.0
-    Cg = torch.full((M + 64, N), guard, dtype=torch.bfloat16, device=A.device) if epi != 3 else None
-    Rg = None
+    f32 = epi in (3, 4)
+    Cg = torch.full((M + 64, N), guard, dtype=torch.bfloat16, device=A.device) if not f32 else None
+    Rg = torch.full((M + 64, N), guard, dtype=torch.float32, device=A.device) if f32 else None
     if epi == 3:
-        Rg = torch.full((M + 64, N), guard, dtype=torch.float32, device=A.device)
         Rg[:M] = R
     s = lib().epd_op_gemm_bf16_form(A.contiguous().data_ptr(), W.data_ptr(), bias.data_ptr(),
                                     Cg.data_ptr() if Cg is not None else None,
-                                    Rg.data_ptr() if Rg is not None else None, M, N, K, epi, form, _stream_ptr())
+                                    Rg.data_ptr() if Rg is not None else None, pos.data_ptr() if pos is not None else None,
+                                    M, N, K, n_tok, epi, form, _stream_ptr())
     if s != EPD_OK:
         raise EpdError(s, lib().epd_last_error(None).decode())
-    tail = Cg[M:] if epi != 3 else Rg[M:]
+    tail = Rg[M:] if f32 else Cg[M:]
     if not bool((tail == guard).all()):
         raise RuntimeError("GEMM form %d wrote rows past M=%d" % (form, M))
+    if epi == 5:
+        return Cg[:M].view(M // n_tok, N, n_tok)
     if epi != 3:
-        return Cg[:M]
+        return Rg[:M] if f32 else Cg[:M]
     R.copy_(Rg[:M])
     return R
 
 
 def op_attention_bf16(q: torch.Tensor, k: torch.Tensor, vt: torch.Tensor, n_slices: int, n_tokens: int,
-                      heads: int, hd_pad: int, ld_qk: int, n_keys: Optional[int] = None) -> torch.Tensor:
+                      heads: int, hd_pad: int, ld_qk: int, n_keys: Optional[int] = None, paired: bool = False) -> torch.Tensor:
     """q must carry the logit scale log2(e) / sqrt(hd): the kernel's weights are 2^(q . k)."""
     o = torch.empty((n_slices * n_tokens, heads * hd_pad), dtype=torch.bfloat16, device=q.device)
     s = lib().epd_op_attention_bf16(q.data_ptr(), k.data_ptr(), vt.data_ptr(), o.data_ptr(), n_slices,
                                     n_tokens, n_tokens if n_keys is None else n_keys, heads, hd_pad, ld_qk,
-                                    _stream_ptr())
+                                    1 if paired else 0, _stream_ptr())
     if s != EPD_OK:
         raise EpdError(s, lib().epd_last_error(None).decode())
     return o
@@ -466,8 +470,9 @@ def op_mfma_probe(A: torch.Tensor, B: torch.Tensor) -> torch.Tensor:
     return D
 
 
-def op_mfma_peak(random_operands: bool, iters: int = 2000, reps: int = 5) -> float:
-    """Dense bf16 TFLOP/s of a register-resident MFMA loop on every CU (random or constant operands)."""
+def op_mfma_peak(random_operands: bool, iters: int = 2000, reps: int = 5, shape: int = 32) -> float:
+    """Dense bf16 TFLOP/s of a register-resident loop of the 32x32x16 (shape 32) or 16x16x32 (16) MFMA on every CU, random or
+    constant operands."""
     cus = torch.cuda.get_device_properties(0).multi_processor_count
     sink = torch.empty(2 * cus * 256, dtype=torch.float32, device="cuda")
     ops = None
@@ -475,7 +480,7 @@ def op_mfma_peak(random_operands: bool, iters: int = 2000, reps: int = 5) -> flo
         g = torch.Generator(device="cuda").manual_seed(1)
         ops = torch.randn(8192, device="cuda", generator=g).to(torch.bfloat16)
     out = ctypes.c_float()
-    s = lib().epd_op_mfma_peak(ops.data_ptr() if ops is not None else None, iters, reps, sink.data_ptr(),
+    s = lib().epd_op_mfma_peak(shape, ops.data_ptr() if ops is not None else None, iters, reps, sink.data_ptr(),
                                ctypes.byref(out), _stream_ptr())
     if s != EPD_OK:
         raise EpdError(s, "mfma peak probe failed")
@@ -564,20 +569,24 @@ def op_mx_rows(x: torch.Tensor, kind: int = 2, gamma: Optional[torch.Tensor] = N
 
 def op_mx_gemm(epi: int, A: torch.Tensor, SA: torch.Tensor, W: torch.Tensor, SW: torch.Tensor, bias: torch.Tensor,
                cscale: Optional[torch.Tensor] = None, R: Optional[torch.Tensor] = None, n_tok: int = 0, heads: int = 0,
-               hd_pad: int = 0):
+               hd_pad: int = 0, tile: int = 0, rows: Optional[int] = None):
     """Product of MXFP8 operands (codes uint8 [M, K] / [N, K], scale words int32 [K / 128, M] / [K / 128, N]).
     epi 0: bf16 [M, N]; 5: bf16 [M / n_tok, heads, hd_pad, n_tok]; 1 / 2: (codes [M, N], scale words [N / 128, M])
-    of the activated output; 3: R (fp32, in place) += product."""
+    of the activated output; 3: R (fp32, in place) += product.  tile 0: as the library picks, 1: 256x256, 2: 128x128.
+    rows: the first of A's rows (a whole number of 256) that are the operand's."""
     M, K = A.shape
+    Mp, M = M, M if rows is None else rows
+    if Mp != (M + 255) // 256 * 256:
+        raise ValueError("A must hold the rows rounded up to 256")
     N = W.shape[0]
     C = Cq = SC = None
     if epi in (0, 5):
         C = torch.full((M, N), float("nan"), dtype=torch.bfloat16, device=A.device)
     elif epi in (1, 2):
         Cq = torch.full((M, N), 0xAA, dtype=torch.uint8, device=A.device)
-        SC = torch.full((N // 128, M), -1, dtype=torch.int32, device=A.device)
+        SC = torch.full((N // 128, Mp), -1, dtype=torch.int32, device=A.device)
     ptr = lambda t: t.data_ptr() if t is not None else None
-    s = lib().epd_op_mx_gemm(epi, A.data_ptr(), SA.data_ptr(), W.data_ptr(), SW.data_ptr(), bias.data_ptr(), ptr(cscale),
+    s = lib().epd_op_mx_gemm(epi, tile, A.data_ptr(), SA.data_ptr(), W.data_ptr(), SW.data_ptr(), bias.data_ptr(), ptr(cscale),
                              M, N, K, ptr(C), ptr(R), ptr(Cq), ptr(SC), n_tok, heads, hd_pad, _stream_ptr())
     if s != EPD_OK:
         raise EpdError(s, lib().epd_last_error(None).decode())
@@ -591,8 +600,8 @@ def op_mx_gemm(epi: int, A: torch.Tensor, SA: torch.Tensor, W: torch.Tensor, SW:
 
 
 def op_mx_mfma_probe(a: torch.Tensor, b: torch.Tensor, sa: torch.Tensor, sb: torch.Tensor) -> torch.Tensor:
-    """One 32x32x64 scaled FP8 MFMA on raw registers: a, b int32 [64, 8], sa, sb int32 [64] -> fp32 [64, 16]."""
-    d = torch.empty((64, 16), dtype=torch.float32, device=a.device)
+    """One 16x16x128 scaled FP8 MFMA on raw registers: a, b int32 [64, 8], sa, sb int32 [64] -> fp32 [64, 4]."""
+    d = torch.empty((64, 4), dtype=torch.float32, device=a.device)
     s = lib().epd_op_mx_mfma_probe(a.data_ptr(), b.data_ptr(), sa.data_ptr(), sb.data_ptr(), d.data_ptr(), _stream_ptr())
     if s != EPD_OK:
         raise EpdError(s, "mx mfma probe failed")

@@ -1353,11 +1353,12 @@ epd_status epd_op_gemm_bf16(const void* A, const void* W, const float* bias, voi
   return EPD_OK;
 }
 
-epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias, void* C, float* R, int32_t M,
-                                 int32_t N, int32_t K, int32_t epi, int32_t form, void* hip_stream) {
-  const bool residual = epi == EPI_BIAS_RESIDUAL;
-  if (!A || !W || !bias || (residual ? !R : !C) || M <= 0 || N <= 0 || K <= 0 || N % 128 || K % 128 ||
-      !(epi == EPI_BIAS || epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH || residual) ||
+epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias, void* C, float* R, const float* pos, int32_t M,
+                                 int32_t N, int32_t K, int32_t n_tok, int32_t epi, int32_t form, void* hip_stream) {
+  const bool residual = epi == EPI_BIAS_RESIDUAL, embed = epi == EPI_BIAS_POS, values = epi == EPI_VT;
+  if (!A || !W || !bias || (residual || embed ? !R : !C) || (embed && (!pos || n_tok <= 0)) ||
+      (values && (n_tok <= 0 || n_tok % 8 || M % n_tok)) || M <= 0 || N <= 0 || K <= 0 || N % 128 || K % 128 ||
+      !(epi == EPI_BIAS || epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH || residual || embed || values) ||
       !(form == 0 || form == 1 || form == 2 || form == 3 || (form >= 6 && form <= 14)) ||
       (form == 3 && K % 256) || (form >= 6 && form <= 10 && N % 256) || (form == 9 && residual) || (form == 10 && !residual) ||
       (form == 12 && (!residual || N % 192))) {
@@ -1406,7 +1407,8 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
   GemmParams p;
   memset(&p, 0, sizeof(p));
   p.epi = epi; p.cfg = form; p.A = (const bf16_t*)(pad_a ? Ap : A); p.lda = K; p.W = (const bf16_t*)(pad_w ? Wp : W); p.bias = pad_w ? bp : bias;
-  p.M = M; p.N = N; p.K = K; p.Npad = Npad; p.C = (bf16_t*)C; p.ldc = N; p.R = pad_r ? Rp : R; p.ldr = N; p.n_pos = 1;
+  p.M = M; p.N = N; p.K = K; p.Npad = Npad; p.C = (bf16_t*)C; p.ldc = N; p.R = pad_r ? Rp : R; p.ldr = N; p.pos = pos; p.n_pos = embed ? n_tok : 1;
+  p.VT = (bf16_t*)C; p.heads = 1; p.hd_pad = N; p.n_tok = n_tok;
   const hipError_t err = bf16_gemm(p, st);
   if (err != hipSuccess) { fail(EPD_ERR_HIP, hipGetErrorString(err)); return EPD_ERR_HIP; }
   if (pad_r && hipMemcpyAsync(R, Rp, (size_t)M * N * 4, hipMemcpyDeviceToDevice, st) != hipSuccess) return fail(EPD_ERR_HIP, "copy failed");
@@ -1505,12 +1507,13 @@ epd_status epd_op_norm_gemm_bf16(const float* x, const float* gamma, const float
 
 epd_status epd_op_attention_bf16(const void* q, const void* k, const void* vt, void* o, int32_t n_slices,
                                  int32_t n_tokens, int32_t n_keys, int32_t heads, int32_t hd_pad, int32_t ld_qk,
-                                 void* hip_stream) {
+                                 int32_t paired, void* hip_stream) {
   if (!q || !k || !vt || !o) return EPD_ERR_INVALID_ARG;
   if (n_tokens % 64) { set_err(g_err, sizeof(g_err), "epd_op_attention_bf16: n_tokens %% 64 != 0"); return EPD_ERR_UNSUPPORTED; }
   if (bf16_attention_init() != hipSuccess) return EPD_ERR_HIP;
   hipError_t e = bf16_attention((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)vt, (bf16_t*)o, n_slices,
-                                n_tokens, n_keys, n_tokens, 0, heads, hd_pad, ld_qk, (long)heads * hd_pad, (hipStream_t)hip_stream);
+                                n_tokens, n_keys, n_tokens, 0, heads, hd_pad, ld_qk, (long)heads * hd_pad, (hipStream_t)hip_stream,
+                                nullptr, nullptr, 0, paired != 0);
   if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "attention launch failed: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_UNSUPPORTED : EPD_ERR_HIP; }
   return EPD_OK;
 }
@@ -1578,22 +1581,23 @@ epd_status epd_op_mx_rows(const void* in, int32_t in_bf16, int64_t rows, int32_t
   return EPD_OK;
 }
 
-epd_status epd_op_mx_gemm(int32_t epi, const void* A, const void* SA, const void* W, const void* SW, const float* bias,
+epd_status epd_op_mx_gemm(int32_t epi, int32_t tile, const void* A, const void* SA, const void* W, const void* SW, const float* bias,
                           const float* cscale, int32_t M, int32_t N, int32_t K, void* C, float* R, void* Cq, void* SC,
                           int32_t n_tok, int32_t heads, int32_t hd_pad, void* hip_stream) {
-  if (!A || !SA || !W || !SW || !bias || M <= 0 || M % 256 || N <= 0 || N % 256 || K <= 0 || K % 128) {
-    set_err(g_err, sizeof(g_err), "epd_op_mx_gemm: bad argument (M %% 256, N %% 256, K %% 128)");
+  if (!A || !SA || !W || !SW || !bias || M <= 0 || N <= 0 || N % 256 || K <= 0 || K % 128 || tile < 0 || tile > 2) {
+    set_err(g_err, sizeof(g_err), "epd_op_mx_gemm: bad argument (N %% 256, K %% 128, tile 0..2)");
     return EPD_ERR_INVALID_ARG;
   }
   if (epi == EPI_VT && (n_tok <= 0 || heads <= 0 || hd_pad <= 0 || M % n_tok || heads * hd_pad != N)) return EPD_ERR_INVALID_ARG;
   if (mx_gemm_init() != hipSuccess) return EPD_ERR_HIP;
+  const long Mp = ((long)M + 255) / 256 * 256;
   MxGemmParams p;
   memset(&p, 0, sizeof(p));
-  p.epi = epi; p.A = (const unsigned char*)A; p.lda = K; p.SA = (const unsigned*)SA; p.sa_ld = M;
+  p.epi = epi; p.tile = tile; p.A = (const unsigned char*)A; p.lda = K; p.SA = (const unsigned*)SA; p.sa_ld = Mp;
   p.W = (const unsigned char*)W; p.SW = (const unsigned*)SW; p.bias = bias; p.cscale = cscale;
   p.M = M; p.N = N; p.K = K; p.Npad = N;
   p.C = (bf16_t*)C; p.ldc = N; p.R = R; p.ldr = N; p.VT = (bf16_t*)C; p.hd_pad = hd_pad; p.heads = heads; p.n_tok = n_tok;
-  p.Cq = (unsigned char*)Cq; p.ldcq = N; p.ncq = N; p.SC = (unsigned*)SC; p.sc_ld = M;
+  p.Cq = (unsigned char*)Cq; p.ldcq = N; p.ncq = N; p.SC = (unsigned*)SC; p.sc_ld = Mp;
   const hipError_t e = mx_gemm(p, (hipStream_t)hip_stream);
   if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "epd_op_mx_gemm: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_INVALID_ARG : EPD_ERR_HIP; }
   return EPD_OK;

@@ -528,18 +528,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
 }
 
 // One instruction on caller-supplied registers: lane l gets a[l][0..7], b[l][0..7] and the scale registers
-// sa[l], sb[l] (byte 0 is used) and leaves its 16 result registers in d[l][0..15].
+// sa[l], sb[l] (byte 0 is used) and leaves its four result registers in d[l][0..3].
 __global__ __launch_bounds__(64) void k_mx_mfma_probe(const int* a, const int* b, const int* sa, const int* sb, float* d) {
   const int l = threadIdx.x;
   i32x8 fa, fb;
 #pragma unroll
   for (int e = 0; e < 8; ++e) { fa[e] = a[l * 8 + e]; fb[e] = b[l * 8 + e]; }
-  f32x16 acc;
+  const f32x4 acc = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(fa, fb, f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0, sa[l], 0, sb[l]);
 #pragma unroll
-  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
-  acc = __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(fa, fb, acc, 0, 0, 0, sa[l], 0, sb[l]);
-#pragma unroll
-  for (int e = 0; e < 16; ++e) d[l * 16 + e] = acc[e];
+  for (int e = 0; e < 4; ++e) d[l * 4 + e] = acc[e];
 }
 
 template <int EPI, int TM, int WAVES_M, int WAVES_N>
@@ -567,7 +564,7 @@ hipError_t launch(const MxGemmParams& p, hipStream_t st) {
   const long full = small / (2 * cus), rem = small % (2 * cus);
   const double us_big = ((big + cus - 1) / cus) * ((RES ? 21.0 : MX ? 9.7 : 5.3) + 1.25 * kt);
   const double us_small = 2.0 + (full + (rem == 0 ? 0.0 : rem <= cus ? 0.7 : 1.0)) * ((RES ? 6.3 : MX ? 3.9 : 0.8) + 0.93 * kt);
-  if (us_small < us_big) return launch_tile<EPI, 4, 2, 2>(p, cols, st);
+  if (p.tile == 2 || (p.tile == 0 && us_small < us_big)) return launch_tile<EPI, 4, 2, 2>(p, cols, st);
   return launch_tile<EPI, 8, 2, 4>(p, cols, st);
 }
 

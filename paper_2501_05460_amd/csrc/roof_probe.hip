@@ -6,12 +6,13 @@
 
 namespace {
 
-// Every wave keeps NACC independent 32 x 32 accumulators and NFRAG operand fragment pairs in registers and
-// issues v_mfma_f32_32x32x16_bf16 back to back: no LDS, no memory traffic inside the loop.  The fragment
+// Every wave keeps NACC independent accumulators and NFRAG operand fragment pairs in registers and issues
+// v_mfma_f32_32x32x16_bf16 or (WIDE = false) v_mfma_f32_16x16x32_bf16 back to back: no LDS, no memory traffic inside the loop.  The fragment
 // pairs rotate, so with random operands the operand buses toggle from one instruction to the next as they
 // do in a real product; with constant operands (all ones) they do not, and the chip clocks higher.
 constexpr int NACC = 8, NFRAG = 8;
 
+template <bool WIDE>
 __global__ __launch_bounds__(256, 2) void k_mfma_loop(const bf16_t* __restrict__ operands, int iters,
                                                       float* __restrict__ sink) {
   const int lane = threadIdx.x & 63;
@@ -27,23 +28,27 @@ __global__ __launch_bounds__(256, 2) void k_mfma_loop(const bf16_t* __restrict__
       for (int e = 0; e < 8; ++e) { a[f][e] = (bf16_t)1.0f; b[f][e] = (bf16_t)1.0f; }
     }
   }
-  f32x16 acc[NACC];
+  constexpr int NE = WIDE ? 16 : 4;
+  typedef float acc_t __attribute__((ext_vector_type(NE)));
+  acc_t acc[NACC];
 #pragma unroll
   for (int i = 0; i < NACC; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) acc[i][e] = 0.f;
+    for (int e = 0; e < NE; ++e) acc[i][e] = 0.f;
   for (int it = 0; it < iters; ++it) {
 #pragma unroll
     for (int f = 0; f < NFRAG; ++f)
 #pragma unroll
-      for (int i = 0; i < NACC; ++i)
-        acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[(f + i) % NFRAG], b[f], acc[i], 0, 0, 0);
+      for (int i = 0; i < NACC; ++i) {
+        if constexpr (WIDE) acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[(f + i) % NFRAG], b[f], acc[i], 0, 0, 0);
+        else acc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[(f + i) % NFRAG], b[f], acc[i], 0, 0, 0);
+      }
   }
   float s = 0.f;
 #pragma unroll
   for (int i = 0; i < NACC; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s += acc[i][e];
+    for (int e = 0; e < NE; ++e) s += acc[i][e];
   sink[(size_t)blockIdx.x * blockDim.x + threadIdx.x] = s;
 }
 
@@ -121,9 +126,9 @@ float time_launches(hipStream_t st, int reps, const F& launch) {
 
 extern "C" {
 
-epd_status epd_op_mfma_peak(const void* operands, int32_t iters, int32_t reps, float* sink, float* tflops,
+epd_status epd_op_mfma_peak(int32_t shape, const void* operands, int32_t iters, int32_t reps, float* sink, float* tflops,
                             void* hip_stream) {
-  if (!sink || !tflops || iters < 1 || reps < 1) return EPD_ERR_INVALID_ARG;
+  if (!sink || !tflops || iters < 1 || reps < 1 || (shape != 16 && shape != 32)) return EPD_ERR_INVALID_ARG;
   int dev = 0, cus = 0;
   if (hipGetDevice(&dev) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
@@ -131,10 +136,11 @@ epd_status epd_op_mfma_peak(const void* operands, int32_t iters, int32_t reps, f
   hipStream_t st = (hipStream_t)hip_stream;
   const int grid = cus * 2;   // two workgroups of four waves per CU: two waves per SIMD
   const float ms = time_launches(st, reps, [&] {
-    k_mfma_loop<<<dim3(grid), dim3(256), 0, st>>>((const bf16_t*)operands, iters, sink);
+    if (shape == 32) k_mfma_loop<true><<<dim3(grid), dim3(256), 0, st>>>((const bf16_t*)operands, iters, sink);
+    else k_mfma_loop<false><<<dim3(grid), dim3(256), 0, st>>>((const bf16_t*)operands, iters, sink);
   });
   if (ms <= 0.f || hipGetLastError() != hipSuccess) return EPD_ERR_HIP;
-  const double flops = (double)grid * 4 * iters * NFRAG * NACC * 2.0 * 32 * 32 * 16;
+  const double flops = (double)grid * 4 * iters * NFRAG * NACC * (shape == 32 ? 2.0 * 32 * 32 * 16 : 2.0 * 16 * 16 * 32);
   *tflops = (float)(flops / (ms * 1e-3) / 1e12);
   return EPD_OK;
 }

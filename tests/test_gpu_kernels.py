@@ -133,10 +133,11 @@ def test_attention_bf16_ignores_rows_past_n_keys(n_tok, n_keys, heads, hd, hd_pa
         assert rel_err(got[r], want) < 1.5e-2, s
 
 
+@pytest.mark.parametrize("paired", [False, True])
 @pytest.mark.parametrize("hd", [64, 72, 96, 128])
 @pytest.mark.parametrize("n_tok,n_keys", [(1024, 1024), (1088, 1025), (1024, 1000), (128, 33), (64, 32), (192, 129)])
-def test_attention_bf16_of_few_and_many_slices_agrees_bit_for_bit(n_tok, n_keys, hd):
-    """Up to 512 workgroups of 128 queries the kernel runs 16 queries per wave, above them 32: the same bits either way,
+def test_attention_bf16_of_few_and_many_slices_agrees_bit_for_bit(n_tok, n_keys, hd, paired):
+    """In either order of summation: up to 512 workgroups of 128 queries the kernel runs 16 queries per wave, above them 32: the same bits either way,
     with reference moves (logits of up to about 30) in both.  Padding rows hold large values and NaN."""
     g = torch.Generator().manual_seed(n_tok * 131 + n_keys + hd)
     heads = 8
@@ -152,12 +153,12 @@ def test_attention_bf16_of_few_and_many_slices_agrees_bit_for_bit(n_tok, n_keys,
     qk_d[:many * n_tok] = qk.reshape(-1, 2 * D).to("cuda", torch.bfloat16)
     vt_d = torch.zeros(many * D * n_tok + 64, dtype=torch.bfloat16, device="cuda")
     vt_d[:many * D * n_tok] = vt.reshape(-1).to("cuda", torch.bfloat16)
-    whole = B.op_attention_bf16(qk_d, qk_d[:, D:], vt_d, many, n_tok, heads, hd, 2 * D, n_keys=n_keys)
+    whole = B.op_attention_bf16(qk_d, qk_d[:, D:], vt_d, many, n_tok, heads, hd, 2 * D, n_keys=n_keys, paired=paired)
     whole = whole.view(many, n_tok, D)[:, :n_keys]
     assert torch.isfinite(whole.float()).all()
     for t in (0, many - 1):
         one = B.op_attention_bf16(qk_d[t * n_tok:], qk_d[t * n_tok:, D:], vt_d[t * D * n_tok:], 1, n_tok, heads, hd, 2 * D,
-                                  n_keys=n_keys)
+                                  n_keys=n_keys, paired=paired)
         assert torch.equal(one[:n_keys], whole[t])
     # and the values are the softmax's: bf16 weights and outputs, 2^-9 each on a handful of effective keys
     q, k = qk_d[:n_keys, :hd].double().cpu(), qk_d[:n_keys, D:D + hd].double().cpu()
@@ -304,7 +305,7 @@ def test_ring_tiles_agree_bit_for_bit(M, N, K, epi):
 ])
 def test_what_the_library_picks_leaves_the_bits_of_one_form(epi, M, N, K, form, cut):
     """The dispatch over weights padded as the library pads them (1152 columns to 1280, 3200 to 3328): every kind of choice is
-    reached, and leaves the bits of 256 x 128 tiles over unpadded weights."""
+    reached, and leaves the bits of 256 x 128 tiles and of 128 x 128 ring tiles, two different kernels, over unpadded weights."""
     taken, rows = B.op_gemm_bf16_choice(M, N, K, epi)
     assert (taken, rows < M) == (form, cut)
     rng = np.random.default_rng(M + N + K + epi)
@@ -312,13 +313,45 @@ def test_what_the_library_picks_leaves_the_bits_of_one_form(epi, M, N, K, form, 
     W = B.to_device(_bf16_grid(rng, (N, K), 0.05), True)
     bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32) * 0.1).cuda()
     r0 = torch.from_numpy(rng.standard_normal((M, N)).astype(np.float32)).cuda() if epi == 3 else None
-    got, want = (B.op_gemm_bf16_form(A, W, bias, epi, f, None if r0 is None else r0.clone()) for f in (0, 1))
+    got, *wanted = (B.op_gemm_bf16_form(A, W, bias, epi, f, None if r0 is None else r0.clone()) for f in (0, 1, 14))
     torch.cuda.synchronize()
     as_int = torch.int32 if epi == 3 else torch.int16
-    assert torch.equal(got.view(as_int), want.view(as_int))
+    for want in wanted:
+        assert torch.equal(got.view(as_int), want.view(as_int))
 
 
-@pytest.mark.parametrize("M,N,K", [(256, 384, 128), (1000, 1152, 256), (2900, 1152, 1152), (77, 384, 384), (10240, 1152, 128)])
+@pytest.mark.parametrize("K", [128, 256, 640])
+@pytest.mark.parametrize("epi,M,N,forms", [
+    (0, 16536, 1024, (9, 1)), (1, 16536, 1024, (9, 1)), (2, 16536, 1024, (9, 1)),   # 260 tiles of 256 x 256, 520 of 256 x 128
+    (3, 16537, 1024, (10, 1)), (4, 16536, 1024, (9, 1)), (5, 16536, 1024, (9, 1)),
+    (3, 11100, 2304, (12, 10, 1)),                                                  # 528 of 256 x 192, 396 of 256 x 256
+    (4, 1240, 1152, (1, 13)), (5, 1240, 1152, (1, 13)), (4, 8200, 1152, (0, 1)), (5, 8200, 1152, (0, 1))])
+def test_persistent_tiles_beyond_the_first_agree_bit_for_bit(epi, M, N, forms, K):
+    """More tiles than CUs, so that workgroups go on to a second tile, whose first slabs and stream rows are fetched under the last
+    products of the one before; two slabs (K = 128: all of a tile's are its last) and more, a ragged last tile row, every
+    epilogue.  Reference: one workgroup per tile on the 32-wide instruction (form 6), ring tiles where a width is no multiple
+    of 256; the patch embedding and the value projection against fp64 too."""
+    n_tok = {16536: 312, 1240: 248, 8200: 200}.get(M, 0)
+    g = torch.Generator().manual_seed(M + N + K + epi)
+    A, W = torch.randn(M, K, generator=g).mul_(0.5).bfloat16().cuda(), torch.randn(N, K, generator=g).mul_(0.05).bfloat16().cuda()
+    bias = torch.randn(N, generator=g).mul_(0.1).cuda()
+    r0 = torch.randn(M, N, generator=g).cuda() if epi == 3 else None
+    pos = torch.randn(n_tok, N, generator=g).cuda() if epi == 4 else None
+    run = lambda form: B.op_gemm_bf16_form(A, W, bias, epi, form, None if r0 is None else r0.clone(), pos=pos, n_tok=n_tok)
+    ref = run(6 if N % 256 == 0 else 14)
+    for form in forms:
+        assert torch.equal(run(form), ref), form
+    if epi in (4, 5):
+        want = A.double().cpu() @ W.double().cpu().T + bias.double().cpu()
+        if epi == 4:
+            want, got = want + pos.double().cpu().repeat(M // n_tok, 1), ref
+        else:
+            got = ref.permute(0, 2, 1).reshape(M, N)
+        # fp32 sums of K products; the transposed values leave in bf16 (2^-9)
+        assert float((got.double().cpu() - want).norm() / want.norm()) < (1e-5 if epi == 4 else 4e-3)
+
+
+@pytest.mark.parametrize("M,N,K", [(256, 384, 128), (1000, 1152, 256), (2900, 1152, 1152), (77, 384, 384), (11100, 1152, 128)])
 def test_gemm_192_wide_tiles_agree_bit_for_bit(M, N, K):
     """The residual product on 256 x 192 tiles (widths that are whole multiples of 192 and not of 256) leaves the
     bits of the other tile shapes: whole and ragged M, one tile and several per workgroup, and a launch with more
@@ -348,8 +381,9 @@ def test_measurement_probes_run_and_report_sane_figures():
     nominal bf16 peak and above a fifth of it, the streaming copy below the nominal HBM rate, and a SIMD that runs a
     wave of MFMAs and a wave of exp + fma pairs together takes longer than either alone and less than both in turn
     (the partial overlap the attention kernel's floor is derived from)."""
-    t = B.op_mfma_peak(True, iters=500, reps=2)
-    assert 500.0 < t < 2600.0, t
+    for shape in (32, 16):
+        t = B.op_mfma_peak(True, iters=500, reps=2, shape=shape)
+        assert 500.0 < t < 2600.0, (shape, t)
     g = B.op_copy_peak(1 << 28, reps=2)
     assert 1000.0 < g < 8000.0, g
     m, v, both = B.op_coissue(1, 1000, 1250, 2), B.op_coissue(2, 1000, 1250, 2), B.op_coissue(3, 1000, 1250, 2)

@@ -53,32 +53,30 @@ def random_codes(rng, shape):
 
 
 def test_scaled_fp8_mfma_operand_and_result_layout():
-    """Lane l supplies row l % 32 of its operand: k = 16 (l / 32) .. + 15 in registers 0-3 and k = 32 + 16 (l / 32)
-    .. + 15 in registers 4-7 (bytes in k order); the scale register of lanes 0-31 holds the scale byte of the row's
-    block k 0..31, that of lanes 32-63 of block k 32..63; result register i of lane l is
-    D[8 (i / 4) + 4 (l / 32) + i % 4][l % 32] with D = A B^T, A the first operand."""
+    """The instruction the products run on, v_mfma_scale_f32_16x16x128_f8f6f4.  Lane l supplies row l % 16 of its operand:
+    k = 16 (l / 16) .. + 15 in registers 0-3 and k = 64 + 16 (l / 16) .. + 15 in registers 4-7 (bytes in k order); its scale
+    register holds the scale byte of the row's block k = 32 (l / 16) .. + 31; result register e of lane l is
+    D[4 (l / 16) + e][l % 16] with D = A B^T, A the first operand."""
     rng = np.random.default_rng(101)
-    ca, cb = random_codes(rng, (32, 64)), random_codes(rng, (32, 64))
-    ea = rng.integers(120, 131, size=(32, 2)).astype(np.uint8)   # scale bytes near 127 (factor 1)
-    eb = rng.integers(120, 131, size=(32, 2)).astype(np.uint8)
+    ca, cb = random_codes(rng, (16, 128)), random_codes(rng, (16, 128))
+    ea = rng.integers(120, 131, size=(16, 4)).astype(np.uint8)   # scale bytes near 127 (factor 1)
+    eb = rng.integers(120, 131, size=(16, 4)).astype(np.uint8)
     a_regs = np.zeros((64, 32), np.uint8); b_regs = np.zeros((64, 32), np.uint8)
     sa = np.zeros(64, np.int32); sb = np.zeros(64, np.int32)
     for l in range(64):
-        k0 = 16 * (l // 32)
-        a_regs[l] = np.concatenate([ca[l % 32, k0:k0 + 16], ca[l % 32, 32 + k0:48 + k0]])
-        b_regs[l] = np.concatenate([cb[l % 32, k0:k0 + 16], cb[l % 32, 32 + k0:48 + k0]])
-        sa[l] = int(ea[l % 32, l // 32]) | (0x7F << 8)           # other bytes must not matter
-        sb[l] = int(eb[l % 32, l // 32]) | (0x11 << 16)
+        r, k0 = l % 16, 16 * (l // 16)
+        a_regs[l] = np.concatenate([ca[r, k0:k0 + 16], ca[r, 64 + k0:80 + k0]])
+        b_regs[l] = np.concatenate([cb[r, k0:k0 + 16], cb[r, 64 + k0:80 + k0]])
+        sa[l] = int(ea[r, l // 16]) | (0x7F << 8)                # other bytes must not matter
+        sb[l] = int(eb[r, l // 16]) | (0x11 << 16)
     d = B.op_mx_mfma_probe(dev(a_regs.view(np.int32)), dev(b_regs.view(np.int32)), dev(sa), dev(sb)).cpu().numpy()
-    A = O.mx_dequantize(ca, ea)
-    Bm = O.mx_dequantize(cb, eb)
-    want = A @ Bm.T
-    got = np.zeros((32, 32))
+    want = O.mx_dequantize(ca, ea) @ O.mx_dequantize(cb, eb).T
+    got = np.zeros((16, 16))
     for l in range(64):
-        for i in range(16):
-            got[8 * (i // 4) + 4 * (l // 32) + i % 4, l % 32] = d[l, i]
-    # the instruction adds its 64 products of wildly different magnitudes (random codes, random scales) with an
-    # internal alignment coarser than fp32's: 2e-5 of the largest result was measured, a misplaced operand gives O(1)
+        for e in range(4):
+            got[4 * (l // 16) + e, l % 16] = d[l, e]
+    # the instruction adds its 128 products of wildly different magnitudes (random codes, random scales) with an
+    # internal alignment coarser than fp32's: a few 1e-5 of the largest result, a misplaced operand gives O(1)
     e = np.abs(got - want).max() / np.abs(want).max()
     print(f"probe: max |d - want| / max |want| = {e:.2e}")
     assert e <= 1e-4
@@ -257,6 +255,7 @@ MX_VARIANTS = {
     "layer_scale": dict(layer_scale=1),
     "class_token_hd128": dict(class_token=1, hidden=384, heads=3, mlp=512),
     "grid7": dict(tile_size=98),
+    "hd72": dict(hidden=1152, heads=16, layers=2),   # attention output converted by a launch of its own
 }
 
 
@@ -438,36 +437,36 @@ def test_attention_output_converted_in_the_kernel(n_tok, n_keys, heads, hd):
     assert same.mean() > 0.9
 
 
-@pytest.mark.parametrize("epi", [0, 1, 3, 5])
-@pytest.mark.parametrize("K", [128, 384, 1024])
+@pytest.mark.parametrize("epi", [0, 1, 2, 3, 5])
+@pytest.mark.parametrize("K", [128, 384, 1024, 1152])
 def test_product_tiles_agree_bit_for_bit(epi, K):
-    """The first rows of a product of many rows (256 x 256 tiles, several of a workgroup, where the estimate takes them)
-    and the product of those rows alone (128 x 128 tiles): the same bits; K of one, three and eight slabs, so that slab
-    buffers change over at tiles of odd depth; and both against fp64 on the codes."""
+    """256 x 256 tiles (104 x 4 of them, more than one for most workgroups) and 128 x 128 tiles (1664 on 512 slots) leave the
+    same bits, and so does the product of the first rows alone; the last rows of a tile are no rows of the operand.  K of one,
+    three, eight and nine slabs: the slab buffers change over at tiles of odd and of even depth.  The values: fp64 on the codes."""
     g = torch.Generator().manual_seed(1000 * epi + K)
-    N, few, many, n_tok, heads, hd = 1024, 512, 26624, 512, 16, 64
+    N, few, rows, padded, n_tok, heads, hd = 1024, 624, 26520, 26624, 312, 16, 64
     code = lambda r: (torch.randint(0x28, 0x40, (r, K), generator=g) | torch.randint(0, 2, (r, K), generator=g) << 7).to(torch.uint8).cuda()
     scale = lambda r: torch.from_numpy(pack_scale_words(torch.randint(122, 127, (r, K // 32), generator=g).numpy())).cuda()
-    A, W, SA, SW = code(many), code(N), scale(many), scale(N)
+    A, W, SA, SW = code(padded), code(N), scale(padded), scale(N)
     bias, cs = torch.randn(N, generator=g).cuda(), torch.rand(N, generator=g).cuda() + 0.5
-    R = torch.randn(many, N, generator=g).cuda() if epi == 3 else None
+    R = torch.randn(rows, N, generator=g).cuda() if epi == 3 else None
 
-    def product(rows):
-        r = R[:rows].clone() if R is not None else None
-        return B.op_mx_gemm(epi, A[:rows].contiguous(), SA[:, :rows].contiguous(), W, SW, bias, cs, r,
-                            n_tok if epi == 5 else 0, heads if epi == 5 else 0, hd if epi == 5 else 0)
+    def product(n, tile):
+        r = R[:n].clone() if R is not None else None
+        whole = (n + 255) // 256 * 256
+        return B.op_mx_gemm(epi, A[:whole].contiguous(), SA[:, :whole].contiguous(), W, SW, bias, cs, r,
+                            n_tok if epi == 5 else 0, heads if epi == 5 else 0, hd if epi == 5 else 0, tile=tile, rows=n)
 
-    whole, part = product(many), product(few)
-    if epi == 1:
-        assert torch.equal(whole[0][:few], part[0]) and torch.equal(whole[1][:, :few], part[1])
+    large, small, chosen = product(rows, 1), product(rows, 2), product(few, 0)
+    if epi in (1, 2):
+        assert torch.equal(large[0], small[0]) and torch.equal(large[1][:, :rows], small[1][:, :rows])
+        assert torch.equal(large[0][:few], chosen[0]) and torch.equal(large[1][:, :few], chosen[1][:, :few])
         return   # the values: test_product_with_activation_and_converted_output
-    assert torch.equal(whole[:part.shape[0]], part)
+    assert torch.equal(large, small) and torch.equal(large[:chosen.shape[0]], chosen)
     value = lambda c, s: torch.from_numpy(O.mx_dequantize(c.cpu().numpy(), unpack_scale_words(s.cpu().numpy())))
-    last = slice(many - few, many)
+    last = slice(rows - n_tok, rows)
     want = value(A[last], SA[:, last]) @ value(W, SW).T * cs.double().cpu() + bias.double().cpu()
-    got = whole[-1:] if epi == 5 else whole[last]
-    if epi == 5:
-        got = got.permute(0, 3, 1, 2).reshape(n_tok, N)
+    got = large[-1:].permute(0, 3, 1, 2).reshape(n_tok, N) if epi == 5 else large[last]
     if epi == 3:
         got = got - R[last]
     # bf16 output 2^-9; fp32 the bound of the products on given codes
