@@ -4,35 +4,36 @@ import pytest
 from paper_2501_05460_amd import binding as B
 
 # (epilogue, rows, columns, K, rows per slice, us by form: number of the form hook, or "cut" for whole rounds of 256 x 256
-# tiles and the rest on ring tiles, or "columns" for the cut by columns).  In the running encoder on MI355X, each form forced for this product alone.
+# tiles and the rest on ring tiles, or "columns" for the cut by columns).  In the running encoder on MI355X, each form forced for
+# this product alone (of 385 products so measured, the one taken is within 3 % of the fastest for 88 %, 5 % for 93 %, 9 % for 99 %).
 MEASURED = [
-    (3, 1024, 1152, 4352, 1024, {11: 30, 13: 34, 14: 46, 1: 74, 12: 101, 10: 112}),
-    (3, 5120, 1152, 4352, 1024, {11: 93, 13: 79, 14: 93, 1: 87, 12: 108, 10: 119}),
-    (3, 6144, 1152, 4352, 1024, {11: 109, 13: 97, 14: 95, 1: 89, 12: 111, 10: 122}),
-    (3, 5888, 1152, 1152, 736, {11: 36, 13: 33, 14: 33, 1: 39, 12: 40, 10: 46}),
-    (3, 16928, 1152, 4352, 736, {11: 303, 13: 255, 14: 238, 1: 258, 12: 224, 10: 247, 'cut': 213}),
-    (5, 16928, 1152, 1152, 736, {11: 74, 13: 63, 14: 64, 1: 71, 9: 68}),
-    (3, 65536, 1152, 4352, 1024, {11: 1287, 13: 1056, 14: 871, 1: 888, 12: 683, 10: 649}),
-    (3, 26624, 1152, 4352, 1024, {13: 435, 14: 377, 1: 426, 12: 335, 10: 334, 'columns': 314, 'cut': 287}),
-    (3, 47104, 1152, 1152, 736, {13: 225, 10: 177}),
-    (0, 10240, 2304, 1152, 1024, {11: 88, 13: 75, 14: 75, 1: 72, 9: 66, 'cut': 66}),
-    (3, 8960, 1152, 4352, 448, {11: 160, 13: 132, 14: 133, 1: 166, 12: 116, 10: 127}),
-    (3, 1024, 1024, 4096, 1024, {11: 23, 13: 33, 14: 41, 1: 69, 10: 103}),
-    (1, 2048, 4096, 1024, 1024, {11: 33, 13: 29, 14: 30, 1: 27, 9: 36}),
-    (3, 3072, 1024, 1024, 1024, {11: 19, 13: 18, 14: 18, 1: 32, 10: 39}),
-    (1, 13312, 4096, 1024, 1024, {11: 177, 13: 144, 14: 156, 1: 158, 9: 128, 'cut': 120}),
-    (0, 13312, 2048, 1024, 1024, {11: 90, 13: 74, 14: 77, 1: 83, 9: 64, 'cut': 70}),
-    (3, 53248, 1024, 4096, 1024, {11: 796, 13: 636, 14: 537, 1: 569, 10: 473, 'cut': 416}),
-    (3, 8256, 1024, 4096, 1032, {11: 138, 13: 120, 14: 118, 1: 145, 10: 115}),
-    (5, 16512, 1024, 1024, 1032, {11: 61, 13: 52, 14: 59, 1: 64, 9: 61}),
-    (0, 1024, 6400, 3200, 1024, {11: 76, 13: 69, 14: 68, 1: 55, 9: 83}),
-    (5, 12288, 3200, 3200, 1024, {11: 374, 13: 296, 14: 258, 1: 282, 9: 232, 'cut': 243}),
-    (3, 2304, 3200, 12800, 576, {11: 334, 13: 267, 14: 234, 1: 224, 10: 328}),
-    (1, 8192, 5120, 12800, 1024, {11: 1832, 13: 1455, 14: 1211, 1: 1147, 9: 990, 'cut': 960}),
-    (0, 8192, 5120, 5120, 1024, {11: 670, 13: 512, 14: 411, 1: 454, 9: 361, 'cut': 387}),
-    (3, 1584, 1024, 1024, 264, {11: 12.1, 13: 14.1, 14: 16.7, 1: 30, 10: 38}),
-    (3, 1536, 1152, 4352, 256, {11: 32.7, 13: 37.1, 14: 46.5, 1: 78, 12: 106, 10: 119}),
-    (1, 864, 5120, 12800, 576, {11: 220, 13: 208, 14: 198, 1: 205, 9: 318}),
+    (3, 1024, 1152, 4352, 1024, {11: 30, 13: 35, 14: 46, 1: 77, 12: 93, 10: 105, 'columns': 46}),
+    (3, 5120, 1152, 4352, 1024, {11: 92, 13: 78, 14: 91, 1: 93, 12: 103, 10: 111, 'columns': 107}),
+    (3, 6144, 1152, 4352, 1024, {11: 106, 13: 96, 14: 93, 1: 97, 12: 106, 10: 116, 'columns': 111}),
+    (3, 5888, 1152, 1152, 736, {11: 35, 13: 34, 14: 33, 1: 34, 12: 39, 10: 44, 'columns': 37}),
+    (3, 16928, 1152, 4352, 736, {11: 298, 13: 252, 14: 234, 1: 268, 12: 213, 10: 232, 'cut': 206, 'columns': 208}),
+    (5, 16928, 1152, 1152, 736, {11: 72, 13: 61, 14: 57, 1: 64, 9: 59}),
+    (3, 65536, 1152, 4352, 1024, {13: 1051, 14: 868, 1: 860, 12: 655, 10: 607, 'columns': 631}),
+    (3, 26624, 1152, 4352, 1024, {11: 522, 13: 431, 14: 375, 1: 389, 12: 323, 10: 312, 'cut': 272, 'columns': 298}),
+    (3, 47104, 1152, 1152, 736, {13: 228, 14: 223, 1: 198, 12: 179, 10: 178, 'cut': 183, 'columns': 183}),
+    (0, 10240, 2304, 1152, 1024, {11: 85, 13: 73, 14: 66, 1: 59, 9: 62, 'cut': 63}),
+    (3, 8960, 1152, 4352, 448, {11: 160, 13: 134, 14: 136, 1: 159, 12: 110, 10: 119, 'columns': 151}),
+    (3, 1024, 1024, 4096, 1024, {11: 23.9, 13: 34, 14: 40, 1: 71, 10: 97}),
+    (1, 2048, 4096, 1024, 1024, {11: 31, 13: 27.7, 14: 28.2, 1: 25.7, 9: 33}),
+    (3, 3072, 1024, 1024, 1024, {11: 18.7, 13: 18.0, 14: 18.6, 1: 27.1, 10: 38}),
+    (1, 13312, 4096, 1024, 1024, {13: 134, 14: 140, 1: 123, 9: 113, 'cut': 112}),
+    (0, 13312, 2048, 1024, 1024, {11: 86, 13: 70, 14: 68, 1: 66, 9: 56, 'cut': 64}),
+    (3, 53248, 1024, 4096, 1024, {13: 632, 14: 532, 1: 590, 10: 450, 'cut': 397}),
+    (3, 8256, 1024, 4096, 1032, {11: 138, 13: 120, 14: 110, 1: 140, 10: 110}),
+    (5, 16512, 1024, 1024, 1032, {11: 60, 13: 51, 14: 53, 1: 58, 9: 58}),
+    (0, 1024, 6400, 3200, 1024, {11: 74, 13: 66, 14: 67, 1: 57, 9: 76}),
+    (5, 12288, 3200, 3200, 1024, {11: 367, 13: 288, 14: 247, 1: 256, 9: 212, 'cut': 221}),
+    (3, 2304, 3200, 12800, 576, {11: 332, 13: 263, 14: 232, 1: 248, 10: 305, 'columns': 301}),
+    (1, 8192, 5120, 12800, 1024, {11: 1830, 13: 1435, 14: 1192, 1: 1275, 9: 934, 'cut': 917}),
+    (0, 8192, 5120, 5120, 1024, {11: 665, 13: 510, 14: 404, 1: 389, 9: 338, 'cut': 363}),
+    (3, 1584, 1024, 1024, 264, {11: 12.8, 13: 14.5, 14: 17.0, 1: 25.8, 10: 36}),
+    (3, 1536, 1152, 4352, 256, {11: 33, 13: 36, 14: 47, 1: 77, 12: 92, 10: 106, 'columns': 53}),
+    (1, 864, 5120, 12800, 576, {11: 211, 13: 200, 14: 192, 1: 206, 9: 289}),
 ]
 
 
