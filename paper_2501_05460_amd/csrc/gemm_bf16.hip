@@ -744,14 +744,13 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
   float* sCol = sBias + BN;   // column sums of the weights, mean and rstd of the tile's rows (folded pre-norm)
   float* sMu = sCol + BN;
   float* sRs = sMu + BM;
-  constexpr bool fold = true;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int wm = wave / WAVES_N, wn = wave % WAVES_N;
   const int l32 = lane & 31, lh = lane >> 5;
   const int KT_ = p.K / BK;  // even
   const int gn = p.Npad / BN;
-  // Per-tile scalars of the epilogue: bias and, with a folded pre-norm, the column sums of the weights and
+  // Per-tile scalars of the epilogue: bias, the column sums of the weights and
   // mean / rstd of the tile's rows.  The statistics pairs of the NEXT tile's rows are loaded into registers at
   // the start of a tile's epilogue (one thread per row, one batch of independent loads whose latency passes
   // under the epilogue) and combined at its end, when nobody reads the current tile's scalars any more.
@@ -761,17 +760,14 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
   auto pairs_of = [&](int t, int mrow0) {
     return p.stats + (long)(mrow0 + t < p.M ? mrow0 + t : p.M - 1) * p.n_part * 2;   // rows past M: any valid row, never stored
   };
-  auto stats_load = [&](int t, RowPairs& rp, int mrow0) { if (fold && t < BM) rp.load(pairs_of(t, mrow0), p.n_part); };
+  auto stats_load = [&](int t, RowPairs& rp, int mrow0) { if (t < BM) rp.load(pairs_of(t, mrow0), p.n_part); };
   auto tile_scalars = [&](int t, const RowPairs& rp, int mrow0, int ncol0) {
-    if (t < BN) sBias[t] = p.bias[ncol0 + t];
-    if (fold) {
-      if (t < BN) sCol[t] = p.colsum[ncol0 + t];
-      if (t < BM) {
-        float mu, rs;
-        rp.finish(p.n_part, p.stat_group, p.norm_dim, p.norm_rms, p.norm_eps, mu, rs);
-        sMu[t] = mu;
-        sRs[t] = rs;
-      }
+    if (t < BN) { sBias[t] = p.bias[ncol0 + t]; sCol[t] = p.colsum[ncol0 + t]; }
+    if (t < BM) {
+      float mu, rs;
+      rp.finish(p.n_part, p.stat_group, p.norm_dim, p.norm_rms, p.norm_eps, mu, rs);
+      sMu[t] = mu;
+      sRs[t] = rs;
     }
   };
 
@@ -936,7 +932,7 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
     for (int pass = 0; pass < 2; ++pass) {
       if (pass > 0) {
         __syncthreads();       // pass 0 has been read out
-        if constexpr (fold) stats_load(tid, rp, m0n);   // half of the accumulators are gone: room for the next tile's pairs (no next tile: m0n = m0, harmless re-read)
+        stats_load(tid, rp, m0n);   // half of the accumulators are gone: room for the next tile's pairs (no next tile: m0n = m0, harmless re-read)
       }
 #pragma unroll
       for (int i = 0; i < TM; ++i)
@@ -947,32 +943,21 @@ __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p
           const int rg = tok_major ? (wn * WN + j * 32 + l32) : (wm * WM + i * 32 + l32);
           const int r = (rg / (2 * G)) * G + rg % G;
           float bl = 0.f, cs = 0.f, mu = 0.f, rs = 1.f;
-          if (tok_major) { bl = sBias[rg]; if (fold) cs = sCol[rg]; }
-          else if (fold) { mu = sMu[rg]; rs = sRs[rg]; }
+          if (tok_major) { bl = sBias[rg]; cs = sCol[rg]; }
+          else { mu = sMu[rg]; rs = sRs[rg]; }
           unsigned char* srow = stage_row(r);
 #pragma unroll
           for (int gi = 0; gi < 4; ++gi) {
             const int cl = (tok_major ? (wm * WM + i * 32) : (wn * WN + j * 32)) + gi * 8 + lh * 4;
             float v[4];
             if (tok_major) {
-              if (fold) {
-                const f32x4 m4 = *reinterpret_cast<const f32x4*>(sMu + cl), r4 = *reinterpret_cast<const f32x4*>(sRs + cl);
+              const f32x4 m4 = *reinterpret_cast<const f32x4*>(sMu + cl), r4 = *reinterpret_cast<const f32x4*>(sRs + cl);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(r4[e], __builtin_fmaf(-m4[e], cs, acc[i][j][gi * 4 + e]), bl);
-              } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[i][j][gi * 4 + e] + bl;
-              }
+              for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(r4[e], __builtin_fmaf(-m4[e], cs, acc[i][j][gi * 4 + e]), bl);
             } else {
-              const f32x4 b4 = *reinterpret_cast<const f32x4*>(sBias + cl);
-              if (fold) {
-                const f32x4 c4 = *reinterpret_cast<const f32x4*>(sCol + cl);
+              const f32x4 b4 = *reinterpret_cast<const f32x4*>(sBias + cl), c4 = *reinterpret_cast<const f32x4*>(sCol + cl);
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(rs, __builtin_fmaf(-mu, c4[e], acc[i][j][gi * 4 + e]), b4[e]);
-              } else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = acc[i][j][gi * 4 + e] + b4[e];
-              }
+              for (int e = 0; e < 4; ++e) v[e] = __builtin_fmaf(rs, __builtin_fmaf(-mu, c4[e], acc[i][j][gi * 4 + e]), b4[e]);
             }
             bf16x4 o;
 #pragma unroll
