@@ -34,7 +34,7 @@ epd_status epd_op_gemm_bf16(const void* A, const void* W, const float* bias, voi
  * other: epi 0 bias, 1 bias + GELU(erf), 2 bias + GELU(tanh) -> C [M,N] bf16; epi 3 -> R [M,N]
  * fp32 += A W^T + bias (C unused); epi 4 -> R [M,N] = A W^T + bias + pos[row % n_tok] (pos [n_tok,N] fp32); epi 5 -> C bf16
  * transposed per slice of n_tok rows, [M / n_tok, N, n_tok] (n_tok % 8 == 0, M % n_tok == 0).  form 0 = what the library would pick (W and bias padded as it pads its weights), 1 = 256x128 tile,
- * 2, 3 (K % 256 == 0) and 14 = 128x128 tile, both operand slabs in an LDS ring (one kernel: 2 and 3 differ in epd_op_norm_gemm_bf16 and
+ * persistent, 4 = the same tile, one per workgroup (not epi 4), 2, 3 (K % 256 == 0) and 14 = 128x128 tile, both operand slabs in an LDS ring (one kernel: 2 and 3 differ in epd_op_norm_gemm_bf16 and
  * epd_op_gemm_residual_stats only), 13 = 128x64 tile of the same kernel, 6 = 256x256 tile with the plain loop, 7 = pipelined loop, 8 = pipelined loop with both operand slabs
  * loaded straight into LDS, 9 = persistent kernel on 256x256 tiles (not epi 3), 10 = persistent kernel of the residual product (epi 3 only),
  * 11 = 64x64 tile of the ring kernel (11, 13, 14: what the library picks from for launches of a few slices).

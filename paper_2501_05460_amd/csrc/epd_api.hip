@@ -1359,7 +1359,7 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
   if (!A || !W || !bias || (residual || embed ? !R : !C) || (embed && (!pos || n_tok <= 0)) ||
       (values && (n_tok <= 0 || n_tok % 8 || M % n_tok)) || M <= 0 || N <= 0 || K <= 0 || N % 128 || K % 128 ||
       !(epi == EPI_BIAS || epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH || residual || embed || values) ||
-      !(form == 0 || form == 1 || form == 2 || form == 3 || (form >= 6 && form <= 14)) ||
+      !((form >= 0 && form <= 4) || (form >= 6 && form <= 14)) || (form == 4 && embed) ||
       (form == 3 && K % 256) || (form >= 6 && form <= 10 && N % 256) || (form == 9 && residual) || (form == 10 && !residual) ||
       (form == 12 && (!residual || N % 192))) {
     set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_form: bad argument");

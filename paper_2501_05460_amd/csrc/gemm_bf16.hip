@@ -694,6 +694,17 @@ __global__ __launch_bounds__(NTHREADS, BM_ == 128 && PIPE == 0 ? 2 : 1) void k_g
       }
     }
   __syncthreads();
+  if constexpr (BN == 128 && BM_ == BM && FOLD == 0 && (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH)) {
+    if (p.c_cached) {   // a loop of its own: the choice inside the loop below costs a launch without it 3 % (FC1 of 2048 rows, 26.3 us)
+#pragma unroll
+      for (int i = 0; i < PER_T; ++i) {
+        const int q = tid + NTHREADS * i, r = q / NCH, c = q % NCH, row = m0 + r, col = n0 + c * 8;
+        if (row < p.M && col < p.N)
+          *reinterpret_cast<u32x4*>(p.C + (long)row * p.ldc + col) = *reinterpret_cast<const u32x4*>(stage + r * ROWB + ((c ^ (r & 15)) << 4));
+      }
+      return;
+    }
+  }
 #pragma unroll
   for (int i = 0; i < PER_T; ++i) {
     const int q = tid + NTHREADS * i;
@@ -1235,15 +1246,13 @@ hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     return p.stats_out ? launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_, 2>(p, st)
                        : launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_, 1>(p, st);
   }
-  if constexpr (BN == 256) {   // (256 x 128 tiles of plain products: gemm_bf16_wide.hip)
-    switch (p.epi) {
-      case EPI_BIAS: return launch<BN, NT, WN, EPI_BIAS, PIPE, BM_>(p, st);
-      case EPI_BIAS_GELU_ERF: return launch<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>(p, st);
-      case EPI_BIAS_GELU_TANH: return launch<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>(p, st);
-      case EPI_BIAS_RESIDUAL: return launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>(p, st);
-      case EPI_BIAS_POS: return launch<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>(p, st);
-      case EPI_VT: return launch<BN, NT, WN, EPI_VT, PIPE, BM_>(p, st);
-    }
+  switch (p.epi) {
+    case EPI_BIAS: return launch<BN, NT, WN, EPI_BIAS, PIPE, BM_>(p, st);
+    case EPI_BIAS_GELU_ERF: return launch<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>(p, st);
+    case EPI_BIAS_GELU_TANH: return launch<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>(p, st);
+    case EPI_BIAS_RESIDUAL: return launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>(p, st);
+    case EPI_VT: return launch<BN, NT, WN, EPI_VT, PIPE, BM_>(p, st);
+    case EPI_BIAS_POS: if constexpr (BN == 256) return launch<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>(p, st);
   }
   return hipErrorInvalidValue;
 }
@@ -1274,14 +1283,13 @@ hipError_t set_attr() {
 template <int BN, int NT, int WN, int PIPE = 0, int BM_ = BM>
 hipError_t set_attr_all() {
   hipError_t e;
-  if constexpr (BN == 256) {
-    if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_>()) != hipSuccess) return e;
-    if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>()) != hipSuccess) return e;
-    if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>()) != hipSuccess) return e;
-    if ((e = set_attr<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>()) != hipSuccess) return e;
+  if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_>()) != hipSuccess) return e;
+  if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>()) != hipSuccess) return e;
+  if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>()) != hipSuccess) return e;
+  if ((e = set_attr<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>()) != hipSuccess) return e;
+  if ((e = set_attr<BN, NT, WN, EPI_VT, PIPE, BM_>()) != hipSuccess) return e;
+  if constexpr (BN == 256)
     if ((e = set_attr<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>()) != hipSuccess) return e;
-    if ((e = set_attr<BN, NT, WN, EPI_VT, PIPE, BM_>()) != hipSuccess) return e;
-  }
   if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_, 2>()) != hipSuccess) return e;
   if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_, 2>()) != hipSuccess) return e;
   if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_, 2>()) != hipSuccess) return e;
@@ -1362,6 +1370,17 @@ static Plain choose_plain(const GemmParams& p) {
   return best;
 }
 
+// 256 x 128 tiles have two kernels with the same bits.  The persistent one (gemm_bf16_wide.hip) has the shorter start and
+// epilogue, the one-tile one (operands two slabs ahead in registers) the shorter slab while a CU holds one workgroup, and the depths
+// where they meet lie between the measured ones.  One round in the running encoder, us, one-tile | persistent: residual,
+// 1024 columns, K = 1024, 8192 rows 39.3 | 33.4, 3200 by 3200, 2304 rows 69.7 | 64.5, 1024 by 4096, 7168 rows 85.9 | 90.2, 1152 by 4352,
+// 6144 rows 90.9 | 97.1, 3200 by 12800, 2304 rows 223 | 250; q/k, 2048 by 1024, 4096 rows 26.3 | 25.4, 6400 by 3200, 1024
+// rows 54.4 | 56.7; projector, 2048 rows, 3584 by 3584 63.2 | 72.5, 4096 by 4096 74.3 | 84.1; GELU, 4096 by 1024, 2048 rows 27.0 | 25.4,
+// 5120 by 12800, 1536 rows 211 | 217.  More rounds of 128 columns: the 6B shape's FC2, 40960 rows, cut by columns 2742 | 2772.
+static bool one_tile_128(const GemmParams& p) {
+  return p.epi != EPI_BIAS_POS && p.K >= (p.epi == EPI_BIAS_RESIDUAL ? 3584 : 2048);
+}
+
 static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
   const bool residual = p.epi == EPI_BIAS_RESIDUAL;
   const Plain c = choose_plain(p);
@@ -1372,7 +1391,7 @@ static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
   };
   switch (c.form) {
     case PLAIN_RING: return launch_ring(p, c.tile, st);
-    case PLAIN_256x128: return launch_wide(p, WIDE_128, st);
+    case PLAIN_256x128: return one_tile_128(p) ? dispatch<128, 512, 64>(without_padded_columns(p), st) : launch_wide(p, WIDE_128, st);
     case PLAIN_192: return launch_wide(p, WIDE_192, st);
     case PLAIN_256: {
       if (c.rows_a == 0) return wide(p);
@@ -1421,7 +1440,7 @@ int bf16_gemm_choice(const GemmParams& p, long* rows) {
   *rows = c.form == PLAIN_256 && c.rows_a > 0 ? c.rows_a * BM : p.M;
   switch (c.form) {
     case PLAIN_RING: return c.tile == RING_64x64 ? 11 : c.tile == RING_128x64 ? 13 : 14;
-    case PLAIN_256x128: return 1;
+    case PLAIN_256x128: return one_tile_128(p) ? 4 : 1;
     case PLAIN_192: return 12;
     case PLAIN_256: return p.epi == EPI_BIAS_RESIDUAL ? 10 : 9;
     case PLAIN_COLUMNS: return 0;
@@ -1444,6 +1463,7 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
     case 1: return ring_has(p) ? launch_wide(p, WIDE_128, st) : dispatch<128, 512, 64>(p, st);
     case 2: return ring_has(p) ? launch_ring(p, RING_128x128, st) : dispatch_128_fold<0>(p, st);
     case 3: if (!ring_has(p)) { if (p.K % 256 == 0) return dispatch_128_fold<2>(p, st); break; } return launch_ring(p, RING_128x128, st);
+    case 4: if (ring_has(p) && p.epi != EPI_BIAS_POS) return dispatch<128, 512, 64>(without_padded_columns(p), st); break;
     case 6: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 0>(p, st); break;
     case 7: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 1>(p, st); break;
     case 8: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 3>(p, st); break;

@@ -302,6 +302,9 @@ def test_ring_tiles_agree_bit_for_bit(M, N, K, epi):
     (0, 14600, 2304, 128, 9, True),
     (2, 4800, 3584, 1152, 9, True),
     (0, 28, 1152, 128, 11, False),
+    (3, 2300, 3200, 4096, 4, False),     # one round of 256 x 128 tiles over long K: one tile per workgroup
+    (0, 2048, 3584, 3584, 4, False),
+    (2, 1500, 4608, 2048, 4, False),
 ])
 def test_what_the_library_picks_leaves_the_bits_of_one_form(epi, M, N, K, form, cut):
     """The dispatch over weights padded as the library pads them (1152 columns to 1280, 3200 to 3328): every kind of choice is
@@ -322,10 +325,10 @@ def test_what_the_library_picks_leaves_the_bits_of_one_form(epi, M, N, K, form, 
 
 @pytest.mark.parametrize("K", [128, 256, 640])
 @pytest.mark.parametrize("epi,M,N,forms", [
-    (0, 16536, 1024, (9, 1)), (1, 16536, 1024, (9, 1)), (2, 16536, 1024, (9, 1)),   # 260 tiles of 256 x 256, 520 of 256 x 128
-    (3, 16537, 1024, (10, 1)), (4, 16536, 1024, (9, 1)), (5, 16536, 1024, (9, 1)),
+    (0, 16536, 1024, (9, 1, 4)), (1, 16536, 1024, (9, 1, 4)), (2, 16536, 1024, (9, 1, 4)),   # 260 tiles of 256 x 256, 520 of 256 x 128
+    (3, 16537, 1024, (10, 1, 4)), (4, 16536, 1024, (9, 1)), (5, 16536, 1024, (9, 1, 4)),
     (3, 11100, 2304, (12, 10, 1)),                                                  # 528 of 256 x 192, 396 of 256 x 256
-    (4, 1240, 1152, (1, 13)), (5, 1240, 1152, (1, 13)), (4, 8200, 1152, (0, 1)), (5, 8200, 1152, (0, 1))])
+    (4, 1240, 1152, (1, 13)), (5, 1240, 1152, (1, 4, 13)), (4, 8200, 1152, (0, 1)), (5, 8200, 1152, (0, 1))])
 def test_persistent_tiles_beyond_the_first_agree_bit_for_bit(epi, M, N, forms, K):
     """More tiles than CUs, so that workgroups go on to a second tile, whose first slabs and stream rows are fetched under the last
     products of the one before; two slabs (K = 128: all of a tile's are its last) and more, a ragged last tile row, every
