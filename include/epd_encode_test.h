@@ -86,6 +86,10 @@ epd_status epd_op_attention_bf16(const void* q, const void* k, const void* vt, v
                                  int32_t n_slices, int32_t n_tokens, int32_t n_keys, int32_t heads,
                                  int32_t hd_pad, int32_t ld_qk, int32_t paired, void* hip_stream);
 
+/* Queries per wave of that call: *queries = 16 or 32 (hd_pad 64, 72, 96 or 128).  Host only: launches nothing, and counts 256 CUs
+ * where there is no device. */
+epd_status epd_op_attention_queries(int32_t n_slices, int32_t n_tokens, int32_t heads, int32_t hd_pad, int32_t paired, int32_t* queries);
+
 /* The same attention with its output leaving as MXFP8 (the out-projection's operand under epd_model_desc::mx_fp8),
  * converted from the kernel's fp32 accumulators: codes dev uint8 [T * n_tokens, H * hd_pad], scales dev uint32
  * [H * hd_pad / 128, T * n_tokens] (layout of epd_op_mx_rows).  hd_pad % 32 == 0, H * hd_pad % 128 == 0. */

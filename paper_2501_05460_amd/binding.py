@@ -33,7 +33,7 @@ EXPORTS = (
     "epd_weight_count", "epd_check_desc", "epd_check_offsets", "epd_create", "epd_encode",
     "epd_encode_range", "epd_tokens_per_tile", "epd_out_dim", "epd_last_error", "epd_destroy",
     "epd_debug_read_stream", "epd_op_gemm_bf16", "epd_op_gemm_bf16_form", "epd_op_gemm_bf16_choice",
-    "epd_op_attention_bf16", "epd_op_mfma_probe",
+    "epd_op_attention_bf16", "epd_op_attention_queries", "epd_op_mfma_probe",
     "epd_profile_enable", "epd_profile_read", "epd_op_mfma_peak", "epd_op_copy_peak", "epd_op_coissue",
     "epd_op_row_stats", "epd_op_gemm_residual_stats", "epd_op_norm_gemm_bf16",
     "epd_op_mx_rows", "epd_op_mx_gemm", "epd_op_mx_mfma_probe", "epd_op_attention_mx",
@@ -104,6 +104,8 @@ def lib() -> ctypes.CDLL:
         L.epd_op_gemm_bf16_choice.restype = i32
         L.epd_op_attention_bf16.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp]
         L.epd_op_attention_bf16.restype = i32
+        L.epd_op_attention_queries.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
+        L.epd_op_attention_queries.restype = i32
         L.epd_op_mfma_probe.argtypes = [vp, vp, vp, vp]
         L.epd_op_mfma_probe.restype = i32
         L.epd_profile_enable.argtypes = [vp, i32]
@@ -460,6 +462,15 @@ def op_attention_bf16(q: torch.Tensor, k: torch.Tensor, vt: torch.Tensor, n_slic
     if s != EPD_OK:
         raise EpdError(s, lib().epd_last_error(None).decode())
     return o
+
+
+def op_attention_queries(n_slices: int, n_tokens: int, heads: int, hd_pad: int, paired: bool = False) -> int:
+    """Queries per wave of such a call, 16 or 32 (host only)."""
+    queries = ctypes.c_int32(0)
+    s = lib().epd_op_attention_queries(n_slices, n_tokens, heads, hd_pad, 1 if paired else 0, ctypes.byref(queries))
+    if s != EPD_OK:
+        raise EpdError(s, lib().epd_last_error(None).decode())
+    return queries.value
 
 
 def op_mfma_probe(A: torch.Tensor, B: torch.Tensor) -> torch.Tensor:

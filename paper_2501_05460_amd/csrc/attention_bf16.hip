@@ -648,16 +648,28 @@ hipError_t launch_attn_m(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf1
   return hipGetLastError();
 }
 
+// 16 queries per wave, or 32: twice as many waves, each with half of a step's chain, while they all run at once.  By the most
+// workgroups a CU gets (a (slice, head) keeps to one XCD), of 64 queries and of 128; the hardware takes four of 64 at head dims 64
+// and 72, three at 96 and two at 128.  us, 32 | 16 queries per wave:
+//   two of 64: head dim 128, one slice of 1024 tokens (25 heads) 26.4 | 24.3; head dim 72, two (16 heads) 21.9 | 20.7
+//   three: 64, three slices 28.1 | 24.2; 72 30.0 | 27.0; 96, four (12 heads) 34.8 | 29.6; but 128, one of 1025 tokens 38.2 | 40.2
+//   four against two of 128: 64, four slices 29.7 | 28.5, PAIRED 32.0 | 34.0; 72 31.6 | 33.4; 96, five 36.4 | 44.6; 128, two 39.4 | 45.8
+//   four against three of 128: 128, four of 576 tokens 35.2 | 30.6; 96, nine of 576 29.2 | 28.2
+// A query's bits are the same.
+bool short_waves(int n_slices, int n_q, int heads, int hd, bool paired) {
+  const long wgs = (long)n_slices * heads * ((n_q + 127) / 128);   // past two of 128 queries per CU always 32
+  const long pairs = ((long)n_slices * heads + 7) / 8, cus = cu_count() >= 8 ? cu_count() / 8 : 1;   // of an XCD
+  auto per_cu = [&](int queries) { return (pairs * ((n_q + queries - 1) / queries) + cus - 1) / cus; };
+  const long of_64 = per_cu(64), of_128 = per_cu(128);
+  return wgs <= 512 && (of_64 <= (hd == 128 ? 2 : 3) || (of_64 == 4 && (of_128 == 3 || (hd == 64 && !paired))));
+}
+
 template <int HD, bool PAIRED>
 hipError_t launch_attn(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                        int n_tok, int n_keys, int n_q, int q_shared, int heads, long ld_qk, long ld_o,
                        unsigned char* oq, unsigned* so, long ld_so, hipStream_t st) {
   const bool mask = n_keys < n_tok || n_tok % BKEY != 0;
-  const long wgs = (long)n_slices * heads * ((n_q + 127) / 128);   // of 128 queries
-  // Up to two workgroups of 128 queries per CU, waves of 16 queries: twice as many waves, each with half of a step's chain
-  // (us, 32 | 16 queries per wave: 128 workgroups of head dim 64 19.1 | 14.0, 384 25.1 | 21.0, 640 33.7 | 36.1; of head dim 72
-  // 128 21.0 | 16.1, 384 28.9 | 25.9, 1280 62.9 | 74.4; of 128 200 25.8 | 23.5, 600 56.5 | 57.6).  A query's bits are the same.
-  if (wgs <= 512)
+  if (short_waves(n_slices, n_q, heads, HD, PAIRED))
     return mask ? launch_attn_m<HD, 1, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
                 : launch_attn_m<HD, 1, false, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
   return mask ? launch_attn_m<HD, 2, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
@@ -688,6 +700,10 @@ hipError_t bf16_attention_init() {
   if (e == hipSuccess) e = set_attr_hd<72>();
   if (e == hipSuccess) e = set_attr_hd<96>();
   return e == hipSuccess ? set_attr_hd<128>() : e;
+}
+
+int bf16_attention_queries(int n_slices, int n_q, int heads, int hd_pad, bool paired) {
+  return short_waves(n_slices, n_q, heads, hd_pad, paired) ? 16 : 32;
 }
 
 hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,

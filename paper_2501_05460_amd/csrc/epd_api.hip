@@ -1436,6 +1436,15 @@ epd_status epd_op_gemm_bf16_choice(int32_t M, int32_t N, int32_t K, int32_t epi,
   return EPD_OK;
 }
 
+epd_status epd_op_attention_queries(int32_t n_slices, int32_t n_tokens, int32_t heads, int32_t hd_pad, int32_t paired, int32_t* queries) {
+  if (!queries || n_slices <= 0 || n_tokens <= 0 || heads <= 0 || !(hd_pad == 64 || hd_pad == 72 || hd_pad == 96 || hd_pad == 128)) {
+    set_err(g_err, sizeof(g_err), "epd_op_attention_queries: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  *queries = bf16_attention_queries(n_slices, n_tokens, heads, hd_pad, paired != 0);
+  return EPD_OK;
+}
+
 epd_status epd_op_row_stats(const float* x, int64_t rows, int32_t dim, void* xb, float* stats, void* hip_stream) {
   if (!x || !xb || !stats || rows < 0 || dim <= 0 || dim % 4) return EPD_ERR_INVALID_ARG;
   bf16_row_stats(x, dim, rows, dim, (bf16_t*)xb, dim, stats, (dim + STAT_GROUP - 1) / STAT_GROUP, (hipStream_t)hip_stream);

@@ -161,6 +161,7 @@ hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf
                           int n_tok, int n_keys, int n_q, int q_shared, int heads, int hd_pad, long ld_qk,
                           long ld_o, hipStream_t st, unsigned char* oq = nullptr, unsigned* so = nullptr, long ld_so = 0,
                           bool paired = false);
+int bf16_attention_queries(int n_slices, int n_q, int heads, int hd_pad, bool paired);   // queries per wave of such a call, 16 or 32 (tests)
 hipError_t bf16_attention_init();   // raises the dynamic-LDS limit on the current device (idempotent); in front of bf16_attention
 
 // W[r][0..cols) *= c (rounded to bf16 again) and b[r] *= c for r < rows: a constant factor of a product's
@@ -254,7 +255,7 @@ struct MxGemmParams {
 int cu_count();   // compute units of the device (see gemm_bf16.hip)
 hipError_t mx_gemm(const MxGemmParams& p, hipStream_t st);
 hipError_t mx_gemm_init();   // raises the dynamic-LDS limit of the kernels (idempotent)
-// one v_mfma_scale_f32_32x32x64_f8f6f4 on caller-supplied registers (operand-layout test): a, b [64][8], sa, sb [64], d [64][16]
+// one v_mfma_scale_f32_16x16x128_f8f6f4 on caller-supplied registers (operand-layout test): a, b [64][8], sa, sb [64], d [64][4]
 void mx_mfma_probe(const int* a, const int* b, const int* sa, const int* sb, float* d, hipStream_t st);
 
 // MFMA lane-layout check: D[32,32] = A[32,16] * B[16,32] with operands loaded
