@@ -164,13 +164,16 @@ __device__ __forceinline__ void static_for(F&& f) {
 
 // QT sub-tiles of 16 queries per wave, four waves.
 // LEAN: one step's S^T registers and weights only, no step issued ahead, so that four (head dim 64), three (72, 96) workgroups
-// share a CU (112, 139, 150 registers); at head dim 128, where LDS holds two, the S^T product of step i + 1 is issued ahead
-// of the softmax of step i.
+// share a CU (112, 142, 144 registers; up to 128, 155, 162 with MASK and PAIRED); at head dim 128, where LDS holds two, the
+// S^T product of step i + 1 is issued ahead of the softmax of step i.
 // PAIRED: a lane's eight keys of a step are 16 (l / 32) + 4 (l / 16 % 2) + {0..3, 8..11}, V^T fragments are two 8-byte halves, and
 // the row sum on the VALU runs over a lane pair's sixteen weights in a row: the order of summation of a kernel on
 // v_mfma_f32_32x32x16_bf16, whose bits this gives.  For calls whose output is converted to MXFP8: there a change of the last
-// bit anywhere re-draws the conversion's rounding in all that follows (6 % of an encoder's output).  It costs about 10 us of
-// 146 (26 slices, 16 heads of 64; the 32x32x16 kernel with this output 143; 10 slices, 25 heads of 128 166 -> 155).
+// bit anywhere re-draws the conversion's rounding in all that follows (6 % of an encoder's output).  It costs twice
+// the instructions of the row sums, 4 to 18 % of a launch (26 slices of 16 heads of 64, bf16 output | this: 136 | 160), and at
+// head dim 64 more than this kernel gains: with this output the 32x32x16 kernel took 151 (five slices 36.2, this 41.6; one 18.1,
+// 18.6); 96, 13 slices of 16 heads 124 -> 110; 128, ten of 25 heads 172 -> 160.  V^T as whole chunks whose halves two lane groups
+// then exchange (v_permlane16_swap): the same bits, 2 to 5 % slower.
 // MASK: the slices carry rows past n_keys (compiled apart: the unmasked kernel keeps its registers and its step free of
 // the key-index compare).
 template <int HD, int QT, bool MASK, bool PAIRED>
@@ -649,8 +652,8 @@ hipError_t launch_attn_m(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf1
 }
 
 // 16 queries per wave, or 32: twice as many waves, each with half of a step's chain, while they all run at once.  By the most
-// workgroups a CU gets (a (slice, head) keeps to one XCD), of 64 queries and of 128; the hardware takes four of 64 at head dims 64
-// and 72, three at 96 and two at 128.  us, 32 | 16 queries per wave:
+// workgroups a CU gets (a (slice, head) keeps to one XCD), of 64 queries and of 128; LDS holds five of 64 at head dim 64,
+// four at 72, three at 96 and two at 128.  us, 32 | 16 queries per wave:
 //   two of 64: head dim 128, one slice of 1024 tokens (25 heads) 26.4 | 24.3; head dim 72, two (16 heads) 21.9 | 20.7
 //   three: 64, three slices 28.1 | 24.2; 72 30.0 | 27.0; 96, four (12 heads) 34.8 | 29.6; but 128, one of 1025 tokens 38.2 | 40.2
 //   four against two of 128: 64, four slices 29.7 | 28.5, PAIRED 32.0 | 34.0; 72 31.6 | 33.4; 96, five 36.4 | 44.6; 128, two 39.4 | 45.8

@@ -9,7 +9,11 @@
 // lanes per 128-bit access phase: rows r and r+1 share a chunk column, so the
 // XOR key is (row >> 1) & 7).  One barrier per slab, two LDS buffers.
 //
-// Main loop of the default shape (PIPE = 1): the activation slab is read two
+// What runs here: the products with a folded pre-norm or emitted rows (EPD_NORM_MODE), 256 x 128 tiles of plain products over
+// long K (one_tile_128), and the forms that tests hold the others against.  All other products run on gemm_bf16_wide.hip and
+// gemm_bf16_ring.hip; the dispatch at the end of this file chooses.
+//
+// Main loop of the 256 x 256 shape (PIPE = 1): the activation slab is read two
 // slabs ahead into registers through a buffer descriptor (L2 / Infinity-Cache
 // latency is longer than one slab of MFMA work) and stored to the other LDS
 // buffer a slab later; the weight slab, which sits in L2, goes from global
@@ -49,10 +53,10 @@ __device__ __forceinline__ f32x16 mfma32(bf16x8 a, bf16x8 b, f32x16 c) {
 }
 
 // Configurations (BN, 512 threads, 64-wide wave tiles), one workgroup per CU, two LDS buffers:
-//   BN = 256  256x256 tile, 128x64 per wave (PIPE = 1: pipelined loop, the default; PIPE = 0:
+//   BN = 256  256x256 tile, 128x64 per wave (PIPE = 1: pipelined loop; PIPE = 0:
 //             both operands two slabs ahead in two register sets, fragment reads left to the
 //             compiler: the reference the pipelined loop is checked against bit for bit);
-//   BN = 128  256x128 tile, 64x64 per wave, PIPE = 0: outputs narrower than 256 columns;
+//   BN = 128  256x128 tile, 64x64 per wave, PIPE = 0: one round of tiles over long K, outputs narrower than 256 columns;
 //   BN = 128, BM = 128  128x128 tile, 32x64 per wave, PIPE = 0 or 2, two workgroups per CU: launches of a few
 //             slices with a folded pre-norm (the others take the tiles of gemm_bf16_ring.hip).
 // (Tried and dropped, none faster on the six workloads: 4 waves of 128x128 with AGPR
@@ -1091,11 +1095,13 @@ hipError_t launch_ring(const GemmParams& p, int tile, hipStream_t st) {
   return bf16_gemm_ring(without_padded_columns(p), tile, st);
 }
 
-// Times of a product by form, in microseconds, as the dispatch compares them.  Fitted to the products of the running
-// encoder, each form forced for one product at a time (three shapes, 256 to 65536 rows, K 1024 to 12800, weights cold; half
-// of them within 2-4 %, rms 4-7 %): a workgroup's chain of KT 64-deep slabs plus its fixed cost (first slab, epilogue),
-// times the rounds the launch's tiles make on the CUs, and a part that grows with the tiles alone (the CUs share memory
-// and power).  Of 697 products measured in all forms, the one taken is within 3 % of the fastest for 87 %, within 5 % for 94 %.
+// Times of a product by form, in microseconds, as the dispatch compares them: a workgroup's chain of KT 64-deep slabs plus its
+// fixed cost (first slab, epilogue), times the rounds the launch's tiles make on the CUs, and a part that grows with the
+// tiles alone (the CUs share memory and power).  Fitted to the products of the running encoder, each form forced for one
+// product at a time (three shapes, 256 to 65536 rows, K 1024 to 12800, weights cold; rms 4-7 %), when the 256-wide tiles
+// still ran on v_mfma_f32_32x32x16_bf16: those are 5 to 14 % faster now, the ring tiles 2 %.  The order of the forms holds on the
+// present kernels: of 385 products measured again, the one taken is within 3 % of the fastest for 88 %, within 5 % for 93 %,
+// within 9 % for 99 %.  Figures below that give one form only are of the earlier kernels.
 struct RingPick { int tile; double us; };
 bool f32_rows(int epi) { return epi == EPI_BIAS_RESIDUAL || epi == EPI_BIAS_POS; }   // reads and writes rows of the stream
 bool has_gelu(int epi) { return epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH; }
@@ -1127,8 +1133,8 @@ double round_192(double tiles, int K) {
   const double kt = K / BK;
   return 13.7 + 1.27 * kt + tiles / cu_count() * (0.234 * kt - 0.5);
 }
-// 256 x 128 tiles, one workgroup per CU: a launch that is one round of them (6400 columns over 1024 rows of K = 3200: 55 us,
-// 68 on 128 x 128 ring tiles; 1152 columns over 5888 rows of K = 4352: 88 against 93); not launched for more
+// 256 x 128 tiles, one workgroup per CU: a launch that is one round of them (6400 columns over 1024 rows of K = 3200: 54 us,
+// 66 on 128 x 128 ring tiles; 1152 columns over 6144 rows of K = 4352: 91 against 94); not launched for more
 double one_round_128(const GemmParams& p) {
   const double kt = p.K / BK, tiles = (double)((p.M + BM - 1) / BM) * (whole_128(p.N) / 128), fill = tiles / cu_count();
   if (fill > 1.0) return INFINITY;
@@ -1169,10 +1175,9 @@ long cut_rows(const GemmParams& p) {
   return rounds_of(rows_a * gn, round) + behind_cut(p, rows_a) < rounds_of(tiles, round) ? rows_a : 0;
 }
 
-// Activation slabs straight into LDS (no register hop): the persistent kernels (-5 % on the q/k, value and FC1
-// products of the 104-slice batch) and the residual product when K is long (FC2 -1 %; the short out-projection
-// is 1 % faster with its rows staged in registers two slabs ahead).  EPD_A_DIRECT=0 keeps the register-staged
-// forms, the ones these were measured against.
+// Residual products of this file's 256 x 256 tiles (emitted rows, EPD_PERSIST_RES=0): activation slabs straight into LDS
+// (no register hop) when K is long (FC2 -1 %; the short out-projection is 1 % faster with its rows staged in registers
+// two slabs ahead).  EPD_A_DIRECT=0 keeps the register-staged form for both.
 bool a_direct() {
   static const bool on = !(getenv("EPD_A_DIRECT") && getenv("EPD_A_DIRECT")[0] == '0');
   return on;

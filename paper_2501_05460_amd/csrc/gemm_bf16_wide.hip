@@ -1,12 +1,13 @@
 // bf16 MFMA GEMM on large tiles with persistent workgroups:  C[M,N] = A[M,K] * W[N,K]^T with the fused epilogues.
 //
-// What bounds it is the chip's power limit: the clock falls until the product fits it (1.5 to 1.8 GHz of 2.4), so what
-// counts is the energy of a flop.  Hence
-//   * v_mfma_f32_16x16x32_bf16, not v_mfma_f32_32x32x16_bf16: a register-resident loop on normal deviates runs 2.10
-//     PFLOP/s with the first and 1.38 with the second (constant operands: both near 2.4).  An element's k-steps are added
+// What bounds it: over a long K the chip's power, under which the clock falls to 1.5 to 2.05 GHz of 2.4; at K = 1024 as much the
+// epilogue, in which all waves of the one workgroup a CU holds stand together (106496 rows: the matrix pipe is busy 59 to 64 %
+// of a product, 49 % of a residual one, at 1.95 to 2.12 GHz).  The energy of a flop counts in both.  Hence
+//   * v_mfma_f32_16x16x32_bf16, not v_mfma_f32_32x32x16_bf16: a register-resident loop on normal deviates runs 2.02
+//     PFLOP/s with the first and 1.74 with the second (constant operands: both near 2.45).  An element's k-steps are added
 //     in the same order inside the instruction: two 32x32x16 steps and one 16x16x32 step leave the same bits.
 //   * the MFMAs of a k-step walk the wave's blocks in serpentine order: consecutive ones share an operand fragment
-//     (register loop: 2.10 PFLOP/s, row-major 2.06, both operands new every time 1.95).
+//     (such a loop on another box: 2.10 PFLOP/s, row-major 2.06, both operands new every time 1.95).
 // A workgroup per CU walks the tile sequence.  Both operand slabs (64 deep) go from global memory straight into one of two
 // LDS buffers; the fragments of a k-step (32 deep) are read while the MFMAs of the step before it run, so that a slab's
 // buffer is free, and the slab after the next is fetched into it, as soon as the slab's first k-step is multiplied: a

@@ -555,7 +555,8 @@ hipError_t launch(const MxGemmParams& p, hipStream_t st) {
   const int cols = (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH) && p.ncq > p.N ? p.ncq : p.N;
   // 256 x 256 tiles, a workgroup of eight waves per CU, or 128 x 128 ones, two of four waves: whichever is estimated to take
   // less.  A round of either: a fixed part by epilogue and a part per slab, us, fitted to 50 products (1024 to 53248 rows,
-  // 1024 to 4352 columns, K 1024 to 12800; the other form was faster by more than 3 % for two of them); the small tiles'
+  // 1024 to 4352 columns, K 1024 to 12800; the other form was faster by more than 3 % for two of them; of 164 others for
+  // 19, ten of these FC1 over K = 1152, by up to 16 %); the small tiles'
   // last round counts 0.7 while one per CU holds it.  us, 256 x 256 | 128 x 128: 1024 rows, 2048 x 1024 14.6 | 8.2, 1024 x 4096
   // residual 43.9 | 26.6; 5120 rows, 4096 x 1024 39.6 | 28.6; 26624 rows, 4096 x 1024 137 | 150, 1024 x 1024 residual 63.9 | 54.7.
   constexpr bool MX = EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH, RES = EPI == EPI_BIAS_RESIDUAL;
