@@ -18,6 +18,10 @@
 // Measured stand-alone beside the 32x32x16 kernels this replaces (us; one box, random operands): 106496 rows, N x K
 // 2048 x 1024 380 -> 339, value projection 204 -> 179, out-projection 283 -> 262, 4096 x 1024 with GELU 829 -> 730,
 // 1024 x 4096 residual 838 -> 782; 8192^3 775 -> 706 (1.56 PFLOP/s); 10240 rows, 1152 x 4352 residual 101 -> 95.
+// With the lines of a slab pair asked for ahead (`touch`) and bands of one width (us, operands cold as in a running encoder): 10240 rows,
+// 1152 x 4352 residual, 256 x 192 tiles 111 -> 95; 106496 rows, 1024 x 4096 residual 790 -> 735, 1024 x 1024 residual 294 -> 276, 4096 x 1024
+// with GELU 772 -> 745; 40960 rows, 9600 x 3200 1895 -> 1805, 12800 x 3200 with GELU 2595 -> 2490; 3200 x 12800 residual 2930 -> 2830.
+// One line a row at a time gives two thirds of that; four lines, or two pairs ahead, the same or less.
 // Tried and not kept: four waves of 128 x 128 (a third fewer fragment reads: 8192^3 equal, K = 1024 2 to 6 % slower, their
 // epilogue runs on half as many waves); a staggered start of the workgroups (residual products -1 to -5 %, FC1 + 1 %); a
 // wait that leaves the epilogue's stores in flight over the next tile's first slab (equal).
@@ -52,7 +56,7 @@ struct Wide {
 
 template <int EPI, int TM, int TN, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(const GemmParams p, const int gm, const int gw,
-                                                                              const int gn, const int n_tiles) {
+                                                                              const int gn, const int n_tiles, const int ahead) {
   using S = Wide<TM, TN, WAVES_M, WAVES_N>;
   constexpr int NT = S::NT, WM = S::WM, WN = S::WN, ROWS = S::ROWS, COLS = S::COLS, SLAB = S::SLAB;
   constexpr int RPL = NT / 8;                       // rows covered by one direct load of the workgroup
@@ -96,6 +100,30 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
     const char* g = i < LA ? ga + i * a_step : gb + (i - LA) * b_step;
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(i < LA ? a_voff : b_voff), "s"(g), "s"(lds0 + buf * SLAB + i * (RPL * 128)) : "memory", "m0");
+  };
+  // A slab's direct loads have half a slab's time to arrive (1 us), less than a line takes that is not in the L2 yet.  So the
+  // lines of the two slabs behind the ones under way are asked for a pair of slabs ahead, each by one workgroup of the XCD
+  // (they share panels: slot % gw picks the part of the activation rows, slot / gw that of the weight rows) and two lines of a
+  // row by two lanes, 256 contiguous bytes.  The load wants a destination: a dword a lane into the wave's staging area, which
+  // nobody uses until the epilogue.  A lane that would ask for a line of its own where few share a panel asks for some only:
+  // the load is a hint, any address inside the operands is right.  `ahead` 0: all lanes ask for the slab's first line.
+  constexpr int HALF_T = NT / 2;
+  const bool a_half = wave < WAVES_M * WAVES_N / 2;   // the first waves ask for activations, the others for weights
+  unsigned t_voff = 0;
+  if (ahead) {
+    const int slot = blockIdx.x >> 3, lt = tid & (HALF_T - 1);
+    const int parts = a_half ? gw : max(1, (int)((gridDim.x + 7) >> 3) / gw), rows = a_half ? ROWS : COLS;
+    const int n = (rows + parts - 1) / parts, ix = 2 * n <= HALF_T ? lt * 2 * n / HALF_T : lt;
+    const int row = min((a_half ? slot % gw : slot / gw % parts) * n + (ix >> 1), rows - 1);
+    t_voff = ((unsigned)row * (unsigned)(a_half ? p.lda : (long)p.K) + (ix & 1) * BK) * 2;
+  }
+  const unsigned t_lds = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem + 2 * SLAB + wave * S::STG;
+  const char *tg, *tgn;   // slab pair to ask for next, and the pairs behind the tile's last: those of the next tile
+  int t_left;             // slabs up to there
+  auto touch = [&]() {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1" :: "v"(t_voff), "s"(tg), "s"(t_lds) : "memory", "m0");
+    tg += 2 * BK * 2;
+    if ((t_left -= 2) == 0) { tg = tgn; t_left = KT; }
   };
   auto wait_vm = [&](auto n) {   // at most n vector-memory accesses of the wave outstanding (they complete in order)
     constexpr int N = decltype(n)::value;
@@ -164,7 +192,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
     for (int i = 0; i < LPS; ++i) issue(i, b);
     ga += BK * 2; gb += BK * 2;
   }
-  wait_vm(std::integral_constant<int, LPS>{});
+  tgn = a_half ? ga - 4 * BK : gb - 4 * BK;   // K = 128: the pair behind the first one is the first one again
+  tg = KT > 2 ? tgn + 4 * BK : tgn;
+  t_left = KT > 2 ? KT - 2 : KT;
+  touch();
+  wait_vm(std::integral_constant<int, LPS + 1>{});
   __syncthreads();
 
   for (;;) {
@@ -173,6 +205,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
     if (has_next) tile_of(nxt, m0n, n0n); else { m0n = m0; n0n = n0; }
     const char* gan = reinterpret_cast<const char*>(p.A + (long)m0n * p.lda);
     const char* gbn = reinterpret_cast<const char*>(p.W + (long)n0n * p.K);
+    tgn = a_half ? gan : gbn;
 #pragma unroll
     for (int r = 0; r < NR; ++r) read(S0{}, 0, 0, r);
 #pragma unroll
@@ -205,7 +238,8 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
     float bias1[TOK ? TN : 1];
     // One slab, in buffer buf with its first fragments in set 0: slab kt + 1 lands in the other buffer meanwhile, slab
     // kt + 2 is fetched into this one behind the barrier.  phase 0: inside the tile; 1: the slab before the last, behind
-    // which the next tile's slabs are fetched, if there is one; 2: the last slab.
+    // which the next tile's slabs are fetched, if there is one; 2: the last slab.  Buffer 0's slabs end with a touch, the
+    // newest access when the next slab waits.
     auto slab = [&](int buf, auto phase) {
       constexpr int PHASE = decltype(phase)::value;
       constexpr int H = MM * 3 / 4;   // the reads go behind the first three quarters of the MFMAs
@@ -215,7 +249,15 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
         });
       });
       if constexpr (PHASE == 1) { ga = gan; gb = gbn; }
-      wait_vm(std::integral_constant<int, 0>{});   // the wave's part of the next slab has landed
+      // the wave's part of the next slab has landed
+      if constexpr (PHASE == 2) {
+        if (has_next) wait_vm(std::integral_constant<int, 1>{});
+        else wait_vm(std::integral_constant<int, 0>{});
+      } else if (buf == 0) {
+        wait_vm(std::integral_constant<int, 0>{});
+      } else {
+        wait_vm(std::integral_constant<int, 1>{});
+      }
       __syncthreads();                             // everyone's has, and everyone holds this slab's fragments: its buffer is free
       if constexpr (PHASE == 2) {
         if constexpr (TOK) {
@@ -240,12 +282,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
         });
       });
       ga += BK * 2; gb += BK * 2;
+      if (buf == 0 && (PHASE == 0 || has_next)) touch();
     };
     using P0 = std::integral_constant<int, 0>;
     for (int kt = 0; kt < KT - 2; kt += 2) { slab(0, P0{}); slab(1, P0{}); }
     slab(0, std::integral_constant<int, 1>{});
     slab(1, std::integral_constant<int, 2>{});
-    // LDS buffer 0 holds slab 0 of the next tile, its slab 1 is on its way to buffer 1
+    // LDS buffer 0 holds slab 0 of the next tile, its slab 1 is on its way to buffer 1; the touch in front of it has left
+    wait_vm(std::integral_constant<int, LPS>{});   // the staging area
 
     {
       // The epilogue's addresses derive from an opaque copy of the thread index, made anew for every tile: computed in
@@ -378,19 +422,24 @@ hipError_t launch_wide(const GemmParams& p, int cus, hipStream_t st) {
   const int gm = (p.M + S::ROWS - 1) / S::ROWS, gn = (p.N + S::COLS - 1) / S::COLS, n_tiles = gm * gn;
   if (gn * S::COLS > p.Npad) return hipErrorInvalidValue;
   if (n_tiles == 0) return hipSuccess;
-  // Band width.  The ~32 workgroups an XCD runs at once cover (32 / gw) tile rows x gw tile columns and move through K
-  // together, so per round of tiles the L2 pulls 32 / gw activation panels and gw weight panels over the fabric; the weight
-  // panels are not pulled again by later rounds while a band's whole weight panel fits the 4 MiB L2.
+  // Band width.  The up to 32 workgroups an XCD runs at once are consecutive tiles of a band and move through K together.
+  // In a band w wide they lie in 1 + 31 / w tile rows on average, 32 / w where that is whole, and w columns: so many panels
+  // the L2 pulls over the fabric per round, the weight panels only once while the band's fit its 4 MiB.  The last band is
+  // what is left over: 16 columns as 4 bands of 4, not as 5, 5, 5 and 1 (K = 1024, 106496 rows, GELU: 774 -> 745 us).
   const double panel_a = (double)S::ROWS * p.K * sizeof(bf16_t), panel_w = (double)S::COLS * p.K * sizeof(bf16_t);
+  const int at_once = n_tiles < cus ? (n_tiles + 7) / 8 : (cus + 7) / 8;
+  auto band_cost = [&](int w) {   // per column of the band
+    const double rows = at_once % w == 0 ? at_once / w : 1.0 + (at_once - 1.0) / w;
+    return w * (rows * panel_a + (w * panel_w <= 2.5 * (1 << 20) ? 0.0 : w * panel_w));
+  };
   int gw = 1;
   double best = 1e30;
   for (int c = 1; c <= gn && c <= 32; ++c) {
-    const bool resident = c * panel_w <= 2.5 * (1 << 20);
-    const double cost = (32.0 / c) * panel_a + (resident ? 0.0 : c * panel_w);
+    const double cost = gn / c * band_cost(c) + (gn % c ? band_cost(gn % c) : 0.0);
     if (cost < best * 0.999) { best = cost; gw = c; }
   }
   if (p.band > 0 && p.band <= gn) gw = p.band;
-  k_gemm_bf16_wide<EPI, TM, TN, WAVES_M, WAVES_N><<<dim3(n_tiles < cus ? n_tiles : cus), dim3(S::NT), S::LDS, st>>>(p, gm, gw, gn, n_tiles);
+  k_gemm_bf16_wide<EPI, TM, TN, WAVES_M, WAVES_N><<<dim3(n_tiles < cus ? n_tiles : cus), dim3(S::NT), S::LDS, st>>>(p, gm, gw, gn, n_tiles, n_tiles > cus || p.K >= 2048);
   return hipGetLastError();
 }
 template <int EPI, int TM, int TN, int WAVES_M, int WAVES_N>
