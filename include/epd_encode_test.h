@@ -40,18 +40,31 @@ epd_status epd_op_gemm_bf16(const void* A, const void* W, const float* bias, voi
  * 11 = 64x64 tile of the ring kernel (11, 13, 14: what the library picks from for launches of a few slices).
  * 12 = the persistent residual product on 256x192 tiles (epi 3 only, N % 192 == 0: what the library picks for a
  * width like 1152, which is six such tile columns and four and a half 256-wide ones).
- * M >= 1 (any), N % 128 == 0 (N % 256 == 0 for forms 6 to 10), K % 128 == 0; bias [N] fp32.
+ * 15 = the persistent kernel on 224x256 tiles (epi 1, 2 and 3).
+ * M >= 1 (any), N % 128 == 0 (N % 256 == 0 for forms 6 to 10 and 15), K % 128 == 0; bias [N] fp32.
  * A [M,K], C [M,N] and R [M,N] hold exactly M rows; no row past M is written.  (The kernels read whole
  * 256-row tiles; for a ragged M, for R and for padded weights the call runs on copies it allocates, and synchronises.) */
 epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias, void* C, float* R, const float* pos,
                                  int32_t M, int32_t N, int32_t K, int32_t n_tok, int32_t epi, int32_t form,
                                  void* hip_stream);
 
-/* Which form the library takes for a product of M rows, N columns (padded as the library pads its weights) and K, by
+/* The form the library weighs first for a product of M rows, N columns (padded as the library pads its weights) and K, by
  * epilogue as above and 4 = patch embedding, 5 = value projection (slices of n_tok rows each): *form as above (10 / 9
  * for 256x256 tiles of residual / other products, 0: whole 256-wide tile columns and the rest apart); *rows: the rows in front of a row cut, M
- * without one.  Host only: launches nothing, and counts 256 CUs where there is no device. */
+ * without one.  A second stage may take another shape in its place, see epd_op_gemm_bf16_shape.  Host only: launches nothing, and counts
+ * 256 CUs where there is no device. */
 epd_status epd_op_gemm_bf16_choice(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t n_tok, int32_t* form, int32_t* rows);
+
+/* The shape that runs, by its number as a form above (10: 9 of a residual product); 0: a product cut into two launches.  n2 > 0 (epi 0):
+ * the q/k projection, N columns, and the value projection over the same rows, n2 columns in slices of n_tok rows: 16 and 17 = 192x256
+ * and 160x256 tiles; 0: two products in a launch each.  Host only, as above. */
+epd_status epd_op_gemm_bf16_shape(int32_t M, int32_t N, int32_t K, int32_t n2, int32_t epi, int32_t n_tok, int32_t* form);
+
+/* Two products over the same rows in one launch: C [M,N] bf16 = A W[:N]^T + bias[:N], and VT bf16 [M / n_tok, n2, n_tok] the
+ * transposed A W[N:]^T + bias[N:].  W [N + n2, K], N % 256 == 0, n2 % 128 == 0 and n2 > 128, K % 128 == 0, n_tok % 8 == 0, M % n_tok == 0; form 9, 11 to 17 as above (12: N and
+ * n2 multiples of 192).  Allocates and synchronises. */
+epd_status epd_op_gemm_bf16_pair(const void* A, const void* W, const float* bias, void* C, void* VT, int32_t M, int32_t N, int32_t n2,
+                                 int32_t K, int32_t n_tok, int32_t form, void* hip_stream);
 
 /* The pre-norms of a layer have no kernel of their own in bf16 mode: the residual epilogue that updates a row
  * x also stores bf16(x) and the row's statistics, and the product that follows the norm runs on bf16(x) against

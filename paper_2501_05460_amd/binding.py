@@ -33,6 +33,7 @@ EXPORTS = (
     "epd_weight_count", "epd_check_desc", "epd_check_offsets", "epd_create", "epd_encode",
     "epd_encode_range", "epd_tokens_per_tile", "epd_out_dim", "epd_last_error", "epd_destroy",
     "epd_debug_read_stream", "epd_op_gemm_bf16", "epd_op_gemm_bf16_form", "epd_op_gemm_bf16_choice",
+    "epd_op_gemm_bf16_shape", "epd_op_gemm_bf16_pair",
     "epd_op_attention_bf16", "epd_op_attention_queries", "epd_op_mfma_probe",
     "epd_profile_enable", "epd_profile_read", "epd_op_mfma_peak", "epd_op_copy_peak", "epd_op_coissue",
     "epd_op_row_stats", "epd_op_gemm_residual_stats", "epd_op_norm_gemm_bf16",
@@ -102,6 +103,10 @@ def lib() -> ctypes.CDLL:
         L.epd_op_gemm_bf16_form.restype = i32
         L.epd_op_gemm_bf16_choice.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.epd_op_gemm_bf16_choice.restype = i32
+        L.epd_op_gemm_bf16_shape.argtypes = [i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
+        L.epd_op_gemm_bf16_shape.restype = i32
+        L.epd_op_gemm_bf16_pair.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
+        L.epd_op_gemm_bf16_pair.restype = i32
         L.epd_op_attention_bf16.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, vp]
         L.epd_op_attention_bf16.restype = i32
         L.epd_op_attention_queries.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
@@ -413,12 +418,39 @@ def op_gemm_bf16(A: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tensor],
 
 
 def op_gemm_bf16_choice(M: int, N: int, K: int, epi: int, n_tok: int = 1):
-    """(form, rows in front of a row cut) the library takes for a product of this shape; host only."""
+    """(form, rows in front of a row cut) the library weighs first for a product of this shape; host only."""
     form, rows = ctypes.c_int32(), ctypes.c_int32()
     s = lib().epd_op_gemm_bf16_choice(M, N, K, epi, n_tok, ctypes.byref(form), ctypes.byref(rows))
     if s != EPD_OK:
         raise EpdError(s, lib().epd_last_error(None).decode())
     return form.value, rows.value
+
+
+def op_gemm_bf16_shape(M: int, N: int, K: int, epi: int, n2: int = 0, n_tok: int = 1) -> int:
+    """Number of the form that runs for a product of this shape, or for two over the same rows (n2 > 0); host only."""
+    form = ctypes.c_int32()
+    s = lib().epd_op_gemm_bf16_shape(M, N, K, n2, epi, n_tok, ctypes.byref(form))
+    if s != EPD_OK:
+        raise EpdError(s, lib().epd_last_error(None).decode())
+    return form.value
+
+
+def op_gemm_bf16_pair(A: torch.Tensor, W: torch.Tensor, bias: torch.Tensor, N: int, n_tok: int, form: int):
+    """(A W[:N]^T + bias[:N], the other columns transposed per slice [M / n_tok, n2, n_tok]) in one launch of the given form.
+
+    Both outputs have guard elements behind them; a call that writes any of them raises."""
+    M, K = A.shape
+    n2 = W.shape[0] - N
+    guard = 12345.0
+    C = torch.full((M + 64, N), guard, dtype=torch.bfloat16, device=A.device)
+    V = torch.full((M + 64, n2), guard, dtype=torch.bfloat16, device=A.device)
+    s = lib().epd_op_gemm_bf16_pair(A.contiguous().data_ptr(), W.contiguous().data_ptr(), bias.data_ptr(), C.data_ptr(), V.data_ptr(), M, N, n2, K,
+                                    n_tok, form, _stream_ptr())
+    if s != EPD_OK:
+        raise EpdError(s, lib().epd_last_error(None).decode())
+    if not bool((C[M:] == C[M, 0]).all() and C[M, 0] == V[M, 0] and (V[M:] == V[M, 0]).all()):
+        raise RuntimeError("pair form %d wrote past its outputs" % form)
+    return C[:M], V[:M].view(M // n_tok, n2, n_tok)
 
 
 def op_gemm_bf16_form(A: torch.Tensor, W: torch.Tensor, bias: torch.Tensor, epi: int, form: int,

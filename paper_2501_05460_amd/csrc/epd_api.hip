@@ -1359,9 +1359,9 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
   if (!A || !W || !bias || (residual || embed ? !R : !C) || (embed && (!pos || n_tok <= 0)) ||
       (values && (n_tok <= 0 || n_tok % 8 || M % n_tok)) || M <= 0 || N <= 0 || K <= 0 || N % 128 || K % 128 ||
       !(epi == EPI_BIAS || epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH || residual || embed || values) ||
-      !((form >= 0 && form <= 4) || (form >= 6 && form <= 14)) || (form == 4 && embed) ||
+      !((form >= 0 && form <= 4) || (form >= 6 && form <= 15)) || (form == 4 && embed) ||
       (form == 3 && K % 256) || (form >= 6 && form <= 10 && N % 256) || (form == 9 && residual) || (form == 10 && !residual) ||
-      (form == 12 && (!residual || N % 192))) {
+      (form == 12 && (!residual || N % 192)) || (form == 15 && (N % 256 || !(residual || epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH)))) {
     set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_form: bad argument");
     return EPD_ERR_INVALID_ARG;
   }
@@ -1433,6 +1433,54 @@ epd_status epd_op_gemm_bf16_choice(int32_t M, int32_t N, int32_t K, int32_t epi,
   long front = 0;
   *form = bf16_gemm_choice(p, &front);
   *rows = (int32_t)front;
+  return EPD_OK;
+}
+
+epd_status epd_op_gemm_bf16_shape(int32_t M, int32_t N, int32_t K, int32_t n2, int32_t epi, int32_t n_tok, int32_t* form) {
+  if (!form || M <= 0 || N <= 0 || N % 4 || K <= 0 || K % 128 || n2 < 0 || n2 % 4 || epi < EPI_BIAS || epi > EPI_VT || (n2 > 0 && epi != EPI_BIAS) ||
+      ((epi == EPI_VT || n2 > 0) && n_tok <= 0)) {
+    set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_shape: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  GemmParams p;
+  memset(&p, 0, sizeof(p));
+  p.epi = epi; p.M = M; p.N = N; p.K = K; p.Npad = pad_n(N); p.n2 = n2; p.n2_pad = n2 > 0 ? pad_n(n2) : 0; p.n_tok = n_tok;
+  *form = bf16_gemm_shape(p);
+  return EPD_OK;
+}
+
+epd_status epd_op_gemm_bf16_pair(const void* A, const void* W, const float* bias, void* C, void* VT, int32_t M, int32_t N, int32_t n2,
+                                 int32_t K, int32_t n_tok, int32_t form, void* hip_stream) {
+  if (!A || !W || !bias || !C || !VT || M <= 0 || N <= 0 || N % 256 || n2 <= 128 || n2 % 128 || K <= 0 || K % 128 || n_tok <= 0 || n_tok % 8 ||
+      M % n_tok || !(form == 9 || (form >= 11 && form <= 17)) || (form == 12 && (N % 192 || n2 % 192))) {
+    set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_pair: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  if (bf16_gemm_init() != hipSuccess) return EPD_ERR_HIP;
+  hipStream_t st = (hipStream_t)hip_stream;
+  // on copies with whole 256-row tiles of activations and the second product's weights padded as the library pads them
+  const long Mp = ((long)M + 255) / 256 * 256, rows = N + pad_n(n2);
+  void *Ap = nullptr, *Wp = nullptr;
+  float* bp = nullptr;
+  hipError_t err = hipMalloc(&Ap, (size_t)Mp * K * 2);
+  if (err == hipSuccess) err = hipMalloc(&Wp, (size_t)rows * K * 2);
+  if (err == hipSuccess) err = hipMalloc((void**)&bp, (size_t)rows * 4);
+  if (err == hipSuccess) err = hipMemsetAsync(Ap, 0, (size_t)Mp * K * 2, st);
+  if (err == hipSuccess) err = hipMemsetAsync(Wp, 0, (size_t)rows * K * 2, st);
+  if (err == hipSuccess) err = hipMemsetAsync(bp, 0, (size_t)rows * 4, st);
+  if (err == hipSuccess) err = hipMemcpyAsync(Ap, A, (size_t)M * K * 2, hipMemcpyDeviceToDevice, st);
+  if (err == hipSuccess) err = hipMemcpyAsync(Wp, W, (size_t)(N + n2) * K * 2, hipMemcpyDeviceToDevice, st);
+  if (err == hipSuccess) err = hipMemcpyAsync(bp, bias, (size_t)(N + n2) * 4, hipMemcpyDeviceToDevice, st);
+  GemmParams p;
+  memset(&p, 0, sizeof(p));
+  p.epi = EPI_BIAS; p.cfg = form; p.A = (const bf16_t*)Ap; p.lda = K; p.W = (const bf16_t*)Wp; p.bias = bp; p.M = M; p.N = N; p.Npad = N; p.K = K;
+  p.C = (bf16_t*)C; p.ldc = N; p.n_pos = 1; p.VT = (bf16_t*)VT; p.heads = 1; p.hd_pad = n2; p.n_tok = n_tok; p.n2 = n2; p.n2_pad = pad_n(n2);
+  if (err == hipSuccess) err = bf16_gemm(p, st);
+  if (err == hipSuccess) err = hipStreamSynchronize(st);
+  if (Ap) (void)hipFree(Ap);
+  if (Wp) (void)hipFree(Wp);
+  if (bp) (void)hipFree(bp);
+  if (err != hipSuccess) { set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_pair: %s", hipGetErrorString(err)); return EPD_ERR_HIP; }
   return EPD_OK;
 }
 

@@ -1208,9 +1208,9 @@ bool persist_res() {   // EPD_PERSIST_RES=0: the residual products stay on the o
   return on;
 }
 
-hipError_t launch_wide(const GemmParams& p, int tile, hipStream_t st) {
+hipError_t launch_wide(const GemmParams& p, int tile, hipStream_t st, int workgroups = cu_count()) {
   ++g_kernel_launches;
-  return bf16_gemm_wide(p, tile, cu_count(), st);
+  return bf16_gemm_wide(p, tile, workgroups, st);
 }
 
 bool tiles_192() {   // EPD_TILES_192=0: widths like 1152 stay on the 256-wide tiles
@@ -1251,15 +1251,17 @@ hipError_t dispatch(const GemmParams& p, hipStream_t st) {
     return p.stats_out ? launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_, 2>(p, st)
                        : launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_, 1>(p, st);
   }
-  switch (p.epi) {
-    case EPI_BIAS: return launch<BN, NT, WN, EPI_BIAS, PIPE, BM_>(p, st);
-    case EPI_BIAS_GELU_ERF: return launch<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>(p, st);
-    case EPI_BIAS_GELU_TANH: return launch<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>(p, st);
-    case EPI_BIAS_RESIDUAL: return launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>(p, st);
-    case EPI_VT: return launch<BN, NT, WN, EPI_VT, PIPE, BM_>(p, st);
-    case EPI_BIAS_POS: if constexpr (BN == 256) return launch<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>(p, st);
+  if constexpr (BN == 256) {
+    switch (p.epi) {
+      case EPI_BIAS: return launch<BN, NT, WN, EPI_BIAS, PIPE, BM_>(p, st);
+      case EPI_BIAS_GELU_ERF: return launch<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>(p, st);
+      case EPI_BIAS_GELU_TANH: return launch<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>(p, st);
+      case EPI_BIAS_RESIDUAL: return launch<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>(p, st);
+      case EPI_VT: return launch<BN, NT, WN, EPI_VT, PIPE, BM_>(p, st);
+      case EPI_BIAS_POS: return launch<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>(p, st);
+    }
   }
-  return hipErrorInvalidValue;
+  return hipErrorInvalidValue;   // 256 x 128 tiles: folded pre-norms and emitted rows only
 }
 
 // 128 x 128 tiles: compiled for the folded pre-norm and the emitting residual epilogues only (ring tiles otherwise)
@@ -1288,13 +1290,14 @@ hipError_t set_attr() {
 template <int BN, int NT, int WN, int PIPE = 0, int BM_ = BM>
 hipError_t set_attr_all() {
   hipError_t e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>()) != hipSuccess) return e;
-  if ((e = set_attr<BN, NT, WN, EPI_VT, PIPE, BM_>()) != hipSuccess) return e;
-  if constexpr (BN == 256)
+  if constexpr (BN == 256) {
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_BIAS_RESIDUAL, PIPE, BM_>()) != hipSuccess) return e;
+    if ((e = set_attr<BN, NT, WN, EPI_VT, PIPE, BM_>()) != hipSuccess) return e;
     if ((e = set_attr<BN, NT, WN, EPI_BIAS_POS, PIPE, BM_>()) != hipSuccess) return e;
+  }
   if ((e = set_attr<BN, NT, WN, EPI_BIAS, PIPE, BM_, 2>()) != hipSuccess) return e;
   if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_ERF, PIPE, BM_, 2>()) != hipSuccess) return e;
   if ((e = set_attr<BN, NT, WN, EPI_BIAS_GELU_TANH, PIPE, BM_, 2>()) != hipSuccess) return e;
@@ -1339,13 +1342,16 @@ hipError_t bf16_gemm_init() {
 // bits: a tile shape changes which lane holds an element, never the order in which its k-steps are summed.
 enum PlainForm { PLAIN_RING, PLAIN_256x128, PLAIN_256, PLAIN_192, PLAIN_COLUMNS };
 struct Plain { PlainForm form; int tile; long rows_a; double us; };   // tile: of the ring launch (whole or behind the cut); rows_a: see cut_rows
+static bool few_128_tiles(const GemmParams& p) {
+  return p.Npad % 256 != 0 || (long)((p.M + 127) / 128) * ((whole_128(p.N) + (p.n2_pad > 0 ? whole_128(p.n2) : 0)) / 128) <= 8L * cu_count();
+}
 static Plain choose_plain(const GemmParams& p) {
   const bool residual = p.epi == EPI_BIAS_RESIDUAL;
   const long gm = (p.M + BM - 1) / BM, cus = cu_count();
   const RingPick ring = best_ring(p.M, p.N, p.K, p.epi);
   // Ring tiles are for launches of a few slices.  Past eight 128 x 128 tiles per CU they were never ahead, and there the
   // stream's rows make them 10 to 25 % slower than estimated (47104 rows of 1152 by K = 1152: 225 us, 177 on 256 x 256 tiles).
-  const bool few = p.Npad % 256 != 0 || (long)((p.M + 127) / 128) * (whole_128(p.N) / 128) <= 8 * cus;
+  const bool few = few_128_tiles(p);
   Plain best = {PLAIN_RING, ring.tile, 0, few ? ring.us : INFINITY};
   auto offer = [&](PlainForm form, int tile, long rows_a, double us) { if (us < best.us) best = {form, tile, rows_a, us}; };
   // 128 columns over many rows stream the activations at the memory's rate: 256 x 128 tiles fetch each row once (the cut
@@ -1375,20 +1381,106 @@ static Plain choose_plain(const GemmParams& p) {
   return best;
 }
 
-// 256 x 128 tiles have two kernels with the same bits.  The persistent one (gemm_bf16_wide.hip) has the shorter start and
-// epilogue, the one-tile one (operands two slabs ahead in registers) the shorter slab while a CU holds one workgroup, and the depths
-// where they meet lie between the measured ones.  One round in the running encoder, us, one-tile | persistent: residual,
-// 1024 columns, K = 1024, 8192 rows 39.3 | 33.4, 3200 by 3200, 2304 rows 69.7 | 64.5, 1024 by 4096, 7168 rows 85.9 | 90.2, 1152 by 4352,
-// 6144 rows 90.9 | 97.1, 3200 by 12800, 2304 rows 223 | 250; q/k, 2048 by 1024, 4096 rows 26.3 | 25.4, 6400 by 3200, 1024
-// rows 54.4 | 56.7; projector, 2048 rows, 3584 by 3584 63.2 | 72.5, 4096 by 4096 74.3 | 84.1; GELU, 4096 by 1024, 2048 rows 27.0 | 25.4,
-// 5120 by 12800, 1536 rows 211 | 217.  More rounds of 128 columns: the 6B shape's FC2, 40960 rows, cut by columns 2742 | 2772.
+// One round of 256 x 128 tiles over long K is reported as the form with a workgroup per tile; it is the same launch.  (The kernel that
+// had one tile per workgroup is gone: with lines asked for ahead the persistent one is faster at every depth.  us, that kernel | this one:
+// residual, 1024 by 4096, 8192 rows 85 | 68, 3200 by 12800, 2048 rows 216 | 174, 1024 by 1024 37 | 29.)
 static bool one_tile_128(const GemmParams& p) {
   return p.epi != EPI_BIAS_POS && p.K >= (p.epi == EPI_BIAS_RESIDUAL ? 3584 : 2048);
 }
 
+// ---- second stage: the shape that runs ----
+// choose_plain weighs the forms there were when its estimates were fitted; this stage takes another shape of the persistent kernel where it
+// is faster on the present kernels.  us = c + ck kt + up (u + uk kt) + r (v + vk kt): kt 64-deep slabs, r tiles per CU, up its rounds
+// (64 x 64 tiles, which share a CU: at least 1).  Fitted to 444 products with cold operands, each in up to nine shapes (encoders of 1024,
+// 1152 and 3200 columns, 736 to 106496 rows; rms 2 to 7 %, no coefficient below zero): the shape with the smallest estimate is 0.3 %
+// behind the fastest on average, the first stage's form 3.2 %, and two launches for q/k and the value projection 14 %.  Which ring
+// tiles, only the first stage says: alone and in the running encoder they differ most.
+static void cut_columns(const GemmParams& p, GemmParams& a, GemmParams& b) {   // whole 256-wide tile columns, and the rest
+  const int n_a = p.N / 256 * 256;
+  a = b = p;
+  a.N = n_a; a.Npad = n_a;
+  b.N = p.N - n_a; b.Npad = 128;
+  b.W = p.W + (long)n_a * p.K; b.bias = p.bias + n_a; b.R = p.R + n_a;
+}
+enum Shape { S_64x64, S_128x64, S_128x128, S_256x128, S_256, S_224, S_192_ROWS, S_160_ROWS, S_192, N_SHAPES };
+constexpr int SHAPE_ROWS[N_SHAPES] = {64, 128, 128, 256, 256, 224, 192, 160, 256};
+constexpr int SHAPE_COLS[N_SHAPES] = {64, 64, 128, 128, 256, 256, 256, 256, 192};
+enum Kind { K_PAIR, K_BIAS, K_GELU, K_RESIDUAL, K_VT, N_KINDS };
+struct Fit { float c, ck, u, uk, v, vk; };   // all zero: not compiled for this kind
+constexpr Fit RING_FIT_64 = {0, 0.202f, 0.211f, 0.093f, 0.211f, 0.093f}, RING_FIT_128x64 = {0, 0.163f, 0, 0.173f, 0.890f, 0.119f},
+              RING_FIT_128 = {0, 0.101f, 0, 0.396f, 4.261f, 0.043f}, NO_FIT = {0, 0, 0, 0, 0, 0};
+static const Fit FITS[N_KINDS][N_SHAPES] = {
+    {RING_FIT_64, RING_FIT_128x64, RING_FIT_128, NO_FIT, {0, 0.226f, 4.699f, 0.788f, 0.840f, 0.571f}, {0, 0.100f, 4.297f, 0.871f, 0, 0.424f},
+     {0, 0.078f, 3.675f, 0.845f, 0, 0.321f}, {0, 0.131f, 2.768f, 0.769f, 0.698f, 0.268f}, {0.013f, 0.002f, 1.862f, 0.969f, 0.551f, 0.277f}},
+    {RING_FIT_64, RING_FIT_128x64, RING_FIT_128, {0, 0.099f, 1.078f, 0.716f, 0, 0.211f}, {0.985f, 0, 0.831f, 1.061f, 5.395f, 0.272f}},
+    {{0, 0.149f, 0.568f, 0.087f, 0.568f, 0.087f}, {0, 0.132f, 0, 0.247f, 2.094f, 0.023f}, {0, 0.181f, 0.460f, 0.390f, 5.288f, 0.009f},
+     {0, 0.168f, 0.076f, 0.874f, 2.415f, 0.038f}, {0, 0.162f, 6.232f, 0.835f, 0, 0.611f}, {0, 0.114f, 1.584f, 1.041f, 3.835f, 0.282f}},
+    {{0, 0.143f, 0.965f, 0, 0.265f, 0.207f}, {0, 0.178f, 0.119f, 0.211f, 2.808f, 0.095f}, {0, 0.042f, 0, 0.486f, 8.305f, 0.037f},
+     {3.683f, 0.003f, 0.601f, 0.813f, 8.356f, 0.141f}, {4.777f, 0, 1.948f, 1.191f, 19.052f, 0.139f}, {0.187f, 0.021f, 7.756f, 0.994f, 10.328f, 0.278f},
+     NO_FIT, NO_FIT, {0, 0, 6.672f, 0.951f, 10.647f, 0.200f}},
+    {RING_FIT_64, RING_FIT_128x64, RING_FIT_128, {0, 0, 2.208f, 0.825f, 0, 0.168f}, {0, 0, 3.195f, 1.110f, 4.354f, 0.227f}},
+};
+static Kind kind_of(const GemmParams& p) {
+  return p.n2_pad > 0 ? K_PAIR : p.epi == EPI_BIAS_RESIDUAL ? K_RESIDUAL : p.epi == EPI_VT ? K_VT : has_gelu(p.epi) ? K_GELU : K_BIAS;
+}
+static double shape_us(const GemmParams& p, int shape) {
+  const Fit& f = FITS[kind_of(p)][shape];
+  const int tm = SHAPE_ROWS[shape], tn = SHAPE_COLS[shape];
+  auto columns = [&](int n) { return ((tn <= 128 ? whole_128(n) : n) + tn - 1) / tn; };
+  const double kt = p.K / BK, cols = p.n2_pad > 0 ? (double)p.Npad / tn + columns(p.n2) : columns(p.N);
+  const double r = (double)((p.M + tm - 1) / tm) * cols / cu_count(), up = shape == S_64x64 ? fmax(1.0, r) : ceil(r);
+  return f.c + f.ck * kt + up * (f.u + f.uk * kt) + r * (f.v + f.vk * kt);
+}
+static bool shape_runs(const GemmParams& p, int shape) {
+  const Fit& f = FITS[kind_of(p)][shape];
+  if (f.uk == 0 && f.vk == 0) return false;
+  if (shape <= S_128x128) return few_128_tiles(p);
+  if (shape == S_256x128) return true;
+  const int tn = SHAPE_COLS[shape], n = p.n2_pad > 0 ? p.n2 : p.N, pad = p.n2_pad > 0 ? p.n2_pad : p.Npad;
+  if (p.n2_pad > 0 && p.Npad % tn != 0) return false;
+  if (shape == S_192 && (!tiles_192() || n % 192 != 0)) return false;
+  if (kind_of(p) == K_RESIDUAL && !persist_res()) return false;
+  return (n + tn - 1) / tn * tn <= pad;
+}
+static hipError_t launch_shape(const GemmParams& p, int shape, hipStream_t st) {
+  static const int tile[N_SHAPES] = {RING_64x64, RING_128x64, RING_128x128, WIDE_128, WIDE_256, WIDE_224, WIDE_192_ROWS, WIDE_160_ROWS, WIDE_192};
+  return shape <= S_128x128 ? launch_ring(p, tile[shape], st) : launch_wide(p, tile[shape], st);
+}
+static int ring_shape(int tile) { return tile == RING_64x64 ? S_64x64 : tile == RING_128x64 ? S_128x64 : S_128x128; }
+struct Choice { Plain first; int shape; double us; };   // shape -1: the first stage's
+static Choice choose(const GemmParams& p) {
+  const Plain c = choose_plain(p);
+  if (p.epi == EPI_BIAS_POS) return {c, -1, c.us};
+  double us = INFINITY;
+  switch (c.form) {
+    case PLAIN_RING: us = shape_us(p, ring_shape(c.tile)); break;
+    case PLAIN_256x128: us = shape_us(p, S_256x128); break;
+    case PLAIN_192: us = shape_us(p, S_192); break;
+    case PLAIN_256: {
+      GemmParams a = p, b = p;
+      if (c.rows_a > 0) { a.M = (int)(c.rows_a * BM); b.M = p.M - a.M; }
+      us = shape_us(a, S_256) + (c.rows_a > 0 ? 2.5 + shape_us(b, ring_shape(c.tile)) : 0.0);
+      break;
+    }
+    case PLAIN_COLUMNS: {
+      GemmParams a, b;
+      cut_columns(p, a, b);
+      us = choose(a).us + choose(b).us + 2.5;
+      break;
+    }
+  }
+  Choice best = {c, -1, us * 0.97};   // of two forms closer than that the first stage's stays
+  for (int shape = S_256x128; shape < N_SHAPES; ++shape)   // which ring tiles, the first stage says: its estimates are from the running encoder
+    if (shape_runs(p, shape) && shape_us(p, shape) < best.us) best = {c, shape, shape_us(p, shape)};
+  if (best.shape < 0) best.us = us;
+  return best;
+}
+
 static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
   const bool residual = p.epi == EPI_BIAS_RESIDUAL;
-  const Plain c = choose_plain(p);
+  const Choice ch = choose(p);
+  if (ch.shape >= 0) return launch_shape(p, ch.shape, st);
+  const Plain& c = ch.first;
   GemmParams a = p, b = p;
   auto wide = [&](const GemmParams& g) {
     if (!residual || persist_res()) return launch_wide(g, WIDE_256, st);
@@ -1396,7 +1488,7 @@ static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
   };
   switch (c.form) {
     case PLAIN_RING: return launch_ring(p, c.tile, st);
-    case PLAIN_256x128: return one_tile_128(p) ? dispatch<128, 512, 64>(without_padded_columns(p), st) : launch_wide(p, WIDE_128, st);
+    case PLAIN_256x128: return launch_wide(p, WIDE_128, st);
     case PLAIN_192: return launch_wide(p, WIDE_192, st);
     case PLAIN_256: {
       if (c.rows_a == 0) return wide(p);
@@ -1411,10 +1503,7 @@ static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
       return e != hipSuccess ? e : launch_ring(b, c.tile, st);
     }
     case PLAIN_COLUMNS: {
-      const int n_a = p.N / 256 * 256;
-      a.N = n_a; a.Npad = n_a;
-      b.N = p.N - n_a; b.Npad = 128;
-      b.W = p.W + (long)n_a * p.K; b.bias = p.bias + n_a; b.R = p.R + n_a;
+      cut_columns(p, a, b);
       const hipError_t e = dispatch_plain(a, st);
       return e != hipSuccess ? e : dispatch_plain(b, st);
     }
@@ -1422,20 +1511,44 @@ static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
   return hipErrorInvalidValue;
 }
 
-// The q/k and the value projection as one launch of ring tiles, where that is estimated to take less than the two
-// launches each in its own best form and the 2.5 us a second launch costs (1024-wide encoder, us per layer: one slice 21.0
-// -> 15.2, five 58.9 -> 45.6, ten 85.5 -> 82.6; 13 slices 98.3 as two launches, 107.6 as one).
-static int pair_columns(const GemmParams& p) { return p.Npad + whole_128(p.n2); }
+// The q/k and the value projection as one launch, where that is estimated to take less than the two launches each in its own
+// best shape and the 2.5 us a second launch costs.  us, cold, two launches | one: 1024-wide encoder, one slice 14.7 | 11.3 (ring
+// tiles), three 29.4 | 21.7 (192 x 256 tiles), ten 81.8 | 55.7, 13 78.4 | 75.9 (224 x 256), 26 155 | 135, 104 551 | 549; 1152-wide, ten
+// 85.9 | 72.2 (256 x 192); 3200-wide, 40 1954 | 1830.
+static bool residual_or_gelu(int epi) { return epi == EPI_BIAS_RESIDUAL || has_gelu(epi); }
+static bool pair_shape(const GemmParams& p) {
+  return p.epi == EPI_BIAS && p.n2_pad > 0 && p.n2_pad % 128 == 0 && p.Npad % 128 == 0 && ring_has(p) && !p.row_map;
+}
+struct Pair { int shape; double us; };
+static Pair choose_pair(const GemmParams& p) {
+  Pair best = {-1, INFINITY};
+  const int ring = ring_shape(best_ring(p.M, p.Npad + whole_128(p.n2), p.K, EPI_BIAS).tile);
+  if (shape_runs(p, ring)) best = {ring, shape_us(p, ring)};
+  for (int shape = S_256x128; shape < N_SHAPES; ++shape)
+    if (shape_runs(p, shape) && shape_us(p, shape) < best.us) best = {shape, shape_us(p, shape)};
+  return best;
+}
 bool bf16_gemm_pair_fits(const GemmParams& p) {
-  if (p.cfg != 0 || p.epi != EPI_BIAS || p.n2_pad <= 0 || p.n2_pad % 128 != 0 || p.Npad % 128 != 0 || !ring_has(p)) return false;
+  if (p.cfg != 0 || !pair_shape(p)) return false;
   GemmParams q = p, v = p;
   q.n2_pad = v.n2_pad = 0; v.epi = EPI_VT; v.N = p.n2; v.Npad = p.n2_pad;
-  return best_ring(p.M, pair_columns(p), p.K, EPI_BIAS).us < choose_plain(q).us + choose_plain(v).us + 2.5;
+  return choose_pair(p).us < choose(q).us + choose(v).us + 2.5;
 }
 
 bool bf16_gemm_on_64x64(const GemmParams& p) {
-  const Plain c = choose_plain(p);
-  return c.form == PLAIN_RING && c.tile == RING_64x64;
+  const Choice c = choose(p);
+  return c.shape < 0 && c.first.form == PLAIN_RING && c.first.tile == RING_64x64;
+}
+
+// For tests: the shape that runs, by its number in GemmParams::cfg; 0: more than one launch (of a pair: two products)
+int bf16_gemm_shape(const GemmParams& p) {
+  static const int number[N_SHAPES] = {11, 13, 14, 1, 9, 15, 16, 17, 12};
+  if (p.n2_pad > 0) return bf16_gemm_pair_fits(p) ? number[choose_pair(p).shape] : 0;
+  const Choice c = choose(p);
+  if (c.shape >= 0) return c.shape == S_256 && p.epi == EPI_BIAS_RESIDUAL ? 10 : number[c.shape];
+  long rows = 0;
+  const int form = bf16_gemm_choice(p, &rows);
+  return rows < p.M ? 0 : form;
 }
 
 // For tests: the form choose_plain takes, by its number in GemmParams::cfg (10 / 9: 256 x 256 tiles of residual / other
@@ -1462,13 +1575,26 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
     return hipErrorInvalidValue;
   const bool f32_out = p.epi == EPI_BIAS_RESIDUAL || p.epi == EPI_BIAS_POS;
   if (!f32_out && p.epi != EPI_VT && (p.N % 8 != 0 || p.ldc % 8 != 0)) return hipErrorInvalidValue;
-  if (p.n2_pad > 0)
-    return bf16_gemm_pair_fits(p) ? launch_ring(p, best_ring(p.M, pair_columns(p), p.K, EPI_BIAS).tile, st) : hipErrorInvalidValue;
+  if (p.n2_pad > 0) {
+    if (!pair_shape(p)) return hipErrorInvalidValue;
+    switch (p.cfg) {
+      case 0: { const Pair c = choose_pair(p); return c.shape < 0 ? hipErrorInvalidValue : launch_shape(p, c.shape, st); }
+      case 11: return launch_ring(p, RING_64x64, st);
+      case 13: return launch_ring(p, RING_128x64, st);
+      case 14: return launch_ring(p, RING_128x128, st);
+      case 9: return launch_wide(p, WIDE_256, st);
+      case 12: return launch_wide(p, WIDE_192, st);
+      case 15: return launch_wide(p, WIDE_224, st);
+      case 16: return launch_wide(p, WIDE_192_ROWS, st);
+      case 17: return launch_wide(p, WIDE_160_ROWS, st);
+    }
+    return hipErrorInvalidValue;
+  }
   switch (p.cfg) {
     case 1: return ring_has(p) ? launch_wide(p, WIDE_128, st) : dispatch<128, 512, 64>(p, st);
     case 2: return ring_has(p) ? launch_ring(p, RING_128x128, st) : dispatch_128_fold<0>(p, st);
     case 3: if (!ring_has(p)) { if (p.K % 256 == 0) return dispatch_128_fold<2>(p, st); break; } return launch_ring(p, RING_128x128, st);
-    case 4: if (ring_has(p) && p.epi != EPI_BIAS_POS) return dispatch<128, 512, 64>(without_padded_columns(p), st); break;
+    case 4: if (ring_has(p) && p.epi != EPI_BIAS_POS) return launch_wide(p, WIDE_128, st, 1 << 30); break;
     case 6: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 0>(p, st); break;
     case 7: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 1>(p, st); break;
     case 8: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 3>(p, st); break;
@@ -1477,6 +1603,7 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
     case 11: if (ring_has(p)) return launch_ring(p, RING_64x64, st); break;
     case 13: if (ring_has(p)) return launch_ring(p, RING_128x64, st); break;
     case 14: if (ring_has(p)) return launch_ring(p, RING_128x128, st); break;
+    case 15: if (p.Npad % 256 == 0 && ring_has(p) && (residual_or_gelu(p.epi))) return launch_wide(p, WIDE_224, st); break;
     case 12: if (p.N % 192 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_wide(p, WIDE_192, st); break;
   }
   if (ring_has(p)) return dispatch_plain(p, st);

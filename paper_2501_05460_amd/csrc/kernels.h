@@ -92,11 +92,21 @@ bool bf16_gemm_pair_fits(const GemmParams& p);
 enum RingTile { RING_64x64 = 0, RING_128x64 = 1, RING_128x128 = 2 };
 hipError_t bf16_gemm_ring(const GemmParams& p, int tile, hipStream_t st);
 hipError_t bf16_gemm_ring_init();   // part of bf16_gemm_init
-// the product on large tiles with persistent workgroups (gemm_bf16_wide.hip), any epilogue without n2_pad; WIDE_192: RESIDUAL only
-enum WideTile { WIDE_256 = 0, WIDE_192 = 1, WIDE_128 = 2 };
+// The product on large tiles with persistent workgroups (gemm_bf16_wide.h): 256 x 256 tiles (waves of 128 x 64) and 256 x 128 (64 x 64)
+// for every epilogue; 224 x 256 (112 x 64) for the residual and the activation epilogues; 256 x 192 (64 x 96) for residual products
+// of widths like 1152, which is six such tile columns and four and a half 256-wide ones; and, with n2_pad > 0, two products
+// in one launch on 256, 224, 192 or 160 x 256 and 256 x 192 tiles.
+enum WideTile { WIDE_256 = 0, WIDE_192 = 1, WIDE_128 = 2, WIDE_224 = 3, WIDE_192_ROWS = 4, WIDE_160_ROWS = 5 };
 hipError_t bf16_gemm_wide(const GemmParams& p, int tile, int cus, hipStream_t st);
+hipError_t bf16_gemm_wide_gelu(const GemmParams& p, int tile, int cus, hipStream_t st);   // its parts, one file each
+hipError_t bf16_gemm_wide_residual(const GemmParams& p, int tile, int cus, hipStream_t st);
+hipError_t bf16_gemm_wide_pair(const GemmParams& p, int tile, int cus, hipStream_t st);
+hipError_t bf16_gemm_wide_gelu_init();
+hipError_t bf16_gemm_wide_residual_init();
+hipError_t bf16_gemm_wide_pair_init();
 hipError_t bf16_gemm_wide_init();   // part of bf16_gemm_init
-int bf16_gemm_choice(const GemmParams& p, long* rows);   // the form of a product without a folded pre-norm (tests)
+int bf16_gemm_choice(const GemmParams& p, long* rows);   // the first stage's form of a product without a folded pre-norm (tests)
+int bf16_gemm_shape(const GemmParams& p);                // the shape that runs (tests)
 long bf16_gemm_kernel_launches();   // kernels launched by bf16_gemm on the calling host thread so far (a figure for the profiling hooks)
 hipError_t bf16_gemm_init();  // raises the dynamic-LDS limit of the kernels (idempotent: safe from any thread, any number of times)
 

@@ -354,6 +354,34 @@ def test_persistent_tiles_beyond_the_first_agree_bit_for_bit(epi, M, N, forms, K
         assert float((got.double().cpu() - want).norm() / want.norm()) < (1e-5 if epi == 4 else 4e-3)
 
 
+@pytest.mark.parametrize("epi,M,N,K", [(1, 1, 256, 128), (2, 224, 512, 256), (3, 225, 256, 128), (3, 1000, 512, 384), (1, 7300, 2048, 128),
+                                       (3, 14600, 1024, 128), (3, 14592, 1024, 640)])
+def test_224_row_tiles_agree_bit_for_bit(epi, M, N, K):
+    """Tiles of a height that does not divide 256: the last one computes rows of the tile above again, which a residual product must
+    add once.  One tile, a last tile of one row, whole and ragged rows, more tiles than CUs."""
+    g = torch.Generator().manual_seed(M + N + K + epi)
+    A, W = torch.randn(M, K, generator=g).mul_(0.5).bfloat16().cuda(), torch.randn(N, K, generator=g).mul_(0.05).bfloat16().cuda()
+    bias = torch.randn(N, generator=g).mul_(0.1).cuda()
+    r0 = torch.randn(M, N, generator=g).cuda() if epi == 3 else None
+    run = lambda form: B.op_gemm_bf16_form(A, W, bias, epi, form, None if r0 is None else r0.clone())
+    assert torch.equal(run(15), run(6))
+
+
+@pytest.mark.parametrize("M,N,n2,K,n_tok", [(8, 256, 256, 128, 8), (248, 256, 384, 128, 248), (1032, 2304, 1152, 256, 1032), (2400, 768, 384, 128, 600),
+                                            (1736, 512, 256, 640, 248), (7344, 2304, 1152, 128, 816), (10240, 2048, 1024, 128, 1024)])
+def test_two_products_in_one_launch_agree_bit_for_bit(M, N, n2, K, n_tok):
+    """Every tile of the pair: ring tiles, 256, 224, 192 and 160 x 256 and 256 x 192.  One tile and more than CUs, slices that end inside a
+    tile, value columns that leave a last tile half empty.  Reference: the two products in a launch each, one workgroup per tile."""
+    g = torch.Generator().manual_seed(M + N + K)
+    A, W = torch.randn(M, K, generator=g).mul_(0.5).bfloat16().cuda(), torch.randn(N + n2, K, generator=g).mul_(0.05).bfloat16().cuda()
+    bias = torch.randn(N + n2, generator=g).mul_(0.1).cuda()
+    c = B.op_gemm_bf16_form(A, W[:N], bias[:N], 0, 6)
+    v = B.op_gemm_bf16_form(A, W[N:].contiguous(), bias[N:].contiguous(), 5, 4, n_tok=n_tok)
+    for form in (9, 11, 13, 14, 15, 16, 17) + ((12,) if N % 192 == 0 and n2 % 192 == 0 else ()):
+        got_c, got_v = B.op_gemm_bf16_pair(A, W, bias, N, n_tok, form)
+        assert torch.equal(got_c, c) and torch.equal(got_v, v), form
+
+
 @pytest.mark.parametrize("M,N,K", [(256, 384, 128), (1000, 1152, 256), (2900, 1152, 1152), (77, 384, 384), (11100, 1152, 128)])
 def test_gemm_192_wide_tiles_agree_bit_for_bit(M, N, K):
     """The residual product on 256 x 192 tiles (widths that are whole multiples of 192 and not of 256) leaves the
