@@ -165,7 +165,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 // QT sub-tiles of 16 queries per wave, four waves.
 // LEAN: one step's S^T registers and weights only, no step issued ahead, so that four (head dim 64), three (72, 96) workgroups
 // share a CU (112, 142, 144 registers; up to 128, 155, 162 with MASK and PAIRED); at head dim 128, where LDS holds two, the
-// S^T product of step i + 1 is issued ahead of the softmax of step i.
+// S^T product of step i + 1 is issued ahead of the softmax of step i.  So it is with 16 queries per wave at head dims 64 and 96, whose
+// few waves leave the registers (us, lean | ahead: 64, one slice of 1024 tokens 18.7 | 17.0, three 28.8 | 27.1; 96, one 22.6 | 20.8, three
+// 35.0 | 32.4; 72 and masked slices: equal, lean).  A third LDS buffer, loads two blocks ahead, gives nothing: a step is the wave's chain.
 // PAIRED: a lane's eight keys of a step are 16 (l / 32) + 4 (l / 16 % 2) + {0..3, 8..11}, V^T fragments are two 8-byte halves, and
 // the row sum on the VALU runs over a lane pair's sixteen weights in a row: the order of summation of a kernel on
 // v_mfma_f32_32x32x16_bf16, whose bits this gives.  For calls whose output is converted to MXFP8: there a change of the last
@@ -184,7 +186,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
                                                         long ld_o, unsigned char* __restrict__ oq,
                                                         unsigned* __restrict__ so, long ld_so) {
   using SM = AttnSmem<HD>;
-  constexpr bool LEAN = HD <= 96;
+  constexpr bool LEAN = HD <= 96 && !(QT == 1 && HD != 72 && !MASK);
   constexpr int BQ = 64 * QT;   // queries per workgroup
   constexpr int KS = SM::KS, OB = SM::OB;
   constexpr int KCH = HD / 8;   // 16-byte chunks per key row

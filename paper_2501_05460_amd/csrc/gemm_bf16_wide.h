@@ -447,22 +447,7 @@ hipError_t launch_wide(const GemmParams& p, int cus, hipStream_t st) {
   if (cols_last * S::COLS > pad_last || (DUAL && p.Npad % S::COLS != 0)) return hipErrorInvalidValue;
   const int gm = (p.M + S::ROWS - 1) / S::ROWS, gn = (DUAL ? p.Npad / S::COLS : 0) + cols_last, n_tiles = gm * gn;
   if (n_tiles == 0) return hipSuccess;
-  // Band width.  The up to 32 workgroups an XCD runs at once are consecutive tiles of a band and move through K together.
-  // In a band w wide they lie in 1 + 31 / w tile rows on average, 32 / w where that is whole, and w columns: so many panels
-  // the L2 pulls over the fabric per round, the weight panels only once while the band's fit its 4 MiB.  The last band is
-  // what is left over: 16 columns as 4 bands of 4, not as 5, 5, 5 and 1 (K = 1024, 106496 rows, GELU: 774 -> 745 us).
-  const double panel_a = (double)S::ROWS * p.K * sizeof(bf16_t), panel_w = (double)S::COLS * p.K * sizeof(bf16_t);
-  const int at_once = n_tiles < 256 ? (n_tiles + 7) / 8 : 32;
-  auto band_cost = [&](int w) {   // per column of the band
-    const double rows = at_once % w == 0 ? at_once / w : 1.0 + (at_once - 1.0) / w;
-    return w * (rows * panel_a + (w * panel_w <= 2.5 * (1 << 20) ? 0.0 : w * panel_w));
-  };
-  int gw = 1;
-  double best = 1e30;
-  for (int c = 1; c <= gn && c <= 32; ++c) {
-    const double cost = gn / c * band_cost(c) + (gn % c ? band_cost(gn % c) : 0.0);
-    if (cost < best * 0.999) { best = cost; gw = c; }
-  }
+  int gw = band_columns(gn, (double)S::ROWS * p.K * sizeof(bf16_t), (double)S::COLS * p.K * sizeof(bf16_t), n_tiles < 256 ? (n_tiles + 7) / 8 : 32);
   if (p.band > 0 && p.band <= gn) gw = p.band;
   // one round of short tiles has nothing to gain (13312 rows, 1024 x 1024 residual, us without | with: 40.7 | 41.6)
   const int ahead = n_tiles > cus || p.K >= 2048;

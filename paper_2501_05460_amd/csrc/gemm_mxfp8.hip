@@ -255,7 +255,25 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
       if (lpos < n_tiles) aim();
     }
   };
-  auto wait_all = [&]() { __builtin_amdgcn_s_waitcnt(0x7 << 4); };   // vmcnt(0), lgkmcnt(0)
+  auto wait_all = [&](bool but_one) {   // LDS reads and all vector-memory accesses, or all but the newest
+    if (but_one) __builtin_amdgcn_s_waitcnt(1 | (0x7 << 4));
+    else __builtin_amdgcn_s_waitcnt(0x7 << 4);
+  };
+  // The lines of the slab behind the newest one under way are asked for a slab ahead, each by one workgroup of the XCD (see
+  // gemm_bf16_wide.h), with a dword a lane into the wave's staging area, which nobody uses until the epilogue.
+  const bool a_half = wave < NT / 128;
+  unsigned t_voff;
+  {
+    const int slot = blockIdx.x >> 3, lt = tid & (NT / 2 - 1), parts = a_half ? gw : max(1, (int)((gridDim.x + 7) >> 3) / gw), rows = a_half ? BM : BN;
+    const int n = (rows + parts - 1) / parts, row = min((a_half ? slot % gw : slot / gw % parts) * n + lt * n / (NT / 2), rows - 1);
+    t_voff = (unsigned)row * (unsigned)(a_half ? p.lda : (long)p.K);
+  }
+  bool touched = false;   // the newest access is such a load
+  auto touch = [&]() {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %0, %1"
+                 :: "v"(t_voff), "s"(a_half ? ga : gb), "s"(lds0 + 2 * SLAB + 2 * SCALES + wave * STAGE) : "memory", "m0");
+    touched = true;
+  };
 
   // Fragments: 16-byte chunks lg and 4 + lg of a row (k = 16 lg .. + 15 and 64 + 16 lg .. + 15), byte lg of its scale word.
   // Addresses of fragment 0 in the buffer of the slab at hand; the buffers lie a power of two apart.
@@ -302,7 +320,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
     for (int i = 0; i < LPS; ++i) issue(i);
     advance();
   }
-  wait_all();
+  wait_all(false);
   __syncthreads();
 
   for (int pos = blockIdx.x;;) {
@@ -349,7 +367,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
           __builtin_amdgcn_sched_barrier(0);
         });
       });
-      wait_all();        // the wave's part of the next slab has landed, its fragments of this one are in registers
+      wait_all(touched);   // the wave's part of the next slab has landed, its fragments of this one are in registers
       __syncthreads();   // everyone's has, and everyone holds this slab's fragments: its buffer is free
       other_buffer();
       if constexpr (LAST) {
@@ -369,11 +387,17 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
         if constexpr (!LAST) read_b(j);
         __builtin_amdgcn_sched_barrier(0);
       });
-      if (more) { issue(LPS - 1); advance(); }
+      touched = false;
+      if (more) {
+        issue(LPS - 1);
+        advance();
+        if (!LAST && lpos < n_tiles) touch();
+      }
     };
 #pragma clang loop unroll(disable)
     for (int kt = 0; kt < KT - 1; ++kt) slab(std::false_type{});
     slab(std::true_type{});
+    __builtin_amdgcn_s_waitcnt((LPS & 0xf) | ((LPS >> 4) << 14) | (0x7 << 4) | (0xf << 8));   // the last touch has left the staging area
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -543,7 +567,7 @@ template <int EPI, int TM, int WAVES_M, int WAVES_N>
 hipError_t launch_tile(const MxGemmParams& p, int cols, hipStream_t st) {
   using T = MxTile<TM, WAVES_M, WAVES_N>;
   const int gm = (p.M + T::BM - 1) / T::BM, gn = (cols + T::BN - 1) / T::BN, n_tiles = gm * gn, slots = cu_count() * (512 / T::NT);
-  const int gw = gn <= 1024 / T::BN ? gn : 1024 / T::BN;
+  const int at_once = 32 * (512 / T::NT), gw = band_columns(gn, (double)T::BM * p.K, (double)T::BN * p.K, n_tiles < 8 * at_once ? (n_tiles + 7) / 8 : at_once);
   if (gn * T::BN > p.Npad) return hipErrorInvalidValue;
   k_gemm_mxfp8<EPI, TM, WAVES_M, WAVES_N><<<dim3((unsigned)(n_tiles < slots ? n_tiles : slots)), dim3(T::NT), T::LDS, st>>>(p, gm, gw, gn, n_tiles);
   return hipGetLastError();
