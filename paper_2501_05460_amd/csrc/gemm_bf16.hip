@@ -1429,7 +1429,10 @@ static double shape_us(const GemmParams& p, int shape) {
   auto columns = [&](int n) { return ((tn <= 128 ? whole_128(n) : n) + tn - 1) / tn; };
   const double kt = p.K / BK, cols = p.n2_pad > 0 ? (double)p.Npad / tn + columns(p.n2) : columns(p.N);
   const double r = (double)((p.M + tm - 1) / tm) * cols / cu_count(), up = shape == S_64x64 ? fmax(1.0, r) : ceil(r);
-  return f.c + f.ck * kt + up * (f.u + f.uk * kt) + r * (f.v + f.vk * kt);
+  // Among other kernels a launch of the persistent one takes 4 us longer than among its own kind, where the fit was taken (3 slices of the
+  // 1024-wide encoder: q/k/v on 160 x 256 tiles 25.5 for 21.7 us, FC1 on 224 x 256 29.5 for 25.6); one of ring tiles does not (29.7, 30.3).
+  const double start = shape >= S_256x128 ? 4.0 : 0.0;
+  return start + f.c + f.ck * kt + up * (f.u + f.uk * kt) + r * (f.v + f.vk * kt);
 }
 static bool shape_runs(const GemmParams& p, int shape) {
   const Fit& f = FITS[kind_of(p)][shape];
