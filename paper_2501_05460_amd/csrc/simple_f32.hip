@@ -73,7 +73,7 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 1) void k_f32_gemm(const F32Norm 
   const int r16 = lane & 15, q = lane >> 4;
   const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
   const int chunks = (K + 15) / 16, share = (chunks + 3) / 4;
-  const int c_begin = wave * share, c_end = min(chunks, c_begin + share);
+  const int c_begin = __builtin_amdgcn_readfirstlane(wave * share), c_end = min(chunks, c_begin + share);
   auto load = [&](const float* base, long ld, int row, int rows, int c) -> f32x4 {
     f32x4 v = {0.f, 0.f, 0.f, 0.f};
     const int k = c * 16 + 4 * q;
@@ -111,18 +111,21 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 1) void k_f32_gemm(const F32Norm 
 #pragma unroll
       for (int i = 0; i < R; ++i) w[S][g][i] = load(W, K, n0 + 16 * i + r16, N, c0 + g);
   };
-  // chunks g0 .. g0 + G - 1 of operand set A against weight set S
-  auto multiply = [&](auto set_a, auto set_w, int g0) {
+  // chunks g0 .. g0 + G - 1 of operand set A against weight set S, the first n of them: the others lie past the share and are zeros (K = 192
+  // fills half a batch; M = 256, us, all | n of them: N = 768 with a norm 6.3 | 5.7, N = 192 3.5 | 3.3; M = 1024 12.5 | 11.0, 5.2 | 4.7)
+  auto multiply = [&](auto set_a, auto set_w, int g0, int n) {
     constexpr int SA = decltype(set_a)::value, S = decltype(set_w)::value;
 #pragma unroll
     for (int g = 0; g < G; ++g)
+      if (g < n) {   // uniform
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int i = 0; i < R; ++i)
+          for (int i = 0; i < R; ++i)
 #pragma unroll
-          for (int j = 0; j < R; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[SA][g0 + g][i][e], w[S][g][j][e], acc[i][j], 0, 0, 0);
+            for (int j = 0; j < R; ++j)
+              acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[SA][g0 + g][i][e], w[S][g][j][e], acc[i][j], 0, 0, 0);
+      }
   };
   using S0 = std::integral_constant<int, 0>;
   using S1 = std::integral_constant<int, 1>;
@@ -180,23 +183,22 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 1) void k_f32_gemm(const F32Norm 
           for (int e = 0; e < 4; ++e) a[0][g][i][e] = fmaf((a[0][g][i][e] - mean[i]) * rstd[i], gm[e], bt[e]);
       }
   }
-  // chunks past the share are zeros
   if constexpr (NORM) {
     static_assert(F32_GROUP % G == 0, "whole batches");
     for_const<F32_GROUP / G>([&](auto b_) {
       constexpr int b = decltype(b_)::value;
       if constexpr ((b + 1) * G < F32_GROUP) fetch_w(std::integral_constant<int, 1 - b % 2>{}, c_begin + (b + 1) * G);
-      multiply(S0{}, std::integral_constant<int, b % 2>{}, b * G);
+      multiply(S0{}, std::integral_constant<int, b % 2>{}, b * G, c_end - c_begin - b * G);
     });
   } else {
     for (int c = c_begin; c < c_end; c += 2 * G) {
       fetch_a(S1{}, c + G, G);
       fetch_w(S1{}, c + G);
-      multiply(S0{}, S0{}, 0);
+      multiply(S0{}, S0{}, 0, c_end - c);
       if (c + G >= c_end) break;
       fetch_a(S0{}, c + 2 * G, G);
       fetch_w(S0{}, c + 2 * G);
-      multiply(S1{}, S1{}, 0);
+      multiply(S1{}, S1{}, 0, c_end - c - G);
     }
   }
   // result register e of lane l: row 4 (l / 16) + e, column l % 16
@@ -394,13 +396,21 @@ __global__ __launch_bounds__(128) void k_f32_attention(const float* __restrict__
 
 // The same on v_mfma_f32_16x16x4_f32: one workgroup per 16 queries of one (slice, head).  The query-per-block kernel
 // above reads every key and value once per query and its time is one thread's chain over head dim and keys; here 16
-// queries share them and the four waves split the keys of the first product and the head dim of the second (one slice of
-// the tiny configuration, 256 tokens, 3 heads of 64: 30 us -> 12 us).  The logits [16][keys] stay in LDS; keys past N count
-// as weight zero and their rows are not read.  hd % 16 == 0, rows 16-byte aligned.
+// queries share them and the four waves split the keys of the first product and, at head dim 64, of the second, else its head
+// dim.  What bounds it is the chain of one workgroup: one slice of the tiny configuration (256 tokens, 3 heads of 64, 48 workgroups)
+// 30 us with the kernel above, 11.1 with four-byte loads of the values and the softmax through LDS shuffles one logit at a time, 8.3 now
+// (1024 tokens 34.0 -> 26.4; of 11.1 us the second product took 4.6, the softmax 2.6, the first product 2.5).  Values asked for
+// ahead of the first product: 9.0.  The logits [16][keys] stay in LDS; keys past N count as weight zero and their rows are not read.
+// hd % 16 == 0, rows 16-byte aligned.
 // A lane's operand registers as in the GEMM: row l % 16, elements 4 (l / 16) .. + 3 of a 16-element chunk.
 constexpr int F32_ATTN_MAX_KEYS = 2048;   // 16 rows of logits in LDS
+constexpr int F32_ATTN_PART = 4 * 16 * 64;   // head dim 64: the waves' shares of the output
 // HC: head dim / 16 when it is compiled in (the loads of a wave's keys and values are then issued as batches: 15.3 -> 11.8 us),
-// 0: any.
+// 0: any, and head dim 64 where values or output rows are not 16-byte aligned.
+template <int N>
+__device__ __forceinline__ float row_turn(float x) {   // of lane (l + N) % 16 in a row of 16
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x120 + N, 0xf, 0xf, true));
+}
 template <int HC>
 __global__ __launch_bounds__(256) void k_f32_attention_mfma(const float* __restrict__ q, long ld_q, int q_shared,
                                                             const float* __restrict__ k, const float* __restrict__ v,
@@ -459,83 +469,132 @@ __global__ __launch_bounds__(256) void k_f32_attention_mfma(const float* __restr
       }
     }
   }
-  // the values of the first 256 keys, for the wave's first head-dim block, are on their way during the softmax
+  // Output, head dim 64: wave w takes keys 64 u + 16 w .. + 15 of every group of 64 and all of the head dim: a lane loads 16 bytes of a
+  // key's row and supplies them as column l % 16 of four blocks, feature 4 (l % 16) + c in block c.  (The chain of a 16-key block
+  // over the groups is the one that the four chains of a wave per head-dim block below have: the same bits.)  The values of
+  // the first 256 keys are on their way during the softmax.
   constexpr int VG = HC > 0 ? 4 : 0;
-  float vpre[VG > 0 ? VG : 1][4][4];
-  auto vload = [&](const float* vp, int j0, float (&b)[4][4]) {
+  f32x4 vpre[VG > 0 ? VG : 1][4];
+  auto vrows = [&](int u, f32x4 (&b)[4]) {
 #pragma unroll
-    for (int c = 0; c < 4; ++c)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { const int j = j0 + 16 * c + 4 * g + e; b[c][e] = j < N ? vp[(long)j * ld] : 0.f; }
+    for (int e = 0; e < 4; ++e) {
+      const int j = 64 * u + 16 * wave + 4 * g + e;
+      b[e] = j < N ? *reinterpret_cast<const f32x4*>(v + (row0 + j) * ld + (long)h * hd + 4 * r16) : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
   };
   if constexpr (HC > 0) {
-    if (wave * 16 < hd) {
 #pragma unroll
-      for (int u = 0; u < VG; ++u) vload(v + row0 * ld + (long)h * hd + wave * 16 + r16, 64 * u, vpre[u]);
-    }
+    for (int u = 0; u < VG; ++u) vrows(u, vpre[u]);
   }
   __syncthreads();
-  // softmax: 16 threads per query
+  // softmax: 16 threads per query, 16 logits of each at a time; exchanges inside a row of 16 lanes (turning by 8, 4, 2 and 1 adds what
+  // the exchange with lane ^ 8, ^ 4, ^ 2 and ^ 1 does)
   {
     float* row = sm + (tid >> 4) * LD;
     const int j0 = tid & 15;
-    float mx = -INFINITY;
-    for (int j = j0; j < NP; j += 16) mx = fmaxf(mx, row[j]);
+    float x[16], mx = -INFINITY;
+    auto fetch = [&](int b) {
 #pragma unroll
-    for (int s = 8; s > 0; s >>= 1) mx = fmaxf(mx, __shfl_xor(mx, s, 64));
-    float sum = 0.f;
-    for (int j = j0; j < NP; j += 16) {
-      const float e = expf(row[j] - mx);
-      row[j] = e;
-      sum += e;
+      for (int i = 0; i < 16; ++i) x[i] = b + 16 * i < NP ? row[b + 16 * i + j0] : -INFINITY;   // NP % 16 == 0: uniform
+    };
+    for (int b = 0; b < NP; b += 256) {
+      fetch(b);
+#pragma unroll
+      for (int i = 0; i < 16; ++i) mx = fmaxf(mx, x[i]);
     }
+    mx = fmaxf(mx, row_turn<8>(mx));
+    mx = fmaxf(mx, row_turn<4>(mx));
+    mx = fmaxf(mx, row_turn<2>(mx));
+    mx = fmaxf(mx, row_turn<1>(mx));
+    float sum = 0.f;
+    for (int b = 0; b < NP; b += 256) {
+      if (NP > 256) fetch(b);
 #pragma unroll
-    for (int s = 8; s > 0; s >>= 1) sum += __shfl_xor(sum, s, 64);
+      for (int i = 0; i < 16; ++i)
+        if (b + 16 * i < NP) {
+          x[i] = expf(x[i] - mx);
+          row[b + 16 * i + j0] = x[i];
+          sum += x[i];
+        }
+    }
+    sum += row_turn<8>(sum);
+    sum += row_turn<4>(sum);
+    sum += row_turn<2>(sum);
+    sum += row_turn<1>(sum);
     if (j0 == 0) inv[tid >> 4] = 1.0f / sum;
   }
   __syncthreads();
-  // output: wave w takes head-dim blocks w, w + 4, ..; lane l supplies keys 4 (l / 16) + e of column l % 16
-  for (int d0 = wave * 16; d0 < hd; d0 += 64) {
-    const float* vp = v + row0 * ld + (long)h * hd + d0 + r16;
+  if constexpr (HC > 0) {
+    static_assert(HC == 4, "four blocks of 16 columns, 16 bytes a lane");
     f32x4 acc[4];
 #pragma unroll
     for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
-    auto group = [&](int j0, const float (&b)[4][4]) {   // four chains, one per 16-key block of a group of 64 keys
-      f32x4 a[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        const int j = j0 + 16 * c + 4 * g;
-        a[c] = j < NP ? *reinterpret_cast<const f32x4*>(sm + r16 * LD + j) : f32x4{0.f, 0.f, 0.f, 0.f};
-      }
+    auto group = [&](int u, const f32x4 (&b)[4]) {
+      const int j = 64 * u + 16 * wave + 4 * g;
+      const f32x4 a = 64 * u + 16 * wave < NP ? *reinterpret_cast<const f32x4*>(sm + r16 * LD + j) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int e = 0; e < 4; ++e)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][e], b[c][e], acc[c], 0, 0, 0);
+        for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[e], b[e][c], acc[c], 0, 0, 0);
     };
-    int j0 = 0;
-    if (HC > 0 && d0 == wave * 16) {
 #pragma unroll
-      for (int u = 0; u < VG; ++u) {
-        if (64 * u < NP) group(64 * u, vpre[u]);   // uniform
+    for (int u = 0; u < VG; ++u) {
+      if (64 * u < NP) group(u, vpre[u]);   // uniform
+    }
+    for (int u = VG; 64 * u < NP; ++u) {
+      f32x4 b[4];
+      vrows(u, b);
+      group(u, b);
+    }
+    // register e of block c: query 4 (l / 16) + e, feature 4 (l % 16) + c.  The waves' shares meet in LDS.
+    float* part = inv + 16;   // [4 waves][16 queries][64]
+#pragma unroll
+    for (int e = 0; e < 4; ++e) *reinterpret_cast<f32x4*>(part + (wave * 16 + 4 * g + e) * 64 + 4 * r16) = f32x4{acc[0][e], acc[1][e], acc[2][e], acc[3][e]};
+    __syncthreads();
+    const int qr = tid >> 4, d = (tid & 15) * 4;
+    const f32x4 p0 = *reinterpret_cast<const f32x4*>(part + qr * 64 + d), p1 = *reinterpret_cast<const f32x4*>(part + (16 + qr) * 64 + d),
+                p2 = *reinterpret_cast<const f32x4*>(part + (32 + qr) * 64 + d), p3 = *reinterpret_cast<const f32x4*>(part + (48 + qr) * 64 + d);
+    if (q0 + qr < n_q) {
+      const float f = inv[qr];
+      f32x4 r;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) r[e] = ((p0[e] + p1[e]) + (p2[e] + p3[e])) * f;
+      *reinterpret_cast<f32x4*>(o + ((long)t * n_q + q0 + qr) * ldo + (long)h * hd + d) = r;
+    }
+  } else {
+    // wave w takes head-dim blocks w, w + 4, ..; lane l supplies keys 4 (l / 16) + e of column l % 16
+    for (int d0 = wave * 16; d0 < hd; d0 += 64) {
+      const float* vp = v + row0 * ld + (long)h * hd + d0 + r16;
+      f32x4 acc[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int j0 = 0; j0 < NP; j0 += 64) {   // four chains, one per 16-key block of a group of 64 keys
+        float b[4][4];
+        f32x4 a[4];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const int j1 = j0 + 16 * c + 4 * g;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) b[c][e] = j1 + e < N ? vp[(long)(j1 + e) * ld] : 0.f;
+          a[c] = j1 < NP ? *reinterpret_cast<const f32x4*>(sm + r16 * LD + j1) : f32x4{0.f, 0.f, 0.f, 0.f};
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[c][e], b[c][e], acc[c], 0, 0, 0);
       }
-      j0 = 64 * VG;
-    }
-    for (; j0 < NP; j0 += 64) {
-      float b[4][4];
-      vload(vp, j0, b);
-      group(j0, b);
-    }
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int row = q0 + 4 * g + e;
-      if (row < n_q) o[((long)t * n_q + row) * ldo + (long)h * hd + d0 + r16] = ((acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e])) * inv[4 * g + e];
+      for (int e = 0; e < 4; ++e) {
+        const int row = q0 + 4 * g + e;
+        if (row < n_q) o[((long)t * n_q + row) * ldo + (long)h * hd + d0 + r16] = ((acc[0][e] + acc[1][e]) + (acc[2][e] + acc[3][e])) * inv[4 * g + e];
+      }
     }
   }
 }
 
 // the rows of logits of more than 1020 keys take more than the 64 KiB a launch may ask for by default
 hipError_t f32_attention_init() {
-  constexpr int most = (int)((16 * (F32_ATTN_MAX_KEYS + 4) + 16) * sizeof(float));
+  constexpr int most = (int)((16 * (F32_ATTN_MAX_KEYS + 4) + 16 + F32_ATTN_PART) * sizeof(float));
   const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_f32_attention_mfma<4>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, most);
   return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&k_f32_attention_mfma<0>),
@@ -547,9 +606,10 @@ void f32_attention(const float* q, long ld_q, int n_q, int q_shared, const float
   if (T == 0) return;
   const bool aligned = ld_q % 4 == 0 && ld % 4 == 0 && (((uintptr_t)q | (uintptr_t)k) & 15) == 0;
   if (hd % 16 == 0 && N <= F32_ATTN_MAX_KEYS && aligned) {
-    const size_t smem = (size_t)(16 * ((N + 15) / 16 * 16 + 4) + 16) * sizeof(float);
+    const bool by_64 = hd == 64 && ldo % 4 == 0 && (((uintptr_t)v | (uintptr_t)o) & 15) == 0;
+    const size_t smem = (size_t)(16 * ((N + 15) / 16 * 16 + 4) + 16 + (by_64 ? F32_ATTN_PART : 0)) * sizeof(float);
     const dim3 grid((n_q + 15) / 16, H, T);
-    if (hd == 64) k_f32_attention_mfma<4><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
+    if (by_64) k_f32_attention_mfma<4><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
     else k_f32_attention_mfma<0><<<grid, dim3(256), smem, st>>>(q, ld_q, q_shared, k, v, ld, o, ldo, n_q, N, hd, scale);
     return;
   }
