@@ -92,15 +92,38 @@ __device__ __forceinline__ unsigned mx_pack4(float a, float b, float c, float d)
 }
 
 
+// Over all lanes of a wave.  A step combines a lane with lane ^ 32, ^ 16, ^ 8, ^ 4, ^ 2 and ^ 1 in turn: the swaps of halves and rows,
+// then turns of the rows of 16 lanes by 8, 4, 2 and 1 (lanes that differ in the bits already combined hold the same value).  On the vector
+// unit: through LDS (__shfl_xor) each of a norm's twelve steps takes 100 cycles and more.
+template <int N>
+__device__ __forceinline__ float row_turn(float x) {   // of lane (l + N) % 16 in a row of 16
+  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x120 + N, 0xf, 0xf, true));
+}
+template <typename F>
+__device__ __forceinline__ float with_lane_32(float v, F f) {   // of lanes l and l ^ 32
+  const unsigned b = __float_as_uint(v);
+  const auto h = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+  return f(__uint_as_float(h[0]), __uint_as_float(h[1]));
+}
+template <typename F>
+__device__ __forceinline__ float with_lane_16(float v, F f) {   // of lanes l and l ^ 16
+  const unsigned b = __float_as_uint(v);
+  const auto r = __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  return f(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+template <typename F>
+__device__ __forceinline__ float wave_combine(float v, F f) {
+  v = with_lane_16(with_lane_32(v, f), f);
+  v = f(v, row_turn<8>(v));
+  v = f(v, row_turn<4>(v));
+  v = f(v, row_turn<2>(v));
+  return f(v, row_turn<1>(v));
+}
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  return wave_combine(v, [](float a, float b) { return a + b; });
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
+  return wave_combine(v, [](float a, float b) { return fmaxf(a, b); });
 }
 
 // Sum over the 32 lanes of each half of a wave (lanes 0-31 and 32-63 apart); every lane of a half gets its

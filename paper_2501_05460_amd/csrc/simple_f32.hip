@@ -138,8 +138,8 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 1) void k_f32_gemm(const F32Norm 
     auto row_sum = [&](int pass, float (&x)[R]) {
 #pragma unroll
       for (int i = 0; i < R; ++i) {
-        x[i] += __shfl_xor(x[i], 16, 64);
-        x[i] += __shfl_xor(x[i], 32, 64);
+        auto add = [](float a, float b) { return a + b; };
+        x[i] = with_lane_32(with_lane_16(x[i], add), add);
         if (q == 0) red[pass][wave][16 * i + r16] = x[i];
       }
       __syncthreads();
@@ -407,10 +407,6 @@ constexpr int F32_ATTN_MAX_KEYS = 2048;   // 16 rows of logits in LDS
 constexpr int F32_ATTN_PART = 4 * 16 * 64;   // head dim 64: the waves' shares of the output
 // HC: head dim / 16 when it is compiled in (the loads of a wave's keys and values are then issued as batches: 15.3 -> 11.8 us),
 // 0: any, and head dim 64 where values or output rows are not 16-byte aligned.
-template <int N>
-__device__ __forceinline__ float row_turn(float x) {   // of lane (l + N) % 16 in a row of 16
-  return __uint_as_float((unsigned)__builtin_amdgcn_update_dpp(0, (int)__float_as_uint(x), 0x120 + N, 0xf, 0xf, true));
-}
 template <int HC>
 __global__ __launch_bounds__(256) void k_f32_attention_mfma(const float* __restrict__ q, long ld_q, int q_shared,
                                                             const float* __restrict__ k, const float* __restrict__ v,
