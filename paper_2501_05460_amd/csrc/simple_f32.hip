@@ -117,7 +117,7 @@ __global__ __launch_bounds__(256, R == 4 ? 2 : 1) void k_f32_gemm(const F32Norm 
     constexpr int SA = decltype(set_a)::value, S = decltype(set_w)::value;
 #pragma unroll
     for (int g = 0; g < G; ++g)
-      if (g < n) {   // uniform
+      if (G == 1 || g < n) {   // uniform
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
