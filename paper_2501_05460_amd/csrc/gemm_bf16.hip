@@ -9,9 +9,8 @@
 // lanes per 128-bit access phase: rows r and r+1 share a chunk column, so the
 // XOR key is (row >> 1) & 7).  One barrier per slab, two LDS buffers.
 //
-// What runs here: the products with a folded pre-norm or emitted rows (EPD_NORM_MODE), 256 x 128 tiles of plain products over
-// long K (one_tile_128), and the forms that tests hold the others against.  All other products run on gemm_bf16_wide.hip and
-// gemm_bf16_ring.hip; the dispatch at the end of this file chooses.
+// What runs here: the products with a folded pre-norm or emitted rows (EPD_NORM_MODE), and the forms that tests hold the others
+// against.  All other products run on gemm_bf16_wide.h and gemm_bf16_ring.hip; the dispatch at the end of this file chooses.
 //
 // Main loop of the 256 x 256 shape (PIPE = 1): the activation slab is read two
 // slabs ahead into registers through a buffer descriptor (L2 / Infinity-Cache
@@ -743,7 +742,7 @@ __global__ __launch_bounds__(NTHREADS, BM_ == 128 && PIPE == 0 ? 2 : 1) void k_g
 // rows: the next tile's main loop starts right behind the last store, without
 // the launch gap and the exposed first-slab latency a fresh workgroup pays.
 // ---------------------------------------------------------------------------
-// For products with a folded pre-norm; the others run on gemm_bf16_wide.hip.
+// For products with a folded pre-norm; the others run on gemm_bf16_wide.h.
 template <int EPI>
 __global__ __launch_bounds__(512, 1) void k_gemm_bf16_persist(const GemmParams p, const int gm_, const int gw,
                                                               const int n_tiles) {

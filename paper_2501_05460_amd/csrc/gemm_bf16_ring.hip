@@ -14,11 +14,13 @@
 //   * What the epilogue reads (bias, residual rows) is fetched in front of the main loop.
 //   * Four waves (2 x 2) of 32 WTM x 32 WTN each: a 64 x 64 wave tile reads half as many LDS bytes per flop as the
 //     32 x 64 wave tiles of an eight-wave 128 x 128 tile.
-//   * v_mfma_f32_16x16x32_bf16, for the reason given in gemm_bf16_wide.hip.
+//   * v_mfma_f32_16x16x32_bf16, for the reason given in gemm_bf16_wide.h.
 // An element's k-steps are added in the order of every other form (k ascending): same bits.
 // Measured stand-alone, K = 4096, N = 1024: 1024 rows 21.8 us with the 64 x 64 form this replaces, 15.4 now; 3096 rows
 // 56.4 us with eight-wave 128 x 128 tiles, 30.5 now.  In the running encoder, weights cold: 24.4 -> 22.9, 55.8 -> 41.5.
-// A deeper ring (8 / 6 / 5 stages, one workgroup per CU) changed nothing in the encoder.
+// A deeper ring (8 / 6 / 5 stages, one workgroup per CU) changed nothing in the encoder.  A fifth wave that asks for the panels' lines
+// ahead, as gemm_bf16_wide.h does, costs 5 to 40 %: what a slab waits for is not memory but LDS (a 64 x 64 slab is 32 KiB read and
+// 16 KiB written, 384 cycles at 128 bytes a cycle; a 128 x 128 one 768) and the chip's share of the L2s.
 //
 // The epilogue goes through LDS wave by wave (a wave stages 32 rows of its own tile and reads them back, no
 // workgroup barrier), so that global memory sees 16-byte pieces of whole 128-byte row parts; bias, activation,

@@ -22,7 +22,11 @@
 // 1152 x 4352 residual, 256 x 192 tiles 111 -> 95; 106496 rows, 1024 x 4096 residual 790 -> 735, 1024 x 1024 residual 294 -> 276, 4096 x 1024
 // with GELU 772 -> 745; 40960 rows, 9600 x 3200 1895 -> 1805, 12800 x 3200 with GELU 2595 -> 2490; 3200 x 12800 residual 2930 -> 2830.
 // One line a row at a time gives two thirds of that; four lines, or two pairs ahead, the same or less.
-// Tried and not kept: four waves of 128 x 128 (a third fewer fragment reads: 8192^3 equal, K = 1024 2 to 6 % slower, their
+// A slab of 256 x 256 reads 192 KiB of LDS and writes 64, as many cycles at 128 bytes each as its products take: 2200 cycles on a CU by
+// itself, 2600 to 3000 with all of them at work under the power limit.
+// Tried and not kept: both operands slab by slab in memory ([K / 64][rows][64], 1 to 3 % on top of the lines asked for ahead); the stream
+// rows' lines asked for ahead of a last tile's epilogue (13312 rows, 1024 x 1024 residual 41 -> 50: they return in order, in front of the
+// rows themselves); the direct loads in the first half or three quarters of their k-step (0 to + 4 %); four waves of 128 x 128 (a third fewer fragment reads: 8192^3 equal, K = 1024 2 to 6 % slower, their
 // epilogue runs on half as many waves); a staggered start of the workgroups (residual products -1 to -5 %, FC1 + 1 %); a
 // wait that leaves the epilogue's stores in flight over the next tile's first slab (equal).
 #pragma once
