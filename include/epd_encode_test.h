@@ -124,6 +124,8 @@ epd_status epd_op_mfma_probe(const void* A, const void* B, float* D, void* hip_s
  *   and SC hold M rounded up to 256 rows; cscale may be null; tile 0 = as the library picks, 1 = 256x256, 2 = 128x128); epi 0 -> C bf16 [M, N]; epi 5 -> C bf16 transposed per
  *   slice and head, [M / n_tok, heads, hd_pad, n_tok] with N = heads * hd_pad; epi 1 / 2 -> GELU (erf / tanh form),
  *   then converted: codes Cq [M, N], scales SC [N / 128, M]; epi 3 -> R fp32 [M, N] += out.
+ * epd_op_mx_gemm_pair: the products with W (epi 0) and W2 (epi 5, one head of n2 features; n2 % 8 == 0; W2, SW2, bias2 and cscale2 hold
+ *   n2_pad rows, n2_pad % 256 == 0) of the same A: tile 0 = as the library picks, in one launch or two, 1 / 2 = one launch.
  * epd_op_mx_mfma_probe: one v_mfma_scale_f32_16x16x128_f8f6f4 on caller-supplied registers (a, b: int32 [64][8],
  *   sa, sb: int32 [64], scale byte 0 used; d: fp32 [64][4]), for the operand-layout test.  All pointers dev. */
 epd_status epd_op_mx_rows(const void* in, int32_t in_bf16, int64_t rows, int32_t dim, int32_t kind, const float* gamma,
@@ -131,6 +133,9 @@ epd_status epd_op_mx_rows(const void* in, int32_t in_bf16, int64_t rows, int32_t
 epd_status epd_op_mx_gemm(int32_t epi, int32_t tile, const void* A, const void* SA, const void* W, const void* SW, const float* bias,
                           const float* cscale, int32_t M, int32_t N, int32_t K, void* C, float* R, void* Cq, void* SC,
                           int32_t n_tok, int32_t heads, int32_t hd_pad, void* hip_stream);
+epd_status epd_op_mx_gemm_pair(int32_t tile, const void* A, const void* SA, const void* W, const void* SW, const float* bias, const float* cscale, const void* W2,
+                               const void* SW2, const float* bias2, const float* cscale2, int32_t M, int32_t N, int32_t n2, int32_t n2_pad, int32_t K,
+                               void* C, void* VT, int32_t n_tok, void* hip_stream);
 epd_status epd_op_mx_mfma_probe(const void* a, const void* b, const void* sa, const void* sb, float* d, void* hip_stream);
 
 /* Per-kernel-family timing of the previous epd_encode / epd_encode_range

@@ -37,7 +37,7 @@ EXPORTS = (
     "epd_op_attention_bf16", "epd_op_attention_queries", "epd_op_mfma_probe",
     "epd_profile_enable", "epd_profile_read", "epd_op_mfma_peak", "epd_op_copy_peak", "epd_op_coissue",
     "epd_op_row_stats", "epd_op_gemm_residual_stats", "epd_op_norm_gemm_bf16",
-    "epd_op_mx_rows", "epd_op_mx_gemm", "epd_op_mx_mfma_probe", "epd_op_attention_mx",
+    "epd_op_mx_rows", "epd_op_mx_gemm", "epd_op_mx_gemm_pair", "epd_op_mx_mfma_probe", "epd_op_attention_mx",
     "epd_mm_cache_create", "epd_mm_cache_destroy", "epd_mm_cache_free_blocks", "epd_mm_cache_base",
     "epd_mm_last_error", "epd_mm_alloc", "epd_mm_free", "epd_encode_paged", "epd_mm_transfer", "epd_mm_transfer_noalloc", "epd_mm_gather",
     "epd_encode_trunk_paged", "epd_project_merge",
@@ -133,6 +133,8 @@ def lib() -> ctypes.CDLL:
         L.epd_op_mx_rows.restype = i32
         L.epd_op_mx_gemm.argtypes = [i32, i32, vp, vp, vp, vp, vp, vp, i32, i32, i32, vp, vp, vp, vp, i32, i32, i32, vp]
         L.epd_op_mx_gemm.restype = i32
+        L.epd_op_mx_gemm_pair.argtypes = [i32, vp, vp, vp, vp, vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, vp, vp, i32, vp]
+        L.epd_op_mx_gemm_pair.restype = i32
         L.epd_op_attention_mx.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
         L.epd_op_attention_mx.restype = i32
         L.epd_op_mx_mfma_probe.argtypes = [vp, vp, vp, vp, vp, vp]
@@ -640,6 +642,23 @@ def op_mx_gemm(epi: int, A: torch.Tensor, SA: torch.Tensor, W: torch.Tensor, SW:
     if epi == 3:
         return R
     return Cq, SC
+
+
+def op_mx_gemm_pair(A: torch.Tensor, SA: torch.Tensor, W: torch.Tensor, SW: torch.Tensor, bias: torch.Tensor, cscale: torch.Tensor, W2: torch.Tensor,
+                    SW2: torch.Tensor, bias2: torch.Tensor, cscale2: torch.Tensor, n2: int, n_tok: int, tile: int, rows: int):
+    """op_mx_gemm with W (epi 0) and with the first n2 rows of W2 (epi 5, one head) of the same A: (bf16 [rows, N], bf16 [rows / n_tok, n2, n_tok])."""
+    N, K = W.shape
+    if A.shape[0] != (rows + 255) // 256 * 256 or A.shape[1] != K or W2.shape[1] != K or SA.shape != (K // 128, A.shape[0]) or SW.shape != (K // 128, N) \
+            or SW2.shape != (K // 128, W2.shape[0]) or min(len(bias), len(cscale)) < N or min(len(bias2), len(cscale2)) < len(W2):
+        raise ValueError("A must hold the rows rounded up to 256, the other operands a row or a word for each of theirs")
+    C = torch.full((rows, N), float("nan"), dtype=torch.bfloat16, device=A.device)
+    V = torch.full((rows // n_tok, n2, n_tok), float("nan"), dtype=torch.bfloat16, device=A.device)
+    s = lib().epd_op_mx_gemm_pair(tile, A.data_ptr(), SA.data_ptr(), W.data_ptr(), SW.data_ptr(), bias.data_ptr(), cscale.data_ptr(), W2.data_ptr(),
+                                  SW2.data_ptr(), bias2.data_ptr(), cscale2.data_ptr(), rows, N, n2, len(W2), K, C.data_ptr(), V.data_ptr(), n_tok,
+                                  _stream_ptr())
+    if s != EPD_OK:
+        raise EpdError(s, lib().epd_last_error(None).decode())
+    return C, V
 
 
 def op_mx_mfma_probe(a: torch.Tensor, b: torch.Tensor, sa: torch.Tensor, sb: torch.Tensor) -> torch.Tensor:

@@ -894,11 +894,9 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
       { ProfScope ps(c, 2, st);
         MxGemmParams p = mxp(EPI_BIAS, XnQ, c->D_k, SXn, w.mqkv);
         p.C = QK; p.ldc = ld_qk;
+        p.W2 = w.mv.W; p.SW2 = w.mv.SW; p.bias2 = w.mv.b; p.cscale2 = w.mv.cs; p.n2 = w.mv.N; p.n2_pad = w.mv.Npad;
+        p.VT = VT; p.hd_pad = c->hd_pad; p.heads = x.H; p.n_tok = x.Ns;
         HIP_TRY(c, mx_gemm(p, st)); }
-      { ProfScope ps(c, 2, st);
-        MxGemmParams pv = mxp(EPI_VT, XnQ, c->D_k, SXn, w.mv);
-        pv.VT = VT; pv.hd_pad = c->hd_pad; pv.heads = x.H; pv.n_tok = x.Ns;
-        HIP_TRY(c, mx_gemm(pv, st)); }
     } else {
     norm_kernel(w.n1_g, w.n1_b, !copy || l == 0);   // the first layer's rows come from the embedding
     bool paired = false;
@@ -1657,6 +1655,26 @@ epd_status epd_op_mx_gemm(int32_t epi, int32_t tile, const void* A, const void* 
   p.Cq = (unsigned char*)Cq; p.ldcq = N; p.ncq = N; p.SC = (unsigned*)SC; p.sc_ld = Mp;
   const hipError_t e = mx_gemm(p, (hipStream_t)hip_stream);
   if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "epd_op_mx_gemm: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_INVALID_ARG : EPD_ERR_HIP; }
+  return EPD_OK;
+}
+
+epd_status epd_op_mx_gemm_pair(int32_t tile, const void* A, const void* SA, const void* W, const void* SW, const float* bias, const float* cscale, const void* W2,
+                               const void* SW2, const float* bias2, const float* cscale2, int32_t M, int32_t N, int32_t n2, int32_t n2_pad, int32_t K, void* C, void* VT, int32_t n_tok, void* hip_stream) {
+  if (!A || !SA || !W || !SW || !bias || !W2 || !SW2 || !bias2 || !C || !VT || M <= 0 || N <= 0 || N % 256 || n2 <= 0 || n2 % 8 || n2_pad < n2 || n2_pad % 256 ||
+      K <= 0 || K % 128 || n_tok <= 0 || n_tok % 8 || M % n_tok || tile < 0 || tile > 2) {
+    set_err(g_err, sizeof(g_err), "epd_op_mx_gemm_pair: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  if (mx_gemm_init() != hipSuccess) return EPD_ERR_HIP;
+  MxGemmParams p;
+  memset(&p, 0, sizeof(p));
+  p.epi = EPI_BIAS; p.tile = tile; p.A = (const unsigned char*)A; p.lda = K; p.SA = (const unsigned*)SA; p.sa_ld = ((long)M + 255) / 256 * 256;
+  p.W = (const unsigned char*)W; p.SW = (const unsigned*)SW; p.bias = bias; p.cscale = cscale; p.M = M; p.N = N; p.K = K;
+  p.Npad = N; p.C = (bf16_t*)C; p.ldc = N;
+  p.W2 = (const unsigned char*)W2; p.SW2 = (const unsigned*)SW2; p.bias2 = bias2; p.cscale2 = cscale2; p.n2 = n2; p.n2_pad = n2_pad;
+  p.VT = (bf16_t*)VT; p.heads = 1; p.hd_pad = n2; p.n_tok = n_tok;
+  const hipError_t e = mx_gemm(p, (hipStream_t)hip_stream);
+  if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "epd_op_mx_gemm_pair: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_INVALID_ARG : EPD_ERR_HIP; }
   return EPD_OK;
 }
 

@@ -183,12 +183,17 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-template <int EPI, int TM, int WAVES_M, int WAVES_N>
-__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES_N)) void k_gemm_mxfp8(const MxGemmParams p, const int gm, const int gw, const int gn, const int n_tiles) {
+// DUAL (EPI_BIAS): the tile columns behind the first product's gq are a second product over the same rows, the value projection
+// (MxGemmParams::n2).  Its tiles read their fragments with the operands' LDS regions exchanged: so the products, which stay as they
+// are, leave four tokens of a feature in a lane, and the bits are EPI_VT's.  (A second main loop with the roles exchanged in
+// the products instead spills 64 registers.)
+template <int EPI, bool DUAL, int TM, int WAVES_M, int WAVES_N>
+__global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES_N)) void k_gemm_mxfp8(const MxGemmParams p, const int gm, const int gw, const int gn, const int gq, const int n_tiles) {
   using T = MxTile<TM, WAVES_M, WAVES_N>;
   constexpr int NT = T::NT, WM = T::WM, WN = T::WN, BM = T::BM, BN = T::BN;
   constexpr unsigned SLAB = T::SLAB, SCALES = T::SCALES, STAGE = T::STAGE;
   constexpr bool TOK = EPI == EPI_VT;
+  static_assert(!DUAL || (EPI == EPI_BIAS && BM == BN), "the second product rides on the plain bias epilogue, on square tiles");
   constexpr bool MX_OUT = EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH;
   constexpr bool F32_OUT = EPI == EPI_BIAS_RESIDUAL;
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // slab buffers 0, 1 | scale words 0, 1 | staging by wave
@@ -210,7 +215,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
     int band = id / band_tiles, in_band = id % band_tiles, bw = gw;
     if (band >= full_bands) { band = full_bands; in_band = id - full_bands * band_tiles; bw = gn - full_bands * gw; }
     m0 = (in_band / bw) * BM;
-    n0 = (band * gw + in_band % bw) * BN;
+    n0 = (band * gw + in_band % bw) * BN;   // of the second product: from gq * BN on
   };
 
   // Direct loads: a wave fills 8 slab rows of 128 bytes linearly; the lane that lands on physical chunk ld_c of its row
@@ -222,7 +227,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   const unsigned s_voff = (unsigned)lane * 4u;
   const long a_step = (long)(NT / 8) * p.lda, b_step = (long)(NT / 8) * p.K;
   constexpr int SA_WAVES = BM / 64;
-  const long s_step = (wave < SA_WAVES ? p.sa_ld : (long)p.Npad) * 4;
+  long s_step = (wave < SA_WAVES ? p.sa_ld : (long)p.Npad) * 4;
   constexpr int LA = BM * 8 / NT, LPS = LA + BN * 8 / NT + 1;
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
   // the slab to fetch next: its position, its index in the tile, its first rows
@@ -232,9 +237,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   auto aim = [&]() {
     int m, n;
     tile_of(lpos, m, n);
+    const bool v = DUAL && n >= gq * BN;
+    if (v) n -= gq * BN;
     ga = p.A + (long)m * p.lda;
-    gb = p.W + (long)n * p.K;
-    gs = reinterpret_cast<const u8*>(wave < SA_WAVES ? p.SA + m + 64 * wave : p.SW + n + 64 * (wave - SA_WAVES));
+    gb = (v ? p.W2 : p.W) + (long)n * p.K;
+    gs = reinterpret_cast<const u8*>(wave < SA_WAVES ? p.SA + m + 64 * wave : (v ? p.SW2 : p.SW) + n + 64 * (wave - SA_WAVES));
+    if (DUAL && wave >= SA_WAVES) s_step = (v ? (long)p.n2_pad : (long)p.Npad) * 4;
   };
   auto issue = [&](int i) {
     if (i < LPS - 1) {
@@ -323,9 +331,19 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   wait_all(false);
   __syncthreads();
 
+  bool v_tile = false;   // uniform
   for (int pos = blockIdx.x;;) {
     int m0, n0;
     tile_of(pos, m0, n0);
+    if constexpr (DUAL) {
+      const bool v = n0 >= gq * BN;
+      if (v != v_tile) {   // the regions are powers of two apart
+        a_lo ^= BM * BKB; a_hi ^= BM * BKB; b_lo ^= BM * BKB; b_hi ^= BM * BKB;
+        sc_a ^= BM * 4; sc_b ^= BM * 4;
+        v_tile = v;
+      }
+      if (v) n0 -= gq * BN;
+    }
 #pragma unroll
     for (int j = 0; j < TN; ++j) read_b(j);
     read_a(0);
@@ -417,6 +435,37 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
         __builtin_amdgcn_wave_barrier();
       };
       auto at = [&](int r, int c) { return stg + r * 128 + ((c ^ SWZ(r)) << 4); };   // 16 rows of eight 16-byte chunks
+      if (DUAL && v_tile) {   // rows of blocks are features, columns of blocks tokens
+        float c1[TM], b1[TM];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+          const int col = n0 + wm * WM + i * 16 + l16;
+          b1[i] = p.bias2[col];
+          c1[i] = p.cscale2 ? p.cscale2[col] : 1.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+#pragma unroll
+          for (int j = 0; j < TN; ++j) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[e] = (bf16_t)__builtin_fmaf(acc[i][j][e], c1[i], b1[i]);
+            *reinterpret_cast<bf16x4*>(at(l16, j * 2 + (lg >> 1)) + ((lg & 1) << 3)) = o;
+          }
+          wave_sync();
+#pragma unroll
+          for (int u = 0; u < 2; ++u) {
+            const int r = (lane + 64 * u) / 8, c = lane % 8;
+            const int f = n0 + wm * WM + i * 16 + r, tok = m0 + wn * WN + c * 8;   // n_tok % 8 == 0: the eight tokens share a slice
+            if (f < p.n2 && tok < p.M) {
+              const u32x4 v = *reinterpret_cast<const u32x4*>(at(r, c));
+              const int t = tok / p.n_tok, n = tok % p.n_tok;
+              __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n));
+            }
+          }
+          wave_sync();
+        }
+      } else {
       // per-column factor and bias: of feature l16 of block j (transposed store), of features 4 lg .. + 3 otherwise
       f32x4 c4[TOK ? 1 : TN], b4[TOK ? 1 : TN];
       float c1[TOK ? TN : 1], b1[TOK ? TN : 1];
@@ -545,6 +594,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
           wave_sync();
         }
       }
+      }
     }
     pos += (int)gridDim.x;
     if (pos >= n_tiles) break;
@@ -563,17 +613,17 @@ __global__ __launch_bounds__(64) void k_mx_mfma_probe(const int* a, const int* b
   for (int e = 0; e < 4; ++e) d[l * 4 + e] = acc[e];
 }
 
-template <int EPI, int TM, int WAVES_M, int WAVES_N>
+template <int EPI, bool DUAL, int TM, int WAVES_M, int WAVES_N>
 hipError_t launch_tile(const MxGemmParams& p, int cols, hipStream_t st) {
   using T = MxTile<TM, WAVES_M, WAVES_N>;
-  const int gm = (p.M + T::BM - 1) / T::BM, gn = (cols + T::BN - 1) / T::BN, n_tiles = gm * gn, slots = cu_count() * (512 / T::NT);
+  const int gm = (p.M + T::BM - 1) / T::BM, gq = (cols + T::BN - 1) / T::BN, gv = DUAL ? (p.n2 + T::BN - 1) / T::BN : 0, gn = gq + gv, n_tiles = gm * gn, slots = cu_count() * (512 / T::NT);
   const int at_once = 32 * (512 / T::NT), gw = band_columns(gn, (double)T::BM * p.K, (double)T::BN * p.K, n_tiles < 8 * at_once ? (n_tiles + 7) / 8 : at_once);
-  if (gn * T::BN > p.Npad) return hipErrorInvalidValue;
-  k_gemm_mxfp8<EPI, TM, WAVES_M, WAVES_N><<<dim3((unsigned)(n_tiles < slots ? n_tiles : slots)), dim3(T::NT), T::LDS, st>>>(p, gm, gw, gn, n_tiles);
+  if (gq * T::BN > p.Npad || gv * T::BN > p.n2_pad) return hipErrorInvalidValue;
+  k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N><<<dim3((unsigned)(n_tiles < slots ? n_tiles : slots)), dim3(T::NT), T::LDS, st>>>(p, gm, gw, gn, gq, n_tiles);
   return hipGetLastError();
 }
 
-template <int EPI>
+template <int EPI, bool DUAL = false>
 hipError_t launch(const MxGemmParams& p, hipStream_t st) {
   // tile columns that hold nothing but padding are not launched (the weights are packed to 256 rows)
   const int cols = (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH) && p.ncq > p.N ? p.ncq : p.N;
@@ -585,23 +635,34 @@ hipError_t launch(const MxGemmParams& p, hipStream_t st) {
   // residual 43.9 | 26.6; 5120 rows, 4096 x 1024 39.6 | 28.6; 26624 rows, 4096 x 1024 137 | 150, 1024 x 1024 residual 63.9 | 54.7.
   constexpr bool MX = EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH, RES = EPI == EPI_BIAS_RESIDUAL;
   const long cus = cu_count(), kt = p.K / BKB;
-  const long big = ((p.M + 255) / 256) * (long)((cols + 255) / 256), small = ((p.M + 127) / 128) * (long)((cols + 127) / 128);
+  const int cols2 = DUAL ? p.n2 : 0;
+  const long big = ((p.M + 255) / 256) * (long)((cols + 255) / 256 + (cols2 + 255) / 256), small = ((p.M + 127) / 128) * (long)((cols + 127) / 128 + (cols2 + 127) / 128);
   const long full = small / (2 * cus), rem = small % (2 * cus);
   const double us_big = ((big + cus - 1) / cus) * ((RES ? 21.0 : MX ? 9.7 : 5.3) + 1.25 * kt);
   const double us_small = 2.0 + (full + (rem == 0 ? 0.0 : rem <= cus ? 0.7 : 1.0)) * ((RES ? 6.3 : MX ? 3.9 : 0.8) + 0.93 * kt);
-  if (p.tile == 2 || (p.tile == 0 && us_small < us_big)) return launch_tile<EPI, 4, 2, 2>(p, cols, st);
-  return launch_tile<EPI, 8, 2, 4>(p, cols, st);
+  if (p.tile == 2 || (p.tile == 0 && us_small < us_big)) return launch_tile<EPI, DUAL, 4, 2, 2>(p, cols, st);
+  return launch_tile<EPI, DUAL, 8, 2, 4>(p, cols, st);
 }
 
-template <int EPI, int TM, int WAVES_M, int WAVES_N>
+// The two products of a pair in one launch: where that saves a round of 256 x 256 tiles, or the start of a launch among few
+// rounds.  Encodes of 448-pixel slices, two launches | one, us: 1 slice, 300M 2541 | 2294; 10, SigLIP (3 rounds, none saved) 9179 |
+// 9073; 16, 300M (3) 9495 | 9315; 40, SigLIP (9, one saved) 32694 | 32374; none saved and more of them, two launches: 48, 300M (9)
+// 26239 | 26320, 104 (20) 55802 | 56182.
+bool together(const MxGemmParams& p) {
+  const long cus = cu_count(), rows = (p.M + 255) / 256, q = rows * ((p.N + 255) / 256), v = rows * ((p.n2 + 255) / 256);
+  const auto rounds = [cus](long tiles) { return (tiles + cus - 1) / cus; };
+  return rounds(q + v) <= 4 || rounds(q + v) < rounds(q) + rounds(v);
+}
+
+template <int EPI, bool DUAL, int TM, int WAVES_M, int WAVES_N>
 hipError_t set_attr_tile() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mxfp8<EPI, TM, WAVES_M, WAVES_N>),
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N>),
                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)MxTile<TM, WAVES_M, WAVES_N>::LDS);
 }
-template <int EPI>
+template <int EPI, bool DUAL = false>
 hipError_t set_attr() {
-  const hipError_t e = set_attr_tile<EPI, 8, 2, 4>();
-  return e != hipSuccess ? e : set_attr_tile<EPI, 4, 2, 2>();
+  const hipError_t e = set_attr_tile<EPI, DUAL, 8, 2, 4>();
+  return e != hipSuccess ? e : set_attr_tile<EPI, DUAL, 4, 2, 2>();
 }
 
 }  // namespace
@@ -610,6 +671,7 @@ hipError_t mx_gemm_init() {
   static const hipError_t once = [] {
     hipError_t e;
     if ((e = set_attr<EPI_BIAS>()) != hipSuccess) return e;
+    if ((e = set_attr<EPI_BIAS, true>()) != hipSuccess) return e;
     if ((e = set_attr<EPI_VT>()) != hipSuccess) return e;
     if ((e = set_attr<EPI_BIAS_GELU_ERF>()) != hipSuccess) return e;
     if ((e = set_attr<EPI_BIAS_GELU_TANH>()) != hipSuccess) return e;
@@ -627,7 +689,19 @@ hipError_t mx_gemm(const MxGemmParams& p, hipStream_t st) {
       !p.A || !p.SA || !p.W || !p.SW || !p.bias)
     return hipErrorInvalidValue;
   switch (p.epi) {
-    case EPI_BIAS: return p.C && p.N % 8 == 0 ? launch<EPI_BIAS>(p, st) : hipErrorInvalidValue;
+    case EPI_BIAS:
+      if (!p.C || p.N % 8) return hipErrorInvalidValue;
+      if (p.n2 == 0) return launch<EPI_BIAS>(p, st);
+      if (p.n2 < 0 || p.n2_pad % BN || p.n2 > p.n2_pad || (long)p.n2_pad * p.K >= (1L << 32) || !p.W2 || !p.SW2 || !p.bias2 || !p.VT || p.n_tok % 8 || p.hd_pad <= 0)
+        return hipErrorInvalidValue;
+      if (p.tile == 0 && !together(p)) {
+        MxGemmParams q = p, v = p;
+        q.n2 = 0;
+        v.epi = EPI_VT; v.W = p.W2; v.SW = p.SW2; v.bias = p.bias2; v.cscale = p.cscale2; v.N = p.n2; v.Npad = p.n2_pad; v.n2 = 0;
+        const hipError_t e = launch<EPI_BIAS>(q, st);
+        return e != hipSuccess ? e : launch<EPI_VT>(v, st);
+      }
+      return launch<EPI_BIAS, true>(p, st);
     case EPI_VT: return p.VT && p.n_tok % 8 == 0 && p.hd_pad > 0 ? launch<EPI_VT>(p, st) : hipErrorInvalidValue;
     case EPI_BIAS_GELU_ERF:
     case EPI_BIAS_GELU_TANH:

@@ -279,6 +279,10 @@ struct MxGemmParams {
   bf16_t* VT; int hd_pad, heads, n_tok;
   unsigned char* Cq; long ldcq; int ncq;
   unsigned* SC; long sc_ld;
+  // a second product over the same rows in the same launch (EPI_BIAS): the value projection next to the q/k projection, n2 columns that leave
+  // through the EPI_VT store; weights, scales [K / 128][n2_pad], bias and factors of its own.  n2 == 0: off.
+  const unsigned char* W2; const unsigned* SW2; const float* bias2; const float* cscale2;
+  int n2, n2_pad;
 };
 int cu_count();   // compute units of the device (see gemm_bf16.hip)
 hipError_t mx_gemm(const MxGemmParams& p, hipStream_t st);

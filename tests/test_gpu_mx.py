@@ -471,3 +471,21 @@ def test_product_tiles_agree_bit_for_bit(epi, K):
         got = got - R[last]
     # bf16 output 2^-9; fp32 the bound of the products on given codes
     assert float((got.double().cpu() - want).norm() / want.norm()) < (TOL_PRODUCT if epi == 3 else 4e-3)
+
+
+@pytest.mark.parametrize("rows,N,n2,K,n_tok", [(8, 256, 8, 128, 8), (264, 512, 128, 384, 88), (1000, 2304, 1152, 256, 1000), (7344, 2304, 1152, 128, 816),
+                                               (26520, 1024, 1024, 1152, 312)])
+def test_two_products_in_one_launch_agree_bit_for_bit(rows, N, n2, K, n_tok):
+    """Both tiles and the library's choice; one tile and more than workgroups, slices that end inside a tile, value columns that leave a
+    last tile half empty or all but empty, one slab and an odd number of them.  Reference: the two products in a launch each."""
+    g = torch.Generator().manual_seed(rows + N + K)
+    code = lambda r: (torch.randint(0x28, 0x40, (r, K), generator=g) | torch.randint(0, 2, (r, K), generator=g) << 7).to(torch.uint8).cuda()
+    scale = lambda r: torch.from_numpy(pack_scale_words(torch.randint(122, 127, (r, K // 32), generator=g).numpy())).cuda()
+    padded, pad2 = (rows + 255) // 256 * 256, (n2 + 255) // 256 * 256
+    A, SA, W, SW, W2, SW2 = code(padded), scale(padded), code(N), scale(N), code(pad2), scale(pad2)
+    bias, cs, bias2, cs2 = (f(n, generator=g).cuda() + d for n in (N, pad2) for f, d in ((torch.randn, 0.0), (torch.rand, 0.5)))
+    c = B.op_mx_gemm(0, A, SA, W, SW, bias, cs, rows=rows)
+    v = B.op_mx_gemm(5, A, SA, W2, SW2, bias2, cs2, n_tok=n_tok, heads=1, hd_pad=pad2, rows=rows)[:, 0, :n2]
+    for tile in (0, 1, 2):
+        got_c, got_v = B.op_mx_gemm_pair(A, SA, W, SW, bias, cs, W2, SW2, bias2, cs2, n2, n_tok, tile, rows)
+        assert torch.equal(got_c, c) and torch.equal(got_v, v), tile
