@@ -121,7 +121,7 @@ epd_status epd_op_mfma_probe(const void* A, const void* B, float* D, void* hip_s
  * epd_op_mx_rows: conversion of `rows` rows of `dim` elements (dim % 128 == 0; fp32, or bf16 if in_bf16), after
  *   a LayerNorm (kind 0, gamma / beta [dim] fp32), an RMSNorm (kind 1, gamma) or as they are (kind 2).
  * epd_op_mx_gemm: out = (A W^T) * cscale[n] + bias[n] on such operands (A [M, K], W [N, K]; N % 256 == 0, K % 128 == 0; A, SA
- *   and SC hold M rounded up to 256 rows; cscale may be null; tile 0 = as the library picks, 1 = 256x256, 2 = 128x128); epi 0 -> C bf16 [M, N]; epi 5 -> C bf16 transposed per
+ *   and SC hold M rounded up to 256 rows; cscale may be null; tile 0 = as the library picks, 1 = 256x256, 2 = 128x128, epi 3 also 3 = 224x256); epi 0 -> C bf16 [M, N]; epi 5 -> C bf16 transposed per
  *   slice and head, [M / n_tok, heads, hd_pad, n_tok] with N = heads * hd_pad; epi 1 / 2 -> GELU (erf / tanh form),
  *   then converted: codes Cq [M, N], scales SC [N / 128, M]; epi 3 -> R fp32 [M, N] += out.
  * epd_op_mx_gemm_pair: the products with W (epi 0) and W2 (epi 5, one head of n2 features; n2 % 8 == 0; W2, SW2, bias2 and cscale2 hold

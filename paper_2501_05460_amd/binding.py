@@ -617,7 +617,7 @@ def op_mx_gemm(epi: int, A: torch.Tensor, SA: torch.Tensor, W: torch.Tensor, SW:
                hd_pad: int = 0, tile: int = 0, rows: Optional[int] = None):
     """Product of MXFP8 operands (codes uint8 [M, K] / [N, K], scale words int32 [K / 128, M] / [K / 128, N]).
     epi 0: bf16 [M, N]; 5: bf16 [M / n_tok, heads, hd_pad, n_tok]; 1 / 2: (codes [M, N], scale words [N / 128, M])
-    of the activated output; 3: R (fp32, in place) += product.  tile 0: as the library picks, 1: 256x256, 2: 128x128.
+    of the activated output; 3: R (fp32, in place) += product.  tile 0: as the library picks, 1: 256x256, 2: 128x128, epi 3 also 3: 224x256.
     rows: the first of A's rows (a whole number of 256) that are the operand's."""
     M, K = A.shape
     Mp, M = M, M if rows is None else rows

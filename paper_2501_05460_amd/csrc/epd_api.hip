@@ -1639,8 +1639,8 @@ epd_status epd_op_mx_rows(const void* in, int32_t in_bf16, int64_t rows, int32_t
 epd_status epd_op_mx_gemm(int32_t epi, int32_t tile, const void* A, const void* SA, const void* W, const void* SW, const float* bias,
                           const float* cscale, int32_t M, int32_t N, int32_t K, void* C, float* R, void* Cq, void* SC,
                           int32_t n_tok, int32_t heads, int32_t hd_pad, void* hip_stream) {
-  if (!A || !SA || !W || !SW || !bias || M <= 0 || N <= 0 || N % 256 || K <= 0 || K % 128 || tile < 0 || tile > 2) {
-    set_err(g_err, sizeof(g_err), "epd_op_mx_gemm: bad argument (N %% 256, K %% 128, tile 0..2)");
+  if (!A || !SA || !W || !SW || !bias || M <= 0 || N <= 0 || N % 256 || K <= 0 || K % 128 || tile < 0 || tile > (epi == EPI_BIAS_RESIDUAL ? 3 : 2)) {
+    set_err(g_err, sizeof(g_err), "epd_op_mx_gemm: bad argument (N %% 256, K %% 128, tile 0..2, epi 3: 0..3)");
     return EPD_ERR_INVALID_ARG;
   }
   if (epi == EPI_VT && (n_tok <= 0 || heads <= 0 || hd_pad <= 0 || M % n_tok || heads * hd_pad != N)) return EPD_ERR_INVALID_ARG;

@@ -42,14 +42,18 @@ constexpr int TN = 4;                  // a wave's blocks of 16 columns
 template <int TM, int WAVES_M, int WAVES_N>
 struct MxTile {
   static constexpr int NT = 64 * WAVES_M * WAVES_N, WM = 16 * TM, WN = 16 * TN, BM = WM * WAVES_M, BN = WN * WAVES_N;
-  static constexpr unsigned SLAB = (BM + BN) * BKB;                // bytes of a slab of both operands,
-  static constexpr unsigned SCALES = (BM + BN) * sizeof(unsigned); // of its scale words: one per row of A and of W,
+  static constexpr int AR = TM == 7 ? 256 : BM;                    // rows of A in a slab: 224-row tiles fetch 256, so that the buffers and the loads stay as they are
+  static constexpr unsigned SLAB = (AR + BN) * BKB;                // bytes of a slab of both operands,
+  static constexpr unsigned SCALES = (AR + BN) * sizeof(unsigned); // of its scale words: one per row of A and of W,
   static constexpr unsigned STAGE = 2048;                          // of a wave's staging space
   static constexpr size_t LDS = 2 * (size_t)SLAB + 2 * SCALES + NT / 64 * STAGE;
   static_assert(LDS <= 160 * 1024, "LDS of a CU");
   static_assert((SLAB & (SLAB - 1)) == 0 && (SCALES & (SCALES - 1)) == 0, "the buffers are told apart by one bit");
-  static_assert(SCALES == NT * 4 && BM % 64 == 0, "a wave loads 64 scale words, of A or of W");
-  static_assert(TM % 4 == 0, "fragment slots");
+  static_assert(SCALES == NT * 4 && AR % 64 == 0, "a wave loads 64 scale words, of A or of W");
+  static_assert(TM % 4 == 0 || TM == 7, "fragment slots");
+  // The register slot of fragment i of A: no other than those of i + 1 and i + 2, and the last two's not those of 0 and 1, which are read for
+  // the next slab while the last two are in use.
+  static constexpr int slot(int i) { return TM % 4 == 0 ? i % 4 : i < TM - 1 ? i % 3 : 3; }
 };
 
 #define SWZ(row) (((row) >> 1) & 7)
@@ -190,7 +194,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 template <int EPI, bool DUAL, int TM, int WAVES_M, int WAVES_N>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES_N)) void k_gemm_mxfp8(const MxGemmParams p, const int gm, const int gw, const int gn, const int gq, const int n_tiles) {
   using T = MxTile<TM, WAVES_M, WAVES_N>;
-  constexpr int NT = T::NT, WM = T::WM, WN = T::WN, BM = T::BM, BN = T::BN;
+  constexpr int NT = T::NT, WM = T::WM, WN = T::WN, BM = T::BM, BN = T::BN, AR = T::AR;
   constexpr unsigned SLAB = T::SLAB, SCALES = T::SCALES, STAGE = T::STAGE;
   constexpr bool TOK = EPI == EPI_VT;
   static_assert(!DUAL || (EPI == EPI_BIAS && BM == BN), "the second product rides on the plain bias epilogue, on square tiles");
@@ -219,26 +223,28 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   };
 
   // Direct loads: a wave fills 8 slab rows of 128 bytes linearly; the lane that lands on physical chunk ld_c of its row
-  // fetches logical chunk ld_c ^ SWZ(row).  The first BM / 64 waves fetch the scale words of A rows, the
+  // fetches logical chunk ld_c ^ SWZ(row).  The first AR / 64 waves fetch the scale words of A rows, the
   // others those of W rows.
   const int ld_row = tid >> 3, ld_c = tid & 7;
   const unsigned a_voff = (unsigned)ld_row * (unsigned)p.lda + (unsigned)((ld_c ^ SWZ(ld_row)) * 16);
   const unsigned b_voff = (unsigned)ld_row * (unsigned)p.K + (unsigned)((ld_c ^ SWZ(ld_row)) * 16);
   const unsigned s_voff = (unsigned)lane * 4u;
   const long a_step = (long)(NT / 8) * p.lda, b_step = (long)(NT / 8) * p.K;
-  constexpr int SA_WAVES = BM / 64;
+  constexpr int SA_WAVES = AR / 64;
   long s_step = (wave < SA_WAVES ? p.sa_ld : (long)p.Npad) * 4;
-  constexpr int LA = BM * 8 / NT, LPS = LA + BN * 8 / NT + 1;
+  constexpr int LA = AR * 8 / NT, LPS = LA + BN * 8 / NT + 1;
   const unsigned lds0 = (unsigned)(size_t)(__attribute__((address_space(3))) void*)smem;
   // the slab to fetch next: its position, its index in the tile, its first rows
   int lpos = blockIdx.x, lk = 0;
   unsigned lbuf = 0;
   const u8 *ga, *gb, *gs;
+  const int last_rows = ((p.M + 255) & ~255) - AR;   // AR != BM: a tile past them fetches the rows from there on
   auto aim = [&]() {
     int m, n;
     tile_of(lpos, m, n);
     const bool v = DUAL && n >= gq * BN;
     if (v) n -= gq * BN;
+    if (AR != BM) m = min(m, last_rows);
     ga = p.A + (long)m * p.lda;
     gb = (v ? p.W2 : p.W) + (long)n * p.K;
     gs = reinterpret_cast<const u8*>(wave < SA_WAVES ? p.SA + m + 64 * wave : (v ? p.SW2 : p.SW) + n + 64 * (wave - SA_WAVES));
@@ -272,7 +278,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   const bool a_half = wave < NT / 128;
   unsigned t_voff;
   {
-    const int slot = blockIdx.x >> 3, lt = tid & (NT / 2 - 1), parts = a_half ? gw : max(1, (int)((gridDim.x + 7) >> 3) / gw), rows = a_half ? BM : BN;
+    const int slot = blockIdx.x >> 3, lt = tid & (NT / 2 - 1), parts = a_half ? gw : max(1, (int)((gridDim.x + 7) >> 3) / gw), rows = a_half ? AR : BN;
     const int n = (rows + parts - 1) / parts, row = min((a_half ? slot % gw : slot / gw % parts) * n + lt * n / (NT / 2), rows - 1);
     t_voff = (unsigned)row * (unsigned)(a_half ? p.lda : (long)p.K);
   }
@@ -286,17 +292,17 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   // Fragments: 16-byte chunks lg and 4 + lg of a row (k = 16 lg .. + 15 and 64 + 16 lg .. + 15), byte lg of its scale word.
   // Addresses of fragment 0 in the buffer of the slab at hand; the buffers lie a power of two apart.
   unsigned a_lo = (unsigned)((wm * WM + l16) * BKB + ((lg ^ SWZ(l16)) * 16)), a_hi = a_lo ^ 64u;
-  unsigned b_lo = (unsigned)(BM * BKB + (wn * WN + l16) * BKB + ((lg ^ SWZ(l16)) * 16)), b_hi = b_lo ^ 64u;
-  unsigned sc_a = (unsigned)(2 * SLAB + (wm * WM + l16) * 4 + lg), sc_b = (unsigned)(2 * SLAB + (BM + wn * WN + l16) * 4 + lg);
+  unsigned b_lo = (unsigned)(AR * BKB + (wn * WN + l16) * BKB + ((lg ^ SWZ(l16)) * 16)), b_hi = b_lo ^ 64u;
+  unsigned sc_a = (unsigned)(2 * SLAB + (wm * WM + l16) * 4 + lg), sc_b = (unsigned)(2 * SLAB + (AR + wn * WN + l16) * 4 + lg);
   auto other_buffer = [&]() { a_lo ^= SLAB; a_hi ^= SLAB; b_lo ^= SLAB; b_hi ^= SLAB; sc_a ^= SCALES; sc_b ^= SCALES; };
   auto frag = [&](unsigned lo, unsigned hi, int r) {
     const u32x4 x = *reinterpret_cast<const u32x4*>(smem + lo + r * (16 * BKB)), y = *reinterpret_cast<const u32x4*>(smem + hi + r * (16 * BKB));
     return __builtin_bit_cast(i32x8, __builtin_shufflevector(x, y, 0, 1, 2, 3, 4, 5, 6, 7));
   };
   f32x4 acc[TM][TN];
-  i32x8 fa[4], fb[TN];   // fragment i of A in slot i % 4
+  i32x8 fa[4], fb[TN];   // fragment i of A in slot(i)
   int sa[4], sb[TN];
-  auto read_a = [&](int i) { fa[i % 4] = frag(a_lo, a_hi, i); sa[i % 4] = smem[sc_a + i * 64]; };
+  auto read_a = [&](int i) { fa[T::slot(i)] = frag(a_lo, a_hi, i); sa[T::slot(i)] = smem[sc_a + i * 64]; };
   auto read_b = [&](int j) { fb[j] = frag(b_lo, b_hi, j); sb[j] = smem[sc_b + j * 64]; };
   // In place, as assembly: the compiler's form moves accumulators from register to register, and spills.  It does not see
   // the wait states such an instruction needs.  Behind it: nothing but products touches an accumulator between the zeros in
@@ -305,11 +311,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   // likes, also next to the product: hence the s_nop of every product.  It costs nothing (a product holds the matrix core
   // for eight wait states; 40 products with it in front of all and of two products a slab: equal to within two runs of one).
   auto mma = [&](auto i, auto j) {
-    constexpr int I = decltype(i)::value, J = decltype(j)::value;
+    constexpr int I = decltype(i)::value, J = decltype(j)::value, S = T::slot(I);
     if constexpr (TOK)
-      asm volatile("s_nop 1\n\tv_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fa[I % 4]), "v"(fb[J]), "v"(sa[I % 4]), "v"(sb[J]));
+      asm volatile("s_nop 1\n\tv_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fa[S]), "v"(fb[J]), "v"(sa[S]), "v"(sb[J]));
     else
-      asm volatile("s_nop 1\n\tv_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fb[J]), "v"(fa[I % 4]), "v"(sb[J]), "v"(sa[I % 4]));
+      asm volatile("s_nop 1\n\tv_mfma_scale_f32_16x16x128_f8f6f4 %0, %1, %2, %0, %3, %4 op_sel_hi:[0,0,0]" : "+v"(acc[I][J]) : "v"(fb[J]), "v"(fa[S]), "v"(sb[J]), "v"(sa[S]));
     __builtin_amdgcn_sched_barrier(0);
   };
 
@@ -332,6 +338,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   __syncthreads();
 
   bool v_tile = false;   // uniform
+  int shift = 0;         // of the tile's rows against those fetched
   for (int pos = blockIdx.x;;) {
     int m0, n0;
     tile_of(pos, m0, n0);
@@ -343,6 +350,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
         v_tile = v;
       }
       if (v) n0 -= gq * BN;
+    }
+    if constexpr (AR != BM) {   // rows the buffer does not hold are none of the operand's: what stands behind it is multiplied and not stored
+      const int sh = max(0, m0 - last_rows), d = sh - shift;   // multiples of 32: a row's swizzle stays
+      a_lo += d * BKB; a_hi += d * BKB; sc_a += d * 4;
+      shift = sh;
     }
 #pragma unroll
     for (int j = 0; j < TN; ++j) read_b(j);
@@ -627,20 +639,40 @@ template <int EPI, bool DUAL = false>
 hipError_t launch(const MxGemmParams& p, hipStream_t st) {
   // tile columns that hold nothing but padding are not launched (the weights are packed to 256 rows)
   const int cols = (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH) && p.ncq > p.N ? p.ncq : p.N;
-  // 256 x 256 tiles, a workgroup of eight waves per CU, or 128 x 128 ones, two of four waves: whichever is estimated to take
-  // less.  A round of either: a fixed part by epilogue and a part per slab, us, fitted to 50 products (1024 to 53248 rows,
-  // 1024 to 4352 columns, K 1024 to 12800; the other form was faster by more than 3 % for two of them; of 164 others for
-  // 19, ten of these FC1 over K = 1152, by up to 16 %); the small tiles'
-  // last round counts 0.7 while one per CU holds it.  us, 256 x 256 | 128 x 128: 1024 rows, 2048 x 1024 14.6 | 8.2, 1024 x 4096
-  // residual 43.9 | 26.6; 5120 rows, 4096 x 1024 39.6 | 28.6; 26624 rows, 4096 x 1024 137 | 150, 1024 x 1024 residual 63.9 | 54.7.
+  // 256 x 256 tiles, a workgroup of eight waves per CU, 128 x 128 ones, two of four waves, or, for the residual product over more
+  // than a round, 224 x 256 ones: the one estimated to take least.  us = start + rounds (fixed + slabs) + rounds without rounding up
+  // (fixed + slabs): the residual product's workgroups drift apart, and over several rounds one's epilogue stands under
+  // another's products.  The small tiles' last round counts 0.7 while one per CU holds it.  Bias and activation: fitted to 50 products
+  // (of 126 others those taken are 0.3 % behind the faster on average, 16 % at most).  Residual: fitted to 162 (1024 to 106496 rows,
+  // 1024 to 3200 columns, K 1024 to 12800), with 4 us for a start of large tiles behind another kernel, which those did
+  // not hold, and 3 % that the 224-row ones have to be ahead: of 78 none slower, 1.3 % faster on average than with rounds alone
+  // and without them.  us, 256 x 256 | 128 x 128 | 224 x 256: 1024 rows, 2048 x 1024 15.4 | 9.1, residual 1024 x 4096 51.0 | 24.7 | 47.2;
+  // 26624 rows, 1152 x 1152 91.9 | 73.9 | 83.8, 1024 x 4096 130 | 151 | 127; 53248, 1024 x 4096 257 | 283 | 247; 106496, 1152 x 4352
+  // 620 | 726 | 633.  In one round the 224-row tiles gain nothing that the 128 x 128 ones do not: 10240, 1152 x 4352 67.0 | 76.8 | 68.6.
+  struct Cost { double start, round, round_slab, work, work_slab; };
   constexpr bool MX = EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH, RES = EPI == EPI_BIAS_RESIDUAL;
+  constexpr Cost LARGE = RES ? Cost{6.54, 9.32, 1.21, 12.25, 0.27} : Cost{0.0, MX ? 9.7 : 5.3, 1.25, 0.0, 0.0};
+  constexpr Cost SMALL = RES ? Cost{3.59, 2.41, 0.75, 6.11, 0.33} : Cost{2.0, MX ? 3.9 : 0.8, 0.93, 0.0, 0.0};
   const long cus = cu_count(), kt = p.K / BKB;
   const int cols2 = DUAL ? p.n2 : 0;
-  const long big = ((p.M + 255) / 256) * (long)((cols + 255) / 256 + (cols2 + 255) / 256), small = ((p.M + 127) / 128) * (long)((cols + 127) / 128 + (cols2 + 127) / 128);
-  const long full = small / (2 * cus), rem = small % (2 * cus);
-  const double us_big = ((big + cus - 1) / cus) * ((RES ? 21.0 : MX ? 9.7 : 5.3) + 1.25 * kt);
-  const double us_small = 2.0 + (full + (rem == 0 ? 0.0 : rem <= cus ? 0.7 : 1.0)) * ((RES ? 6.3 : MX ? 3.9 : 0.8) + 0.93 * kt);
-  if (p.tile == 2 || (p.tile == 0 && us_small < us_big)) return launch_tile<EPI, DUAL, 4, 2, 2>(p, cols, st);
+  const auto estimate = [&](const Cost& c, int bm, int bn, long slots, double half_round) {
+    const long tiles = (p.M + bm - 1) / bm * (long)((cols + bn - 1) / bn + (cols2 + bn - 1) / bn), rem = tiles % slots;
+    const double rounds = (double)(tiles / slots) + (rem == 0 ? 0.0 : 2 * rem <= slots ? half_round : 1.0);
+    return c.start + rounds * (c.round + c.round_slab * kt) + (double)tiles / slots * (c.work + c.work_slab * kt);
+  };
+  int tile = p.tile;
+  if (tile == 0) {
+    double best = estimate(LARGE, 256, 256, cus, 1.0);
+    tile = 1;
+    const auto offer = [&](double us, int t) { if (us < best) { best = us; tile = t; } };
+    offer(estimate(SMALL, 128, 128, 2 * cus, 0.7), 2);
+    if constexpr (RES)
+      if ((p.M + 223) / 224 * (long)((cols + 255) / 256) > cus) offer(1.03 * estimate(Cost{6.58, 8.30, 1.10, 9.21, 0.31}, 224, 256, cus, 1.0), 3);
+  }
+  if constexpr (RES) {
+    if (tile == 3) return launch_tile<EPI, DUAL, 7, 2, 4>(p, cols, st);
+  }
+  if (tile == 2) return launch_tile<EPI, DUAL, 4, 2, 2>(p, cols, st);
   return launch_tile<EPI, DUAL, 8, 2, 4>(p, cols, st);
 }
 
@@ -661,7 +693,10 @@ hipError_t set_attr_tile() {
 }
 template <int EPI, bool DUAL = false>
 hipError_t set_attr() {
-  const hipError_t e = set_attr_tile<EPI, DUAL, 8, 2, 4>();
+  hipError_t e = set_attr_tile<EPI, DUAL, 8, 2, 4>();
+  if constexpr (EPI == EPI_BIAS_RESIDUAL) {
+    if (e == hipSuccess) e = set_attr_tile<EPI, DUAL, 7, 2, 4>();
+  }
   return e != hipSuccess ? e : set_attr_tile<EPI, DUAL, 4, 2, 2>();
 }
 

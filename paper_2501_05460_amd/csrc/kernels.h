@@ -265,7 +265,7 @@ hipError_t mx_rows(const MxRowParams& p, hipStream_t st);
 // A and SA must be readable for round_up(M, 256) rows, W / SW / bias / cscale for Npad rows (Npad % 256 == 0,
 // zero rows past N); K % 128 == 0.  cscale may be null (all ones).
 struct MxGemmParams {
-  int tile;                   // 0: chosen by an estimate; tests / timing: 1 = 256 x 256, 2 = 128 x 128
+  int tile;                   // 0: chosen by an estimate; tests / timing: 1 = 256 x 256, 2 = 128 x 128, 3 = 224 x 256 (residual)
   int epi;
   const unsigned char* A; long lda;
   const unsigned* SA; long sa_ld;

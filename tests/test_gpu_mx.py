@@ -489,3 +489,17 @@ def test_two_products_in_one_launch_agree_bit_for_bit(rows, N, n2, K, n_tok):
     for tile in (0, 1, 2):
         got_c, got_v = B.op_mx_gemm_pair(A, SA, W, SW, bias, cs, W2, SW2, bias2, cs2, n2, n_tok, tile, rows)
         assert torch.equal(got_c, c) and torch.equal(got_v, v), tile
+
+
+@pytest.mark.parametrize("rows,K", [(8, 128), (224, 384), (250, 1024), (480, 128), (7400, 1152), (26520, 384)])
+def test_224_row_tiles_agree_bit_for_bit(rows, K):
+    """A height that does not divide the rows fetched: the last tile's rows stand further on in its buffer (by 192, 224 and 64
+    of them), and past its end; a tile of one row block, whole tiles, more tiles than CUs."""
+    g = torch.Generator().manual_seed(rows + K)
+    N, padded = 1280, (rows + 255) // 256 * 256
+    code = lambda r: (torch.randint(0x28, 0x40, (r, K), generator=g) | torch.randint(0, 2, (r, K), generator=g) << 7).to(torch.uint8).cuda()
+    scale = lambda r: torch.from_numpy(pack_scale_words(torch.randint(122, 127, (r, K // 32), generator=g).numpy())).cuda()
+    A, W, SA, SW = code(padded), code(N), scale(padded), scale(N)
+    bias, cs, R = torch.randn(N, generator=g).cuda(), torch.rand(N, generator=g).cuda() + 0.5, torch.randn(rows, N, generator=g).cuda()
+    run = lambda tile: B.op_mx_gemm(3, A, SA, W, SW, bias, cs, R.clone(), tile=tile, rows=rows)
+    assert torch.equal(run(3), run(1))
