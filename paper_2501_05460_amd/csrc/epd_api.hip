@@ -853,11 +853,17 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
     if (fold) { p.stats_out = c->stats; p.n_part_out = c->n_part; }
   };
   // pre-norm as a kernel of its own: from the fp32 stream, or in place on the bf16 rows a residual epilogue left
-  auto norm_kernel = [&](const float* g, const float* b, bool from_stream) {
+  auto norm_kernel = [&](const float* g, const float* b, bool from_stream, const GemmParams& next) {
     if (fold) return;
     ProfScope ps(c, 1, st);
     if (from_stream) {
       RowOpParams r{d.norm, X, x.D, Xn, c->D_k, g, b, M, x.D, 0, x.g, x.D, d.eps};
+      // A product of few rows on the persistent kernel waits for its weights in its only round: the norm in front of it asks for them, while
+      // rows (6 bytes an element) and weights fit the 32 MiB of L2 or nearly.  Encodes, us: three slices of the 1024-wide encoder
+      // 3583 -> 3512, six 5992 -> 5941, two of the 1152-wide one 4081 -> 4030; seven and eight 6878 -> 6904, 7016 -> 7059, so not there, nor
+      // in front of ring tiles (one slice 1965 -> 1980) or of more weights (6B shape, 64 MB and more: 26.8 -> 27.7 ms).
+      const long bytes = (long)(next.Npad + next.n2_pad) * next.K * 2;
+      if (bytes <= 16 << 20 && (long)M * x.D * 6 <= 40 << 20 && bf16_gemm_on_wide(next)) { r.ahead = (const unsigned char*)next.W; r.ahead_bytes = bytes; }
       bf16_rowop(r, st);
     } else {
       bf16_norm_rows(Xn, c->D_k, g, b, M, x.D, d.norm, d.eps, st);
@@ -898,17 +904,16 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
         p.VT = VT; p.hd_pad = c->hd_pad; p.heads = x.H; p.n_tok = x.Ns;
         HIP_TRY(c, mx_gemm(p, st)); }
     } else {
-    norm_kernel(w.n1_g, w.n1_b, !copy || l == 0);   // the first layer's rows come from the embedding
-    bool paired = false;
+    GemmParams p = gp(EPI_BIAS, Xn, c->D_k, w.qkv, M);
+    p.C = QK; p.ldc = ld_qk;
+    with_norm(p, w.qkv_cs);
+    // few slices: the value projection rides in the same launch (its weights follow the q/k projection's)
+    GemmParams pp = p;
+    pp.n2 = w.v.N; pp.n2_pad = w.v.Npad; pp.VT = VT; pp.hd_pad = c->hd_pad; pp.heads = x.H; pp.n_tok = x.Ns;
+    const bool paired = (const bf16_t*)w.v.W == (const bf16_t*)w.qkv.W + (size_t)w.qkv.Npad * w.qkv.K && w.v.b == w.qkv.b + w.qkv.Npad &&
+                        bf16_gemm_pair_fits(pp);
+    norm_kernel(w.n1_g, w.n1_b, !copy || l == 0, paired ? pp : p);   // the first layer's rows come from the embedding
     { ProfScope ps(c, 2, st);
-      GemmParams p = gp(EPI_BIAS, Xn, c->D_k, w.qkv, M);
-      p.C = QK; p.ldc = ld_qk;
-      with_norm(p, w.qkv_cs);
-      // few slices: the value projection rides in the same launch (its weights follow the q/k projection's)
-      GemmParams pp = p;
-      pp.n2 = w.v.N; pp.n2_pad = w.v.Npad; pp.VT = VT; pp.hd_pad = c->hd_pad; pp.heads = x.H; pp.n_tok = x.Ns;
-      paired = (const bf16_t*)w.v.W == (const bf16_t*)w.qkv.W + (size_t)w.qkv.Npad * w.qkv.K && w.v.b == w.qkv.b + w.qkv.Npad &&
-               bf16_gemm_pair_fits(pp);
       HIP_TRY(c, bf16_gemm(paired ? pp : p, st)); }
     if (!paired) { ProfScope ps(c, 2, st);
       GemmParams pv = gp(EPI_VT, Xn, c->D_k, w.v, M);
@@ -964,14 +969,13 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
         HIP_TRY(c, mx_gemm(p2, st)); }
       continue;
     }
-    norm_kernel(w.n2_g, w.n2_b, !copy);
-    GemmParams p2 = gp(EPI_BIAS_RESIDUAL, Hd, c->F_k, w.fc2, M);
+    GemmParams p1 = gp(act_epi, Xn, c->D_k, w.fc1, M), p2 = gp(EPI_BIAS_RESIDUAL, Hd, c->F_k, w.fc2, M);
+    p1.C = Hd; p1.ldc = c->F_k;
+    p1.c_cached = bf16_gemm_on_64x64(p2);
+    with_norm(p1, w.fc1_cs);
+    norm_kernel(w.n2_g, w.n2_b, !copy, p1);
     { ProfScope ps(c, 7, st);
-      GemmParams p = gp(act_epi, Xn, c->D_k, w.fc1, M);
-      p.C = Hd; p.ldc = c->F_k;
-      p.c_cached = bf16_gemm_on_64x64(p2);
-      with_norm(p, w.fc1_cs);
-      HIP_TRY(c, bf16_gemm(p, st)); }
+      HIP_TRY(c, bf16_gemm(p1, st)); }
     { ProfScope ps(c, 8, st);
       p2.R = X; p2.ldr = x.D;
       with_emit(p2, l + 1 < n_layers);   // the next layer's first norm; nothing reads it after the last layer

@@ -1542,6 +1542,12 @@ bool bf16_gemm_on_64x64(const GemmParams& p) {
   return c.shape < 0 && c.first.form == PLAIN_RING && c.first.tile == RING_64x64;
 }
 
+bool bf16_gemm_on_wide(const GemmParams& p) {
+  if (p.n2_pad > 0) return choose_pair(p).shape >= S_256x128;
+  const Choice c = choose(p);
+  return c.shape >= 0 ? c.shape >= S_256x128 : c.first.form != PLAIN_RING;
+}
+
 // For tests: the shape that runs, by its number in GemmParams::cfg; 0: more than one launch (of a pair: two products)
 int bf16_gemm_shape(const GemmParams& p) {
   static const int number[N_SHAPES] = {11, 13, 14, 1, 9, 15, 16, 17, 12};

@@ -88,6 +88,7 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st);
 bool bf16_gemm_on_64x64(const GemmParams& p);   // whether p, without a folded pre-norm, takes 64 x 64 ring tiles
 // true: bf16_gemm runs p with its second product (n2_pad > 0) as one launch; false: the caller issues two products
 bool bf16_gemm_pair_fits(const GemmParams& p);
+bool bf16_gemm_on_wide(const GemmParams& p);    // whether p, without a folded pre-norm, starts with the persistent kernel (n2_pad > 0: as one launch)
 // the product on the ring kernel's tiles (gemm_bf16_ring.hip: launches of a few slices), any epilogue, n2_pad included
 enum RingTile { RING_64x64 = 0, RING_128x64 = 1, RING_128x128 = 2 };
 hipError_t bf16_gemm_ring(const GemmParams& p, int tile, hipStream_t st);
@@ -164,6 +165,8 @@ struct RowOpParams {
   int g, D;                       // grid side and source row length (shuffle only)
   float eps;
   SliceRows src;                  // source row of patch token r (shuffle: of grid cell r) = src.row(r)
+  const unsigned char* ahead;     // the next product's weights, ahead_bytes of them (whole 128-byte lines), to be on their way while the rows are
+  long ahead_bytes;               // normalised; 0: none
 };
 void bf16_rowop(const RowOpParams& p, hipStream_t st);
 

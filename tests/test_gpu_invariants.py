@@ -104,6 +104,19 @@ def test_micro_batch_size_does_not_change_the_bits(setup):
         enc2.close()
 
 
+@pytest.mark.parametrize("hidden,mlp,tile,n", [(1024, 4096, 448, 3), (1152, 4304, 448, 5), (1152, 4304, 378, 4), (1024, 4096, 448, 7)])
+def test_weights_asked_for_in_front_of_a_product_change_no_bits(hidden, mlp, tile, n):
+    """Norms that ask for the next product's weights (the persistent kernel behind them, few enough rows; the last: too many) against
+    the slices alone (ring tiles: no such norm)."""
+    desc = desc_for(wl.DT_BF16, tile_size=tile, hidden=hidden, heads=16, mlp=mlp, layers=2, act=wl.ACT_GELU_TANH, pixel_shuffle=tile % 28 == 0)
+    enc = make_encoder(desc, wl.gen_weights(desc, 41, std=0.03))
+    tiles = torch.from_numpy(wl.gen_tiles(desc, 41, n)).cuda()
+    full, per = bits(enc.encode(tiles, [0, n])), enc.tokens_per_tile
+    for t in (0, n - 1):
+        assert np.array_equal(bits(enc.encode(tiles[t:t + 1].contiguous(), [0, 1])), full[t * per:(t + 1) * per]), t
+    enc.close()
+
+
 @pytest.mark.parametrize("tile,n,cls,act", [(336, 3, 0, wl.ACT_GELU_ERF), (224, 6, 1, wl.ACT_GELU_TANH)])
 def test_wide_layers_of_a_few_slices_leave_the_bits_of_each_slice_alone(tile, n, cls, act):
     """1728 and 1584 rows (ragged: 1584 is no whole number of 256-row tiles): FC1 on 256 x 128 tiles with FC2 behind it on
