@@ -1202,7 +1202,7 @@ hipError_t launch_persist(const GemmParams& p, hipStream_t st) {
   return hipGetLastError();
 }
 
-bool persist_res() {   // EPD_PERSIST_RES=0: the residual products stay on the one-tile-per-workgroup kernels
+bool persist_res() {   // EPD_PERSIST_RES=0: the residual products stay on the one-tile-per-workgroup kernels (ring tiles and this file's 256 x 256 ones)
   static const bool on = !(getenv("EPD_PERSIST_RES") && getenv("EPD_PERSIST_RES")[0] == '0');
   return on;
 }
@@ -1355,8 +1355,9 @@ static Plain choose_plain(const GemmParams& p) {
   auto offer = [&](PlainForm form, int tile, long rows_a, double us) { if (us < best.us) best = {form, tile, rows_a, us}; };
   // 128 columns over many rows stream the activations at the memory's rate: 256 x 128 tiles fetch each row once (the cut
   // columns of the 6B shape's FC2, 40960 rows: 277 us, on 128 x 64 ring tiles 315)
-  if (p.Npad == 128 && gm * 2 > cus) return {PLAIN_256x128, 0, 0, ring.us};
-  offer(PLAIN_256x128, 0, 0, one_round_128(p));
+  const bool persistent = !residual || persist_res();
+  if (p.Npad == 128 && gm * 2 > cus && persistent) return {PLAIN_256x128, 0, 0, ring.us};
+  if (persistent) offer(PLAIN_256x128, 0, 0, one_round_128(p));
   if (p.Npad % 256 != 0) return best;
   const long tiles = gm * (p.Npad / 256);
   // A width like 3200 leaves the last 256-wide tile column half used.  When that column is also what
@@ -1375,7 +1376,7 @@ static Plain choose_plain(const GemmParams& p) {
   // A width of 1152 is four and a half 256-wide tile columns and six 192-wide ones: 240 tiles in one round instead of
   // 200 for the residual products of the 10-slice SigLIP-shaped request (-8 % on both), but 6 rounds for 5 in 64 slices
   // (FC2 642 us on 256 x 256 tiles, 677 on these).
-  if (residual && persist_res() && tiles_192() && p.N % 192 == 0 && p.N % 256 != 0)
+  if (residual && persistent && tiles_192() && p.N % 192 == 0 && p.N % 256 != 0)
     offer(PLAIN_192, 0, 0, rounds_of(gm * (p.N / 192), [&](double n) { return round_192(n, p.K); }));
   return best;
 }
@@ -1437,11 +1438,11 @@ static bool shape_runs(const GemmParams& p, int shape) {
   const Fit& f = FITS[kind_of(p)][shape];
   if (f.uk == 0 && f.vk == 0) return false;
   if (shape <= S_128x128) return few_128_tiles(p);
+  if (kind_of(p) == K_RESIDUAL && !persist_res()) return false;
   if (shape == S_256x128) return true;
   const int tn = SHAPE_COLS[shape], n = p.n2_pad > 0 ? p.n2 : p.N, pad = p.n2_pad > 0 ? p.n2_pad : p.Npad;
   if (p.n2_pad > 0 && p.Npad % tn != 0) return false;
   if (shape == S_192 && (!tiles_192() || n % 192 != 0)) return false;
-  if (kind_of(p) == K_RESIDUAL && !persist_res()) return false;
   return (n + tn - 1) / tn * tn <= pad;
 }
 static hipError_t launch_shape(const GemmParams& p, int shape, hipStream_t st) {
@@ -1554,6 +1555,7 @@ int bf16_gemm_shape(const GemmParams& p) {
   if (p.n2_pad > 0) return bf16_gemm_pair_fits(p) ? number[choose_pair(p).shape] : 0;
   const Choice c = choose(p);
   if (c.shape >= 0) return c.shape == S_256 && p.epi == EPI_BIAS_RESIDUAL ? 10 : number[c.shape];
+  if (c.first.form == PLAIN_256 && c.first.rows_a == 0 && p.epi == EPI_BIAS_RESIDUAL && !persist_res()) return a_direct() && p.K >= 2048 ? 8 : 7;
   long rows = 0;
   const int form = bf16_gemm_choice(p, &rows);
   return rows < p.M ? 0 : form;

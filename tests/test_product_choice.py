@@ -1,4 +1,8 @@
 """Which form of the bf16 product and of attention the library takes, held against measured times of the forms (host only)."""
+import os
+import subprocess
+import sys
+
 import pytest
 
 from paper_2501_05460_amd import binding as B
@@ -105,3 +109,21 @@ def test_attention_width_rejects_what_attention_does_not_take():
     for args in ((0, 1024, 16, 64), (1, 0, 16, 64), (1, 1024, 0, 64), (1, 1024, 16, 80)):
         with pytest.raises(B.EpdError):
             B.op_attention_queries(*args)
+
+
+def test_residual_products_leave_the_persistent_kernels_when_told_to():
+    """EPD_PERSIST_RES=0 (read once a process): ring tiles, the 256 x 256 kernels with a tile per workgroup (7, 8), or cuts of these
+    two (0); with the switch as it is by default the same products reach the persistent forms."""
+    shapes = [(m, n, k) for m in (1024, 2304, 5120, 8192, 16928, 40960, 65536, 106496)
+              for n, k in ((1152, 4352), (1152, 1152), (1024, 4096), (1024, 1024), (3200, 12800), (3200, 3200), (128, 1024))]
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    code = "from paper_2501_05460_amd import binding as B; print(*[B.op_gemm_bf16_shape(m, n, k, 3) for m, n, k in %r])" % (shapes,)
+
+    def taken(value):
+        r = subprocess.run([sys.executable, "-c", code], env=dict(os.environ, EPD_PERSIST_RES=value), cwd=root, capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr
+        return {int(v) for v in r.stdout.split()}
+
+    assert {1, 10, 12, 15} <= taken("1")
+    off = taken("0")
+    assert {7, 8, 11, 13, 14} <= off <= {0, 7, 8, 11, 13, 14}, off
