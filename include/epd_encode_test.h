@@ -34,31 +34,35 @@ epd_status epd_op_gemm_bf16(const void* A, const void* W, const float* bias, voi
  * other: epi 0 bias, 1 bias + GELU(erf), 2 bias + GELU(tanh) -> C [M,N] bf16; epi 3 -> R [M,N]
  * fp32 += A W^T + bias (C unused); epi 4 -> R [M,N] = A W^T + bias + pos[row % n_tok] (pos [n_tok,N] fp32); epi 5 -> C bf16
  * transposed per slice of n_tok rows, [M / n_tok, N, n_tok] (n_tok % 8 == 0, M % n_tok == 0).  form 0 = what the library would pick (W and bias padded as it pads its weights), 1 = 256x128 tile,
- * persistent, 4 = the same tile, one per workgroup (not epi 4), 2, 3 (K % 256 == 0) and 14 = 128x128 tile, both operand slabs in an LDS ring (one kernel: 2 and 3 differ in epd_op_norm_gemm_bf16 and
+ * persistent, 5 = 256x256 tiles in whole rounds and the rows behind them on ring tiles (where the library's estimate has such a cut: an
+ * error otherwise), 18 = whole 256-wide tile columns and the last 128 columns apart (epi 3, N % 256 in 1 .. 128 and N > 256), 2, 3 (K % 256 == 0) and 14 = 128x128 tile, both operand slabs in an LDS ring (one kernel: 2 and 3 differ in epd_op_norm_gemm_bf16 and
  * epd_op_gemm_residual_stats only), 13 = 128x64 tile of the same kernel, 6 = 256x256 tile with the plain loop, 7 = pipelined loop, 8 = pipelined loop with both operand slabs
  * loaded straight into LDS, 9 = persistent kernel on 256x256 tiles (not epi 3), 10 = persistent kernel of the residual product (epi 3 only),
  * 11 = 64x64 tile of the ring kernel (11, 13, 14: what the library picks from for launches of a few slices).
  * 12 = the persistent residual product on 256x192 tiles (epi 3 only, N % 192 == 0: what the library picks for a
  * width like 1152, which is six such tile columns and four and a half 256-wide ones).
  * 15 = the persistent kernel on 224x256 tiles (epi 1, 2 and 3).
- * M >= 1 (any), N % 128 == 0 (N % 256 == 0 for forms 6 to 10 and 15), K % 128 == 0; bias [N] fp32.
+ * M >= 1 (any), N % 128 == 0 (N % 256 == 0 for forms 6 to 10 and 15; W and bias of forms 0, 5 and 18 are padded by the call), K % 128 == 0; bias [N] fp32.
  * A [M,K], C [M,N] and R [M,N] hold exactly M rows; no row past M is written.  (The kernels read whole
  * 256-row tiles; for a ragged M, for R and for padded weights the call runs on copies it allocates, and synchronises.) */
 epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias, void* C, float* R, const float* pos,
                                  int32_t M, int32_t N, int32_t K, int32_t n_tok, int32_t epi, int32_t form,
                                  void* hip_stream);
 
-/* The form the library weighs first for a product of M rows, N columns (padded as the library pads its weights) and K, by
- * epilogue as above and 4 = patch embedding, 5 = value projection (slices of n_tok rows each): *form as above (10 / 9
- * for 256x256 tiles of residual / other products, 0: whole 256-wide tile columns and the rest apart); *rows: the rows in front of a row cut, M
- * without one.  A second stage may take another shape in its place, see epd_op_gemm_bf16_shape.  Host only: launches nothing, and counts
- * 256 CUs where there is no device. */
-epd_status epd_op_gemm_bf16_choice(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t n_tok, int32_t* form, int32_t* rows);
-
-/* The shape that runs, by its number as a form above (10: 9 of a residual product); 0: a product cut into two launches.  n2 > 0 (epi 0):
- * the q/k projection, N columns, and the value projection over the same rows, n2 columns in slices of n_tok rows: 16 and 17 = 192x256
- * and 160x256 tiles; 0: two products in a launch each.  Host only, as above. */
+/* What runs for a product of M rows, N columns (padded as the library pads its weights) and K, by epilogue as above (5 = value projection,
+ * slices of n_tok rows each): *form as above.  n2 > 0 (epi 0): the q/k projection, N columns, and the value projection over the same rows, n2
+ * columns in slices of n_tok rows: 16 and 17 = 192x256 and 160x256 tiles; 0: two products in a launch each.  Host only: launches
+ * nothing, and counts 256 CUs where there is no device. */
 epd_status epd_op_gemm_bf16_shape(int32_t M, int32_t N, int32_t K, int32_t n2, int32_t epi, int32_t n_tok, int32_t* form);
+
+/* Microseconds of such a product (form as above, n2 > 0: of a pair, 0 = as the library picks) among other kernels: `reps` times an RMSNorm of
+ * x [M,K] fp32 (gain gamma [K]) into A and the product of A with the next of n_w weight matrices, less the same norms by themselves; the
+ * median of five such differences.  A [M rounded up to 256, K] bf16, W [n_w][rows, K] bf16 and bias [rows] fp32 with rows as the library pads them: N to a
+ * multiple of 256 (128 up to 128), n2 > 0 likewise behind them; C [M,N] bf16 (epi 0 to 2), V bf16 of M * N (epi 5) or M * n2 elements, R fp32 of
+ * M rounded up to 256 times N, plus 256 elements (epi 3).  Synchronises. */
+epd_status epd_op_gemm_bf16_us(const float* x, const float* gamma, void* A, const void* W, int32_t n_w, const float* bias, void* C, void* V, float* R,
+                               int32_t M, int32_t N, int32_t n2, int32_t K, int32_t epi, int32_t n_tok, int32_t form, int32_t reps, float* us,
+                               void* hip_stream);
 
 /* Two products over the same rows in one launch: C [M,N] bf16 = A W[:N]^T + bias[:N], and VT bf16 [M / n_tok, n2, n_tok] the
  * transposed A W[N:]^T + bias[N:].  W [N + n2, K], N % 256 == 0, n2 % 128 == 0 and n2 > 128, K % 128 == 0, n_tok % 8 == 0, M % n_tok == 0; form 9, 11 to 17 as above (12: N and
@@ -94,10 +98,14 @@ epd_status epd_op_norm_gemm_bf16(const float* x, const float* gamma, const float
  * bf16 [T * n_tokens, H * hd_pad].  hd_pad in {64, 72, 96, 128}, n_tokens % 64 == 0.
  * Only the first n_keys (1 .. n_tokens) rows of a slice are tokens:
  * the others are left out of every softmax as keys, and their rows of o hold unused values.
- * paired: the order of summation of calls of the MXFP8 option. */
+ * paired: the order of summation of calls of the MXFP8 option.
+ * epd_op_attention_us: microseconds of such a call with 16 or 32 queries per wave (0: as the library picks), mean of `reps` back to back. */
 epd_status epd_op_attention_bf16(const void* q, const void* k, const void* vt, void* o,
                                  int32_t n_slices, int32_t n_tokens, int32_t n_keys, int32_t heads,
                                  int32_t hd_pad, int32_t ld_qk, int32_t paired, void* hip_stream);
+epd_status epd_op_attention_us(const void* q, const void* k, const void* vt, void* o, int32_t n_slices, int32_t n_tokens, int32_t n_keys,
+                               int32_t heads, int32_t hd_pad, int32_t ld_qk, int32_t paired, int32_t queries, int32_t reps, float* us,
+                               void* hip_stream);
 
 /* Queries per wave of that call: *queries = 16 or 32 (hd_pad 64, 72, 96 or 128).  Host only: launches nothing, and counts 256 CUs
  * where there is no device. */
@@ -126,6 +134,12 @@ epd_status epd_op_mfma_probe(const void* A, const void* B, float* D, void* hip_s
  *   then converted: codes Cq [M, N], scales SC [N / 128, M]; epi 3 -> R fp32 [M, N] += out.
  * epd_op_mx_gemm_pair: the products with W (epi 0) and W2 (epi 5, one head of n2 features; n2 % 8 == 0; W2, SW2, bias2 and cscale2 hold
  *   n2_pad rows, n2_pad % 256 == 0) of the same A: tile 0 = as the library picks, in one launch or two, 1 / 2 = one launch.
+ * epd_op_mx_gemm_tile: the tile as the library picks it for such a product (n2 > 0: a pair, 0 = a launch each).  Host only, counts 256 CUs where
+ *   there is no device.
+ * epd_op_mx_gemm_us: microseconds of such a product or pair among other kernels, as epd_op_gemm_bf16_us: x [M, K] fp32 -> codes A, words SA by an
+ *   RMSNorm with conversion, then the product with the next of n_w weight matrices W [n_w][Np + n2p rows, K], SW [n_w][K / 128][Np], SW2 [n_w][K / 128][n2p],
+ *   N and n2 multiples of 8, Np and n2p these rounded up to 256, rows of W2 behind those of W; bias and cscale hold Np + n2p values, Cq and SC (epi 1, 2) rows
+ *   of N rounded up to 128.
  * epd_op_mx_mfma_probe: one v_mfma_scale_f32_16x16x128_f8f6f4 on caller-supplied registers (a, b: int32 [64][8],
  *   sa, sb: int32 [64], scale byte 0 used; d: fp32 [64][4]), for the operand-layout test.  All pointers dev. */
 epd_status epd_op_mx_rows(const void* in, int32_t in_bf16, int64_t rows, int32_t dim, int32_t kind, const float* gamma,
@@ -136,6 +150,10 @@ epd_status epd_op_mx_gemm(int32_t epi, int32_t tile, const void* A, const void* 
 epd_status epd_op_mx_gemm_pair(int32_t tile, const void* A, const void* SA, const void* W, const void* SW, const float* bias, const float* cscale, const void* W2,
                                const void* SW2, const float* bias2, const float* cscale2, int32_t M, int32_t N, int32_t n2, int32_t n2_pad, int32_t K,
                                void* C, void* VT, int32_t n_tok, void* hip_stream);
+epd_status epd_op_mx_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t n2, int32_t epi, int32_t* tile);
+epd_status epd_op_mx_gemm_us(const float* x, const float* gamma, void* A, void* SA, const void* W, const void* SW, const void* SW2, int32_t n_w,
+                             const float* bias, const float* cscale, void* C, void* V, float* R, void* Cq, void* SC, int32_t M, int32_t N, int32_t n2, int32_t K,
+                             int32_t epi, int32_t n_tok, int32_t tile, int32_t reps, float* us, void* hip_stream);
 epd_status epd_op_mx_mfma_probe(const void* a, const void* b, const void* sa, const void* sb, float* d, void* hip_stream);
 
 /* Per-kernel-family timing of the previous epd_encode / epd_encode_range

@@ -32,12 +32,12 @@ PROF_FAMILIES = ("embed", "norm", "gemm_qkv", "attention", "qk_norm", "proj_inpu
 EXPORTS = (
     "epd_weight_count", "epd_check_desc", "epd_check_offsets", "epd_create", "epd_encode",
     "epd_encode_range", "epd_tokens_per_tile", "epd_out_dim", "epd_last_error", "epd_destroy",
-    "epd_debug_read_stream", "epd_op_gemm_bf16", "epd_op_gemm_bf16_form", "epd_op_gemm_bf16_choice",
-    "epd_op_gemm_bf16_shape", "epd_op_gemm_bf16_pair",
-    "epd_op_attention_bf16", "epd_op_attention_queries", "epd_op_mfma_probe",
+    "epd_debug_read_stream", "epd_op_gemm_bf16", "epd_op_gemm_bf16_form", "epd_op_gemm_bf16_shape",
+    "epd_op_gemm_bf16_us", "epd_op_gemm_bf16_pair",
+    "epd_op_attention_bf16", "epd_op_attention_us", "epd_op_attention_queries", "epd_op_mfma_probe",
     "epd_profile_enable", "epd_profile_read", "epd_op_mfma_peak", "epd_op_copy_peak", "epd_op_coissue",
     "epd_op_row_stats", "epd_op_gemm_residual_stats", "epd_op_norm_gemm_bf16",
-    "epd_op_mx_rows", "epd_op_mx_gemm", "epd_op_mx_gemm_pair", "epd_op_mx_mfma_probe", "epd_op_attention_mx",
+    "epd_op_mx_rows", "epd_op_mx_gemm", "epd_op_mx_gemm_pair", "epd_op_mx_gemm_tile", "epd_op_mx_gemm_us", "epd_op_mx_mfma_probe", "epd_op_attention_mx",
     "epd_mm_cache_create", "epd_mm_cache_destroy", "epd_mm_cache_free_blocks", "epd_mm_cache_base",
     "epd_mm_last_error", "epd_mm_alloc", "epd_mm_free", "epd_encode_paged", "epd_mm_transfer", "epd_mm_transfer_noalloc", "epd_mm_gather",
     "epd_encode_trunk_paged", "epd_project_merge",
@@ -101,8 +101,14 @@ def lib() -> ctypes.CDLL:
         L.epd_op_gemm_bf16.restype = i32
         L.epd_op_gemm_bf16_form.argtypes = [vp, vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
         L.epd_op_gemm_bf16_form.restype = i32
-        L.epd_op_gemm_bf16_choice.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(i32), ctypes.POINTER(i32)]
-        L.epd_op_gemm_bf16_choice.restype = i32
+        L.epd_op_gemm_bf16_us.argtypes = [vp, vp, vp, vp, i32, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, i32, ctypes.POINTER(ctypes.c_float), vp]
+        L.epd_op_gemm_bf16_us.restype = i32
+        L.epd_op_attention_us.argtypes = [vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, i32, i32, i32, ctypes.POINTER(ctypes.c_float), vp]
+        L.epd_op_attention_us.restype = i32
+        L.epd_op_mx_gemm_tile.argtypes = [i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
+        L.epd_op_mx_gemm_tile.restype = i32
+        L.epd_op_mx_gemm_us.argtypes = [vp] * 7 + [i32] + [vp] * 7 + [i32] * 8 + [ctypes.POINTER(ctypes.c_float), vp]
+        L.epd_op_mx_gemm_us.restype = i32
         L.epd_op_gemm_bf16_shape.argtypes = [i32, i32, i32, i32, i32, i32, ctypes.POINTER(i32)]
         L.epd_op_gemm_bf16_shape.restype = i32
         L.epd_op_gemm_bf16_pair.argtypes = [vp, vp, vp, vp, vp, i32, i32, i32, i32, i32, i32, vp]
@@ -419,22 +425,22 @@ def op_gemm_bf16(A: torch.Tensor, W: torch.Tensor, bias: Optional[torch.Tensor],
     return C, ms.value
 
 
-def op_gemm_bf16_choice(M: int, N: int, K: int, epi: int, n_tok: int = 1):
-    """(form, rows in front of a row cut) the library weighs first for a product of this shape; host only."""
-    form, rows = ctypes.c_int32(), ctypes.c_int32()
-    s = lib().epd_op_gemm_bf16_choice(M, N, K, epi, n_tok, ctypes.byref(form), ctypes.byref(rows))
-    if s != EPD_OK:
-        raise EpdError(s, lib().epd_last_error(None).decode())
-    return form.value, rows.value
-
-
 def op_gemm_bf16_shape(M: int, N: int, K: int, epi: int, n2: int = 0, n_tok: int = 1) -> int:
-    """Number of the form that runs for a product of this shape, or for two over the same rows (n2 > 0); host only."""
+    """Number of the form that runs for a product of this shape, or for two over the same rows (n2 > 0; 0: a launch each); host only."""
     form = ctypes.c_int32()
     s = lib().epd_op_gemm_bf16_shape(M, N, K, n2, epi, n_tok, ctypes.byref(form))
     if s != EPD_OK:
         raise EpdError(s, lib().epd_last_error(None).decode())
     return form.value
+
+
+def op_mx_gemm_tile(M: int, N: int, K: int, epi: int, n2: int = 0) -> int:
+    """Tile that op_mx_gemm takes for a product of this shape, or for two over the same rows (n2 > 0; 0: a launch each); host only."""
+    tile = ctypes.c_int32()
+    s = lib().epd_op_mx_gemm_tile(M, N, K, n2, epi, ctypes.byref(tile))
+    if s != EPD_OK:
+        raise EpdError(s, lib().epd_last_error(None).decode())
+    return tile.value
 
 
 def op_gemm_bf16_pair(A: torch.Tensor, W: torch.Tensor, bias: torch.Tensor, N: int, n_tok: int, form: int):

@@ -672,9 +672,9 @@ bool short_waves(int n_slices, int n_q, int heads, int hd, bool paired) {
 template <int HD, bool PAIRED>
 hipError_t launch_attn(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                        int n_tok, int n_keys, int n_q, int q_shared, int heads, long ld_qk, long ld_o,
-                       unsigned char* oq, unsigned* so, long ld_so, hipStream_t st) {
+                       unsigned char* oq, unsigned* so, long ld_so, int queries, hipStream_t st) {
   const bool mask = n_keys < n_tok || n_tok % BKEY != 0;
-  if (short_waves(n_slices, n_q, heads, HD, PAIRED))
+  if (queries == 16 || (queries == 0 && short_waves(n_slices, n_q, heads, HD, PAIRED)))
     return mask ? launch_attn_m<HD, 1, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
                 : launch_attn_m<HD, 1, false, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
   return mask ? launch_attn_m<HD, 2, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
@@ -713,7 +713,7 @@ int bf16_attention_queries(int n_slices, int n_q, int heads, int hd_pad, bool pa
 
 hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                           int n_tok, int n_keys, int n_q, int q_shared, int heads, int hd_pad, long ld_qk,
-                          long ld_o, hipStream_t st, unsigned char* oq, unsigned* so, long ld_so, bool paired) {
+                          long ld_o, hipStream_t st, unsigned char* oq, unsigned* so, long ld_so, bool paired, int queries) {
   if (n_slices == 0) return hipSuccess;
   // MXFP8 output: whole blocks of 32 per head only, rows of at least heads * hd_pad bytes, 4-byte pieces
   if (oq && (hd_pad % 32 != 0 || !so || ld_o % 4 != 0 || ld_o < (long)heads * hd_pad || ld_so < (long)n_slices * n_q)) return hipErrorInvalidValue;
@@ -722,8 +722,8 @@ hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf
   if (n_tok % 8 != 0 || n_tok <= 0 || n_keys < 1 || n_keys > n_tok || n_q < 1) return hipErrorInvalidValue;
   if (!q_shared && n_q != n_tok) return hipErrorInvalidValue;   // a slice's own rows: one query per row
 #define LAUNCH(HD)                                                                                                       \
-  return paired || oq ? launch_attn<HD, true>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st) \
-                      : launch_attn<HD, false>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
+  return paired || oq ? launch_attn<HD, true>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, queries, st) \
+                      : launch_attn<HD, false>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, queries, st)
   switch (hd_pad) {
     case 64: LAUNCH(64);
     case 72: LAUNCH(72);

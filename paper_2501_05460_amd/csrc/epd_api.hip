@@ -1110,6 +1110,36 @@ epd_status encode_range_impl(epd_ctx* c, const float* tiles, int32_t n_total, in
 // ============================================================================
 // exported functions
 // ============================================================================
+// Microseconds of op(i) behind pre(): `reps` of both less `reps` of pre() alone, the median of five such differences.
+template <typename Pre, typename Op>
+static hipError_t time_behind(Pre pre, Op op, int reps, float* us, hipStream_t st) {
+  hipEvent_t e0, e1, e2;
+  hipError_t err = hipEventCreate(&e0);
+  if (err != hipSuccess) return err;
+  if ((err = hipEventCreate(&e1)) != hipSuccess) { (void)hipEventDestroy(e0); return err; }
+  if ((err = hipEventCreate(&e2)) != hipSuccess) { (void)hipEventDestroy(e0); (void)hipEventDestroy(e1); return err; }
+  float t[5];
+  int n = 0;
+  pre();
+  err = op(n++);
+  for (int r = 0; r < 5 && err == hipSuccess; ++r) {
+    (void)hipEventRecord(e0, st);
+    for (int i = 0; i < reps; ++i) pre();
+    (void)hipEventRecord(e1, st);
+    for (int i = 0; i < reps && err == hipSuccess; ++i) { pre(); err = op(n++); }
+    (void)hipEventRecord(e2, st);
+    const hipError_t s = hipEventSynchronize(e2);
+    float alone = 0.f, both = 0.f;
+    if (err == hipSuccess) err = s;
+    if (err == hipSuccess) err = hipEventElapsedTime(&alone, e0, e1);
+    if (err == hipSuccess) err = hipEventElapsedTime(&both, e1, e2);
+    t[r] = (both - alone) * 1e3f / reps;
+  }
+  (void)hipEventDestroy(e0); (void)hipEventDestroy(e1); (void)hipEventDestroy(e2);
+  if (err == hipSuccess) { std::sort(t, t + 5); *us = t[2]; }
+  return err;
+}
+
 extern "C" {
 
 int32_t epd_weight_count(const epd_model_desc* desc) {
@@ -1361,7 +1391,7 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
   if (!A || !W || !bias || (residual || embed ? !R : !C) || (embed && (!pos || n_tok <= 0)) ||
       (values && (n_tok <= 0 || n_tok % 8 || M % n_tok)) || M <= 0 || N <= 0 || K <= 0 || N % 128 || K % 128 ||
       !(epi == EPI_BIAS || epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH || residual || embed || values) ||
-      !((form >= 0 && form <= 4) || (form >= 6 && form <= 15)) || (form == 4 && embed) ||
+      !((form >= 0 && form <= 3) || (form >= 5 && form <= 15) || form == 18) ||
       (form == 3 && K % 256) || (form >= 6 && form <= 10 && N % 256) || (form == 9 && residual) || (form == 10 && !residual) ||
       (form == 12 && (!residual || N % 192)) || (form == 15 && (N % 256 || !(residual || epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH)))) {
     set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_form: bad argument");
@@ -1375,8 +1405,8 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
   void* Ap = nullptr;
   float* Rp = nullptr;
   const bool pad_a = Mp != M, pad_r = residual;   // R also needs 256 floats of slack behind its last row
-  // what the library picks (form 0) is picked for weights padded as the library pads them
-  const int Npad = form == 0 ? pad_n(N) : N;
+  // what the library picks (form 0), and its cuts, are picked for weights padded as the library pads them
+  const int Npad = form == 0 || form == 5 || form == 18 ? pad_n(N) : N;
   const bool pad_w = Npad != N;
   void* Wp = nullptr;
   float* bp = nullptr;
@@ -1424,20 +1454,6 @@ epd_status epd_op_gemm_bf16_form(const void* A, const void* W, const float* bias
   return EPD_OK;
 }
 
-epd_status epd_op_gemm_bf16_choice(int32_t M, int32_t N, int32_t K, int32_t epi, int32_t n_tok, int32_t* form, int32_t* rows) {
-  if (!form || !rows || M <= 0 || N <= 0 || N % 4 || K <= 0 || K % 128 || epi < EPI_BIAS || epi > EPI_VT || (epi == EPI_VT && n_tok <= 0)) {
-    set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_choice: bad argument");
-    return EPD_ERR_INVALID_ARG;
-  }
-  GemmParams p;
-  memset(&p, 0, sizeof(p));
-  p.epi = epi; p.M = M; p.N = N; p.K = K; p.Npad = pad_n(N); p.n_tok = n_tok;
-  long front = 0;
-  *form = bf16_gemm_choice(p, &front);
-  *rows = (int32_t)front;
-  return EPD_OK;
-}
-
 epd_status epd_op_gemm_bf16_shape(int32_t M, int32_t N, int32_t K, int32_t n2, int32_t epi, int32_t n_tok, int32_t* form) {
   if (!form || M <= 0 || N <= 0 || N % 4 || K <= 0 || K % 128 || n2 < 0 || n2 % 4 || epi < EPI_BIAS || epi > EPI_VT || (n2 > 0 && epi != EPI_BIAS) ||
       ((epi == EPI_VT || n2 > 0) && n_tok <= 0)) {
@@ -1448,6 +1464,30 @@ epd_status epd_op_gemm_bf16_shape(int32_t M, int32_t N, int32_t K, int32_t n2, i
   memset(&p, 0, sizeof(p));
   p.epi = epi; p.M = M; p.N = N; p.K = K; p.Npad = pad_n(N); p.n2 = n2; p.n2_pad = n2 > 0 ? pad_n(n2) : 0; p.n_tok = n_tok;
   *form = bf16_gemm_shape(p);
+  return EPD_OK;
+}
+
+epd_status epd_op_gemm_bf16_us(const float* x, const float* gamma, void* A, const void* W, int32_t n_w, const float* bias, void* C, void* V, float* R,
+                               int32_t M, int32_t N, int32_t n2, int32_t K, int32_t epi, int32_t n_tok, int32_t form, int32_t reps, float* us,
+                               void* hip_stream) {
+  const bool residual = epi == EPI_BIAS_RESIDUAL, values = epi == EPI_VT;
+  if (!x || !gamma || !A || !W || n_w < 1 || !bias || !us || reps < 1 || M <= 0 || N <= 0 || N % 8 || K <= 0 || K % 128 || n2 < 0 || n2 % 8 ||
+      epi < EPI_BIAS || epi > EPI_VT || epi == EPI_BIAS_POS || (n2 > 0 && epi != EPI_BIAS) || (residual ? !R : values ? !V : !C) || (n2 > 0 && !V) ||
+      ((values || n2 > 0) && (n_tok <= 0 || n_tok % 8 || M % n_tok))) {
+    set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_us: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  if (bf16_gemm_init() != hipSuccess) return EPD_ERR_HIP;
+  hipStream_t st = (hipStream_t)hip_stream;
+  GemmParams p;
+  memset(&p, 0, sizeof(p));
+  p.epi = epi; p.cfg = form; p.A = (const bf16_t*)A; p.lda = K; p.bias = bias; p.M = M; p.N = N; p.Npad = pad_n(N); p.K = K; p.C = (bf16_t*)C; p.ldc = N;
+  p.R = R; p.ldr = N; p.n_pos = 1; p.VT = (bf16_t*)V; p.heads = 1; p.hd_pad = n2 > 0 ? n2 : N; p.n_tok = n_tok; p.n2 = n2; p.n2_pad = n2 > 0 ? pad_n(n2) : 0;
+  const RowOpParams r{1, x, K, (bf16_t*)A, K, gamma, nullptr, M, K, 0, 1, K, 1e-6f};
+  const long step = (long)(p.Npad + p.n2_pad) * K;
+  const hipError_t e = time_behind([&] { bf16_rowop(r, st); },
+                                   [&](int i) { p.W = (const bf16_t*)W + i % n_w * step; return bf16_gemm(p, st); }, reps, us, st);
+  if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "epd_op_gemm_bf16_us: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_INVALID_ARG : EPD_ERR_HIP; }
   return EPD_OK;
 }
 
@@ -1577,6 +1617,21 @@ epd_status epd_op_attention_bf16(const void* q, const void* k, const void* vt, v
   return EPD_OK;
 }
 
+epd_status epd_op_attention_us(const void* q, const void* k, const void* vt, void* o, int32_t n_slices, int32_t n_tokens, int32_t n_keys,
+                               int32_t heads, int32_t hd_pad, int32_t ld_qk, int32_t paired, int32_t queries, int32_t reps, float* us, void* hip_stream) {
+  if (!q || !k || !vt || !o || !us || reps < 1 || n_tokens % 64 || !(queries == 0 || queries == 16 || queries == 32)) {
+    set_err(g_err, sizeof(g_err), "epd_op_attention_us: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  if (bf16_attention_init() != hipSuccess) return EPD_ERR_HIP;
+  hipStream_t st = (hipStream_t)hip_stream;
+  const hipError_t e = time_behind([] {}, [&](int) {
+    return bf16_attention((const bf16_t*)q, (const bf16_t*)k, (const bf16_t*)vt, (bf16_t*)o, n_slices, n_tokens, n_keys, n_tokens, 0, heads, hd_pad,
+                          ld_qk, (long)heads * hd_pad, st, nullptr, nullptr, 0, paired != 0, queries); }, reps, us, st);
+  if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "epd_op_attention_us: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_INVALID_ARG : EPD_ERR_HIP; }
+  return EPD_OK;
+}
+
 epd_status epd_op_attention_mx(const void* q, const void* k, const void* vt, void* codes, void* scales, int32_t n_slices,
                                int32_t n_tokens, int32_t n_keys, int32_t heads, int32_t hd_pad, int32_t ld_qk, void* hip_stream) {
   if (!q || !k || !vt || !codes || !scales) return EPD_ERR_INVALID_ARG;
@@ -1679,6 +1734,49 @@ epd_status epd_op_mx_gemm_pair(int32_t tile, const void* A, const void* SA, cons
   p.VT = (bf16_t*)VT; p.heads = 1; p.hd_pad = n2; p.n_tok = n_tok;
   const hipError_t e = mx_gemm(p, (hipStream_t)hip_stream);
   if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "epd_op_mx_gemm_pair: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_INVALID_ARG : EPD_ERR_HIP; }
+  return EPD_OK;
+}
+
+epd_status epd_op_mx_gemm_tile(int32_t M, int32_t N, int32_t K, int32_t n2, int32_t epi, int32_t* tile) {
+  if (!tile || M <= 0 || N <= 0 || K <= 0 || K % 128 || n2 < 0 || epi < EPI_BIAS || epi > EPI_VT || epi == EPI_BIAS_POS || (n2 > 0 && epi != EPI_BIAS)) {
+    set_err(g_err, sizeof(g_err), "epd_op_mx_gemm_tile: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  MxGemmParams p;
+  memset(&p, 0, sizeof(p));
+  p.epi = epi; p.M = M; p.N = N; p.K = K; p.n2 = n2;
+  *tile = mx_gemm_tile(p);
+  return EPD_OK;
+}
+
+epd_status epd_op_mx_gemm_us(const float* x, const float* gamma, void* A, void* SA, const void* W, const void* SW, const void* SW2, int32_t n_w,
+                             const float* bias, const float* cscale, void* C, void* V, float* R, void* Cq, void* SC, int32_t M, int32_t N, int32_t n2, int32_t K,
+                             int32_t epi, int32_t n_tok, int32_t tile, int32_t reps, float* us, void* hip_stream) {
+  const bool residual = epi == EPI_BIAS_RESIDUAL, values = epi == EPI_VT;
+  if (!x || !gamma || !A || !SA || !W || !SW || n_w < 1 || !bias || !cscale || !us || reps < 1 || M <= 0 || N <= 0 || N % 8 || K <= 0 || K % 128 || n2 < 0 || n2 % 8 ||
+      epi < EPI_BIAS || epi > EPI_VT || epi == EPI_BIAS_POS || (n2 > 0 && (epi != EPI_BIAS || !SW2 || !V)) || (residual ? !R : values ? !V : epi == EPI_BIAS ? !C : !Cq || !SC) ||
+      ((values || n2 > 0) && (n_tok <= 0 || n_tok % 8 || M % n_tok)) || tile < 0 || tile > (residual ? 3 : 2)) {
+    set_err(g_err, sizeof(g_err), "epd_op_mx_gemm_us: bad argument");
+    return EPD_ERR_INVALID_ARG;
+  }
+  if (mx_gemm_init() != hipSuccess) return EPD_ERR_HIP;
+  hipStream_t st = (hipStream_t)hip_stream;
+  const long Mp = ((long)M + 255) / 256 * 256;
+  MxRowParams r;
+  memset(&r, 0, sizeof(r));
+  r.kind = 1; r.in = x; r.ld_in = K; r.gamma = gamma; r.eps = 1e-6f; r.rows = M; r.dim = K; r.codes = (unsigned char*)A; r.ld_codes = K; r.scales = (unsigned*)SA; r.ld_scales = Mp;
+  MxGemmParams p;
+  memset(&p, 0, sizeof(p));
+  p.epi = epi; p.tile = tile; p.A = (const unsigned char*)A; p.lda = K; p.SA = (const unsigned*)SA; p.sa_ld = Mp; p.bias = bias; p.cscale = cscale;
+  p.M = M; p.N = N; p.K = K; p.Npad = round_up(N, 256); p.C = (bf16_t*)C; p.ldc = N; p.R = R; p.ldr = N; p.VT = (bf16_t*)V; p.heads = 1; p.hd_pad = n2 > 0 ? n2 : N; p.n_tok = n_tok;
+  p.Cq = (unsigned char*)Cq; p.ncq = round_up(N, 128); p.ldcq = p.ncq; p.SC = (unsigned*)SC; p.sc_ld = Mp;
+  p.n2 = n2; p.n2_pad = round_up(n2, 256); p.bias2 = bias + p.Npad; p.cscale2 = cscale + p.Npad;
+  const hipError_t e = time_behind([&] { (void)mx_rows(r, st); }, [&](int i) {
+    const long k = i % n_w;
+    p.W = (const unsigned char*)W + k * (p.Npad + p.n2_pad) * K; p.SW = (const unsigned*)SW + k * (K / 128) * p.Npad;
+    p.W2 = p.W + (long)p.Npad * K; p.SW2 = (const unsigned*)SW2 + k * (K / 128) * p.n2_pad;
+    return mx_gemm(p, st); }, reps, us, st);
+  if (e != hipSuccess) { set_err(g_err, sizeof(g_err), "epd_op_mx_gemm_us: %s", hipGetErrorString(e)); return e == hipErrorInvalidValue ? EPD_ERR_INVALID_ARG : EPD_ERR_HIP; }
   return EPD_OK;
 }
 

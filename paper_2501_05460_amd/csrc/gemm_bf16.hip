@@ -1207,9 +1207,9 @@ bool persist_res() {   // EPD_PERSIST_RES=0: the residual products stay on the o
   return on;
 }
 
-hipError_t launch_wide(const GemmParams& p, int tile, hipStream_t st, int workgroups = cu_count()) {
+hipError_t launch_wide(const GemmParams& p, int tile, hipStream_t st) {
   ++g_kernel_launches;
-  return bf16_gemm_wide(p, tile, workgroups, st);
+  return bf16_gemm_wide(p, tile, cu_count(), st);
 }
 
 bool tiles_192() {   // EPD_TILES_192=0: widths like 1152 stay on the 256-wide tiles
@@ -1381,13 +1381,6 @@ static Plain choose_plain(const GemmParams& p) {
   return best;
 }
 
-// One round of 256 x 128 tiles over long K is reported as the form with a workgroup per tile; it is the same launch.  (The kernel that
-// had one tile per workgroup is gone: with lines asked for ahead the persistent one is faster at every depth.  us, that kernel | this one:
-// residual, 1024 by 4096, 8192 rows 85 | 68, 3200 by 12800, 2048 rows 216 | 174, 1024 by 1024 37 | 29.)
-static bool one_tile_128(const GemmParams& p) {
-  return p.epi != EPI_BIAS_POS && p.K >= (p.epi == EPI_BIAS_RESIDUAL ? 3584 : 2048);
-}
-
 // ---- second stage: the shape that runs ----
 // choose_plain weighs the forms there were when its estimates were fitted; this stage takes another shape of the persistent kernel where it
 // is faster on the present kernels.  us = c + ck kt + up (u + uk kt) + r (v + vk kt): kt 64-deep slabs, r tiles per CU, up its rounds
@@ -1479,11 +1472,9 @@ static Choice choose(const GemmParams& p) {
   return best;
 }
 
-static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
+static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st);
+static hipError_t launch_first(const GemmParams& p, const Plain& c, hipStream_t st) {
   const bool residual = p.epi == EPI_BIAS_RESIDUAL;
-  const Choice ch = choose(p);
-  if (ch.shape >= 0) return launch_shape(p, ch.shape, st);
-  const Plain& c = ch.first;
   GemmParams a = p, b = p;
   auto wide = [&](const GemmParams& g) {
     if (!residual || persist_res()) return launch_wide(g, WIDE_256, st);
@@ -1512,6 +1503,20 @@ static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
     }
   }
   return hipErrorInvalidValue;
+}
+static hipError_t dispatch_plain(const GemmParams& p, hipStream_t st) {
+  const Choice c = choose(p);
+  return c.shape >= 0 ? launch_shape(p, c.shape, st) : launch_first(p, c.first, st);
+}
+// the two cuts as forms of their own (tests, timing): by rows where cut_rows finds one, by columns where the last tile column is half empty
+static hipError_t launch_cut_rows(const GemmParams& p, hipStream_t st) {
+  const long rows_a = p.Npad % 256 == 0 ? cut_rows(p) : 0;
+  if (rows_a == 0) return hipErrorInvalidValue;
+  return launch_first(p, {PLAIN_256, best_ring(p.M - (int)(rows_a * BM), p.N, p.K, p.epi).tile, rows_a, 0.0}, st);
+}
+static hipError_t launch_cut_columns(const GemmParams& p, hipStream_t st) {
+  if (p.epi != EPI_BIAS_RESIDUAL || p.N <= 256 || p.N % 256 == 0 || p.N % 256 > 128) return hipErrorInvalidValue;
+  return launch_first(p, {PLAIN_COLUMNS, 0, 0, 0.0}, st);
 }
 
 // The q/k and the value projection as one launch, where that is estimated to take less than the two launches each in its own
@@ -1549,29 +1554,19 @@ bool bf16_gemm_on_wide(const GemmParams& p) {
   return c.shape >= 0 ? c.shape >= S_256x128 : c.first.form != PLAIN_RING;
 }
 
-// For tests: the shape that runs, by its number in GemmParams::cfg; 0: more than one launch (of a pair: two products)
+// For tests: what runs, by its number in GemmParams::cfg (5 and 18: the cuts by rows and by columns); of a pair 0: two products
 int bf16_gemm_shape(const GemmParams& p) {
   static const int number[N_SHAPES] = {11, 13, 14, 1, 9, 15, 16, 17, 12};
   if (p.n2_pad > 0) return bf16_gemm_pair_fits(p) ? number[choose_pair(p).shape] : 0;
   const Choice c = choose(p);
-  if (c.shape >= 0) return c.shape == S_256 && p.epi == EPI_BIAS_RESIDUAL ? 10 : number[c.shape];
-  if (c.first.form == PLAIN_256 && c.first.rows_a == 0 && p.epi == EPI_BIAS_RESIDUAL && !persist_res()) return a_direct() && p.K >= 2048 ? 8 : 7;
-  long rows = 0;
-  const int form = bf16_gemm_choice(p, &rows);
-  return rows < p.M ? 0 : form;
-}
-
-// For tests: the form choose_plain takes, by its number in GemmParams::cfg (10 / 9: 256 x 256 tiles of residual / other
-// products, 0: the cut by columns); *rows: the rows in front of a row cut, M without one
-int bf16_gemm_choice(const GemmParams& p, long* rows) {
-  const Plain c = choose_plain(p);
-  *rows = c.form == PLAIN_256 && c.rows_a > 0 ? c.rows_a * BM : p.M;
-  switch (c.form) {
-    case PLAIN_RING: return c.tile == RING_64x64 ? 11 : c.tile == RING_128x64 ? 13 : 14;
-    case PLAIN_256x128: return one_tile_128(p) ? 4 : 1;
+  const bool residual = p.epi == EPI_BIAS_RESIDUAL;
+  if (c.shape >= 0) return c.shape == S_256 && residual ? 10 : number[c.shape];
+  switch (c.first.form) {
+    case PLAIN_RING: return number[ring_shape(c.first.tile)];
+    case PLAIN_256x128: return 1;
     case PLAIN_192: return 12;
-    case PLAIN_256: return p.epi == EPI_BIAS_RESIDUAL ? 10 : 9;
-    case PLAIN_COLUMNS: return 0;
+    case PLAIN_256: return c.first.rows_a > 0 ? 5 : !residual ? 9 : persist_res() ? 10 : a_direct() && p.K >= 2048 ? 8 : 7;
+    case PLAIN_COLUMNS: return 18;
   }
   return -1;
 }
@@ -1604,7 +1599,7 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
     case 1: return ring_has(p) ? launch_wide(p, WIDE_128, st) : dispatch<128, 512, 64>(p, st);
     case 2: return ring_has(p) ? launch_ring(p, RING_128x128, st) : dispatch_128_fold<0>(p, st);
     case 3: if (!ring_has(p)) { if (p.K % 256 == 0) return dispatch_128_fold<2>(p, st); break; } return launch_ring(p, RING_128x128, st);
-    case 4: if (ring_has(p) && p.epi != EPI_BIAS_POS) return launch_wide(p, WIDE_128, st, 1 << 30); break;
+    case 5: return ring_has(p) ? launch_cut_rows(p, st) : hipErrorInvalidValue;
     case 6: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 0>(p, st); break;
     case 7: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 1>(p, st); break;
     case 8: if (p.Npad % 256 == 0) return dispatch<256, 512, 64, 3>(p, st); break;
@@ -1615,6 +1610,7 @@ hipError_t bf16_gemm(const GemmParams& p, hipStream_t st) {
     case 14: if (ring_has(p)) return launch_ring(p, RING_128x128, st); break;
     case 15: if (p.Npad % 256 == 0 && ring_has(p) && (residual_or_gelu(p.epi))) return launch_wide(p, WIDE_224, st); break;
     case 12: if (p.N % 192 == 0 && p.epi == EPI_BIAS_RESIDUAL && !p.xb) return launch_wide(p, WIDE_192, st); break;
+    case 18: return ring_has(p) ? launch_cut_columns(p, st) : hipErrorInvalidValue;
   }
   if (ring_has(p)) return dispatch_plain(p, st);
   // from here on: products with a folded pre-norm or an emitting residual epilogue (EPD_NORM_MODE)

@@ -635,10 +635,13 @@ hipError_t launch_tile(const MxGemmParams& p, int cols, hipStream_t st) {
   return hipGetLastError();
 }
 
+// tile columns that hold nothing but padding are not launched (the weights are packed to 256 rows)
+template <int EPI>
+int launched_columns(const MxGemmParams& p) { return (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH) && p.ncq > p.N ? p.ncq : p.N; }
+
 template <int EPI, bool DUAL = false>
-hipError_t launch(const MxGemmParams& p, hipStream_t st) {
-  // tile columns that hold nothing but padding are not launched (the weights are packed to 256 rows)
-  const int cols = (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH) && p.ncq > p.N ? p.ncq : p.N;
+int tile_for(const MxGemmParams& p) {
+  const int cols = launched_columns<EPI>(p);
   // 256 x 256 tiles, a workgroup of eight waves per CU, 128 x 128 ones, two of four waves, or, for the residual product over more
   // than a round, 224 x 256 ones: the one estimated to take least.  us = start + rounds (fixed + slabs) + rounds without rounding up
   // (fixed + slabs): the residual product's workgroups drift apart, and over several rounds one's epilogue stands under
@@ -660,16 +663,19 @@ hipError_t launch(const MxGemmParams& p, hipStream_t st) {
     const double rounds = (double)(tiles / slots) + (rem == 0 ? 0.0 : 2 * rem <= slots ? half_round : 1.0);
     return c.start + rounds * (c.round + c.round_slab * kt) + (double)tiles / slots * (c.work + c.work_slab * kt);
   };
-  int tile = p.tile;
-  if (tile == 0) {
-    double best = estimate(LARGE, 256, 256, cus, 1.0);
-    tile = 1;
-    const auto offer = [&](double us, int t) { if (us < best) { best = us; tile = t; } };
-    offer(estimate(SMALL, 128, 128, 2 * cus, 0.7), 2);
-    if constexpr (RES)
-      if ((p.M + 223) / 224 * (long)((cols + 255) / 256) > cus) offer(1.03 * estimate(Cost{6.58, 8.30, 1.10, 9.21, 0.31}, 224, 256, cus, 1.0), 3);
-  }
-  if constexpr (RES) {
+  double best = estimate(LARGE, 256, 256, cus, 1.0);
+  int tile = 1;
+  const auto offer = [&](double us, int t) { if (us < best) { best = us; tile = t; } };
+  offer(estimate(SMALL, 128, 128, 2 * cus, 0.7), 2);
+  if constexpr (RES)
+    if ((p.M + 223) / 224 * (long)((cols + 255) / 256) > cus) offer(1.03 * estimate(Cost{6.58, 8.30, 1.10, 9.21, 0.31}, 224, 256, cus, 1.0), 3);
+  return tile;
+}
+
+template <int EPI, bool DUAL = false>
+hipError_t launch(const MxGemmParams& p, hipStream_t st) {
+  const int cols = launched_columns<EPI>(p), tile = p.tile > 0 ? p.tile : tile_for<EPI, DUAL>(p);
+  if constexpr (EPI == EPI_BIAS_RESIDUAL) {
     if (tile == 3) return launch_tile<EPI, DUAL, 7, 2, 4>(p, cols, st);
   }
   if (tile == 2) return launch_tile<EPI, DUAL, 4, 2, 2>(p, cols, st);
@@ -713,6 +719,17 @@ hipError_t mx_gemm_init() {
     return set_attr<EPI_BIAS_RESIDUAL>();
   }();
   return once;
+}
+
+int mx_gemm_tile(const MxGemmParams& p) {
+  switch (p.epi) {
+    case EPI_BIAS: return p.n2 == 0 ? tile_for<EPI_BIAS>(p) : together(p) ? tile_for<EPI_BIAS, true>(p) : 0;
+    case EPI_VT: return tile_for<EPI_VT>(p);
+    case EPI_BIAS_GELU_ERF: return tile_for<EPI_BIAS_GELU_ERF>(p);
+    case EPI_BIAS_GELU_TANH: return tile_for<EPI_BIAS_GELU_TANH>(p);
+    case EPI_BIAS_RESIDUAL: return tile_for<EPI_BIAS_RESIDUAL>(p);
+  }
+  return -1;
 }
 
 hipError_t mx_gemm(const MxGemmParams& p, hipStream_t st) {

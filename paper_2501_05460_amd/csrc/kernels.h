@@ -124,8 +124,7 @@ hipError_t bf16_gemm_wide_gelu_init();
 hipError_t bf16_gemm_wide_residual_init();
 hipError_t bf16_gemm_wide_pair_init();
 hipError_t bf16_gemm_wide_init();   // part of bf16_gemm_init
-int bf16_gemm_choice(const GemmParams& p, long* rows);   // the first stage's form of a product without a folded pre-norm (tests)
-int bf16_gemm_shape(const GemmParams& p);                // the shape that runs (tests)
+int bf16_gemm_shape(const GemmParams& p);   // what runs for a product without a folded pre-norm, by its number in cfg (tests)
 long bf16_gemm_kernel_launches();   // kernels launched by bf16_gemm on the calling host thread so far (a figure for the profiling hooks)
 hipError_t bf16_gemm_init();  // raises the dynamic-LDS limit of the kernels (idempotent: safe from any thread, any number of times)
 
@@ -191,7 +190,7 @@ void bf16_qknorm(bf16_t* buf, long ld, long k_off, const float* gamma_q, const f
 hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                           int n_tok, int n_keys, int n_q, int q_shared, int heads, int hd_pad, long ld_qk,
                           long ld_o, hipStream_t st, unsigned char* oq = nullptr, unsigned* so = nullptr, long ld_so = 0,
-                          bool paired = false);
+                          bool paired = false, int queries = 0);   // queries per wave: 16, 32 or 0: as the rule picks
 int bf16_attention_queries(int n_slices, int n_q, int heads, int hd_pad, bool paired);   // queries per wave of such a call, 16 or 32 (tests)
 hipError_t bf16_attention_init();   // raises the dynamic-LDS limit on the current device (idempotent); in front of bf16_attention
 
@@ -290,6 +289,7 @@ struct MxGemmParams {
 int cu_count();   // compute units of the device (see gemm_bf16.hip)
 hipError_t mx_gemm(const MxGemmParams& p, hipStream_t st);
 hipError_t mx_gemm_init();   // raises the dynamic-LDS limit of the kernels (idempotent)
+int mx_gemm_tile(const MxGemmParams& p);   // the tile that mx_gemm takes for p.tile == 0 (n2 > 0: 0 = two launches); sizes and epilogue alone count (tests)
 // one v_mfma_scale_f32_16x16x128_f8f6f4 on caller-supplied registers (operand-layout test): a, b [64][8], sa, sb [64], d [64][4]
 void mx_mfma_probe(const int* a, const int* b, const int* sa, const int* sb, float* d, hipStream_t st);
 

@@ -122,8 +122,8 @@ def test_wide_layers_of_a_few_slices_leave_the_bits_of_each_slice_alone(tile, n,
     """1728 and 1584 rows (ragged: 1584 is no whole number of 256-row tiles): FC1 on 256 x 128 tiles with FC2 behind it on
     64 x 64 ring tiles, where FC1 stores its output without the streaming hint; a slice alone takes other forms."""
     rows = n * (((tile // 14) ** 2 + cls + 7) // 8 * 8)
-    assert B.op_gemm_bf16_choice(rows, 4096, 1024, 1 if act == wl.ACT_GELU_ERF else 2)[0] == 1
-    assert B.op_gemm_bf16_choice(rows, 1024, 4096, 3)[0] == 11
+    assert B.op_gemm_bf16_shape(rows, 4096, 1024, 1 if act == wl.ACT_GELU_ERF else 2) == 1
+    assert B.op_gemm_bf16_shape(rows, 1024, 4096, 3) == 11
     desc = desc_for(wl.DT_BF16, tile_size=tile, hidden=1024, heads=16, mlp=4096, layers=1, act=act, class_token=cls)
     enc = make_encoder(desc, wl.gen_weights(desc, 37, std=0.03))
     tiles = torch.from_numpy(wl.gen_tiles(desc, 37, n)).cuda()

@@ -291,26 +291,29 @@ def test_ring_tiles_agree_bit_for_bit(M, N, K, epi):
         assert np.array_equal(run(form), ref), form
 
 
-@pytest.mark.parametrize("epi,M,N,K,form,cut", [
-    (3, 9200, 1152, 256, 12, False),     # 256 x 192 tiles
-    (3, 2600, 1152, 1152, 14, False),    # ring tiles over nine columns of 128, the tenth all padding
-    (3, 3570, 1152, 256, 13, False),     # 128 x 64: eighteen of twenty
-    (3, 14600, 1152, 1152, 10, True),    # whole rounds, the rows behind on ring tiles
-    (3, 6700, 3200, 1152, 10, True),
-    (3, 5000, 3200, 128, 0, False),      # whole 256-wide tile columns, the last 128 columns apart
-    (0, 3000, 2304, 1152, 1, False),     # one round of 256 x 128 tiles
-    (0, 14600, 2304, 128, 9, True),
-    (2, 4800, 3584, 1152, 9, True),
-    (0, 28, 1152, 128, 11, False),
-    (3, 2300, 3200, 4096, 4, False),     # one round of 256 x 128 tiles over long K: one tile per workgroup
-    (0, 2048, 3584, 3584, 4, False),
-    (2, 1500, 4608, 2048, 4, False),
+@pytest.mark.parametrize("epi,M,N,K,form", [
+    (3, 9200, 1152, 256, 12),     # 256 x 192 tiles
+    (3, 2600, 1152, 1152, 14),    # ring tiles over nine columns of 128, the tenth all padding
+    (3, 3570, 1152, 256, 13),     # 128 x 64: eighteen of twenty
+    (3, 14600, 1152, 1152, 5),    # whole rounds, the rows behind on ring tiles
+    (3, 9400, 3584, 640, 5),
+    (0, 15000, 2304, 640, 5),
+    (2, 4800, 3584, 1152, 5),
+    (3, 5000, 3200, 128, 18),     # whole 256-wide tile columns, the last 128 columns apart
+    (3, 6700, 3200, 1152, 15),    # 224 x 256 tiles
+    (1, 2400, 3584, 128, 15),
+    (0, 3000, 2304, 1152, 1),     # one round of 256 x 128 tiles
+    (3, 2300, 3200, 4096, 1),
+    (2, 1500, 4608, 2048, 1),
+    (0, 14600, 2304, 128, 1),     # several
+    (3, 11500, 1152, 640, 10),    # 256 x 256 tiles
+    (1, 11500, 1152, 640, 9),
+    (0, 28, 1152, 128, 11),
 ])
-def test_what_the_library_picks_leaves_the_bits_of_one_form(epi, M, N, K, form, cut):
-    """The dispatch over weights padded as the library pads them (1152 columns to 1280, 3200 to 3328): every kind of choice is
+def test_what_the_library_picks_leaves_the_bits_of_one_form(epi, M, N, K, form):
+    """The dispatch over weights padded as the library pads them (1152 columns to 1280, 3200 to 3328): every form that runs is
     reached, and leaves the bits of 256 x 128 tiles and of 128 x 128 ring tiles, two different kernels, over unpadded weights."""
-    taken, rows = B.op_gemm_bf16_choice(M, N, K, epi)
-    assert (taken, rows < M) == (form, cut)
+    assert B.op_gemm_bf16_shape(M, N, K, epi) == form
     rng = np.random.default_rng(M + N + K + epi)
     A = B.to_device(_bf16_grid(rng, (M, K), 0.5), True)
     W = B.to_device(_bf16_grid(rng, (N, K), 0.05), True)
@@ -325,10 +328,10 @@ def test_what_the_library_picks_leaves_the_bits_of_one_form(epi, M, N, K, form, 
 
 @pytest.mark.parametrize("K", [128, 256, 640])
 @pytest.mark.parametrize("epi,M,N,forms", [
-    (0, 16536, 1024, (9, 1, 4)), (1, 16536, 1024, (9, 1, 4)), (2, 16536, 1024, (9, 1, 4)),   # 260 tiles of 256 x 256, 520 of 256 x 128
-    (3, 16537, 1024, (10, 1, 4)), (4, 16536, 1024, (9, 1)), (5, 16536, 1024, (9, 1, 4)),
+    (0, 16536, 1024, (9, 1)), (1, 16536, 1024, (9, 1)), (2, 16536, 1024, (9, 1)),   # 260 tiles of 256 x 256, 520 of 256 x 128
+    (3, 16537, 1024, (10, 1)), (4, 16536, 1024, (9, 1)), (5, 16536, 1024, (9, 1)),
     (3, 11100, 2304, (12, 10, 1)),                                                  # 528 of 256 x 192, 396 of 256 x 256
-    (4, 1240, 1152, (1, 13)), (5, 1240, 1152, (1, 4, 13)), (4, 8200, 1152, (0, 1)), (5, 8200, 1152, (0, 1))])
+    (4, 1240, 1152, (1, 13)), (5, 1240, 1152, (1, 13)), (4, 8200, 1152, (0, 1)), (5, 8200, 1152, (0, 1))])
 def test_persistent_tiles_beyond_the_first_agree_bit_for_bit(epi, M, N, forms, K):
     """More tiles than CUs, so that workgroups go on to a second tile, whose first slabs and stream rows are fetched under the last
     products of the one before; two slabs (K = 128: all of a tile's are its last) and more, a ragged last tile row, every
@@ -368,15 +371,18 @@ def test_224_row_tiles_agree_bit_for_bit(epi, M, N, K):
 
 
 @pytest.mark.parametrize("M,N,n2,K,n_tok", [(8, 256, 256, 128, 8), (248, 256, 384, 128, 248), (1032, 2304, 1152, 256, 1032), (2400, 768, 384, 128, 600),
-                                            (1736, 512, 256, 640, 248), (7344, 2304, 1152, 128, 816), (10240, 2048, 1024, 128, 1024)])
+                                            (1736, 512, 256, 640, 248), (7344, 2304, 1152, 128, 816), (10240, 2048, 1024, 128, 1024),
+                                            (7344, 2304, 1152, 640, 816), (7392, 2304, 1152, 640, 1056), (7624, 2048, 1024, 768, 7624)])
 def test_two_products_in_one_launch_agree_bit_for_bit(M, N, n2, K, n_tok):
     """Every tile of the pair: ring tiles, 256, 224, 192 and 160 x 256 and 256 x 192.  One tile and more than CUs, slices that end inside a
-    tile, value columns that leave a last tile half empty.  Reference: the two products in a launch each, one workgroup per tile."""
+    tile, value columns that leave a last tile half empty; the last three: workgroups that go from a q/k tile on to a value tile over more
+    than two slabs, and last tile rows of 160 and 192 (7392 rows) and of 224 (7624) that lie over the one above.  Reference: the two
+    products in a launch each, on the kernels with one workgroup per tile."""
     g = torch.Generator().manual_seed(M + N + K)
     A, W = torch.randn(M, K, generator=g).mul_(0.5).bfloat16().cuda(), torch.randn(N + n2, K, generator=g).mul_(0.05).bfloat16().cuda()
     bias = torch.randn(N + n2, generator=g).mul_(0.1).cuda()
     c = B.op_gemm_bf16_form(A, W[:N], bias[:N], 0, 6)
-    v = B.op_gemm_bf16_form(A, W[N:].contiguous(), bias[N:].contiguous(), 5, 4, n_tok=n_tok)
+    v = B.op_gemm_bf16_form(A, W[N:].contiguous(), bias[N:].contiguous(), 5, 14, n_tok=n_tok)
     for form in (9, 11, 13, 14, 15, 16, 17) + ((12,) if N % 192 == 0 and n2 % 192 == 0 else ()):
         got_c, got_v = B.op_gemm_bf16_pair(A, W, bias, N, n_tok, form)
         assert torch.equal(got_c, c) and torch.equal(got_v, v), form

@@ -1,4 +1,4 @@
-"""Which form of the bf16 product and of attention the library takes, held against measured times of the forms (host only)."""
+"""What the library takes for a product and for attention, held against measured times of the forms (host only)."""
 import os
 import subprocess
 import sys
@@ -7,66 +7,70 @@ import pytest
 
 from paper_2501_05460_amd import binding as B
 
-# (epilogue, rows, columns, K, rows per slice, us by form: number of the form hook, or "cut" for whole rounds of 256 x 256
-# tiles and the rest on ring tiles, or "columns" for the cut by columns).  In the running encoder on MI355X, each form forced for
-# this product alone (of 385 products so measured, the one taken is within 3 % of the fastest for 88 %, 5 % for 93 %, 9 % for 99 %).
-MEASURED = [
-    (3, 1024, 1152, 4352, 1024, {11: 30, 13: 35, 14: 46, 1: 77, 4: 75, 12: 93, 10: 105}),
-    (3, 5120, 1152, 4352, 1024, {11: 94, 13: 80, 14: 92, 1: 94, 4: 88, 12: 104, 10: 113}),
-    (3, 6144, 1152, 4352, 1024, {11: 110, 13: 99, 14: 94, 1: 97, 4: 91, 12: 107, 10: 118}),
-    (3, 5888, 1152, 1152, 736, {11: 36, 13: 35, 14: 34, 1: 35, 4: 40, 12: 39, 10: 45}),
-    (3, 16928, 1152, 4352, 736, {11: 298, 13: 252, 14: 234, 1: 268, 12: 213, 10: 232, 'cut': 206, 'columns': 208}),
-    (5, 16928, 1152, 1152, 736, {11: 72, 13: 61, 14: 57, 1: 64, 9: 59}),
-    (3, 65536, 1152, 4352, 1024, {13: 1051, 14: 868, 1: 860, 12: 655, 10: 607, 'columns': 631}),
-    (3, 26624, 1152, 4352, 1024, {11: 522, 13: 431, 14: 375, 1: 389, 12: 323, 10: 312, 'cut': 272, 'columns': 298}),
-    (3, 47104, 1152, 1152, 736, {13: 228, 14: 223, 1: 198, 12: 179, 10: 178, 'cut': 183, 'columns': 183}),
-    (0, 10240, 2304, 1152, 1024, {11: 85, 13: 73, 14: 66, 1: 59, 9: 62, 'cut': 63}),
-    (3, 8960, 1152, 4352, 448, {11: 160, 13: 134, 14: 136, 1: 159, 12: 110, 10: 119, 'columns': 151}),
-    (3, 1024, 1024, 4096, 1024, {11: 23.7, 13: 34, 14: 40, 1: 71, 4: 68, 10: 97}),
-    (1, 2048, 4096, 1024, 1024, {11: 31, 13: 27.3, 14: 29.0, 1: 25.4, 4: 27.0, 9: 33}),
-    (3, 3072, 1024, 1024, 1024, {11: 18.7, 13: 18.0, 14: 18.6, 1: 27.3, 4: 32, 10: 38}),
-    (1, 13312, 4096, 1024, 1024, {13: 134, 14: 140, 1: 123, 9: 113, 'cut': 112}),
-    (0, 13312, 2048, 1024, 1024, {11: 86, 13: 70, 14: 68, 1: 66, 9: 56, 'cut': 64}),
-    (3, 53248, 1024, 4096, 1024, {13: 632, 14: 532, 1: 590, 10: 450, 'cut': 397}),
-    (3, 8256, 1024, 4096, 1032, {11: 138, 13: 120, 14: 110, 1: 140, 10: 110}),
-    (5, 16512, 1024, 1024, 1032, {11: 60, 13: 51, 14: 53, 1: 58, 9: 58}),
-    (0, 1024, 6400, 3200, 1024, {11: 72, 13: 66, 14: 66, 1: 57, 4: 54, 9: 76}),
-    (5, 12288, 3200, 3200, 1024, {11: 367, 13: 288, 14: 247, 1: 256, 9: 212, 'cut': 221}),
-    (3, 2304, 3200, 12800, 576, {11: 338, 13: 266, 14: 233, 1: 250, 4: 223, 10: 308}),
-    (1, 8192, 5120, 12800, 1024, {11: 1830, 13: 1435, 14: 1192, 1: 1275, 9: 934, 'cut': 917}),
-    (0, 8192, 5120, 5120, 1024, {11: 665, 13: 510, 14: 404, 1: 389, 9: 338, 'cut': 363}),
-    (3, 1584, 1024, 1024, 264, {11: 12.8, 13: 14.5, 14: 17.0, 1: 25.8, 10: 36}),
-    (3, 1536, 1152, 4352, 256, {11: 33, 13: 36, 14: 47, 1: 77, 4: 76, 12: 92, 10: 106}),
-    (1, 864, 5120, 12800, 576, {11: 213, 13: 202, 14: 193, 1: 212, 4: 188, 9: 289}),
-    (3, 7168, 1024, 4096, 1024, {11: 114, 13: 101, 14: 84, 1: 90, 4: 86, 10: 109}),
-    (0, 2048, 4096, 4096, 1024, {11: 123, 13: 97, 14: 78, 1: 84, 4: 74, 9: 98}),
-    (0, 2048, 3584, 3584, 1024, {11: 80, 13: 73, 14: 72, 1: 72, 4: 63, 9: 87}),
-    (3, 2304, 3200, 3200, 576, {11: 88, 13: 74, 14: 64, 1: 64, 4: 70, 10: 88}),
-    (1, 1536, 5120, 12800, 1024, {11: 327, 13: 259, 14: 207, 1: 217, 4: 211, 9: 295}),
-]
+TIMES = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "product_times.txt")   # written by product_times.py
 
 
-@pytest.mark.parametrize("epi,M,N,K,n_tok,us", MEASURED)
-def test_the_form_taken_is_among_the_fastest(epi, M, N, K, n_tok, us):
-    """Bound: the dispatch's estimates are within 4 to 7 % (rms) of the times, so of two forms less than 9 % apart either
-    may be taken."""
-    form, rows = B.op_gemm_bf16_choice(M, N, K, epi, n_tok)
-    taken = "cut" if rows < M else "columns" if form == 0 else form
-    assert us[taken] <= 1.09 * min(us.values()), (taken, us)
+def measured(kind):
+    """[((the first six fields), {form: us})] of the lines of one kind"""
+    rows = [line.split() for line in open(TIMES)]
+    return [(tuple(map(int, r[1:7])), {int(f): float(us) for f, us in (v.split(":") for v in r[7:])}) for r in rows if r[0] == kind]
+
+
+def behind(times, taken):
+    """Of every line the time of the form taken over the fastest form's"""
+    return {case: us[taken(*case)] / min(us.values()) for case, us in times}
+
+
+# Of each kind of product (epilogues, one product or two in a launch): the share of lines at least that is within 9 % of the fastest form, and the
+# furthest behind that any is.  The estimates the choice compares are within 2 to 8 % (rms) of the times, so of two forms
+# less than 9 % apart either may be taken; a line measured twice differs by 1 % (rms).  Past that stand a few products of 1024
+# rows (1024 x 5120 x 12800 on ring tiles 199, on 256 x 128 ones 151) and of 3200 columns over K = 12800 (the cut by columns, 493 for 560).
+BF16 = [("q/k and value", (0,), True, 0.97, 1.12), ("bias", (0,), False, 0.94, 1.30), ("GELU", (1, 2), False, 0.95, 1.34),
+        ("residual", (3,), False, 0.92, 1.17), ("values", (5,), False, 0.94, 1.15)]
+
+
+@pytest.mark.parametrize("name,epilogues,pair,share,most", BF16, ids=[k[0] for k in BF16])
+def test_the_product_that_runs_is_among_the_fastest(name, epilogues, pair, share, most):
+    times = [(c, us) for c, us in measured("bf16") if c[0] in epilogues and (c[4] > 0) == pair]
+    assert len(times) >= 60
+    ratio = behind(times, lambda epi, M, N, K, n2, n_tok: B.op_gemm_bf16_shape(M, N, K, epi, n2, n_tok))
+    assert sum(r <= 1.09 for r in ratio.values()) >= share * len(ratio) and max(ratio.values()) <= most, sorted(ratio.items(), key=lambda v: -v[1])[:8]
+    assert sum(ratio.values()) / len(ratio) <= 1.02
+
+
+@pytest.mark.parametrize("epilogues,pair", [((0,), True), ((0,), False), ((1, 2), False), ((3,), False), ((5,), False)])
+def test_the_mx_product_that_runs_is_among_the_fastest(epilogues, pair):
+    times = [(c, us) for c, us in measured("mx") if c[0] in epilogues and (c[4] > 0) == pair]
+    assert len(times) >= 60
+    ratio = behind(times, lambda epi, M, N, K, n2, n_tok: B.op_mx_gemm_tile(M, N, K, epi, n2))
+    assert sum(r <= 1.09 for r in ratio.values()) >= 0.97 * len(ratio) and max(ratio.values()) <= 1.15, sorted(ratio.items(), key=lambda v: -v[1])[:8]
+    assert sum(ratio.values()) / len(ratio) <= 1.01
+
+
+def test_every_form_runs_somewhere():
+    """Of the measured products, and of pairs, each form that the library has is taken for some; a launch each for a pair of other sizes."""
+    taken = {(c[4] > 0, B.op_gemm_bf16_shape(c[1], c[2], c[3], c[0], c[4], c[5])) for c, _ in measured("bf16")}
+    assert {f for pair, f in taken if pair} == {9, 11, 12, 13, 14, 15, 16, 17}
+    assert {f for pair, f in taken if not pair} == {1, 5, 9, 10, 11, 12, 13, 14, 15, 18}
+    assert B.op_gemm_bf16_shape(4608, 6400, 3200, 0, 3200, 576) == 0
+    assert {B.op_mx_gemm_tile(c[1], c[2], c[3], c[0], c[4]) for c, _ in measured("mx")} == {0, 1, 2, 3}
 
 
 @pytest.mark.parametrize("M,N,K", [(1024, 1024, 640), (13312, 1024, 640), (106496, 1024, 640), (40960, 3200, 640), (65536, 1152, 640)])
 def test_the_patch_embedding_is_reported_by_the_kernel_that_runs(M, N, K):
     """Its forms are the ring tiles, 256 x 128 tiles and the persistent 256 x 256 tiles (9), as for the other products."""
-    form, rows = B.op_gemm_bf16_choice(M, N, K, 4)
-    assert form in (1, 9, 11, 13, 14) and rows == M
+    form = B.op_gemm_bf16_shape(M, N, K, 4)
+    assert form in (1, 9, 11, 13, 14)
     assert (form == 9) == (M > 1024)
 
 
 def test_choice_rejects_what_the_products_do_not_take():
-    for args in ((0, 128, 128, 0), (1, 126, 128, 0), (1, 128, 64, 0), (1, 128, 128, 6), (1, 128, 128, 5, 0)):
+    for args in ((0, 128, 128, 0), (1, 126, 128, 0), (1, 128, 64, 0), (1, 128, 128, 6), (1, 128, 128, 5, 0, 0), (1, 128, 128, 1, 128, 8), (1, 128, 128, 0, 130, 8)):
         with pytest.raises(B.EpdError):
-            B.op_gemm_bf16_choice(*args)
+            B.op_gemm_bf16_shape(*args)
+    for args in ((0, 128, 128, 0), (1, 0, 128, 0), (1, 128, 64, 0), (1, 128, 128, 4), (1, 128, 128, 3, 128)):
+        with pytest.raises(B.EpdError):
+            B.op_mx_gemm_tile(*args)
 
 
 # (head dim, heads, rows per slice, slices, order of summation of the MXFP8 option, us with 16 and with 32 queries per wave), on MI355X
@@ -112,8 +116,8 @@ def test_attention_width_rejects_what_attention_does_not_take():
 
 
 def test_residual_products_leave_the_persistent_kernels_when_told_to():
-    """EPD_PERSIST_RES=0 (read once a process): ring tiles, the 256 x 256 kernels with a tile per workgroup (7, 8), or cuts of these
-    two (0); with the switch as it is by default the same products reach the persistent forms."""
+    """EPD_PERSIST_RES=0 (read once a process): ring tiles, the 256 x 256 kernels with a tile per workgroup (7, 8), or cuts into
+    these two (5, 18); with the switch as it is by default the same products reach the persistent forms."""
     shapes = [(m, n, k) for m in (1024, 2304, 5120, 8192, 16928, 40960, 65536, 106496)
               for n, k in ((1152, 4352), (1152, 1152), (1024, 4096), (1024, 1024), (3200, 12800), (3200, 3200), (128, 1024))]
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -126,4 +130,4 @@ def test_residual_products_leave_the_persistent_kernels_when_told_to():
 
     assert {1, 10, 12, 15} <= taken("1")
     off = taken("0")
-    assert {7, 8, 11, 13, 14} <= off <= {0, 7, 8, 11, 13, 14}, off
+    assert {7, 8, 11, 13, 14} <= off <= {5, 7, 8, 11, 13, 14, 18}, off
