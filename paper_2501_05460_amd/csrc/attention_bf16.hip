@@ -166,8 +166,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // LEAN: one step's S^T registers and weights only, no step issued ahead, so that four (head dim 64), three (72, 96) workgroups
 // share a CU (112, 142, 144 registers; up to 128, 155, 162 with MASK and PAIRED); at head dim 128, where LDS holds two, the
 // S^T product of step i + 1 is issued ahead of the softmax of step i.  So it is with 16 queries per wave at head dims 64 and 96, whose
-// few waves leave the registers (us, lean | ahead: 64, one slice of 1024 tokens 18.7 | 17.0, three 28.8 | 27.1; 96, one 22.6 | 20.8, three
-// 35.0 | 32.4; 72 and masked slices: equal, lean).  A third LDS buffer, loads two blocks ahead, gives nothing: a step is the wave's chain.
+// few waves leave the registers (us, lean | ahead: 64, one slice of 1024 tokens 14.1 | 12.5, three 22.4 | 21.6; 96, one 17.3 | 15.8, three
+// 27.9 | 27.1; 72 and masked slices: equal, lean).  A third LDS buffer, loads two blocks ahead, gives nothing: a step is the wave's chain.
 // PAIRED: a lane's eight keys of a step are 16 (l / 32) + 4 (l / 16 % 2) + {0..3, 8..11}, V^T fragments are two 8-byte halves, and
 // the row sum on the VALU runs over a lane pair's sixteen weights in a row: the order of summation of a kernel on
 // v_mfma_f32_32x32x16_bf16, whose bits this gives.  For calls whose output is converted to MXFP8: there a change of the last
@@ -655,18 +655,19 @@ hipError_t launch_attn_m(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf1
 
 // 16 queries per wave, or 32: twice as many waves, each with half of a step's chain, while they all run at once.  By the most
 // workgroups a CU gets (a (slice, head) keeps to one XCD), of 64 queries and of 128; LDS holds five of 64 at head dim 64,
-// four at 72, three at 96 and two at 128.  us, 32 | 16 queries per wave:
-//   two of 64: head dim 128, one slice of 1024 tokens (25 heads) 26.4 | 24.3; head dim 72, two (16 heads) 21.9 | 20.7
-//   three: 64, three slices 28.1 | 24.2; 72 30.0 | 27.0; 96, four (12 heads) 34.8 | 29.6; but 128, one of 1025 tokens 38.2 | 40.2
-//   four against two of 128: 64, four slices 29.7 | 28.5, PAIRED 32.0 | 34.0; 72 31.6 | 33.4; 96, five 36.4 | 44.6; 128, two 39.4 | 45.8
-//   four against three of 128: 128, four of 576 tokens 35.2 | 30.6; 96, nine of 576 29.2 | 28.2
+// four at 72, three at 96 and two at 128.  us, 32 | 16 queries per wave (16 heads of 64 and 72, 12 of 96, 25 of 128; slices of 1024 tokens):
+//   two of 64: head dim 128, one slice 26.0 | 23.8; 72, two 21.6 | 20.5
+//   three: 64, three slices 25.8 | 20.6; 72 28.8 | 26.4; 96, four 33.7 | 28.9; but 128, one of 1025 tokens 38.2 | 39.9
+//   four against two of 128: 64, four slices 27.1 | 25.7, PAIRED 29.3 | 28.9 and three of 1025 29.5 | 30.5; 72, four 30.1 | 33.1; 96, five
+//     34.5 | 38.7; 128, two 38.2 | 44.7
+//   four against three of 128: 64, seven of 576 tokens 21.0 | 16.3, 17 of 192 10.8 | 8.3; 72, seven of 576 24.9 | 21.8; 96, nine of 576
+//     28.0 | 25.4; 128, four of 576 34.0 | 30.2; four of 128 (slices of up to 64 tokens): 64 6.4 | 6.0; 72 10.5 | 9.0; 96 13.0 | 11.7; 128 15.9 | 14.2
 // A query's bits are the same.
 bool short_waves(int n_slices, int n_q, int heads, int hd, bool paired) {
-  const long wgs = (long)n_slices * heads * ((n_q + 127) / 128);   // past two of 128 queries per CU always 32
   const long pairs = ((long)n_slices * heads + 7) / 8, cus = cu_count() >= 8 ? cu_count() / 8 : 1;   // of an XCD
   auto per_cu = [&](int queries) { return (pairs * ((n_q + queries - 1) / queries) + cus - 1) / cus; };
   const long of_64 = per_cu(64), of_128 = per_cu(128);
-  return wgs <= 512 && (of_64 <= (hd == 128 ? 2 : 3) || (of_64 == 4 && (of_128 == 3 || (hd == 64 && !paired))));
+  return of_64 <= (hd == 128 ? 2 : 3) || (of_64 == 4 && (of_128 >= 3 || (hd == 64 && !paired)));
 }
 
 template <int HD, bool PAIRED>
