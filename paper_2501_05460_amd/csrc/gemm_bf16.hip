@@ -1424,7 +1424,10 @@ static double shape_us(const GemmParams& p, int shape) {
   const double r = (double)((p.M + tm - 1) / tm) * cols / cu_count(), up = shape == S_64x64 ? fmax(1.0, r) : ceil(r);
   // Among other kernels a launch of the persistent one takes 4 us longer than among its own kind, where the fit was taken (3 slices of the
   // 1024-wide encoder: q/k/v on 160 x 256 tiles 25.5 for 21.7 us, FC1 on 224 x 256 29.5 for 25.6); one of ring tiles does not (29.7, 30.3).
-  const double start = shape >= S_256x128 ? 4.0 : 0.0;
+  // Residual products over a short K (up to 1536) 7 us: with 4, the out-projection of nine and ten slices of that encoder left 128 x 64 ring tiles
+  // for 224 x 256 ones, and the calls took 8609 for 8536 and 8818 for 8748 us.  us, ring | persistent: 10240 rows, 1024 x 1024 35.9 | 40.6;
+  // 8192 30.2 | 34.5; 6144, 1152 x 1152 31.7 | 33.6; 4608, 1536 x 1536 36.8 | 40.7; over K = 4096 4 us are right: 6144 rows 65.4 | 59.6.
+  const double start = shape < S_256x128 ? 0.0 : kind_of(p) == K_RESIDUAL && kt <= 24 ? 7.0 : 4.0;
   return start + f.c + f.ck * kt + up * (f.u + f.uk * kt) + r * (f.v + f.vk * kt);
 }
 static bool shape_runs(const GemmParams& p, int shape) {

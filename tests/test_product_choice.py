@@ -26,7 +26,7 @@ def behind(times, taken):
 # less than 9 % apart either may be taken; a line measured twice differs by 1 % (rms).  Past that stand a few products of 1024
 # rows (1024 x 5120 x 12800 on ring tiles 199, on 256 x 128 ones 151) and of 3200 columns over K = 12800 (the cut by columns, 493 for 560).
 BF16 = [("q/k and value", (0,), True, 0.97, 1.12), ("bias", (0,), False, 0.94, 1.30), ("GELU", (1, 2), False, 0.95, 1.34),
-        ("residual", (3,), False, 0.92, 1.17), ("values", (5,), False, 0.94, 1.15)]
+        ("residual", (3,), False, 0.95, 1.15), ("values", (5,), False, 0.94, 1.15)]
 
 
 @pytest.mark.parametrize("name,epilogues,pair,share,most", BF16, ids=[k[0] for k in BF16])
@@ -54,6 +54,12 @@ def test_every_form_runs_somewhere():
     assert {f for pair, f in taken if not pair} == {1, 5, 9, 10, 11, 12, 13, 14, 15, 18}
     assert B.op_gemm_bf16_shape(4608, 6400, 3200, 0, 3200, 576) == 0
     assert {B.op_mx_gemm_tile(c[1], c[2], c[3], c[0], c[4]) for c, _ in measured("mx")} == {0, 1, 2, 3}
+
+
+@pytest.mark.parametrize("rows", [9216, 10240])
+def test_short_residual_products_of_a_few_slices_stay_on_ring_tiles(rows):
+    """The out-projection of nine and ten slices of 1024 tokens: 34.5 and 35.9 us on 128 x 64 ring tiles, 40.3 and 40.6 on 224 x 256 ones."""
+    assert B.op_gemm_bf16_shape(rows, 1024, 1024, 3) == 13
 
 
 @pytest.mark.parametrize("M,N,K", [(1024, 1024, 640), (13312, 1024, 640), (106496, 1024, 640), (40960, 3200, 640), (65536, 1152, 640)])
