@@ -1188,6 +1188,7 @@ hipError_t launch_persist(const GemmParams& p, hipStream_t st) {
   const int n_tiles = gm * gn;
   if (n_tiles == 0) return hipSuccess;
   const double panel = 256.0 * p.K * sizeof(bf16_t);
+  // a search of its own: with band_columns, which counts the narrower last band, 104 slices of the 1024-wide encoder take 83.4 ms for 83.2
   int gw = 1;
   double best = 1e30;
   for (int c = 1; c <= gn && c <= 32; ++c) {

@@ -451,7 +451,7 @@ hipError_t launch_wide(const GemmParams& p, int cus, hipStream_t st) {
   if (cols_last * S::COLS > pad_last || (DUAL && p.Npad % S::COLS != 0)) return hipErrorInvalidValue;
   const int gm = (p.M + S::ROWS - 1) / S::ROWS, gn = (DUAL ? p.Npad / S::COLS : 0) + cols_last, n_tiles = gm * gn;
   if (n_tiles == 0) return hipSuccess;
-  int gw = band_columns(gn, (double)S::ROWS * p.K * sizeof(bf16_t), (double)S::COLS * p.K * sizeof(bf16_t), n_tiles < 256 ? (n_tiles + 7) / 8 : 32);
+  int gw = band_columns(gn, (double)S::ROWS * p.K * sizeof(bf16_t), (double)S::COLS * p.K * sizeof(bf16_t), (n_tiles < cus ? n_tiles + 7 : cus) / 8);
   if (p.band > 0 && p.band <= gn) gw = p.band;
   // one round of short tiles has nothing to gain (13312 rows, 1024 x 1024 residual, us without | with: 40.7 | 41.6)
   const int ahead = n_tiles > cus || p.K >= 2048;

@@ -629,7 +629,7 @@ template <int EPI, bool DUAL, int TM, int WAVES_M, int WAVES_N>
 hipError_t launch_tile(const MxGemmParams& p, int cols, hipStream_t st) {
   using T = MxTile<TM, WAVES_M, WAVES_N>;
   const int gm = (p.M + T::BM - 1) / T::BM, gq = (cols + T::BN - 1) / T::BN, gv = DUAL ? (p.n2 + T::BN - 1) / T::BN : 0, gn = gq + gv, n_tiles = gm * gn, slots = cu_count() * (512 / T::NT);
-  const int at_once = 32 * (512 / T::NT), gw = band_columns(gn, (double)T::BM * p.K, (double)T::BN * p.K, n_tiles < 8 * at_once ? (n_tiles + 7) / 8 : at_once);
+  const int at_once = slots / 8, gw = band_columns(gn, (double)T::BM * p.K, (double)T::BN * p.K, n_tiles < 8 * at_once ? (n_tiles + 7) / 8 : at_once);
   if (gq * T::BN > p.Npad || gv * T::BN > p.n2_pad) return hipErrorInvalidValue;
   k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N><<<dim3((unsigned)(n_tiles < slots ? n_tiles : slots)), dim3(T::NT), T::LDS, st>>>(p, gm, gw, gn, gq, n_tiles);
   return hipGetLastError();

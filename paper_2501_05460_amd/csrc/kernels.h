@@ -99,6 +99,7 @@ hipError_t bf16_gemm_ring_init();   // part of bf16_gemm_init
 // panels only once while the band's fit its 4 MiB.  The last band is what is left over: 16 columns as 4 bands of 4, not as 5, 5, 5
 // and 1 (K = 1024, 106496 rows, GELU: 774 -> 745 us).
 inline int band_columns(int gn, double panel_a, double panel_w, int at_once) {
+  if (at_once < 1) at_once = 1;
   auto cost = [&](int w) {   // of a band, per tile row
     const double rows = at_once % w == 0 ? at_once / w : 1.0 + (at_once - 1.0) / w;
     return w * (rows * panel_a + (w * panel_w <= 2.5 * (1 << 20) ? 0.0 : w * panel_w));
