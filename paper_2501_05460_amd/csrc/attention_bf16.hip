@@ -13,7 +13,7 @@
 //
 // What bounds it: the SIMD's issue port, which exponentials and products share, and in calls of one or two slices the chain
 // product -> exponentials -> product of a wave.  Beside the v_mfma_f32_32x32x16_bf16 kernel this replaces (32 queries per
-// wave, V^T through registers; us per launch, 1024 tokens, one box): 104 slices x 16 heads of 64 517 -> 511, 13 slices
+// wave, V^T through registers; us per launch, 1024 tokens, on one card): 104 slices x 16 heads of 64 517 -> 511, 13 slices
 // 71.3 -> 67.7; 10 slices x 16 heads of 72 69.9 -> 62.9, 23 of 729 tokens 108 -> 83; 40 slices x 25 heads of 128
 // 649 -> 581; one slice 16.9 -> 14.0 (64), 22.1 -> 16.1 (72), 27.9 -> 23.5 (128), three of 1025 tokens 26.4 -> 24.9.
 // What gave it: head dim 72 takes 96 + 80 rows of products a step instead of 80 + 96 of twice the width, and no pass of the

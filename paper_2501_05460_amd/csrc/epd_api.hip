@@ -858,10 +858,12 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
     ProfScope ps(c, 1, st);
     if (from_stream) {
       RowOpParams r{d.norm, X, x.D, Xn, c->D_k, g, b, M, x.D, 0, x.g, x.D, d.eps};
-      // A product of few rows on the persistent kernel waits for its weights in its only round: the norm in front of it asks for them, while
-      // rows (6 bytes an element) and weights fit the 32 MiB of L2 or nearly.  Encodes, us: three slices of the 1024-wide encoder
-      // 3583 -> 3512, six 5992 -> 5941, two of the 1152-wide one 4081 -> 4030; seven and eight 6878 -> 6904, 7016 -> 7059, so not there, nor
-      // in front of ring tiles (one slice 1965 -> 1980) or of more weights (6B shape, 64 MB and more: 26.8 -> 27.7 ms).
+      // A product of few rows on the persistent kernel waits for its weights in its only round: the norm in front of it asks for them.  Both
+      // bounds are cut-offs found by encoding, not a size of the L2 (32 MiB over the XCDs): up to 40 MiB of rows (6 bytes an element) in front
+      // of the 6 to 8 MiB of weights of 1024 columns and the 8 to 11 of 1152.  us, without | with the weights asked for: 1024 columns, three
+      // slices of 1024 tokens 3520 | 3432, six 5727 | 5681, eight (48 MiB, past the bound) 6965 | 6991; 1152, two 4043 | 3972, four 5907 | 5860,
+      // five and six (34, 41 MiB) 7318 | 7317, 7345 | 7343; eight of 729 tokens (39 MiB) 7357 | 7369.  Not in front of ring tiles (one slice
+      // 1965 | 1980) nor of more weights (6B shape, 64 MB and more, 26.8 | 27.7 ms); between 11 and 64 MB nothing was measured.
       const long bytes = (long)(next.Npad + next.n2_pad) * next.K * 2;
       if (bytes <= 16 << 20 && (long)M * x.D * 6 <= 40 << 20 && bf16_gemm_on_wide(next)) { r.ahead = (const unsigned char*)next.W; r.ahead_bytes = bytes; }
       bf16_rowop(r, st);
@@ -907,7 +909,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
     GemmParams p = gp(EPI_BIAS, Xn, c->D_k, w.qkv, M);
     p.C = QK; p.ldc = ld_qk;
     with_norm(p, w.qkv_cs);
-    // few slices: the value projection rides in the same launch (its weights follow the q/k projection's)
+    // the value projection rides in the same launch where that is estimated to be faster (its weights follow the q/k projection's)
     GemmParams pp = p;
     pp.n2 = w.v.N; pp.n2_pad = w.v.Npad; pp.VT = VT; pp.hd_pad = c->hd_pad; pp.heads = x.H; pp.n_tok = x.Ns;
     const bool paired = (const bf16_t*)w.v.W == (const bf16_t*)w.qkv.W + (size_t)w.qkv.Npad * w.qkv.K && w.v.b == w.qkv.b + w.qkv.Npad &&

@@ -1098,9 +1098,8 @@ hipError_t launch_ring(const GemmParams& p, int tile, hipStream_t st) {
 // fixed cost (first slab, epilogue), times the rounds the launch's tiles make on the CUs, and a part that grows with the
 // tiles alone (the CUs share memory and power).  Fitted to the products of the running encoder, each form forced for one
 // product at a time (three shapes, 256 to 65536 rows, K 1024 to 12800, weights cold; rms 4-7 %), when the 256-wide tiles
-// still ran on v_mfma_f32_32x32x16_bf16: those are 5 to 14 % faster now, the ring tiles 2 %.  The order of the forms holds on the
-// present kernels: of 385 products measured again, the one taken is within 3 % of the fastest for 88 %, within 5 % for 93 %,
-// within 9 % for 99 %.  Figures below that give one form only are of the earlier kernels.
+// still ran on v_mfma_f32_32x32x16_bf16: those are 5 to 14 % faster now, the ring tiles 2 %.  They order the forms for the second
+// stage below, whose choice tests hold against times of the present kernels.  Figures below that give one form only are of the earlier kernels.
 struct RingPick { int tile; double us; };
 bool f32_rows(int epi) { return epi == EPI_BIAS_RESIDUAL || epi == EPI_BIAS_POS; }   // reads and writes rows of the stream
 bool has_gelu(int epi) { return epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH; }
@@ -1385,10 +1384,11 @@ static Plain choose_plain(const GemmParams& p) {
 // ---- second stage: the shape that runs ----
 // choose_plain weighs the forms there were when its estimates were fitted; this stage takes another shape of the persistent kernel where it
 // is faster on the present kernels.  us = c + ck kt + up (u + uk kt) + r (v + vk kt): kt 64-deep slabs, r tiles per CU, up its rounds
-// (64 x 64 tiles, which share a CU: at least 1).  Fitted to 444 products with cold operands, each in up to nine shapes (encoders of 1024,
-// 1152 and 3200 columns, 736 to 106496 rows; rms 2 to 7 %, no coefficient below zero): the shape with the smallest estimate is 0.3 %
-// behind the fastest on average, the first stage's form 3.2 %, and two launches for q/k and the value projection 14 %.  Which ring
-// tiles, only the first stage says: alone and in the running encoder they differ most.
+// (64 x 64 tiles, which share a CU: at least 1).  Fitted to products with cold operands and among their own kind, each in up to nine shapes
+// (encoders of 1024, 1152 and 3200 columns, 736 to 106496 rows; rms 2 to 7 %, no coefficient below zero).  Against 410 products and pairs
+// among other kernels (tests/golden/product_times.txt, which tests/product_times.py takes) what runs is behind the fastest form by, on
+// average: pairs 0.7 %, bias 1.5, activation 0.9, residual 1.3, values 1.2; furthest 1024 rows of 5120 columns over K = 12800, 199 us on ring tiles,
+// 151 on 256 x 128 ones.  Which ring tiles, only the first stage says: alone and in the running encoder they differ most.
 static void cut_columns(const GemmParams& p, GemmParams& a, GemmParams& b) {   // whole 256-wide tile columns, and the rest
   const int n_a = p.N / 256 * 256;
   a = b = p;

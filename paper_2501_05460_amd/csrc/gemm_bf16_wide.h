@@ -7,15 +7,16 @@
 //     PFLOP/s with the first and 1.74 with the second (constant operands: both near 2.45).  An element's k-steps are added
 //     in the same order inside the instruction: two 32x32x16 steps and one 16x16x32 step leave the same bits.
 //   * the MFMAs of a k-step walk the wave's blocks in serpentine order: consecutive ones share an operand fragment
-//     (such a loop on another box: 2.10 PFLOP/s, row-major 2.06, both operands new every time 1.95).
+//     (such a loop on another card: 2.10 PFLOP/s, row-major 2.06, both operands new every time 1.95).
 // A workgroup per CU walks the tile sequence.  Both operand slabs (64 deep) go from global memory straight into one of two
 // LDS buffers; the fragments of a k-step (32 deep) are read while the MFMAs of the step before it run, so that a slab's
-// buffer is free, and the slab after the next is fetched into it, as soon as the slab's first k-step is multiplied: a
-// load has a whole slab's time to arrive, and a slab costs one barrier.  Reads and loads sit one by one between the MFMAs.
+// buffer is free, and the slab after the next is fetched into it, as soon as the slab's first k-step is multiplied: the
+// loads issue through the second k-step and are waited for behind the next slab's first, so that the first has nearly a slab's time to
+// arrive (1.3 us, 1.6 to 1.9 over cold operands) and the last half of one; a slab costs one barrier.  Reads and loads sit one by one between the MFMAs.
 // The loads past a tile's last slab fetch the next tile's first two.  A wave stages its part of the finished tile through
 // LDS behind the buffers, 4 to 6 KiB at a time and without a workgroup barrier, so that global memory sees whole lines.
 //
-// Measured stand-alone beside the 32x32x16 kernels this replaces (us; one box, random operands): 106496 rows, N x K
+// Measured stand-alone beside the 32x32x16 kernels this replaces (us; on one card, random operands): 106496 rows, N x K
 // 2048 x 1024 380 -> 339, value projection 204 -> 179, out-projection 283 -> 262, 4096 x 1024 with GELU 829 -> 730,
 // 1024 x 4096 residual 838 -> 782; 8192^3 775 -> 706 (1.56 PFLOP/s); 10240 rows, 1152 x 4352 residual 101 -> 95.
 // With the lines of a slab pair asked for ahead (`touch`) and bands of one width (us, operands cold as in a running encoder): 10240 rows,
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
     asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
                  :: "v"(i < LA ? a_voff : b_voff), "s"(g), "s"(lds0 + buf * SLAB + (i < LA ? i * RPL : ROWS + (i - LA) * RPL) * 128) : "memory", "m0");
   };
-  // A slab's direct loads have half a slab's time to arrive (1 us), less than a line takes that is not in the L2 yet.  So the
+  // The last of a slab's direct loads have half a slab's time to arrive (0.65 to 0.95 us), less than a line takes that is not in the L2 yet.  So the
   // lines of the two slabs behind the ones under way are asked for a pair of slabs ahead, each by one workgroup of the XCD
   // (they share panels: slot % gw picks the part of the activation rows, slot / gw that of the weight rows) and two lines of a
   // row by two lanes, 256 contiguous bytes.  The load wants a destination: a dword a lane into the wave's staging area, which

@@ -645,11 +645,10 @@ int tile_for(const MxGemmParams& p) {
   // 256 x 256 tiles, a workgroup of eight waves per CU, 128 x 128 ones, two of four waves, or, for the residual product over more
   // than a round, 224 x 256 ones: the one estimated to take least.  us = start + rounds (fixed + slabs) + rounds without rounding up
   // (fixed + slabs): the residual product's workgroups drift apart, and over several rounds one's epilogue stands under
-  // another's products.  The small tiles' last round counts 0.7 while one per CU holds it.  Bias and activation: fitted to 50 products
-  // (of 126 others those taken are 0.3 % behind the faster on average, 16 % at most).  Residual: fitted to 162 (1024 to 106496 rows,
-  // 1024 to 3200 columns, K 1024 to 12800), with 4 us for a start of large tiles behind another kernel, which those did
-  // not hold, and 3 % that the 224-row ones have to be ahead: of 78 none slower, 1.3 % faster on average than with rounds alone
-  // and without them.  us, 256 x 256 | 128 x 128 | 224 x 256: 1024 rows, 2048 x 1024 15.4 | 9.1, residual 1024 x 4096 51.0 | 24.7 | 47.2;
+  // another's products.  The small tiles' last round counts 0.7 while one per CU holds it.  Fitted to products of 1024 to 106496 rows, 1024 to
+  // 3200 columns and K 1024 to 12800; residual ones with 4 us for a start of large tiles behind another kernel, which those did
+  // not hold, and 3 % that the 224-row ones have to be ahead.  Against the 372 products and pairs of tests/golden/product_times.txt the tile
+  // taken is 0.2 to 0.6 % behind the fastest on average, 13 % at most (8256 rows, residual 1024 x 4096: 62.4 us, 224-row tiles 55.4).  us, 256 x 256 | 128 x 128 | 224 x 256: 1024 rows, 2048 x 1024 15.4 | 9.1, residual 1024 x 4096 51.0 | 24.7 | 47.2;
   // 26624 rows, 1152 x 1152 91.9 | 73.9 | 83.8, 1024 x 4096 130 | 151 | 127; 53248, 1024 x 4096 257 | 283 | 247; 106496, 1152 x 4352
   // 620 | 726 | 633.  In one round the 224-row tiles gain nothing that the 128 x 128 ones do not: 10240, 1152 x 4352 67.0 | 76.8 | 68.6.
   struct Cost { double start, round, round_slab, work, work_slab; };

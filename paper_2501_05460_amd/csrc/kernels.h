@@ -43,10 +43,11 @@ void f32_take_rows(const float* in, SliceRows src, float* out, long rows, int D,
 // beyond N); K % 128 == 0; N % 4 == 0 (N % 8 == 0 for bf16 outputs); Npad % 128 == 0.
 struct GemmParams {
   int epi;
-  int cfg;                    // 0: chosen by shape and epilogue; tests / timing: 1 = 256x128 tile, persistent, 4 = one tile per workgroup, 2 / 3 = 128x128 ring tiles (folded pre-norm: loads two / four slabs ahead), 6 = 256x256 plain loop,
+  int cfg;                    // 0: chosen by shape and epilogue; tests / timing: 1 = 256x128 tile, persistent, 5 = 256x256 tiles in whole rounds and the rest on ring tiles, 18 = the last 128 columns apart, 2 / 3 = 128x128 ring tiles (folded pre-norm: loads two / four slabs ahead), 6 = 256x256 plain loop,
                               // 7 = 256x256 pipelined loop, 8 = the same with both operands straight into LDS,
                               // 9 = 256x256 persistent (all but the residual epilogue), 10 = persistent residual product, 11 / 13 / 14 = ring tiles 64x64 / 128x64 / 128x128,
-                              // 12 = persistent residual product on 256x192 tiles (N % 192 == 0)
+                              // 12 = persistent residual product, or pair, on 256x192 tiles (N % 192 == 0), 15 = persistent 224x256 tiles (activations, residual, pairs),
+                              // 16 / 17 = persistent 192x256 / 160x256 tiles (pairs)
   int band;                   // 0: automatic; else tile columns per L2 band (must divide Npad / BN)
   const bf16_t* A; long lda;
   const bf16_t* W;            // packed [Npad, K]

@@ -109,6 +109,9 @@ def test_weights_asked_for_in_front_of_a_product_change_no_bits(hidden, mlp, til
     """Norms that ask for the next product's weights (the persistent kernel behind them, few enough rows; the last: too many) against
     the slices alone (ring tiles: no such norm)."""
     desc = desc_for(wl.DT_BF16, tile_size=tile, hidden=hidden, heads=16, mlp=mlp, layers=2, act=wl.ACT_GELU_TANH, pixel_shuffle=tile % 28 == 0)
+    ring, tok = (11, 13, 14), ((tile // 14) ** 2 + 7) // 8 * 8
+    pair = lambda k: B.op_gemm_bf16_shape(tok * k, 2 * hidden, hidden, 0, hidden, tok)
+    assert pair(1) in ring and pair(n) not in ring
     enc = make_encoder(desc, wl.gen_weights(desc, 41, std=0.03))
     tiles = torch.from_numpy(wl.gen_tiles(desc, 41, n)).cuda()
     full, per = bits(enc.encode(tiles, [0, n])), enc.tokens_per_tile
