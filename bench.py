@@ -25,19 +25,24 @@ PEAK_FP32_TFLOPS = 157.3
 TOL = {"bf16": 2e-2, "f32": 1e-4}   # max |gpu - oracle| / max |oracle| the parity sample must meet
 
 
-def traffic_from_profile(workload: str):
+def traffic_from_profile(workload: str, launches_per_call: float):
     """L2 <-> fabric bytes per GEMM launch (FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, the factors a plain 1 GiB
     copy kernel gives on the same counters), as the committed rocprofv3 --pmc summary of this command states
-    it: the line `traffic_bytes_per_gemm_launch: <number>` of profiles/<workload>_bench_hbm_traffic.txt.
+    it: the line `traffic_bytes_per_gemm_launch: <number>` of profiles/<workload>_bench_hbm_traffic.txt.  A summary of
+    other launches (`gemm_launches_per_call` is not what a call makes now) says nothing about these.
     Returns (bytes or None, source)."""
     rel = os.path.join("profiles", f"{workload}_bench_hbm_traffic.txt")
+    stated = {}
     try:
         for line in open(os.path.join(ROOT, rel)):
-            if line.startswith("traffic_bytes_per_gemm_launch:"):
-                return float(line.split(":", 1)[1].split()[0]), rel
+            if line.startswith(("traffic_bytes_per_gemm_launch:", "gemm_launches_per_call:")):
+                key, value = line.split(":", 1)
+                stated[key] = float(value.split()[0])
     except OSError:
         pass
-    return None, None
+    if stated.get("gemm_launches_per_call") != launches_per_call or "traffic_bytes_per_gemm_launch" not in stated:
+        return None, None
+    return stated["traffic_bytes_per_gemm_launch"], rel
 
 
 def roof_report(B, torch):
@@ -235,7 +240,7 @@ def main():
     gemm_launches = sum(fam[k]["launches"] for k in gf)
     gemm_flops = sum(gf.values()) * T * prof_steps
     achieved = gemm_flops / (gemm_ms * 1e-3) / 1e12 if gemm_ms > 0 else 0.0
-    traffic, traffic_source = (traffic_from_profile(args.workload)
+    traffic, traffic_source = (traffic_from_profile(args.workload, gemm_launches / prof_steps)
                                if desc.max_tiles_per_call == wk.desc.max_tiles_per_call and not args.mx_fp8 else (None, None))
     roofline = {
         "bound": "mfma", "kernel": ("k_gemm_mxfp8 (q/k/v, out-proj, FC1, FC2) + k_gemm_bf16 (the rest)" if args.mx_fp8 else "k_gemm_bf16 (all epilogue variants)") if bf16 else "k_f32_gemm",

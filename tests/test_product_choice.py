@@ -112,3 +112,17 @@ def test_residual_products_leave_the_persistent_kernels_when_told_to():
     assert {1, 10, 12, 15} <= taken("1")
     off = taken("0")
     assert {7, 8, 11, 13, 14} <= off <= {5, 7, 8, 11, 13, 14, 18}, off
+
+
+@pytest.mark.parametrize("workload", ["c2", "c3"])
+def test_the_benchmark_states_traffic_of_the_launches_it_times_only(workload):
+    """The committed counter summaries say how many products a call launched; for another number the benchmark states none."""
+    import bench
+    launches = 0
+    for line in open(os.path.join(bench.ROOT, "profiles", workload + "_bench_hbm_traffic.txt")):
+        if line.startswith("gemm_launches_per_call:"):
+            launches = int(line.split(":")[1])
+    assert launches > 0
+    traffic, source = bench.traffic_from_profile(workload, launches)
+    assert 5e7 < traffic < 5e9 and source.endswith("_hbm_traffic.txt")
+    assert bench.traffic_from_profile(workload, launches + 24) == (None, None)
