@@ -46,7 +46,7 @@ def traffic_from_profile(workload: str, launches_per_call: float):
 
 
 def roof_report(B, torch):
-    """Measured ceilings of this box, one JSON line: register-resident MFMA loop (random and constant
+    """Measured ceilings of this machine, one JSON line: register-resident MFMA loop (random and constant
     operands, either bf16 instruction), streaming copy, and the vendor BLAS (through torch.matmul) next to this library's plain
     bias-epilogue product on the four per-layer shapes of the C3 workload and a large cube, ten launches
     back to back each, random operands."""
@@ -129,7 +129,7 @@ def main():
     ap.add_argument("--no-shard-sweep", action="store_true",
                     help="skip the brief per-worker-share sweep a default run takes (profiling runs of the headline step)")
     ap.add_argument("--roof", action="store_true",
-                    help="measure this box's ceilings instead of the workload (MFMA loop, streaming copy, vendor "
+                    help="measure this machine's ceilings instead of the workload (MFMA loop, streaming copy, vendor "
                          "BLAS and this library on the per-layer shapes) and print them as one JSON line")
     ap.add_argument("--mx-fp8", action="store_true",
                     help="the checkpoint-fidelity option epd_model_desc::mx_fp8: q/k/v, out-projection, FC1 and FC2 products on MXFP8 "
@@ -245,7 +245,7 @@ def main():
     roofline = {
         "bound": "mfma", "kernel": ("k_gemm_mxfp8 (q/k/v, out-proj, FC1, FC2) + k_gemm_bf16 (the rest)" if args.mx_fp8 else "k_gemm_bf16 (all epilogue variants)") if bf16 else "k_f32_gemm",
         "achieved": round(achieved, 2), "peak": peak, "unit": "TFLOP/s", "frac": round(achieved / peak, 4),
-        # what a register-resident MFMA loop reaches on this machine right now (random operands; no memory, no LDS)
+        # what a register-resident MFMA loop reaches on this card right now (random operands; no memory, no LDS)
         "achievable_peak": round(max(B.op_mfma_peak(True), B.op_mfma_peak(True, shape=16)), 1) if bf16 else None,
         "traffic": traffic, "traffic_source": traffic_source,
         "flops_per_launch": gemm_flops / max(gemm_launches, 1),

@@ -19,8 +19,10 @@
 // Measured stand-alone, K = 4096, N = 1024: 1024 rows 21.8 us with the 64 x 64 form this replaces, 15.4 now; 3096 rows
 // 56.4 us with eight-wave 128 x 128 tiles, 30.5 now.  In the running encoder, weights cold: 24.4 -> 22.9, 55.8 -> 41.5.
 // A deeper ring (8 / 6 / 5 stages, one workgroup per CU) changed nothing in the encoder.  A fifth wave that asks for the panels' lines
-// ahead, as gemm_bf16_wide.h does, costs 5 to 40 %: what a slab waits for is not memory but LDS (a 64 x 64 slab is 32 KiB read and
-// 16 KiB written, 384 cycles at 128 bytes a cycle; a 128 x 128 one 768) and the chip's share of the L2s.
+// ahead, as gemm_bf16_wide.h does, costs 5 to 40 %.  LDS is half of a slab (a 64 x 64 one is 32 KiB read and 16 KiB written, 384
+// cycles at 128 bytes a cycle; a 128 x 128 one 768): FC2 of 3096 rows of the 1024-wide encoder, one 128 x 128 tile on each of 200 CUs,
+// takes 41 us in the encoder, 1500 cycles a slab, of which the products are 512.  Its waves spend 17 % of their cycles waiting for data or
+// a barrier and 53 % waiting for an instruction to issue (counters); which instruction, is not measured.
 //
 // The epilogue goes through LDS wave by wave (a wave stages 32 rows of its own tile and reads them back, no
 // workgroup barrier), so that global memory sees 16-byte pieces of whole 128-byte row parts; bias, activation,

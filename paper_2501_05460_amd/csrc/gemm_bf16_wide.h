@@ -1,8 +1,8 @@
 // bf16 MFMA GEMM on large tiles with persistent workgroups:  C[M,N] = A[M,K] * W[N,K]^T with the fused epilogues.
 //
 // What bounds it: over a long K the chip's power, under which the clock falls to 1.5 to 2.05 GHz of 2.4; at K = 1024 as much the
-// epilogue, in which all waves of the one workgroup a CU holds stand together (106496 rows: the matrix pipe is busy 59 to 64 %
-// of a product, 49 % of a residual one, at 1.95 to 2.12 GHz).  The energy of a flop counts in both.  Hence
+// epilogue, in which all waves of the one workgroup a CU holds stand together (106496 rows: the matrix pipe is busy 63 to 67 %
+// of a product, 56 % of a residual one, at 1.95 to 2.06 GHz).  The energy of a flop counts in both.  Hence
 //   * v_mfma_f32_16x16x32_bf16, not v_mfma_f32_32x32x16_bf16: a register-resident loop on normal deviates runs 2.02
 //     PFLOP/s with the first and 1.74 with the second (constant operands: both near 2.45).  An element's k-steps are added
 //     in the same order inside the instruction: two 32x32x16 steps and one 16x16x32 step leave the same bits.
