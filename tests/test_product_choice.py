@@ -116,13 +116,19 @@ def test_residual_products_leave_the_persistent_kernels_when_told_to():
 
 @pytest.mark.parametrize("workload", ["c2", "c3"])
 def test_the_benchmark_states_traffic_of_the_launches_it_times_only(workload):
-    """The committed counter summaries say how many products a call launched; for another number the benchmark states none."""
+    """The committed counter summaries say how many products a call launched: as many as the library launches for the workload now, all
+    slices in one micro-batch (a cut is two).  For another number the benchmark states none."""
     import bench
-    launches = 0
-    for line in open(os.path.join(bench.ROOT, "profiles", workload + "_bench_hbm_traffic.txt")):
-        if line.startswith("gemm_launches_per_call:"):
-            launches = int(line.split(":")[1])
-    assert launches > 0
+    import workloads as wl
+    wk = wl.workload(workload)
+    d, M = wk.desc, wk.n_tiles * wk.desc.seq_len
+    assert wk.n_tiles <= d.max_tiles_per_call and d.proj_kind == 1
+    act, kernels = 1 if d.act == wl.ACT_GELU_ERF else 2, lambda *shape: 2 if B.op_gemm_bf16_shape(*shape) in (5, 18) else 1
+    assert B.op_gemm_bf16_shape(M, 2 * d.hidden, d.hidden, 0, d.hidden, d.seq_len) > 0
+    up = lambda n: (n + 127) // 128 * 128
+    layer = 1 + kernels(M, d.hidden, up(d.hidden), 3) + kernels(M, d.mlp, up(d.hidden), act) + kernels(M, d.hidden, up(d.mlp), 3)
+    out = wk.n_tiles * d.tokens_per_tile
+    launches = d.layers * layer + kernels(out, d.proj_mid, up(d.proj_in), 1) + kernels(out, d.proj_out, up(d.proj_mid), 0)
     traffic, source = bench.traffic_from_profile(workload, launches)
-    assert 5e7 < traffic < 5e9 and source.endswith("_hbm_traffic.txt")
-    assert bench.traffic_from_profile(workload, launches + 24) == (None, None)
+    assert source and source.endswith("_hbm_traffic.txt") and 5e7 < traffic < 5e9
+    assert bench.traffic_from_profile(workload, launches + d.layers) == (None, None)
