@@ -137,11 +137,12 @@ def test_attention_bf16_ignores_rows_past_n_keys(n_tok, n_keys, heads, hd, hd_pa
 @pytest.mark.parametrize("hd", [64, 72, 96, 128])
 @pytest.mark.parametrize("n_tok,n_keys", [(1024, 1024), (1088, 1025), (1024, 1000), (128, 33), (64, 32), (192, 129)])
 def test_attention_bf16_of_few_and_many_slices_agrees_bit_for_bit(n_tok, n_keys, hd, paired):
-    """In either order of summation: one slice runs 16 queries per wave, more than 512 workgroups of 128 queries 32: the same bits either way,
+    """In either order of summation: one slice runs 16 queries per wave, the fewest slices that take 32 those: the same bits either way,
     with reference moves (logits of up to about 30) in both.  Padding rows hold large values and NaN."""
     g = torch.Generator().manual_seed(n_tok * 131 + n_keys + hd)
     heads = 8
-    many = 512 // (heads * ((n_tok + 127) // 128)) + 1
+    many = next(n for n in range(2, 300) if B.op_attention_queries(n, n_tok, heads, hd, paired) == 32)
+    assert B.op_attention_queries(1, n_tok, heads, hd, paired) == 16
     D = heads * hd
     qk = torch.randn(many, n_tok, 2 * D, generator=g)
     qk[:, :, :D] *= 6.0 * hd ** -0.5
