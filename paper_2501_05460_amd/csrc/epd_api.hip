@@ -973,7 +973,6 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
     }
     GemmParams p1 = gp(act_epi, Xn, c->D_k, w.fc1, M), p2 = gp(EPI_BIAS_RESIDUAL, Hd, c->F_k, w.fc2, M);
     p1.C = Hd; p1.ldc = c->F_k;
-    p1.c_cached = bf16_gemm_on_64x64(p2);
     with_norm(p1, w.fc1_cs);
     norm_kernel(w.n2_g, w.n2_b, !copy, p1);
     { ProfScope ps(c, 7, st);

@@ -697,17 +697,6 @@ __global__ __launch_bounds__(NTHREADS, BM_ == 128 && PIPE == 0 ? 2 : 1) void k_g
       }
     }
   __syncthreads();
-  if constexpr (BN == 128 && BM_ == BM && FOLD == 0 && (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH)) {
-    if (p.c_cached) {   // a loop of its own: the choice inside the loop below costs a launch without it 3 % (FC1 of 2048 rows, 26.3 us)
-#pragma unroll
-      for (int i = 0; i < PER_T; ++i) {
-        const int q = tid + NTHREADS * i, r = q / NCH, c = q % NCH, row = m0 + r, col = n0 + c * 8;
-        if (row < p.M && col < p.N)
-          *reinterpret_cast<u32x4*>(p.C + (long)row * p.ldc + col) = *reinterpret_cast<const u32x4*>(stage + r * ROWB + ((c ^ (r & 15)) << 4));
-      }
-      return;
-    }
-  }
 #pragma unroll
   for (int i = 0; i < PER_T; ++i) {
     const int q = tid + NTHREADS * i;
@@ -1545,11 +1534,6 @@ bool bf16_gemm_pair_fits(const GemmParams& p) {
   GemmParams q = p, v = p;
   q.n2_pad = v.n2_pad = 0; v.epi = EPI_VT; v.N = p.n2; v.Npad = p.n2_pad;
   return choose_pair(p).us < choose(q).us + choose(v).us + 2.5;
-}
-
-bool bf16_gemm_on_64x64(const GemmParams& p) {
-  const Choice c = choose(p);
-  return c.shape < 0 && c.first.form == PLAIN_RING && c.first.tile == RING_64x64;
 }
 
 bool bf16_gemm_on_wide(const GemmParams& p) {

@@ -268,6 +268,11 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
   };
+  // the output the tile is part of: V^T, rows of the stream or C (each under 4 GiB; what these tiles write is under NEAR_OUT)
+  const __amdgpu_buffer_rsrc_t rsrc =
+      vt_tile ? __builtin_amdgcn_make_buffer_rsrc(p.VT, 0, (int)(unsigned)((long)p.M * p.heads * p.hd_pad * 2), 0x00020000)
+      : F32_OUT ? __builtin_amdgcn_make_buffer_rsrc(p.R, 0, (int)(unsigned)(((long)(p.M - 1) * p.ldr + p.N) * 4), 0x00020000)
+                : __builtin_amdgcn_make_buffer_rsrc(p.C, 0, (int)(unsigned)(((long)(p.M - 1) * p.ldc + p.N) * 2), 0x00020000);
   if (vt_tile) {
     constexpr int ROWF = 32 * WTM + 4;      // floats per staging row (16 bytes of padding: rows start 4 banks apart)
     float* stg = reinterpret_cast<float*>(smem) + wave * 32 * ROWF;
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
 #pragma unroll
           for (int e = 0; e < 4; ++e) { o[e] = (bf16_t)(lo[e] + vb[HAS_VT ? j : 0][HAS_VT ? u : 0]); o[4 + e] = (bf16_t)(hi[e] + vb[HAS_VT ? j : 0][HAS_VT ? u : 0]); }
           // feature h * hd_pad + d of slice t: row ((t * heads + h) * hd_pad + d) = t * heads * hd_pad + f of V^T
-          *reinterpret_cast<bf16x8*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n) = o;
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rsrc, ((unsigned)(t * p.heads * p.hd_pad + f) * (unsigned)p.n_tok + (unsigned)n) * 2u, 0, THROUGH);
         }
       }
       wave_sync();
@@ -319,7 +324,8 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
         const int row = x_row + 32 * i + (64 / XCH) * c;
         if (row < p.M && x_col < p.N) {
           const f32x4 v = *reinterpret_cast<const f32x4*>(stg + (lane / XCH + (64 / XCH) * c) * ROWF + (lane % XCH) * 4) + bias0;
-          if constexpr (EPI == EPI_BIAS_RESIDUAL) *reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + x_col) = xr[i][c] + v;
+          if constexpr (EPI == EPI_BIAS_RESIDUAL)
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, xr[i][c] + v), rsrc, ((unsigned)row * (unsigned)p.ldr + (unsigned)x_col) * 4u, 0, THROUGH);
           else *reinterpret_cast<f32x4*>(p.R + p.xrows.row(row) * p.ldr + x_col) = v + xr[i][c];   // through the slice layout
         }
       }
@@ -342,8 +348,10 @@ __global__ __launch_bounds__(256, OCC) void k_gemm_bf16_ring(const GemmParams p,
             o[e] = (bf16_t)apply_act_fast<EPI>(lo[e]);
             o[4 + e] = (bf16_t)apply_act_fast<EPI>(hi[e]);
           }
-          const long orow = p.row_map ? (long)p.row_map[row / p.block_tokens] * p.block_tokens + row % p.block_tokens : row;
-          *reinterpret_cast<bf16x8*>(p.C + orow * p.ldc + c_col) = o;
+          if (p.row_map)   // paged output: rows go through the block map
+            *reinterpret_cast<bf16x8*>(p.C + ((long)p.row_map[row / p.block_tokens] * p.block_tokens + row % p.block_tokens) * p.ldc + c_col) = o;
+          else
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rsrc, ((unsigned)row * (unsigned)p.ldc + (unsigned)c_col) * 2u, 0, THROUGH);
         }
       }
       wave_sync();
@@ -359,6 +367,7 @@ hipError_t launch_ring(const GemmParams& p, hipStream_t st) {
   if (p.Npad % TN != 0 || p.n2_pad % TN != 0) return hipErrorInvalidValue;
   const int gm = (p.M + TM - 1) / TM, gn = (p.Npad + (DUAL ? p.n2_pad : 0)) / TN;
   if (gm * gn == 0) return hipSuccess;
+  if ((EPI == EPI_VT || DUAL) && (long)p.M * p.heads * p.hd_pad * 2 >= (1L << 32)) return hipErrorInvalidValue;   // V^T through 32-bit offsets
   // bands of up to eight tile columns, equally wide: within 2 % of four at any size, 4 % ahead on average with 128 x 64 tiles
   const int bands = (gn + 7) / 8;
   k_gemm_bf16_ring<EPI, DUAL, WTM, WTN, RING, OCC><<<dim3(gm * gn), dim3(256), ring_lds<WTM, WTN, RING>(), st>>>(p, gm, (gn + bands - 1) / bands);

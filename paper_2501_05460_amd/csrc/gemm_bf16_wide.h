@@ -63,7 +63,9 @@ struct Wide {
 
 // DUAL (EPI_BIAS): tile columns from Npad on are a second product over the same activations, the value projection, whose tiles run
 // with the operand roles of EPI_VT and leave through its store (GemmParams::n2).
-template <int EPI, bool DUAL, int TM, int TN, int WAVES_M, int WAVES_N>
+// NEAR: the output goes THROUGH, stream rows are read without a hint (NEAR_OUT, NEAR_ROWS).  Compiled apart: with both ways in one kernel the residual
+// one spills, and the others take 0.5 to 2 % longer at 104 slices.
+template <int EPI, bool DUAL, int TM, int TN, int WAVES_M, int WAVES_N, bool NEAR>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(const GemmParams p, const int gm, const int gw,
                                                                               const int gn, const int n_tiles, const int ahead) {
   using S = Wide<TM, TN, WAVES_M, WAVES_N>;
@@ -200,6 +202,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
   __amdgpu_buffer_rsrc_t rsrc_c = __builtin_amdgcn_make_buffer_rsrc(
       p.C, 0, (EPI == EPI_VT || F32_OUT || !p.C) ? 0 : (int)(unsigned)(((long)(p.M - 1) * p.ldc + p.N) * 2), 0x00020000);
 
+  // V^T, T x heads x hd_pad rows of n_tok (written through only while it is small)
+  __amdgpu_buffer_rsrc_t rsrc_v = __builtin_amdgcn_make_buffer_rsrc(
+      p.VT, 0, (EPI == EPI_VT || DUAL) && NEAR ? (int)(unsigned)((long)p.M * p.heads * p.hd_pad * 2) : 0, 0x00020000);
+
   int pos = blockIdx.x, m0, n0, m0n, n0n;
   tile_of(pos, m0, n0);
   ga = reinterpret_cast<const char*>(p.A + (long)m0 * p.lda);
@@ -250,7 +256,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
           const int row = m0 + wm * WM + i * 16 + r, col = n0 + wn * WN + c * 4;
           if constexpr (EPI == EPI_BIAS_RESIDUAL)   // the whole offset is the lane's, so that the range check sees it: rows past M come back as zero
             xr[i % XAHEAD][u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(
-                rsrc_x, ((unsigned)row * (unsigned)p.ldr + (unsigned)col) * 4u, 0, 2));
+                rsrc_x, ((unsigned)row * (unsigned)p.ldr + (unsigned)col) * 4u, 0, NEAR ? 0 : STREAM));
           else
             xr[i % XAHEAD][u] = *reinterpret_cast<const f32x4*>(p.pos + (long)(row % p.n_pos) * p.N + (col < p.N ? col : 0));
         }
@@ -350,11 +356,14 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
             const int q = lane + 64 * u, r = q / XCH, c = q % XCH;
             const int row = m0 + wm * WM + i * 16 + r, col = n0 + wn * WN + c * 4;
             const f32x4 v = *reinterpret_cast<const f32x4*>(at(NCH{}, r, c));
-            if (row >= first_row && row < p.M && col < p.N) {
-              if constexpr (EPI == EPI_BIAS_RESIDUAL)   // streamed: read next by a row kernel, not by this launch
-                __builtin_nontemporal_store(xr[i % XAHEAD][u] + v, reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + col));
+            if (row >= first_row && row < p.M && col < p.N) {   // read next by a row kernel, not by this launch
+              if constexpr (EPI == EPI_BIAS_POS)   // through the slice layout
+                *reinterpret_cast<f32x4*>(p.R + p.xrows.row(row) * p.ldr + col) = v + xr[i % XAHEAD][u];
+              else if constexpr (NEAR)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, xr[i % XAHEAD][u] + v), rsrc_x,
+                                                       ((unsigned)row * (unsigned)p.ldr + (unsigned)col) * 4u, 0, THROUGH);
               else
-                *reinterpret_cast<f32x4*>(p.R + p.xrows.row(row) * p.ldr + col) = v + xr[i % XAHEAD][u];   // through the slice layout
+                __builtin_nontemporal_store(xr[i % XAHEAD][u] + v, reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + col));
             }
           }
           wave_sync();
@@ -380,7 +389,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
               const u32x4 v = *reinterpret_cast<const u32x4*>(at(NCH{}, r, c));
               const int t = tok / p.n_tok, n = tok % p.n_tok;
               // feature h * hd_pad + d of slice t: row ((t * heads + h) * hd_pad + d) = t * heads * hd_pad + f of V^T
-              __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n));
+              if constexpr (NEAR)
+                __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_v, ((unsigned)(t * p.heads * p.hd_pad + f) * (unsigned)p.n_tok + (unsigned)n) * 2u, 0, THROUGH);
+              else
+                __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n));
             }
           }
           wave_sync();
@@ -416,19 +428,12 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 1) void k_gemm_bf16_wide(co
             });
         } else {
           // buffer stores whose whole offset is the lane's: the range check drops the rows past M
-          const auto streamed = [&](int row, int col, u32x4 v) {
-            if (col < p.N) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_c, ((unsigned)row * (unsigned)p.ldc + (unsigned)col) * 2u, 0, 2);
-          };
-          if (COLS == 128 && (EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH) && p.c_cached) {   // see GemmParams
 #pragma unroll
-            for (int i2 = 0; i2 < TM; i2 += 2)
-              pass(i2, [&](int row, int col, u32x4 v) {
-                if (col < p.N) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_c, ((unsigned)row * (unsigned)p.ldc + (unsigned)col) * 2u, 0, 0);
-              });
-          } else {
-#pragma unroll
-            for (int i2 = 0; i2 < TM; i2 += 2) pass(i2, streamed);
-          }
+          for (int i2 = 0; i2 < TM; i2 += 2)
+            pass(i2, [&](int row, int col, u32x4 v) {
+              if (col < p.N)
+                __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_c, ((unsigned)row * (unsigned)p.ldc + (unsigned)col) * 2u, 0, NEAR ? THROUGH : STREAM);
+            });
         }
       }
     }
@@ -456,13 +461,22 @@ hipError_t launch_wide(const GemmParams& p, int cus, hipStream_t st) {
   if (p.band > 0 && p.band <= gn) gw = p.band;
   // one round of short tiles has nothing to gain (13312 rows, 1024 x 1024 residual, us without | with: 40.7 | 41.6)
   const int ahead = n_tiles > cus || p.K >= 2048;
-  k_gemm_bf16_wide<EPI, DUAL, TM, TN, WAVES_M, WAVES_N><<<dim3(n_tiles < cus ? n_tiles : cus), dim3(S::NT), S::LDS, st>>>(p, gm, gw, gn, n_tiles, ahead);
+  const dim3 grid(n_tiles < cus ? n_tiles : cus), block(S::NT);
+  constexpr bool HAS_NEAR = EPI != EPI_BIAS_POS;
+  if (HAS_NEAR && (EPI == EPI_BIAS_RESIDUAL ? 4.0 * p.M * p.N <= NEAR_ROWS : 2.0 * p.M * (p.N > p.n2 ? p.N : p.n2) <= NEAR_OUT))
+    k_gemm_bf16_wide<EPI, DUAL, TM, TN, WAVES_M, WAVES_N, HAS_NEAR><<<grid, block, S::LDS, st>>>(p, gm, gw, gn, n_tiles, ahead);
+  else
+    k_gemm_bf16_wide<EPI, DUAL, TM, TN, WAVES_M, WAVES_N, false><<<grid, block, S::LDS, st>>>(p, gm, gw, gn, n_tiles, ahead);
   return hipGetLastError();
 }
 template <int EPI, bool DUAL, int TM, int TN, int WAVES_M, int WAVES_N>
 hipError_t set_attr_wide() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_wide<EPI, DUAL, TM, TN, WAVES_M, WAVES_N>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)Wide<TM, TN, WAVES_M, WAVES_N>::LDS);
+  constexpr int LDS = (int)Wide<TM, TN, WAVES_M, WAVES_N>::LDS;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_wide<EPI, DUAL, TM, TN, WAVES_M, WAVES_N, false>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  if (e != hipSuccess || EPI == EPI_BIAS_POS) return e;
+  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_bf16_wide<EPI, DUAL, TM, TN, WAVES_M, WAVES_N, EPI != EPI_BIAS_POS>),
+                             hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
 }
 }  // namespace
 

@@ -38,6 +38,17 @@ void f32_shuffle(const float* in, SliceRows src, float* out, int T, int g, int D
 void f32_take_rows(const float* in, SliceRows src, float* out, long rows, int D, hipStream_t st);
 
 // ---- bf16 mode -------------------------------------------------------------
+// Cache policy of a store, as the last argument of the raw buffer builtins takes it.  STREAM (nt) leaves nothing in the caches and reads
+// come from memory.  THROUGH (sc1) writes past the XCD's L2 into the Infinity Cache, from which every XCD reads; unlike a plain
+// store it leaves no dirty lines in the L2, which the end of the launch would have to wait for.
+constexpr int STREAM = 2, THROUGH = 16;
+// Whether an output that the next launches read goes THROUGH: as long as it, what they read beside it and the weights are well under the 256 MiB
+// of the Infinity Cache.  Encoder calls, ms, all outputs of the large tiles STREAM | plain | bf16 ones THROUGH, rows of the stream STREAM | all THROUGH:
+// 1024-wide, three slices of 1025 tokens 3.69 | 3.69 | 3.67 | 3.48, eight (67 MB of MLP activations, 33 of rows) 6.55 | 6.35 | 6.44 | 6.24, 16 (134,
+// 67) 12.07 | 11.53 | 11.68 | 11.14, 20 (168, 84) 15.53 | 15.30 | 15.27 | 14.78, 26 (218, 109) 19.80 | 19.76 | 19.64 | 19.55, 52 36.1 | 37.2 | 36.6 | 36.9;
+// 1152-wide, 16 17.33 | 16.89 | 17.13 | 16.68; 6B shape, eight (210, 105) 80.5 | 81.4 | 80.9 | 81.4.
+constexpr double NEAR_OUT = 180e6, NEAR_ROWS = 75e6;
+
 // GEMM  C[M,N] = A[M,K] * W[N,K]^T with fused epilogue (gemm_bf16.hip).
 // A must be readable for round_up(M,256) rows, W for Npad rows (zero rows
 // beyond N); K % 128 == 0; N % 4 == 0 (N % 8 == 0 for bf16 outputs); Npad % 128 == 0.
@@ -54,10 +65,6 @@ struct GemmParams {
   const float* bias;          // [Npad]
   int M, N, K, Npad;
   bf16_t* C; long ldc;        // bf16 output (BIAS, GELU_*)
-  // 1: 256 x 128 tiles store C without the streaming hint (one round of them writes at most 17 MB, which the caches keep),
-  // for a reader on 64 x 64 ring tiles, which wait for their rows in several rounds.  Rows of the 1024-wide encoder, us:
-  // 1728, FC1 25.0 -> 26.6 and FC2 behind it on 64 x 64 tiles 34 -> 29; 2048, 26.3 -> 27.6 and on 128 x 64 tiles 34.0 | 34.0.
-  int c_cached;
   const int* row_map;         // optional paged output: row r -> row_map[r / block_tokens] * block_tokens + r % block_tokens
   int block_tokens;
   float* R; long ldr;         // fp32 residual stream (RESIDUAL, POS); RESIDUAL reads whole tiles: R must hold
@@ -86,7 +93,6 @@ struct GemmParams {
   int n2, n2_pad;
 };
 hipError_t bf16_gemm(const GemmParams& p, hipStream_t st);
-bool bf16_gemm_on_64x64(const GemmParams& p);   // whether p, without a folded pre-norm, takes 64 x 64 ring tiles
 // true: bf16_gemm runs p with its second product (n2_pad > 0) as one launch; false: the caller issues two products
 bool bf16_gemm_pair_fits(const GemmParams& p);
 bool bf16_gemm_on_wide(const GemmParams& p);    // whether p, without a folded pre-norm, starts with the persistent kernel (n2_pad > 0: as one launch)
@@ -122,9 +128,11 @@ hipError_t bf16_gemm_wide(const GemmParams& p, int tile, int cus, hipStream_t st
 hipError_t bf16_gemm_wide_gelu(const GemmParams& p, int tile, int cus, hipStream_t st);   // its parts, one file each
 hipError_t bf16_gemm_wide_residual(const GemmParams& p, int tile, int cus, hipStream_t st);
 hipError_t bf16_gemm_wide_pair(const GemmParams& p, int tile, int cus, hipStream_t st);
+hipError_t bf16_gemm_wide_pair_low(const GemmParams& p, int tile, int cus, hipStream_t st);
 hipError_t bf16_gemm_wide_gelu_init();
 hipError_t bf16_gemm_wide_residual_init();
 hipError_t bf16_gemm_wide_pair_init();
+hipError_t bf16_gemm_wide_pair_low_init();
 hipError_t bf16_gemm_wide_init();   // part of bf16_gemm_init
 int bf16_gemm_shape(const GemmParams& p);   // what runs for a product without a folded pre-norm, by its number in cfg (tests)
 long bf16_gemm_kernel_launches();   // kernels launched by bf16_gemm on the calling host thread so far (a figure for the profiling hooks)

@@ -54,7 +54,8 @@ void bf16_im2col(const float* tiles, bf16_t* A, int lda, int T, int S, int p, hi
 // it runs on XCD b % 8, whose run of the product's tiles is about that part of the columns.  In front of the rows' workgroups:
 // behind them they end last (three slices of the 1152-wide encoder 4606 us, in front 4596; seven 9114, 9032).
 constexpr int AHEAD = 64;
-template <int NV, int NORM>
+// NEAR: the source rows are in the Infinity Cache and the output goes THROUGH (NEAR_ROWS).
+template <int NV, int NORM, bool NEAR>
 __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
   if (NORM) {
     if ((int)blockIdx.x < AHEAD && p.ahead_bytes > 0) {
@@ -102,7 +103,8 @@ __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
     for (int i = 0; i < NV; ++i) {
       const int c = lane + 64 * i;
       if (c < nchunk) {
-        const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(src(c)));
+        const f32x4* at = reinterpret_cast<const f32x4*>(src(c));
+        const f32x4 t = NEAR ? *at : __builtin_nontemporal_load(at);
         v[i] = make_float4(t[0], t[1], t[2], t[3]);
       } else {
         v[i] = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -168,7 +170,10 @@ __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
     bf16x4 o;
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = (bf16_t)r[e];
-    *(reinterpret_cast<bf16x4*>(out) + c) = o;
+    if constexpr (NEAR)   // a relaxed store at the device's scope is one that goes THROUGH
+      __hip_atomic_store(reinterpret_cast<unsigned long long*>(out) + c, __builtin_bit_cast(unsigned long long, o), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    else
+      *(reinterpret_cast<bf16x4*>(out) + c) = o;
   };
   if (NV > 0) {
 #pragma unroll
@@ -189,7 +194,8 @@ void bf16_rowop(const RowOpParams& p, hipStream_t st) {
   if (p.rows == 0) return;
   dim3 grid((unsigned)((p.rows + 3) / 4 + (p.ahead_bytes > 0 ? AHEAD : 0))), block(256);
   const int per_lane = (p.dim / 4 + 63) / 64;
-#define ROWOP(NV, NORM) k_bf16_rowop<NV, NORM><<<grid, block, 0, st>>>(p)
+  const bool near = 4.0 * p.rows * p.dim <= NEAR_ROWS;
+#define ROWOP(NV, NORM) (near ? k_bf16_rowop<NV, NORM, true> : k_bf16_rowop<NV, NORM, false>)<<<grid, block, 0, st>>>(p)
   if (p.kind == 2) {
     if (per_lane <= 4) ROWOP(4, 0); else if (per_lane <= 8) ROWOP(8, 0); else if (per_lane <= 16) ROWOP(16, 0); else ROWOP(0, 0);
     return;

@@ -389,6 +389,23 @@ def test_two_products_in_one_launch_agree_bit_for_bit(M, N, n2, K, n_tok):
         assert torch.equal(got_c, c) and torch.equal(got_v, v), form
 
 
+@pytest.mark.parametrize("epi,N,forms,rows,more", [(0, 4096, (9, 1), 21970, 32), (1, 4096, (9, 15, 1), 21970, 32), (2, 4352, (9, 15), 20672, 32),
+                                                   (3, 1024, (10, 15, 1), 18300, 32), (3, 1152, (12,), 16270, 32), (5, 2048, (9, 1), 43936, 16)])
+def test_outputs_that_stay_in_the_cache_and_larger_ones_agree_bit_for_bit(epi, N, forms, rows, more):
+    """Either side of the size from which a product's output is streamed past the caches (90 million bf16 elements, 18.75 million of the
+    stream): kernels of their own, the same bits in the rows they share.  The transposed store in slices of 16 rows."""
+    g = torch.Generator().manual_seed(N + epi)
+    M, K = rows + more, 128
+    assert (rows * N <= 18.75e6 < M * N) if epi == 3 else (rows * N <= 90e6 < M * N)
+    A, W = torch.randn(M, K, generator=g).mul_(0.5).bfloat16().cuda(), torch.randn(N, K, generator=g).mul_(0.05).bfloat16().cuda()
+    bias = torch.randn(N, generator=g).mul_(0.1).cuda()
+    r0 = torch.randn(M, N, generator=g).cuda() if epi == 3 else None
+    for form in forms:
+        near, far = (B.op_gemm_bf16_form(A[:m], W, bias, epi, form, None if r0 is None else r0[:m].clone(), n_tok=16 if epi == 5 else 0)
+                     for m in (rows, M))
+        assert torch.equal(near, far[:len(near)]), form
+
+
 @pytest.mark.parametrize("M,N,K", [(256, 384, 128), (1000, 1152, 256), (2900, 1152, 1152), (77, 384, 384), (11100, 1152, 128)])
 def test_gemm_192_wide_tiles_agree_bit_for_bit(M, N, K):
     """The residual product on 256 x 192 tiles (widths that are whole multiples of 192 and not of 256) leaves the
