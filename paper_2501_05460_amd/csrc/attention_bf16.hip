@@ -37,6 +37,7 @@
 // the common step computes no maximum at all: a step whose weights sum to
 // more than 2^RESCALE_LOG2 (or overflow) is what triggers the maximum, the
 // move of the reference and a second round of exponentials.
+#include <algorithm>
 #include <type_traits>
 
 #include "kernels.h"
@@ -162,6 +163,26 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
+// A launch of a few slices leaves the memory idle, and the products behind it wait for weights that come from memory (a slab of a
+// 128 x 128 tile takes 1500 cycles with 72, 128 or 200 tiles at work, 1100 with its weights in the Infinity Cache).  So `wgs` workgroups in
+// front of the attention's read every line of the weights of the out-projection, of both MLP products and of the next layer's q, k and v.
+// us without | with: attention of one slice of 16 heads of 64 12.5 | 14.9 (24 MB), FC2 behind it 21.0 | 16.0, FC1 15.0 | 13.4, out-projection
+// 8.1 | 6.8; of three slices of 1025 tokens 27.1 | 28.9, FC2 40.3 | 32.5, out-projection 15.5 | 13.7.  Two loads in flight a thread: with
+// eight on half as many workgroups the attention takes 16.2; on 32 of them 22.5 (they end last); one dword a line 15.9.
+__device__ __forceinline__ void ask_for(const Ahead& a, int wgs) {
+  const unsigned from = blockIdx.x * 256 + threadIdx.x, step = wgs * 256;
+#pragma clang loop unroll(disable)
+  for (int r = 0; r < a.n; ++r) {
+    const u32x4* p = reinterpret_cast<const u32x4*>(a.at[r]);
+    const unsigned n = a.pieces[r];
+#pragma clang loop unroll(disable)
+    for (unsigned i = from; i < n; i += 2 * step) {
+      const u32x4 v = p[i], w = p[min(i + step, n - 1)];
+      asm volatile("" :: "v"(v), "v"(w));
+    }
+  }
+}
+
 // QT sub-tiles of 16 queries per wave, four waves.
 // LEAN: one step's S^T registers and weights only, no step issued ahead, so that four (head dim 64), three (72, 96) workgroups
 // share a CU (112, 142, 144 registers; up to 128, 155, 162 with MASK and PAIRED); at head dim 128, where LDS holds two, the
@@ -178,13 +199,19 @@ __device__ __forceinline__ void static_for(F&& f) {
 // then exchange (v_permlane16_swap): the same bits, 2 to 5 % slower.
 // MASK: the slices carry rows past n_keys (compiled apart: the unmasked kernel keeps its registers and its step free of
 // the key-index compare).
+template <int HD, int QT>
+constexpr int per_cu() { return HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 96 ? 3 : 2; }   // workgroups that share a CU
 template <int HD, int QT, bool MASK, bool PAIRED>
-__global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 96 ? 3 : 2) void k_attention_bf16(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
+__global__ __launch_bounds__(256, (per_cu<HD, QT>())) void k_attention_bf16(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k,
                                                         const bf16_t* __restrict__ vt,
                                                         bf16_t* __restrict__ o, int n_tok, int n_keys, int n_q,
                                                         int q_shared, int heads, int n_pairs, long ld_qk,
                                                         long ld_o, unsigned char* __restrict__ oq,
-                                                        unsigned* __restrict__ so, long ld_so) {
+                                                        unsigned* __restrict__ so, long ld_so, int n_ahead, const Ahead ahead) {
+  if ((int)blockIdx.x < n_ahead) {   // uniform over the workgroup
+    ask_for(ahead, n_ahead);
+    return;
+  }
   using SM = AttnSmem<HD>;
   constexpr bool LEAN = HD <= 96 && !(QT == 1 && HD != 72 && !MASK);
   constexpr int BQ = 64 * QT;   // queries per workgroup
@@ -205,7 +232,7 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
   // Workgroups are dealt round-robin to the 8 XCDs: keep the q-blocks of one
   // (slice, head) on one XCD so that its K / V^T block is fetched into one L2.
   const int n_qb = (n_q + BQ - 1) / BQ;
-  const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+  const int xcd = blockIdx.x & 7, seq = (blockIdx.x - n_ahead) >> 3;   // n_ahead % 8 == 0
   const int pair = (seq / n_qb) * 8 + xcd;          // (slice, head) index
   if (pair >= n_pairs) return;                      // whole workgroup leaves before any barrier
   const int qb = seq % n_qb, h = pair % heads, t = pair / heads;
@@ -643,13 +670,17 @@ __global__ __launch_bounds__(256, HD == 64 || (HD == 72 && QT == 1) ? 4 : HD <= 
 template <int HD, int QT, bool MASK, bool PAIRED>
 hipError_t launch_attn_m(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                          int n_tok, int n_keys, int n_q, int q_shared, int heads, long ld_qk, long ld_o,
-                         unsigned char* oq, unsigned* so, long ld_so, hipStream_t st) {
+                         unsigned char* oq, unsigned* so, long ld_so, const Ahead* ahead, hipStream_t st) {
   constexpr int BQ = 64 * QT;
   const int n_qb = (n_q + BQ - 1) / BQ, n_pairs = n_slices * heads;
   const long n_wg = (long)((n_pairs + 7) / 8) * 8 * n_qb;
-  if (n_wg > 0x7fffffffL) return hipErrorInvalidValue;
-  k_attention_bf16<HD, QT, MASK, PAIRED><<<dim3((unsigned)n_wg), dim3(256), AttnSmem<HD>::BYTES, st>>>(
-      q, k, vt, o, n_tok, n_keys, n_q, q_shared, heads, n_pairs, ld_qk, ld_o, oq, so, ld_so);
+  // 256 workgroups ask for the lines, fewer where they would take places of workgroups that could all run at once (three slices of 1025 tokens, 816
+  // workgroups and 1024 places: 3.53 ms with 256, 3.46 with 128).  Where they must, the more of them the sooner they leave.
+  const long free = (long)cu_count() * per_cu<HD, QT>() - n_wg;
+  const int n_ahead = !ahead || ahead->n == 0 ? 0 : free < 128 ? 256 : (int)std::min(256L, free / 64 * 64);
+  if (n_wg + n_ahead > 0x7fffffffL) return hipErrorInvalidValue;
+  k_attention_bf16<HD, QT, MASK, PAIRED><<<dim3((unsigned)n_wg + n_ahead), dim3(256), AttnSmem<HD>::BYTES, st>>>(
+      q, k, vt, o, n_tok, n_keys, n_q, q_shared, heads, n_pairs, ld_qk, ld_o, oq, so, ld_so, n_ahead, n_ahead ? *ahead : Ahead{});
   return hipGetLastError();
 }
 
@@ -673,13 +704,13 @@ bool short_waves(int n_slices, int n_q, int heads, int hd, bool paired) {
 template <int HD, bool PAIRED>
 hipError_t launch_attn(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                        int n_tok, int n_keys, int n_q, int q_shared, int heads, long ld_qk, long ld_o,
-                       unsigned char* oq, unsigned* so, long ld_so, int queries, hipStream_t st) {
+                       unsigned char* oq, unsigned* so, long ld_so, int queries, const Ahead* ahead, hipStream_t st) {
   const bool mask = n_keys < n_tok || n_tok % BKEY != 0;
   if (queries == 16 || (queries == 0 && short_waves(n_slices, n_q, heads, HD, PAIRED)))
-    return mask ? launch_attn_m<HD, 1, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
-                : launch_attn_m<HD, 1, false, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
-  return mask ? launch_attn_m<HD, 2, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st)
-              : launch_attn_m<HD, 2, false, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, st);
+    return mask ? launch_attn_m<HD, 1, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, ahead, st)
+                : launch_attn_m<HD, 1, false, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, ahead, st);
+  return mask ? launch_attn_m<HD, 2, true, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, ahead, st)
+              : launch_attn_m<HD, 2, false, PAIRED>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, ahead, st);
 }
 
 template <int HD, int QT, bool MASK, bool PAIRED>
@@ -714,7 +745,8 @@ int bf16_attention_queries(int n_slices, int n_q, int heads, int hd_pad, bool pa
 
 hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                           int n_tok, int n_keys, int n_q, int q_shared, int heads, int hd_pad, long ld_qk,
-                          long ld_o, hipStream_t st, unsigned char* oq, unsigned* so, long ld_so, bool paired, int queries) {
+                          long ld_o, hipStream_t st, unsigned char* oq, unsigned* so, long ld_so, bool paired, int queries,
+                          const Ahead* ahead) {
   if (n_slices == 0) return hipSuccess;
   // MXFP8 output: whole blocks of 32 per head only, rows of at least heads * hd_pad bytes, 4-byte pieces
   if (oq && (hd_pad % 32 != 0 || !so || ld_o % 4 != 0 || ld_o < (long)heads * hd_pad || ld_so < (long)n_slices * n_q)) return hipErrorInvalidValue;
@@ -723,8 +755,8 @@ hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf
   if (n_tok % 8 != 0 || n_tok <= 0 || n_keys < 1 || n_keys > n_tok || n_q < 1) return hipErrorInvalidValue;
   if (!q_shared && n_q != n_tok) return hipErrorInvalidValue;   // a slice's own rows: one query per row
 #define LAUNCH(HD)                                                                                                       \
-  return paired || oq ? launch_attn<HD, true>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, queries, st) \
-                      : launch_attn<HD, false>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, queries, st)
+  return paired || oq ? launch_attn<HD, true>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, queries, ahead, st) \
+                      : launch_attn<HD, false>(q, k, vt, o, n_slices, n_tok, n_keys, n_q, q_shared, heads, ld_qk, ld_o, oq, so, ld_so, queries, ahead, st)
   switch (hd_pad) {
     case 64: LAUNCH(64);
     case 72: LAUNCH(72);

@@ -812,6 +812,12 @@ GemmParams gp(int epi, const void* A, long lda, const Linear& lin, int M) {
   return p;
 }
 
+// Calls whose attention asks for weights (weights_behind).  us without | with: 1024-wide encoder, one slice 1910 | 1695, two 2737 | 2415, three of 1025
+// tokens 3515 | 3098, five 4900 | 4629, eight 6299 | 6245, ten (126 MB of rows and MLP activations) 7922 | 7926, 16 11309 | 11303, 20 14930 | 14987;
+// 1152-wide, one 2708 | 2534, two 4025 | 3462, four 5636 | 5410, ten (135 MB) 10436 | 10387, 14 14674 | 14755, 20 20850 | 20997.
+constexpr long ASK_LAYER = 40 << 20;
+constexpr double ASK_ROWS = 140e6;
+
 epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStream_t st, int stage) {
   const epd_model_desc& d = c->d;
   const Dims& x = c->x;
@@ -853,19 +859,11 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
     if (fold) { p.stats_out = c->stats; p.n_part_out = c->n_part; }
   };
   // pre-norm as a kernel of its own: from the fp32 stream, or in place on the bf16 rows a residual epilogue left
-  auto norm_kernel = [&](const float* g, const float* b, bool from_stream, const GemmParams& next) {
+  auto norm_kernel = [&](const float* g, const float* b, bool from_stream) {
     if (fold) return;
     ProfScope ps(c, 1, st);
     if (from_stream) {
       RowOpParams r{d.norm, X, x.D, Xn, c->D_k, g, b, M, x.D, 0, x.g, x.D, d.eps};
-      // A product of few rows on the persistent kernel waits for its weights in its only round: the norm in front of it asks for them.  Both
-      // bounds are cut-offs found by encoding, not a size of the L2 (32 MiB over the XCDs): up to 40 MiB of rows (6 bytes an element) in front
-      // of the 6 to 8 MiB of weights of 1024 columns and the 8 to 11 of 1152.  us, without | with the weights asked for: 1024 columns, three
-      // slices of 1024 tokens 3520 | 3432, six 5727 | 5681, eight (48 MiB, past the bound) 6965 | 6991; 1152, two 4043 | 3972, four 5907 | 5860,
-      // five and six (34, 41 MiB) 7318 | 7317, 7345 | 7343; eight of 729 tokens (39 MiB) 7357 | 7369.  Not in front of ring tiles (one slice
-      // 1965 | 1980) nor of more weights (6B shape, 64 MB and more, 26.8 | 27.7 ms); between 11 and 64 MB nothing was measured.
-      const long bytes = (long)(next.Npad + next.n2_pad) * next.K * 2;
-      if (bytes <= 16 << 20 && (long)M * x.D * 6 <= 40 << 20 && bf16_gemm_on_wide(next)) { r.ahead = (const unsigned char*)next.W; r.ahead_bytes = bytes; }
       bf16_rowop(r, st);
     } else {
       bf16_norm_rows(Xn, c->D_k, g, b, M, x.D, d.norm, d.eps, st);
@@ -895,8 +893,28 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
     bf16_row_stats(X, x.D, M, x.D, Xn, c->D_k, c->stats, c->n_part, st);
   }
   if (n_layers > 0) combine();
+  // Weights that the launches between an attention and the next one read, for the attention to ask for (attention_bf16.hip), where a layer has
+  // at most ASK_LAYER bytes of them (24 to 32 MB at widths of 1024 and 1152, which an attention of one slice hides most of; of the 6B shape's 245 MB the
+  // out-projection's 20 alone cost one slice 1 %, with the MXFP8 option 5) and the rows and MLP activations leave them in the Infinity Cache.
+  auto weights_behind = [&](int l) {
+    Ahead a{};
+    if ((double)M * (4 * x.D + 2 * x.F) > ASK_ROWS) return a;
+    auto add = [&](const Linear& m) { a.add(m.W, (long)m.Npad * m.K * 2); };
+    auto add_mx = [&](const MxLinear& m) { a.add(m.W, (long)m.Npad * m.K); a.add(m.SW, (long)m.Npad * (m.K / 128) * 4); };
+    const LayerW &w = c->layers[l], *next = l + 1 < n_layers ? &c->layers[l + 1] : nullptr;
+    if (c->mx) {
+      if (c->mx_o) add_mx(w.mo); else add(w.o);
+      add_mx(w.mfc1); add_mx(w.mfc2);
+      if (next) { add_mx(next->mqkv); add_mx(next->mv); }
+    } else {
+      add(w.o); add(w.fc1); add(w.fc2);
+      if (next) { add(next->qkv); add(next->v); }
+    }
+    return a.bytes <= ASK_LAYER ? a : Ahead{};
+  };
   for (int l = 0; l < n_layers; ++l) {
     const LayerW& w = c->layers[l];
+    const Ahead ahead = weights_behind(l);
     if (c->mx) {
       HIP_TRY(c, mx_norm(w.n1_g, w.n1_b));
       { ProfScope ps(c, 2, st);
@@ -914,7 +932,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
     pp.n2 = w.v.N; pp.n2_pad = w.v.Npad; pp.VT = VT; pp.hd_pad = c->hd_pad; pp.heads = x.H; pp.n_tok = x.Ns;
     const bool paired = (const bf16_t*)w.v.W == (const bf16_t*)w.qkv.W + (size_t)w.qkv.Npad * w.qkv.K && w.v.b == w.qkv.b + w.qkv.Npad &&
                         bf16_gemm_pair_fits(pp);
-    norm_kernel(w.n1_g, w.n1_b, !copy || l == 0, paired ? pp : p);   // the first layer's rows come from the embedding
+    norm_kernel(w.n1_g, w.n1_b, !copy || l == 0);   // the first layer's rows come from the embedding
     { ProfScope ps(c, 2, st);
       HIP_TRY(c, bf16_gemm(paired ? pp : p, st)); }
     if (!paired) { ProfScope ps(c, 2, st);
@@ -937,7 +955,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
       const bool fused = c->hd_pad % 32 == 0;
       { ProfScope ps(c, 3, st);
         HIP_TRY(c, bf16_attention(QK, QK + c->Dq, VT, O, T, x.Ns, x.Nt, x.Ns, 0, x.H, c->hd_pad, ld_qk, c->Dq_k, st,
-                                  fused ? OQ : nullptr, fused ? SO : nullptr, c->Mp, true));
+                                  fused ? OQ : nullptr, fused ? SO : nullptr, c->Mp, true, 0, &ahead));
         if (!fused) {
           MxRowParams r;
           memset(&r, 0, sizeof(r));
@@ -951,7 +969,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
         HIP_TRY(c, mx_gemm(p, st)); }
     } else {
     { ProfScope ps(c, 3, st);
-      HIP_TRY(c, bf16_attention(QK, QK + c->Dq, VT, O, T, x.Ns, x.Nt, x.Ns, 0, x.H, c->hd_pad, ld_qk, c->Dq_k, st, nullptr, nullptr, 0, d.mx_fp8 != 0)); }
+      HIP_TRY(c, bf16_attention(QK, QK + c->Dq, VT, O, T, x.Ns, x.Nt, x.Ns, 0, x.H, c->hd_pad, ld_qk, c->Dq_k, st, nullptr, nullptr, 0, d.mx_fp8 != 0, 0, &ahead)); }
     { ProfScope ps(c, 6, st);
       GemmParams p = gp(EPI_BIAS_RESIDUAL, O, c->Dq_k, w.o, M);
       p.R = X; p.ldr = x.D;
@@ -974,7 +992,7 @@ epd_status run_bf16(epd_ctx* c, const float* tiles, int T, bf16_t* out, hipStrea
     GemmParams p1 = gp(act_epi, Xn, c->D_k, w.fc1, M), p2 = gp(EPI_BIAS_RESIDUAL, Hd, c->F_k, w.fc2, M);
     p1.C = Hd; p1.ldc = c->F_k;
     with_norm(p1, w.fc1_cs);
-    norm_kernel(w.n2_g, w.n2_b, !copy, p1);
+    norm_kernel(w.n2_g, w.n2_b, !copy);
     { ProfScope ps(c, 7, st);
       HIP_TRY(c, bf16_gemm(p1, st)); }
     { ProfScope ps(c, 8, st);

@@ -1536,12 +1536,6 @@ bool bf16_gemm_pair_fits(const GemmParams& p) {
   return choose_pair(p).us < choose(q).us + choose(v).us + 2.5;
 }
 
-bool bf16_gemm_on_wide(const GemmParams& p) {
-  if (p.n2_pad > 0) return choose_pair(p).shape >= S_256x128;
-  const Choice c = choose(p);
-  return c.shape >= 0 ? c.shape >= S_256x128 : c.first.form != PLAIN_RING;
-}
-
 // For tests: what runs, by its number in GemmParams::cfg (5 and 18: the cuts by rows and by columns); of a pair 0: two products
 int bf16_gemm_shape(const GemmParams& p) {
   static const int number[N_SHAPES] = {11, 13, 14, 1, 9, 15, 16, 17, 12};

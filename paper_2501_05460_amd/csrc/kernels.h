@@ -95,7 +95,6 @@ struct GemmParams {
 hipError_t bf16_gemm(const GemmParams& p, hipStream_t st);
 // true: bf16_gemm runs p with its second product (n2_pad > 0) as one launch; false: the caller issues two products
 bool bf16_gemm_pair_fits(const GemmParams& p);
-bool bf16_gemm_on_wide(const GemmParams& p);    // whether p, without a folded pre-norm, starts with the persistent kernel (n2_pad > 0: as one launch)
 // the product on the ring kernel's tiles (gemm_bf16_ring.hip: launches of a few slices), any epilogue, n2_pad included
 enum RingTile { RING_64x64 = 0, RING_128x64 = 1, RING_128x128 = 2 };
 hipError_t bf16_gemm_ring(const GemmParams& p, int tile, hipStream_t st);
@@ -174,8 +173,6 @@ struct RowOpParams {
   int g, D;                       // grid side and source row length (shuffle only)
   float eps;
   SliceRows src;                  // source row of patch token r (shuffle: of grid cell r) = src.row(r)
-  const unsigned char* ahead;     // the next product's weights, ahead_bytes of them (whole 128-byte lines), to be on their way while the rows are
-  long ahead_bytes;               // normalised; 0: none
 };
 void bf16_rowop(const RowOpParams& p, hipStream_t st);
 
@@ -197,10 +194,24 @@ void bf16_qknorm(bf16_t* buf, long ld, long k_off, const float* gamma_q, const f
 // accumulators: codes oq [rows][ld_o bytes] (column h * hd_pad + d), scale words so [column / 128][ld_so]
 // (ld_so >= rows; layout of gemm_mxfp8.hip); o is not written then.
 // paired (always with oq): the order of summation for calls of the MXFP8 option, see the kernel.
+// ahead: weights that the launches behind this one read, to be on their way into the Infinity Cache meanwhile (see ask_for).
+struct Ahead {
+  static constexpr int RANGES = 10;
+  const unsigned char* at[RANGES];
+  unsigned pieces[RANGES];   // of 16 bytes
+  int n;                     // ranges in use
+  long bytes;                // of all of them
+  void add(const void* p, long size) {   // size < 64 GiB
+    if (n == RANGES || !p || size < 16) return;
+    at[n] = (const unsigned char*)p; pieces[n++] = (unsigned)(size / 16);
+    bytes += size;
+  }
+};
 hipError_t bf16_attention(const bf16_t* q, const bf16_t* k, const bf16_t* vt, bf16_t* o, int n_slices,
                           int n_tok, int n_keys, int n_q, int q_shared, int heads, int hd_pad, long ld_qk,
                           long ld_o, hipStream_t st, unsigned char* oq = nullptr, unsigned* so = nullptr, long ld_so = 0,
-                          bool paired = false, int queries = 0);   // queries per wave: 16, 32 or 0: as the rule picks
+                          bool paired = false, int queries = 0,   // queries per wave: 16, 32 or 0: as the rule picks
+                          const Ahead* ahead = nullptr);
 int bf16_attention_queries(int n_slices, int n_q, int heads, int hd_pad, bool paired);   // queries per wave of such a call, 16 or 32 (tests)
 hipError_t bf16_attention_init();   // raises the dynamic-LDS limit on the current device (idempotent); in front of bf16_attention
 

@@ -50,27 +50,10 @@ void bf16_im2col(const float* tiles, bf16_t* A, int lda, int T, int S, int p, hi
 // as much as one that does (65536 rows of 1152, in us: NORM 1 69.1, NORM 2 65.0 with NV = 5 and 79.0 with NV = 8; 32768
 // rows of 1024, NV = 4: 35.0 -> 30.4; 1024 rows of 1152: 7.5 -> 7.1).  At 13 chunks and more it loses (32768 rows of 3200:
 // 117 -> 138).
-// With p.ahead the first AHEAD workgroups read no rows but one dword of every line of the next product's weights, workgroup b in part b % 8:
-// it runs on XCD b % 8, whose run of the product's tiles is about that part of the columns.  In front of the rows' workgroups:
-// behind them they end last (three slices of the 1152-wide encoder 4606 us, in front 4596; seven 9114, 9032).
-constexpr int AHEAD = 64;
 // NEAR: the source rows are in the Infinity Cache and the output goes THROUGH (NEAR_ROWS).
 template <int NV, int NORM, bool NEAR>
 __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
-  if (NORM) {
-    if ((int)blockIdx.x < AHEAD && p.ahead_bytes > 0) {
-      const long lines = p.ahead_bytes / 128, from = lines * (blockIdx.x & 7) / 8, to = lines * ((blockIdx.x & 7) + 1) / 8, step = AHEAD / 8 * 256;
-      for (long l = from + blockIdx.x / 8 * 256 + threadIdx.x; l < to; l += step * 8) {
-        unsigned t[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) t[i] = *reinterpret_cast<const unsigned*>(p.ahead + min(l + step * i, to - 1) * 128);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) asm volatile("" :: "v"(t[i]));
-      }
-      return;
-    }
-  }
-  const long R = (long)(blockIdx.x - (NORM && p.ahead_bytes > 0 ? AHEAD : 0)) * 4 + (threadIdx.x >> 6);
+  const long R = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (R >= p.rows) return;
   const int lane = threadIdx.x & 63;
   const int nchunk = p.dim >> 2;
@@ -192,7 +175,7 @@ __global__ __launch_bounds__(256) void k_bf16_rowop(const RowOpParams p) {
 
 void bf16_rowop(const RowOpParams& p, hipStream_t st) {
   if (p.rows == 0) return;
-  dim3 grid((unsigned)((p.rows + 3) / 4 + (p.ahead_bytes > 0 ? AHEAD : 0))), block(256);
+  dim3 grid((unsigned)((p.rows + 3) / 4)), block(256);
   const int per_lane = (p.dim / 4 + 63) / 64;
   const bool near = 4.0 * p.rows * p.dim <= NEAR_ROWS;
 #define ROWOP(NV, NORM) (near ? k_bf16_rowop<NV, NORM, true> : k_bf16_rowop<NV, NORM, false>)<<<grid, block, 0, st>>>(p)
