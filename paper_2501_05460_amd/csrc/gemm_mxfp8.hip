@@ -75,7 +75,8 @@ __device__ __forceinline__ float max4abs(float a, float b, float c, float d) {
 // PRE (a norm, kind 0 or 1): gain and shift are fetched in front of the sums.  It pays while they fit beside the row, with
 // NV the row's own count of chunks (65536 rows of 768 | 1024 | 1152 in us: 45.3 -> 44.4 | 55.9 -> 53.6 | 65.2 -> 64.2,
 // 1152 with NV = 8 77.7); at six chunks and more it loses (1536 | 2048: 94.3 -> 96.2 | 128.7 -> 137.5).
-template <bool IN_BF16, int NV, bool PRE>
+// NEAR: rows of the stream that are in the Infinity Cache, codes that go THROUGH (NEAR_ROWS_MX).
+template <bool IN_BF16, int NV, bool PRE, bool NEAR>
 __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
   const long R = (long)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (R >= p.rows) return;
@@ -86,7 +87,8 @@ __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
       const bf16x4 t = *(reinterpret_cast<const bf16x4*>(reinterpret_cast<const bf16_t*>(p.in) + R * p.ld_in) + c);
       return make_float4((float)t[0], (float)t[1], (float)t[2], (float)t[3]);
     }
-    const f32x4 t = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.in) + R * p.ld_in) + c);
+    const f32x4* at = reinterpret_cast<const f32x4*>(reinterpret_cast<const float*>(p.in) + R * p.ld_in) + c;
+    const f32x4 t = NEAR ? *at : __builtin_nontemporal_load(at);
     return make_float4(t[0], t[1], t[2], t[3]);
   };
   constexpr int NVR = NV > 0 ? NV : 1;
@@ -156,7 +158,10 @@ __global__ __launch_bounds__(256) void k_mx_rows(const MxRowParams p) {
     const float inv = mx_inv_scale(byte);
     const unsigned word = mx_pack4(r[0] * inv, r[1] * inv, r[2] * inv, r[3] * inv);
     if (in_row) {
-      codes[c] = word;
+      if constexpr (NEAR)   // a relaxed store at the device's scope is one that goes THROUGH
+        __hip_atomic_store(codes + c, word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else
+        codes[c] = word;
       // block c / 8 of the row = byte (c / 8) % 4 of scale word (c / 32, R): the block's first lane stores it
       if ((lane & 7) == 0) reinterpret_cast<unsigned char*>(p.scales + (long)(c >> 5) * p.ld_scales + R)[(c >> 3) & 3] = (unsigned char)byte;
     }
@@ -191,7 +196,8 @@ __device__ __forceinline__ void static_for(F&& f) {
 // (MxGemmParams::n2).  Its tiles read their fragments with the operands' LDS regions exchanged: so the products, which stay as they
 // are, leave four tokens of a feature in a lane, and the bits are EPI_VT's.  (A second main loop with the roles exchanged in
 // the products instead spills 64 registers.)
-template <int EPI, bool DUAL, int TM, int WAVES_M, int WAVES_N>
+// NEAR: the output goes THROUGH, stream rows are read without a hint (NEAR_OUT, NEAR_ROWS_MX); compiled apart as in gemm_bf16_wide.h.
+template <int EPI, bool DUAL, int TM, int WAVES_M, int WAVES_N, bool NEAR>
 __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES_N)) void k_gemm_mxfp8(const MxGemmParams p, const int gm, const int gw, const int gn, const int gq, const int n_tiles) {
   using T = MxTile<TM, WAVES_M, WAVES_N>;
   constexpr int NT = T::NT, WM = T::WM, WN = T::WN, BM = T::BM, BN = T::BN, AR = T::AR;
@@ -324,6 +330,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
   constexpr int XAHEAD = 4, PASSES = 2 * TM;
   __amdgpu_buffer_rsrc_t rsrc_x = __builtin_amdgcn_make_buffer_rsrc(
       p.R, 0, F32_OUT ? (int)(unsigned)(((long)(p.M - 1) * p.ldr + p.N) * 4) : 0, 0x00020000);
+  // the outputs that go THROUGH (each under 4 GiB: see NEAR_OUT)
+  __amdgpu_buffer_rsrc_t rsrc_v = __builtin_amdgcn_make_buffer_rsrc(
+      p.VT, 0, NEAR && (TOK || DUAL) ? (int)(unsigned)((long)p.M * p.heads * p.hd_pad * 2) : 0, 0x00020000);
+  __amdgpu_buffer_rsrc_t rsrc_c = __builtin_amdgcn_make_buffer_rsrc(
+      p.C, 0, NEAR && !MX_OUT && !F32_OUT && !TOK ? (int)(unsigned)(((long)(p.M - 1) * p.ldc + p.N) * 2) : 0, 0x00020000);
+  __amdgpu_buffer_rsrc_t rsrc_q = __builtin_amdgcn_make_buffer_rsrc(
+      p.Cq, 0, NEAR && MX_OUT ? (int)(unsigned)((long)(p.M - 1) * p.ldcq + p.ncq) : 0, 0x00020000);
 
   aim();
 #pragma unroll
@@ -379,7 +392,7 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
           const int r = (lane + 64 * u) / 8, c = lane % 8;
           const int row = m0 + wm * WM + (q / 2) * 16 + r, col = n0 + wn * WN + (q % 2) * 32 + c * 4;
           xr[q % XAHEAD][u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(   // rows past M come back as zero
-              rsrc_x, ((unsigned)row * (unsigned)p.ldr + (unsigned)col) * 4u, 0, 2));
+              rsrc_x, ((unsigned)row * (unsigned)p.ldr + (unsigned)col) * 4u, 0, NEAR ? 0 : STREAM));
         }
       }
     };
@@ -472,7 +485,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
             if (f < p.n2 && tok < p.M) {
               const u32x4 v = *reinterpret_cast<const u32x4*>(at(r, c));
               const int t = tok / p.n_tok, n = tok % p.n_tok;
-              __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n));
+              if constexpr (NEAR)
+                __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_v, ((unsigned)(t * p.heads * p.hd_pad + f) * (unsigned)p.n_tok + (unsigned)n) * 2u, 0, THROUGH);
+              else
+                __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n));
             }
           }
           wave_sync();
@@ -511,8 +527,13 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
             const int r = (lane + 64 * u) / 8, c = lane % 8;
             const int row = m0 + wm * WM + (q / 2) * 16 + r, col = n0 + wn * WN + (q % 2) * 32 + c * 4;
             const f32x4 v = *reinterpret_cast<const f32x4*>(at(r, c));
-            if (row < p.M && col < p.N)   // streamed: read next by a row kernel, not by this launch
-              __builtin_nontemporal_store(xr[q % XAHEAD][u] + v, reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + col));
+            if (row < p.M && col < p.N) {   // read next by a row kernel, not by this launch
+              if constexpr (NEAR)
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, xr[q % XAHEAD][u] + v), rsrc_x,
+                                                       ((unsigned)row * (unsigned)p.ldr + (unsigned)col) * 4u, 0, THROUGH);
+              else
+                __builtin_nontemporal_store(xr[q % XAHEAD][u] + v, reinterpret_cast<f32x4*>(p.R + (long)row * p.ldr + col));
+            }
           }
           wave_sync();
           if (q + XAHEAD < PASSES) xload(lane, q + XAHEAD);
@@ -537,7 +558,10 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
               if (f < p.N && tok < p.M) {
                 const u32x4 v = *reinterpret_cast<const u32x4*>(at(r, c));
                 const int t = tok / p.n_tok, n = tok % p.n_tok;
-                __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n));
+                if constexpr (NEAR)
+                  __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_v, ((unsigned)(t * p.heads * p.hd_pad + f) * (unsigned)p.n_tok + (unsigned)n) * 2u, 0, THROUGH);
+                else
+                  __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.VT + ((long)t * p.heads * p.hd_pad + f) * p.n_tok + n));
               }
             }
             wave_sync();
@@ -580,8 +604,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
           for (int u = 0; u < 2; ++u) {
             const int r = (lane + 64 * u) / 4, c = lane % 4;
             const int row = m0 + wm * WM + i2 * 16 + r, col = n0 + wn * WN + c * 16;
-            if (row < p.M && col < p.ncq)
-              __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(code_at(r, c)), reinterpret_cast<u32x4*>(p.Cq + (long)row * p.ldcq + col));
+            if (row < p.M && col < p.ncq) {
+              const u32x4 v = *reinterpret_cast<const u32x4*>(code_at(r, c));
+              if constexpr (NEAR) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_q, (unsigned)row * (unsigned)p.ldcq + (unsigned)col, 0, THROUGH);
+              else __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.Cq + (long)row * p.ldcq + col));
+            }
           }
           wave_sync();
         }
@@ -600,8 +627,11 @@ __global__ __launch_bounds__(64 * WAVES_M * WAVES_N, 512 / (64 * WAVES_M * WAVES
           for (int u = 0; u < 2; ++u) {
             const int r = (lane + 64 * u) / 8, c = lane % 8;
             const int row = m0 + wm * WM + i * 16 + r, col = n0 + wn * WN + c * 8;
-            if (row < p.M && col < p.N)
-              __builtin_nontemporal_store(*reinterpret_cast<const u32x4*>(at(r, c)), reinterpret_cast<u32x4*>(p.C + (long)row * p.ldc + col));
+            if (row < p.M && col < p.N) {
+              const u32x4 v = *reinterpret_cast<const u32x4*>(at(r, c));
+              if constexpr (NEAR) __builtin_amdgcn_raw_buffer_store_b128(v, rsrc_c, ((unsigned)row * (unsigned)p.ldc + (unsigned)col) * 2u, 0, THROUGH);
+              else __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(p.C + (long)row * p.ldc + col));
+            }
           }
           wave_sync();
         }
@@ -631,7 +661,12 @@ hipError_t launch_tile(const MxGemmParams& p, int cols, hipStream_t st) {
   const int gm = (p.M + T::BM - 1) / T::BM, gq = (cols + T::BN - 1) / T::BN, gv = DUAL ? (p.n2 + T::BN - 1) / T::BN : 0, gn = gq + gv, n_tiles = gm * gn, slots = cu_count() * (512 / T::NT);
   const int at_once = slots / 8, gw = band_columns(gn, (double)T::BM * p.K, (double)T::BN * p.K, n_tiles < 8 * at_once ? (n_tiles + 7) / 8 : at_once);
   if (gq * T::BN > p.Npad || gv * T::BN > p.n2_pad) return hipErrorInvalidValue;
-  k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N><<<dim3((unsigned)(n_tiles < slots ? n_tiles : slots)), dim3(T::NT), T::LDS, st>>>(p, gm, gw, gn, gq, n_tiles);
+  constexpr bool MX_OUT = EPI == EPI_BIAS_GELU_ERF || EPI == EPI_BIAS_GELU_TANH;
+  const dim3 grid((unsigned)(n_tiles < slots ? n_tiles : slots)), block(T::NT);
+  if (EPI == EPI_BIAS_RESIDUAL ? 4.0 * p.M * p.N <= NEAR_ROWS_MX : (double)p.M * (MX_OUT ? p.ncq : 2 * (p.N > p.n2 ? p.N : p.n2)) <= NEAR_OUT)
+    k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N, true><<<grid, block, T::LDS, st>>>(p, gm, gw, gn, gq, n_tiles);
+  else
+    k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N, false><<<grid, block, T::LDS, st>>>(p, gm, gw, gn, gq, n_tiles);
   return hipGetLastError();
 }
 
@@ -693,8 +728,11 @@ bool together(const MxGemmParams& p) {
 
 template <int EPI, bool DUAL, int TM, int WAVES_M, int WAVES_N>
 hipError_t set_attr_tile() {
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N>),
-                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)MxTile<TM, WAVES_M, WAVES_N>::LDS);
+  constexpr int LDS = (int)MxTile<TM, WAVES_M, WAVES_N>::LDS;
+  const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N, true>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+  return e != hipSuccess ? e : hipFuncSetAttribute(reinterpret_cast<const void*>(&k_gemm_mxfp8<EPI, DUAL, TM, WAVES_M, WAVES_N, false>),
+                                                   hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
 }
 template <int EPI, bool DUAL = false>
 hipError_t set_attr() {
@@ -772,7 +810,8 @@ hipError_t mx_rows(const MxRowParams& p, hipStream_t st) {
     return hipErrorInvalidValue;
   const dim3 grid((unsigned)((p.rows + 3) / 4)), block(256);
   const int per_lane = (p.dim / 4 + 63) / 64;
-#define MX_ROWS(BF, NV, PRE) k_mx_rows<BF, NV, PRE><<<grid, block, 0, st>>>(p)
+  const bool near = !p.in_bf16 && 4.0 * p.rows * p.dim <= NEAR_ROWS_MX;
+#define MX_ROWS(BF, NV, PRE) (near ? k_mx_rows<BF, NV, PRE, true> : k_mx_rows<BF, NV, PRE, false>)<<<grid, block, 0, st>>>(p)
   if (p.in_bf16) {
     if (per_lane <= 4) MX_ROWS(true, 4, false); else if (per_lane <= 8) MX_ROWS(true, 8, false);
     else if (per_lane <= 16) MX_ROWS(true, 16, false); else MX_ROWS(true, 0, false);

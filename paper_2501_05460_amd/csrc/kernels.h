@@ -48,6 +48,11 @@ constexpr int STREAM = 2, THROUGH = 16;
 // 67) 12.07 | 11.53 | 11.68 | 11.14, 20 (168, 84) 15.53 | 15.30 | 15.27 | 14.78, 26 (218, 109) 19.80 | 19.76 | 19.64 | 19.55, 52 36.1 | 37.2 | 36.6 | 36.9;
 // 1152-wide, 16 17.33 | 16.89 | 17.13 | 16.68; 6B shape, eight (210, 105) 80.5 | 81.4 | 80.9 | 81.4.
 constexpr double NEAR_OUT = 180e6, NEAR_ROWS = 75e6;
+// Rows of the stream in calls of the MXFP8 option, whose codes and weights beside them take half as much.  Such calls, us, all outputs of its products and
+// pre-norms STREAM or plain | THROUGH up to NEAR_OUT and 75 MB of rows | 120 MB: 1024-wide, one slice 2130 | 2065 | 2066, five 4197 | 3862 | 3868, 26 (109 MB
+// of codes, 109 of rows) 15414 | 15190 | 14826, 52 (218 each, past the bounds; with codes of up to 300 MB 29825) 29706 | 29715 | 29742; 1152-wide, ten 9144 | 8742 | 8776,
+// three of 729 tokens 3484 | 3417 | 3414; 6B shape, four 29981 | 29537 | 29524.
+constexpr double NEAR_ROWS_MX = 120e6;
 
 // GEMM  C[M,N] = A[M,K] * W[N,K]^T with fused epilogue (gemm_bf16.hip).
 // A must be readable for round_up(M,256) rows, W for Npad rows (zero rows

@@ -503,3 +503,32 @@ def test_224_row_tiles_agree_bit_for_bit(rows, K):
     bias, cs, R = torch.randn(N, generator=g).cuda(), torch.rand(N, generator=g).cuda() + 0.5, torch.randn(rows, N, generator=g).cuda()
     run = lambda tile: B.op_mx_gemm(3, A, SA, W, SW, bias, cs, R.clone(), tile=tile, rows=rows)
     assert torch.equal(run(3), run(1))
+
+
+@pytest.mark.parametrize("epi,N,rows,more", [(0, 4096, 21970, 32), (1, 4096, 43940, 32), (2, 4352, 41350, 32), (3, 1024, 29290, 32), (5, 2048, 43936, 16)])
+def test_outputs_that_stay_in_the_cache_and_larger_ones_agree_bit_for_bit(epi, N, rows, more):
+    """Either side of the size from which a product's output is streamed past the caches (180 MB, 120 MB of the stream's rows) and a pre-norm's
+    rows are: kernels of their own, the same bits in the rows they share.  The transposed store in slices of 16 rows."""
+    g = torch.Generator().manual_seed(N + epi)
+    M, K, bytes_ = rows + more, 128, 4 if epi == 3 else 1 if epi in (1, 2) else 2
+    assert rows * N * bytes_ <= (120e6 if epi == 3 else 180e6) < M * N * bytes_
+    A, W = torch.randn((M + 255) // 256 * 256, K, generator=g).cuda(), torch.randn(N, K, generator=g).mul_(0.05).cuda()
+    (ca, sa), (cw, sw) = B.op_mx_rows(A), B.op_mx_rows(W)
+    bias, R = torch.randn(N, generator=g).cuda(), torch.randn(M, N, generator=g).cuda() if epi == 3 else None
+
+    def product(n, tile):
+        whole = (n + 255) // 256 * 256
+        return B.op_mx_gemm(epi, ca[:whole].contiguous(), sa[:, :whole].contiguous(), cw, sw, bias, None, None if R is None else R[:n].clone(),
+                            16 if epi == 5 else 0, N // 64 if epi == 5 else 0, 64 if epi == 5 else 0, tile=tile, rows=n)
+
+    for tile in (1, 2, 3) if epi == 3 else (1, 2):
+        near, far = product(rows, tile), product(M, tile)
+        if epi in (1, 2):
+            assert torch.equal(near[0], far[0][:rows]) and torch.equal(near[1][:, :rows], far[1][:, :rows]), tile
+        else:
+            assert torch.equal(near, far[:len(near)]), tile
+    if epi == 3:   # the pre-norm on these rows
+        gain, shift = torch.rand(N, generator=g).cuda() + 0.5, torch.randn(N, generator=g).cuda()
+        for kind in (0, 1, 2):
+            near, far = (B.op_mx_rows(R[:n].contiguous(), kind, gain, shift if kind == 0 else None, 1e-6) for n in (rows, M))
+            assert torch.equal(near[0], far[0][:rows]) and torch.equal(near[1], far[1][:, :rows]), kind
