@@ -1092,20 +1092,29 @@ hipError_t launch_ring(const GemmParams& p, int tile, hipStream_t st) {
 struct RingPick { int tile; double us; };
 bool f32_rows(int epi) { return epi == EPI_BIAS_RESIDUAL || epi == EPI_BIAS_POS; }   // reads and writes rows of the stream
 bool has_gelu(int epi) { return epi == EPI_BIAS_GELU_ERF || epi == EPI_BIAS_GELU_TANH; }
+// ring tiles half as wide again (ring_wider), one round of them; fitted to 11 products with cold operands, 960 to 2688 rows
+double wider_us(int tile, double kt) {
+  return tile == RING_64x64 ? 3.7 + 0.40 * kt : tile == RING_128x64 ? 8.3 + 0.455 * kt : 11.1 + 0.54 * kt;
+}
+// One round of 128 x 128 tiles takes 1 us less than the fit for values and pairs (epi EPI_VT), since fragments are read by k-step and pairs read their bias behind
+// the loop, and 2.3 with an activation: pairs, 736 rows of 2304 and 1152 columns 16.6 us on 64 x 64 tiles, 14.6 on 128 x 128; values, 4096 rows, 1024 x 1024
+// 18.1 on 128 x 64, 15.5; activation, 1024 rows, 4096 x 1024 16.9, 14.7.  Over more rounds 128 x 64 tiles stay ahead.  (The plain bias likewise would part the
+// pair of two slices of the 1024-wide encoder: 2368 | 2399 us a call.)
 RingPick best_ring(int M, int n_cols, int K, int epi) {
   const double cus = cu_count(), kt = K / BK;
   const bool f32 = f32_rows(epi);
   auto per_cu = [&](int tm, int tn) { return (double)((M + tm - 1) / tm) * ((n_cols + tn - 1) / tn) / cus; };
-  const double t0 = f32 ? 6.0 + 0.09 * kt + fmax(1.0, per_cu(64, 64)) * (0.4 + 0.217 * kt)
+  auto wider = [&](int tile) { return ring_wider(epi, M, whole_128(n_cols), K, tile); };
+  const double t0 = wider(RING_64x64) ? wider_us(RING_64x64, kt) : f32 ? 6.0 + 0.09 * kt + fmax(1.0, per_cu(64, 64)) * (0.4 + 0.217 * kt)
                         : 5.0 + 0.12 * kt + fmax(1.0, per_cu(64, 64)) * 0.198 * kt;
   RingPick best = {RING_64x64, t0};
   const double r1 = ceil(per_cu(128, 64));   // two workgroups share a CU: a tile alone on its CU takes 3/4 of two
-  const double t1 = f32 ? 6.2 + (r1 == 1.0 ? 2.15 + 0.445 * kt : r1 * (1.2 + 0.33 * kt))
+  const double t1 = wider(RING_128x64) ? wider_us(RING_128x64, kt) : f32 ? 6.2 + (r1 == 1.0 ? 2.15 + 0.445 * kt : r1 * (1.2 + 0.33 * kt))
                         : 5.4 + (r1 == 1.0 ? 0.35 + 0.42 * kt : r1 * 0.318 * kt) + (has_gelu(epi) ? 0.8 : 0.0);
   if (t1 < best.us) best = {RING_128x64, t1};
   const double r2 = per_cu(128, 128);
-  const double t2 = f32 ? 5.5 + ceil(r2) * (4.5 + 0.4 * kt) + r2 * 0.187 * kt
-                        : 5.8 + ceil(r2) * (2.3 + 0.34 * kt) + r2 * 0.18 * kt + (has_gelu(epi) ? 1.7 : 0.0);
+  const double t2 = wider(RING_128x128) ? wider_us(RING_128x128, kt) : f32 ? 5.5 + ceil(r2) * (4.5 + 0.4 * kt) + r2 * 0.187 * kt
+                        : 5.8 + ceil(r2) * (2.3 + 0.34 * kt) + r2 * 0.18 * kt + (r2 > 1.0 ? (has_gelu(epi) ? 1.7 : 0.0) : has_gelu(epi) ? -0.6 : epi == EPI_VT ? -1.0 : 0.0);
   if (t2 < best.us) best = {RING_128x128, t2};
   return best;
 }
@@ -1406,7 +1415,9 @@ static const Fit FITS[N_KINDS][N_SHAPES] = {
 static Kind kind_of(const GemmParams& p) {
   return p.n2_pad > 0 ? K_PAIR : p.epi == EPI_BIAS_RESIDUAL ? K_RESIDUAL : p.epi == EPI_VT ? K_VT : has_gelu(p.epi) ? K_GELU : K_BIAS;
 }
+static int ring_tile(int shape) { return shape == S_64x64 ? RING_64x64 : shape == S_128x64 ? RING_128x64 : RING_128x128; }
 static double shape_us(const GemmParams& p, int shape) {
+  if (shape <= S_128x128 && p.n2_pad == 0 && ring_wider(p.epi, p.M, whole_128(p.N), p.K, ring_tile(shape))) return wider_us(ring_tile(shape), p.K / BK);
   const Fit& f = FITS[kind_of(p)][shape];
   const int tm = SHAPE_ROWS[shape], tn = SHAPE_COLS[shape];
   auto columns = [&](int n) { return ((tn <= 128 ? whole_128(n) : n) + tn - 1) / tn; };
@@ -1523,7 +1534,7 @@ static bool pair_shape(const GemmParams& p) {
 struct Pair { int shape; double us; };
 static Pair choose_pair(const GemmParams& p) {
   Pair best = {-1, INFINITY};
-  const int ring = ring_shape(best_ring(p.M, p.Npad + whole_128(p.n2), p.K, EPI_BIAS).tile);
+  const int ring = ring_shape(best_ring(p.M, p.Npad + whole_128(p.n2), p.K, EPI_VT).tile);
   if (shape_runs(p, ring)) best = {ring, shape_us(p, ring)};
   for (int shape = S_256x128; shape < N_SHAPES; ++shape)
     if (shape_runs(p, shape) && shape_us(p, shape) < best.us) best = {shape, shape_us(p, shape)};

@@ -103,6 +103,7 @@ bool bf16_gemm_pair_fits(const GemmParams& p);
 // the product on the ring kernel's tiles (gemm_bf16_ring.hip: launches of a few slices), any epilogue, n2_pad included
 enum RingTile { RING_64x64 = 0, RING_128x64 = 1, RING_128x128 = 2 };
 hipError_t bf16_gemm_ring(const GemmParams& p, int tile, hipStream_t st);
+bool ring_wider(int epi, int M, int n_cols, int K, int tile);   // whether such a launch over n_cols columns, whole 128s, takes tiles half as wide again
 hipError_t bf16_gemm_ring_init();   // part of bf16_gemm_init
 // Tile columns of a band of the tile sequence, for persistent products.  The `at_once` workgroups an XCD runs at once are consecutive
 // tiles of a band and move through K together.  In a band w wide they lie in 1 + (at_once - 1) / w tile rows on average, at_once / w where that

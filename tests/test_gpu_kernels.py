@@ -293,6 +293,22 @@ def test_ring_tiles_agree_bit_for_bit(M, N, K, epi):
 
 
 @pytest.mark.parametrize("epi,M,N,K,form", [
+    (3, 961, 1152, 128, 11), (3, 1344, 1152, 384, 11), (3, 1345, 1152, 128, 11),      # 64 x 96: 16 rows of tiles, whole rounds, one too many for a round
+    (3, 1793, 1152, 128, 13), (3, 2560, 1152, 640, 13), (3, 2688, 1152, 1664, 13),    # 128 x 96: ragged, full as far as a short K goes, a long one
+    (2, 897, 4352, 128, 14), (1, 1025, 4096, 256, 14), (1, 1408, 4352, 384, 14),      # 128 x 192: the last column of tiles begins inside the one before
+])
+def test_ring_tiles_half_as_wide_again_agree_bit_for_bit(epi, M, N, K, form):
+    """Tiles of 96 and 192 columns, in one round where 64 and 128 wide ones are in two: the bits of the 256 x 128 form, and
+    rows past M are not written."""
+    g = torch.Generator().manual_seed(M + N + K)
+    A, W = torch.randn(M, K, generator=g).mul_(0.5).bfloat16().cuda(), torch.randn(N, K, generator=g).mul_(0.05).bfloat16().cuda()
+    bias = torch.randn(N, generator=g).mul_(0.1).cuda()
+    r0 = torch.randn(M, N, generator=g).cuda() if epi == 3 else None
+    got, want = (B.op_gemm_bf16_form(A, W, bias, epi, f, None if r0 is None else r0.clone()) for f in (form, 1))
+    assert torch.equal(got, want)
+
+
+@pytest.mark.parametrize("epi,M,N,K,form", [
     (3, 9200, 1152, 256, 12),     # 256 x 192 tiles
     (3, 2600, 1152, 1152, 14),    # ring tiles over nine columns of 128, the tenth all padding
     (3, 3570, 1152, 256, 13),     # 128 x 64: eighteen of twenty
