@@ -1385,7 +1385,7 @@ static Plain choose_plain(const GemmParams& p) {
 // (64 x 64 tiles, which share a CU: at least 1).  Fitted to products with cold operands and among their own kind, each in up to nine shapes
 // (encoders of 1024, 1152 and 3200 columns, 736 to 106496 rows; rms 2 to 7 %, no coefficient below zero).  Against 410 products and pairs
 // among other kernels (tests/golden/product_times.txt, which tests/product_times.py takes) what runs is behind the fastest form by, on
-// average: pairs 0.7 %, bias 1.5, activation 0.9, residual 1.3, values 1.2; furthest 1024 rows of 5120 columns over K = 12800, 199 us on ring tiles,
+// average: pairs 0.5 %, bias 1.9, activation 0.3, residual 0.9, values 0.5; furthest 1024 rows of 5120 columns over K = 12800, 199 us on ring tiles,
 // 151 on 256 x 128 ones.  Which ring tiles, only the first stage says: alone and in the running encoder they differ most.
 static void cut_columns(const GemmParams& p, GemmParams& a, GemmParams& b) {   // whole 256-wide tile columns, and the rest
   const int n_a = p.N / 256 * 256;

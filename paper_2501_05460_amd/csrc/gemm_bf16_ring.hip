@@ -1,4 +1,5 @@
-// bf16 MFMA GEMM for launches of a few slices:  C[M,N] = A[M,K] * W[N,K]^T on 64 x 64, 128 x 64 and 128 x 128 tiles.
+// bf16 MFMA GEMM for launches of a few slices:  C[M,N] = A[M,K] * W[N,K]^T on 64 x 64, 128 x 64 and 128 x 128 tiles,
+// and on 64 x 96, 128 x 96 and 128 x 192 ones where those make one round of two (ring_wider).
 //
 // A call of one to some ten slices does not fill the chip with 256 x 256 tiles.  What bounds a launch of smaller tiles
 // is the chain one wave walks per 64-deep slab: a wave issues in order, so the barrier, the fragment reads, the direct
@@ -11,7 +12,7 @@
 //     per operand walks along K.  (With the waits chosen by branches and addresses computed per load, 573 instead of
 //     377 cycles a slab for a 64 x 64 tile; reads in front of all MFMAs, 885 instead of 733 for a 128 x 128 tile, whose
 //     MFMAs alone are 512.)
-//   * What the epilogue reads (bias, residual rows) is fetched in front of the main loop.
+//   * What the epilogue reads (bias, residual rows) is fetched in front of the main loop; the bias of two products in a launch behind it.
 //   * Four waves (2 x 2), each on BM x BN blocks of 16 x 16: a 64 x 64 wave tile reads half as many LDS bytes per flop as the
 //     32 x 64 wave tiles of an eight-wave 128 x 128 tile.
 //   * v_mfma_f32_16x16x32_bf16, for the reason given in gemm_bf16_wide.h.
@@ -22,7 +23,7 @@
 // ahead, as gemm_bf16_wide.h does, costs 5 to 40 %.  LDS is half of a slab (a 64 x 64 one is 32 KiB read and 16 KiB written, 384
 // cycles at 128 bytes a cycle; a 128 x 128 one 768): FC2 of 3096 rows of the 1024-wide encoder, one 128 x 128 tile on each of 200 CUs,
 // takes 41 us in the encoder, 1500 cycles a slab, of which the products are 512.  Its waves spend 17 % of their cycles waiting for data or
-// a barrier and 53 % waiting for an instruction to issue (counters); which instruction, is not measured.
+// a barrier and 53 % waiting for an instruction to issue (counters of the loop that held fragments of whole slabs); which instruction, is not measured.
 //
 // The epilogue goes through LDS wave by wave (a wave stages 32 rows of its own tile and reads them back, no
 // workgroup barrier), so that global memory sees 16-byte pieces of whole 128-byte row parts; bias, activation,
